@@ -303,8 +303,8 @@ double alpha_ctl_reward(double slo_satisfaction, double p99_latency_ms, double s
  *      one group) is bracketed by HIP events on the caller's stream.  racer_prof_read waits
  *      for the pool's last stream, adds up the intervals recorded since the previous read and
  *      clears them. */
-#define RACER_PROF_EMB_GATHER 0 /* probe + hit gather kernel */
-#define RACER_PROF_EMB_MISS 1   /* the miss-path kernels of one emb_lookup, as a group */
+#define RACER_PROF_EMB_GATHER 0 /* probe + hit gather kernel (it also fetches the missing rows from the host table) */
+#define RACER_PROF_EMB_MISS 1   /* the kernels behind it: cache insertion, output rows that waited for a miss; emb_refill */
 #define RACER_PROF_LAYERNORM 2
 #define RACER_PROF_GEMM_FRONT 3
 #define RACER_PROF_ATTENTION 4

@@ -1,6 +1,6 @@
 // Embedding hot-cache kernels for gfx950: wavefront-parallel set probe fused with the
-// row gather, and the miss path (LDS-staged compaction, dedupe by first occurrence,
-// ordered per-set victim choice, zero-copy fetch from the pinned host table).
+// row gather, dedupe and the zero-copy fetch of missing rows from the pinned host table; then
+// the ordered per-set victim choice and the output rows that waited for a miss.
 //
 // The policy these kernels realise (paper Sec. IV-B: an LRU-managed EMB slab with
 // page-granular allocation; the batch rules are this build's reading):
@@ -89,8 +89,40 @@ __device__ __forceinline__ uint4 pack_chunk(const float acc[8], bool bf16) {
 // Resolve a `loc` code to a row address (nullptr = all-zero row).
 __device__ __forceinline__ const uint8_t* row_address(const EmbView& v, const MissWs& ws, int64_t loc) {
   if (loc >= 0) return v.base + loc;
-  if (loc <= -3) return ws.staging + static_cast<uint64_t>(-(loc + 3)) * v.row_bytes;
+  if (loc <= -3) return ws.staging + static_cast<uint64_t>(ws.hslot_u[-(loc + 3)]) * v.row_bytes;
   return nullptr;
+}
+
+// The id of lookup i: as the caller gave it, or, for (table, row) pairs, the row's global id (-1 where the table or
+// the row does not exist).
+__device__ __forceinline__ int64_t global_id(const EmbView& v, uint32_t t, int64_t id) {
+  if (t >= v.n_tables || id < 0 || static_cast<uint64_t>(id) >= v.tables[t].rows) return -1;
+  return static_cast<int64_t>(v.tables[t].base) + id;
+}
+
+// The ids of R lookups i[0 .. R) of this lane (-1 from n on), all loads in flight together.
+template <uint32_t R>
+__device__ __forceinline__ void load_ids(const EmbView& v, const IdSrc& src, const uint64_t (&i)[R], uint32_t n, int64_t (&id)[R]) {
+#pragma unroll
+  for (uint32_t r = 0; r < R; ++r) id[r] = i[r] < n ? src.ids[i[r]] : -1;
+  if (src.table_of) {
+    uint32_t t[R];
+#pragma unroll
+    for (uint32_t r = 0; r < R; ++r) t[r] = i[r] < n ? src.table_of[i[r]] : 0;
+#pragma unroll
+    for (uint32_t r = 0; r < R; ++r) id[r] = global_id(v, t[r], id[r]);
+  }
+}
+
+// Where a row lives in the pinned host tables, and how many of its 16-byte chunks exist there (a table's row may be
+// narrower than a slot).
+__device__ __forceinline__ const uint8_t* host_row(const EmbView& v, uint32_t id32, uint32_t* chunks) {
+  *chunks = v.row_bytes / 16;
+  if (v.n_tables <= 1) return v.table + static_cast<uint64_t>(id32) * v.row_bytes;
+  uint32_t t = 0;
+  while (t + 1 < v.n_tables && v.tables[t + 1].base <= id32) ++t;
+  *chunks = v.tables[t].row_bytes / 16;
+  return v.tables[t].ptr + (id32 - v.tables[t].base) * v.tables[t].row_bytes;
 }
 
 // One output row handled by `lpr` lanes (`sub` = this lane's number in the group): bag == 1
@@ -119,30 +151,130 @@ __device__ __forceinline__ void emit_row(const EmbView& v, const MissWs& ws, uin
 }
 
 // ---------------------------------------------------------------------------------------
+// What a probe block does with its misses (s_miss: {lookup, id}, s_n of them, after a barrier).  Each missing id is
+// claimed in the dedupe table by the first lookup of it that gets there (the number of the earliest lookup is settled
+// by atomicMax); the block that claims an id numbers it, hangs it into its set's chain and, for a lookup, reads its
+// row from the pinned host table into the staging row, so that the host link works while other blocks still probe.
+// Everything a block lists goes to its own stretch of the lists (block b: b * ws.seg ..), with its counts in
+// ws.seg_cnt[b]: no list counter that all blocks would have to bump one after the other (4096 blocks on one counter
+// took longer than the probe itself).
+// ---------------------------------------------------------------------------------------
+__device__ __forceinline__ uint32_t mix32(uint32_t x) {
+  x ^= x >> 16; x *= 0x7FEB352Du; x ^= x >> 15; x *= 0x846CA68Bu; x ^= x >> 16;
+  return x;
+}
+
+// Slot of (batch, id) in the dedupe table; *won: this call put it there.
+__device__ __forceinline__ uint32_t claim_slot(const MissWs& ws, uint32_t batch, uint32_t id32, bool* won) {
+  const unsigned long long key = (static_cast<unsigned long long>(batch) << 32) | id32;
+  uint32_t h = mix32(id32) & ws.hmask;
+  *won = false;
+  for (;;) {
+    const unsigned long long k = __atomic_load_n(&ws.hents[h].key, __ATOMIC_RELAXED);
+    if (k == key) return h;
+    if ((k >> 32) != batch) {  // older batch or never used: free for this batch
+      const unsigned long long prev = atomicCAS(&ws.hents[h].key, k, key);
+      if (prev == k) *won = true;
+      if (prev == k || prev == key) return h;
+      continue;  // someone else took the slot: look at it again
+    }
+    h = (h + 1) & ws.hmask;
+  }
+}
+
+// FETCH: a lookup (rows are staged, waiting lookups learn their slot); else a refill.  s_n: claimed ids, output rows
+// that wait (zero at first with DIRECT, the caller's count otherwise).
+template <bool FETCH, bool DIRECT>
+__device__ __forceinline__ void miss_tail(const EmbView& v, const MissWs& ws, uint32_t batch, const uint2* s_miss,
+                                          uint32_t n_miss, uint4* s_win, uint32_t* s_n, uint8_t* __restrict__ out) {
+  const uint32_t tid = threadIdx.x, seg0 = blockIdx.x * ws.seg;
+  if (n_miss == 0) {  // uniform over the block
+    if (tid == 0) ws.seg_cnt[blockIdx.x] = 0;
+    return;
+  }
+  for (uint32_t k = tid; k < n_miss; k += 256) {
+    const uint2 m = s_miss[k];
+    bool won;
+    const uint32_t h = claim_slot(ws, batch, m.y, &won);
+    atomicMax(&ws.hents[h].val, (static_cast<unsigned long long>(batch) << 32) | (0xFFFFFFFFu - m.x));
+    if (FETCH && !(DIRECT && won)) ws.loc[m.x] = -(static_cast<int64_t>(h) + 3);
+    if (won) s_win[atomicAdd(&s_n[0], 1u)] = make_uint4(m.y, h, m.x, 0);
+    else if (DIRECT) ws.def_list[seg0 + atomicAdd(&s_n[1], 1u)] = m.x;
+  }
+  __syncthreads();
+  const uint32_t n_win = s_n[0];
+  if (tid == 0) {
+    ws.seg_cnt[blockIdx.x] = (s_n[1] << 16) | n_win;
+    *ws.any = batch;
+  }
+  for (uint32_t k = tid; k < n_win; k += 256) {
+    const uint4 w = s_win[k];
+    const uint32_t u = seg0 + k, set = set_of(v, static_cast<int64_t>(w.x));
+    const unsigned long long prev =
+        atomicExch(&ws.heads[mix32(set) & ws.headmask], (static_cast<unsigned long long>(batch) << 32) | u);
+    const uint32_t next = (prev >> 32) == batch ? static_cast<uint32_t>(prev) : kEmpty;
+    ws.rec[u] = make_uint4(w.x, set, next, w.y);
+    ws.hslot_u[w.y] = u;
+  }
+  if (!FETCH) return;
+  // host rows -> staging rows, four rows in flight per lane group
+  constexpr uint32_t kFly = 4;
+  const uint32_t chunks = v.row_bytes / 16, lpr = lanes_per_row(chunks);
+  const uint32_t groups = 256 / lpr, grp = tid / lpr, sub = tid % lpr;
+  for (uint32_t k0 = grp; k0 < n_win; k0 += groups * kFly) {
+    for (uint32_t c = sub; c < chunks; c += lpr) {
+      uint4 val[kFly];
+#pragma unroll
+      for (uint32_t r = 0; r < kFly; ++r) {
+        const uint32_t k = k0 + r * groups;
+        val[r] = make_uint4(0, 0, 0, 0);
+        if (k < n_win) {
+          uint32_t there;
+          const uint8_t* src = host_row(v, s_win[k].x, &there);
+          if (c < there) val[r] = *reinterpret_cast<const uint4*>(src + 16 * c);
+        }
+      }
+#pragma unroll
+      for (uint32_t r = 0; r < kFly; ++r) {
+        const uint32_t k = k0 + r * groups;
+        if (k < n_win) {
+          *reinterpret_cast<uint4*>(ws.staging + static_cast<uint64_t>(seg0 + k) * v.row_bytes + 16 * c) = val[r];
+          if (DIRECT) *reinterpret_cast<uint4*>(out + static_cast<uint64_t>(s_win[k].z) * v.row_bytes + 16 * c) = val[r];
+        }
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------------------
 // Probe + hit gather.  One wavefront takes `lb` consecutive lookups (a whole number of
 // bags, at most 64): lane i owns lookup i, two lookups are probed per step with 32 lanes
 // reading one set's tag line each (128 B, coalesced), then rows are copied with
-// 16-byte lanes.  Misses and the output rows that must wait for them are staged in LDS
-// and appended to the global lists with one atomic per block.
+// 16-byte lanes.  Misses and the output rows that must wait for them are staged in LDS.
 // ---------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void emb_probe_gather(EmbView v, MissWs ws, const int64_t* __restrict__ ids,
+__global__ __launch_bounds__(256) void emb_probe_gather(EmbView v, MissWs ws, IdSrc ids,
                                                         uint32_t n, uint32_t bag, uint32_t lb,
                                                         uint8_t* __restrict__ out,
                                                         uint8_t* __restrict__ hit_flags, uint32_t batch) {
-  __shared__ uint32_t s_miss[256];
-  __shared__ uint32_t s_def[256];
-  __shared__ uint32_t s_n[2], s_base[2];
+  __shared__ uint2 s_miss[256];
+  __shared__ uint4 s_win[256];
+  __shared__ uint32_t s_n[3];  // misses, claimed ids, waiting output rows
   __shared__ uint32_t s_cnt[3];
   const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (tid < 2) s_n[tid] = 0;
-  if (tid < 3) s_cnt[tid] = 0;
-  if (blockIdx.x == 0 && tid < 3) ws.ctr_next[tid] = 0;  // the next call's list counters
+  if (tid < 3) s_n[tid] = s_cnt[tid] = 0;
+  if (blockIdx.x == 0 && tid == 0) *ws.bar = 0;
   __syncthreads();
 
   const uint64_t i0 = (static_cast<uint64_t>(blockIdx.x) * 4 + wave) * lb;
   const uint64_t i = i0 + lane;
   const bool active = lane < lb && i < n;
-  const int64_t id = active ? ids[i] : -1;
+  int64_t id;
+  {
+    const uint64_t at[1] = {active ? i : n};
+    int64_t got[1];
+    load_ids<1>(v, ids, at, n, got);
+    id = got[0];
+  }
   const bool valid = active && id >= 0 && static_cast<uint64_t>(id) < v.rows;
   const uint32_t id32 = static_cast<uint32_t>(id);
   const uint32_t set = valid ? set_of(v, id) : 0;
@@ -172,7 +304,7 @@ __global__ __launch_bounds__(256) void emb_probe_gather(EmbView v, MissWs ws, co
     loc = slot_offset(v, set, static_cast<uint32_t>(my_way));
     v.stamps[static_cast<uint64_t>(set) * v.w_max + my_way] = batch;
   } else if (miss) {
-    loc = -2;  // replaced by the staging row once the miss is resolved
+    loc = -2;  // the miss path writes the lookup's location
   }
   if (hit_flags && active) hit_flags[i] = hit ? 1 : 0;
 
@@ -188,7 +320,7 @@ __global__ __launch_bounds__(256) void emb_probe_gather(EmbView v, MissWs ws, co
     uint32_t base = 0;
     if (lane == 0) base = atomicAdd(&s_n[0], __popcll(miss_m));
     base = __shfl(base, 0, kWave);
-    if (miss) s_miss[base + __popcll(miss_m & lt_mask)] = static_cast<uint32_t>(i);
+    if (miss) s_miss[base + __popcll(miss_m & lt_mask)] = make_uint2(static_cast<uint32_t>(i), id32);
   }
   // an output row waits if any lookup of its bag missed
   const uint32_t b = lane / bag;  // bag of this lane inside the wave's batch
@@ -196,12 +328,12 @@ __global__ __launch_bounds__(256) void emb_probe_gather(EmbView v, MissWs ws, co
   const bool deferred = active && (miss_m & bag_mask) != 0;
   const bool def_leader = deferred && (lane % bag) == 0;
   const unsigned long long def_m = __ballot(def_leader);
-  if (deferred) ws.loc[i] = loc;
+  if (deferred && !miss) ws.loc[i] = loc;
   if (def_m) {
     uint32_t base = 0;
-    if (lane == 0) base = atomicAdd(&s_n[1], __popcll(def_m));
+    if (lane == 0) base = atomicAdd(&s_n[2], __popcll(def_m));
     base = __shfl(base, 0, kWave);
-    if (def_leader) s_def[base + __popcll(def_m & lt_mask)] = static_cast<uint32_t>(i / bag);
+    if (def_leader) ws.def_list[blockIdx.x * ws.seg + base + __popcll(def_m & lt_mask)] = static_cast<uint32_t>(i / bag);
   }
 
   // gather the rows that are complete
@@ -244,16 +376,12 @@ __global__ __launch_bounds__(256) void emb_probe_gather(EmbView v, MissWs ws, co
 
   __syncthreads();
   if (tid == 0) {
-    s_base[0] = s_n[0] ? atomicAdd(&ws.ctr[0], s_n[0]) : 0;
-    s_base[1] = s_n[1] ? atomicAdd(&ws.ctr[1], s_n[1]) : 0;
     if (s_cnt[1]) atomicAdd(&v.counters[ctr_index(kCtrLookups)], static_cast<unsigned long long>(s_cnt[1]));
     if (s_cnt[0]) atomicAdd(&v.counters[ctr_index(kCtrHits)], static_cast<unsigned long long>(s_cnt[0]));
     if (s_cnt[1] - s_cnt[0]) atomicAdd(&v.counters[ctr_index(kCtrMisses)], static_cast<unsigned long long>(s_cnt[1] - s_cnt[0]));
     if (s_cnt[2]) atomicAdd(&v.counters[ctr_index(kCtrInvalid)], static_cast<unsigned long long>(s_cnt[2]));
   }
-  __syncthreads();
-  for (uint32_t k = tid; k < s_n[0]; k += 256) ws.miss_list[s_base[0] + k] = s_miss[k];
-  for (uint32_t k = tid; k < s_n[1]; k += 256) ws.def_list[s_base[1] + k] = s_def[k];
+  miss_tail<true, false>(v, ws, batch, s_miss, s_n[0], s_win, &s_n[1], out);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -265,18 +393,17 @@ __global__ __launch_bounds__(256) void emb_probe_gather(EmbView v, MissWs ws, co
 // ---------------------------------------------------------------------------------------
 constexpr uint32_t kW32Rounds = 2;  // lookups per group of eight lanes (more leaves too few blocks for a Mid-sized batch)
 template <int PASSES>  // row_bytes / 128
-__global__ __launch_bounds__(256) void emb_probe_gather_w32(EmbView v, MissWs ws, const int64_t* __restrict__ ids,
-                                                            uint32_t n, uint8_t* __restrict__ out,
+__global__ __launch_bounds__(256) void emb_probe_gather_w32(EmbView v, MissWs ws, IdSrc ids, uint32_t n, uint8_t* __restrict__ out,
                                                             uint8_t* __restrict__ hit_flags, uint32_t batch) {
   constexpr uint32_t kRounds = kW32Rounds;
   constexpr uint32_t kPerBlock = 32 * kRounds;  // lookups per block: 4 waves x 8 groups x rounds
-  __shared__ uint32_t s_miss[kPerBlock];
-  __shared__ uint32_t s_n, s_base_m, s_base_d;
+  __shared__ uint2 s_miss[kPerBlock];
+  __shared__ uint4 s_win[kPerBlock];
+  __shared__ uint32_t s_n[3];  // misses, claimed ids, waiting output rows
   __shared__ uint32_t s_cnt[3];
   const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, grp = lane >> 3, j = lane & 7;
-  if (tid == 0) s_n = 0;
-  if (tid < 3) s_cnt[tid] = 0;
-  if (blockIdx.x == 0 && tid < 3) ws.ctr_next[tid] = 0;  // the next call's list counters
+  if (tid < 3) s_n[tid] = s_cnt[tid] = 0;
+  if (blockIdx.x == 0 && tid == 0) *ws.bar = 0;
   __syncthreads();
   const uint4* tags4 = reinterpret_cast<const uint4*>(v.tags);
   // The dependent memory steps (ids -> tag lines -> rows -> output) are each taken for all rounds at once:
@@ -290,8 +417,8 @@ __global__ __launch_bounds__(256) void emb_probe_gather_w32(EmbView v, MissWs ws
   for (uint32_t r = 0; r < kRounds; ++r) {
     idx[r] = static_cast<uint64_t>(blockIdx.x) * kPerBlock + (r * 4 + wave) * 8 + grp;
     active[r] = idx[r] < n;
-    id[r] = active[r] ? ids[idx[r]] : -1;
   }
+  load_ids<kRounds>(v, ids, idx, n, id);
 #pragma unroll
   for (uint32_t r = 0; r < kRounds; ++r) {
     valid[r] = active[r] && id[r] >= 0 && static_cast<uint64_t>(id[r]) < v.rows;
@@ -344,8 +471,7 @@ __global__ __launch_bounds__(256) void emb_probe_gather_w32(EmbView v, MissWs ws
 #pragma unroll
       for (int c = 0; c < PASSES; ++c) *reinterpret_cast<uint4*>(dst + 16 * (j + 8 * c)) = row[r][c];
     } else if (miss && j == 0) {
-      ws.loc[idx[r]] = -2;  // replaced by the staging row once the miss is resolved
-      s_miss[atomicAdd(&s_n, 1u)] = static_cast<uint32_t>(idx[r]);
+      s_miss[atomicAdd(&s_n[0], 1u)] = make_uint2(static_cast<uint32_t>(idx[r]), static_cast<uint32_t>(id[r]));
     }
   }
   if (j == 0) {
@@ -355,19 +481,12 @@ __global__ __launch_bounds__(256) void emb_probe_gather_w32(EmbView v, MissWs ws
   }
   __syncthreads();
   if (tid == 0) {
-    // with one lookup per row the missing lookups are also the output rows that wait
-    s_base_m = s_n ? atomicAdd(&ws.ctr[0], s_n) : 0;
-    s_base_d = s_n ? atomicAdd(&ws.ctr[1], s_n) : 0;
     if (s_cnt[1]) atomicAdd(&v.counters[ctr_index(kCtrLookups)], static_cast<unsigned long long>(s_cnt[1]));
     if (s_cnt[0]) atomicAdd(&v.counters[ctr_index(kCtrHits)], static_cast<unsigned long long>(s_cnt[0]));
     if (s_cnt[1] - s_cnt[0]) atomicAdd(&v.counters[ctr_index(kCtrMisses)], static_cast<unsigned long long>(s_cnt[1] - s_cnt[0]));
     if (s_cnt[2]) atomicAdd(&v.counters[ctr_index(kCtrInvalid)], static_cast<unsigned long long>(s_cnt[2]));
   }
-  __syncthreads();
-  for (uint32_t k = tid; k < s_n; k += 256) {
-    ws.miss_list[s_base_m + k] = s_miss[k];
-    ws.def_list[s_base_d + k] = s_miss[k];
-  }
+  miss_tail<true, true>(v, ws, batch, s_miss, s_n[0], s_win, &s_n[1], out);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -377,21 +496,22 @@ __global__ __launch_bounds__(256) void emb_probe_gather_w32(EmbView v, MissWs ws
 // row over the bag's members in order, in fp32, and rounds once (the definition of the pooled
 // row).  A bag with a missing member is left to the miss path, as in the generic kernel.
 // ---------------------------------------------------------------------------------------
+// (The second launch bound keeps the registers where they allow 6, 5, 4, 4 wavefronts per SIMD: at 98 instead of 96 a
+// pooled gather of 2.1M 256-byte rows took 220 us instead of 198.)
 template <int PASSES>  // row_bytes / 128
-__global__ __launch_bounds__(256) void emb_probe_gather_w32_bag(EmbView v, MissWs ws, const int64_t* __restrict__ ids,
-                                                                uint32_t n, uint32_t bag, uint8_t* __restrict__ out,
+__global__ __launch_bounds__(256, PASSES == 1 ? 6 : PASSES == 2 ? 5 : 4) void emb_probe_gather_w32_bag(EmbView v, MissWs ws, IdSrc ids, uint32_t n, uint32_t bag, uint8_t* __restrict__ out,
                                                                 uint8_t* __restrict__ hit_flags, uint32_t batch) {
   constexpr uint32_t kRounds = 4;
   constexpr uint32_t kPerBlock = 32 * kRounds;  // lookups per block: 4 waves x 8 groups x rounds
   constexpr uint32_t kRowWords = PASSES * 32;   // 4-byte words per row
-  __shared__ uint32_t s_miss[kPerBlock], s_def[kPerBlock];
-  __shared__ uint32_t s_n[2], s_base[2];
+  __shared__ uint2 s_miss[kPerBlock];
+  __shared__ uint4 s_win[kPerBlock];
+  __shared__ uint32_t s_n[3];  // misses, claimed ids, waiting output rows
   __shared__ uint32_t s_cnt[3];
   __shared__ __attribute__((aligned(16))) uint32_t s_rows[4][8][kRowWords];
   const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, grp = lane >> 3, j = lane & 7;
-  if (tid < 2) s_n[tid] = 0;
-  if (tid < 3) s_cnt[tid] = 0;
-  if (blockIdx.x == 0 && tid < 3) ws.ctr_next[tid] = 0;  // the next call's list counters
+  if (tid < 3) s_n[tid] = s_cnt[tid] = 0;
+  if (blockIdx.x == 0 && tid == 0) *ws.bar = 0;
   __syncthreads();
   const uint4* tags4 = reinterpret_cast<const uint4*>(v.tags);
   const bool bf16 = v.elem == 1;
@@ -407,8 +527,12 @@ __global__ __launch_bounds__(256) void emb_probe_gather_w32_bag(EmbView v, MissW
     active[r] = i0[r] + grp < n;
   }
   int64_t id[kRounds];
+  {
+    uint64_t at[kRounds];
 #pragma unroll
-  for (uint32_t r = 0; r < kRounds; ++r) id[r] = active[r] ? ids[i0[r] + grp] : -1;
+    for (uint32_t r = 0; r < kRounds; ++r) at[r] = i0[r] + grp;
+    load_ids<kRounds>(v, ids, at, n, id);
+  }
 #pragma unroll
   for (uint32_t r = 0; r < kRounds; ++r) {
     valid[r] = active[r] && id[r] >= 0 && static_cast<uint64_t>(id[r]) < v.rows;
@@ -440,7 +564,7 @@ __global__ __launch_bounds__(256) void emb_probe_gather_w32_bag(EmbView v, MissW
     hit[r] = valid[r] && cand != 255;
     miss[r] = valid[r] && !hit[r];
     // the member's row (zeros for an invalid id or a miss)
-    loc[r] = miss[r] ? -2 : -1;  // -2: replaced by the staging row once the miss is resolved
+    loc[r] = -1;
 #pragma unroll
     for (int c = 0; c < PASSES; ++c) row[r][c] = make_uint4(0, 0, 0, 0);
     if (hit[r]) {
@@ -472,9 +596,10 @@ __global__ __launch_bounds__(256) void emb_probe_gather_w32_bag(EmbView v, MissW
     const unsigned long long bag_mask = bag == 8 ? ~0ull : (1ull << (8 * bag)) - 1ull;
     const bool deferred = active[r] && ((miss_m >> (8 * bag_first)) & bag_mask) != 0;
     if (j == 0) {
-      if (deferred) ws.loc[i] = loc[r];
-      if (miss[r]) s_miss[atomicAdd(&s_n[0], 1u)] = static_cast<uint32_t>(i);
-      if (deferred && grp == bag_first) s_def[atomicAdd(&s_n[1], 1u)] = static_cast<uint32_t>(i / bag);
+      if (deferred && !miss[r]) ws.loc[i] = loc[r];  // the miss path writes the location of a missing member
+      if (miss[r]) s_miss[atomicAdd(&s_n[0], 1u)] = make_uint2(static_cast<uint32_t>(i), id32[r]);
+      if (deferred && grp == bag_first)
+        ws.def_list[blockIdx.x * ws.seg + atomicAdd(&s_n[2], 1u)] = static_cast<uint32_t>(i / bag);
     }
     // ordered sums: word w of the wavefront's output rows
     const uint32_t out_words = kRowWords * (8 / bag);
@@ -509,221 +634,299 @@ __global__ __launch_bounds__(256) void emb_probe_gather_w32_bag(EmbView v, MissW
   }
   __syncthreads();
   if (tid == 0) {
-    s_base[0] = s_n[0] ? atomicAdd(&ws.ctr[0], s_n[0]) : 0;
-    s_base[1] = s_n[1] ? atomicAdd(&ws.ctr[1], s_n[1]) : 0;
     if (s_cnt[1]) atomicAdd(&v.counters[ctr_index(kCtrLookups)], static_cast<unsigned long long>(s_cnt[1]));
     if (s_cnt[0]) atomicAdd(&v.counters[ctr_index(kCtrHits)], static_cast<unsigned long long>(s_cnt[0]));
     if (s_cnt[1] - s_cnt[0]) atomicAdd(&v.counters[ctr_index(kCtrMisses)], static_cast<unsigned long long>(s_cnt[1] - s_cnt[0]));
     if (s_cnt[2]) atomicAdd(&v.counters[ctr_index(kCtrInvalid)], static_cast<unsigned long long>(s_cnt[2]));
   }
-  __syncthreads();
-  for (uint32_t k = tid; k < s_n[0]; k += 256) ws.miss_list[s_base[0] + k] = s_miss[k];
-  for (uint32_t k = tid; k < s_n[1]; k += 256) ws.def_list[s_base[1] + k] = s_def[k];
+  miss_tail<true, false>(v, ws, batch, s_miss, s_n[0], s_win, &s_n[1], out);
 }
 
 // ---------------------------------------------------------------------------------------
-// Miss path.  All kernels read the list lengths from device memory and return at once
+// Behind the probe: which way each new id takes (settle), the output rows that waited (gather), and the new tags and
+// stamps (apply).  A set's victim candidates are fixed once the probe has stamped the hits, so every new id works out
+// its own rank among the set's new ids and takes the candidate of that rank; tags are written only after all of them
+// have been read.  Units of work are quarters of a probe block's stretch of the lists; everything returns at once
 // when the batch had no miss.
 // ---------------------------------------------------------------------------------------
-__device__ __forceinline__ uint32_t mix32(uint32_t x) {
-  x ^= x >> 16; x *= 0x7FEB352Du; x ^= x >> 15; x *= 0x846CA68Bu; x ^= x >> 16;
-  return x;
+constexpr uint32_t kQuarter = 16;  // new ids a wavefront takes at a time
+
+__device__ __forceinline__ uint32_t nth_bit(uint32_t m, uint32_t k) {  // position of the k-th set bit
+  for (; k; --k) m &= m - 1;
+  return static_cast<uint32_t>(__ffs(m)) - 1;
 }
 
-// slot of (batch, id) in the dedupe table; inserts when `insert`
-__device__ __forceinline__ uint32_t dedupe_slot(const MissWs& ws, uint32_t batch, uint32_t id32, bool insert) {
-  const unsigned long long key = (static_cast<unsigned long long>(batch) << 32) | id32;
-  uint32_t h = mix32(id32) & ws.hmask;
-  for (;;) {
-    const unsigned long long k = __atomic_load_n(&ws.hkeys[h], __ATOMIC_RELAXED);
-    if (k == key) return h;
-    if ((k >> 32) != batch) {  // older batch or never used: free for this batch
-      if (!insert) return h;   // cannot happen for ids that were inserted
-      const unsigned long long prev = atomicCAS(&ws.hkeys[h], k, key);
-      if (prev == k || prev == key) return h;
-      continue;  // someone else took the slot: look at it again
-    }
-    h = (h + 1) & ws.hmask;
-  }
-}
+struct SettleCounts { uint32_t unique, inserted, evicted, bypassed; };
 
-__global__ __launch_bounds__(256) void miss_dedupe(MissWs ws, const int64_t* __restrict__ ids, uint32_t batch) {
-  const uint32_t n_miss = ws.ctr[0];
-  for (uint32_t m = blockIdx.x * 256 + threadIdx.x; m < n_miss; m += gridDim.x * 256) {
-    const uint32_t i = ws.miss_list[m];
-    const uint32_t id32 = static_cast<uint32_t>(ids[i]);
-    const uint32_t h = dedupe_slot(ws, batch, id32, true);
-    atomicMax(&ws.hvals[h], (static_cast<unsigned long long>(batch) << 32) | (0xFFFFFFFFu - i));
-  }
-}
-
-__global__ __launch_bounds__(256) void miss_link(EmbView v, MissWs ws, const int64_t* __restrict__ ids,
-                                                 uint32_t batch) {
-  const uint32_t n_miss = ws.ctr[0];
-  for (uint32_t m = blockIdx.x * 256 + threadIdx.x; m < n_miss; m += gridDim.x * 256) {
-    const uint32_t i = ws.miss_list[m];
-    const int64_t id = ids[i];
-    const uint32_t id32 = static_cast<uint32_t>(id);
-    const uint32_t h = dedupe_slot(ws, batch, id32, false);
-    const uint32_t first_i = 0xFFFFFFFFu - static_cast<uint32_t>(ws.hvals[h]);
-    if (first_i != i) continue;  // a later duplicate of this id
-    const uint32_t u = atomicAdd(&ws.ctr[2], 1u);
-    const uint32_t set = set_of(v, id);
-    ws.u_i[u] = i;
-    ws.u_id[u] = id32;
-    ws.u_set[u] = set;
-    ws.hslot_u[h] = u;
-    const unsigned long long prev =
-        atomicExch(&ws.heads[mix32(set) & ws.headmask], (static_cast<unsigned long long>(batch) << 32) | u);
-    ws.u_next[u] = (prev >> 32) == batch ? static_cast<int32_t>(static_cast<uint32_t>(prev)) : -1;
-  }
-}
-
-// Half a wavefront per unique miss: lane = way.  rank = number of unique misses of the same
-// set that occur earlier in the batch; the miss takes the rank-th victim candidate of the
-// set in (empty ways by index, then (stamp, way) ascending among stamps older than the batch).
-// With `refill` only empty ways are candidates (a refill never evicts) and only insertions are counted.
-__global__ __launch_bounds__(256) void miss_decide(EmbView v, MissWs ws, uint32_t batch, bool refill) {
-  const uint32_t n_unique = ws.ctr[2];
+// New ids [w0, w0 + 16) of stretch `seg`, by one wavefront.  With REFILL only empty ways are candidates (a refill
+// never evicts), only insertions are counted, and an id that enters the cache is fetched from the host table here.
+template <bool REFILL>
+__device__ __forceinline__ void settle_quarter(const EmbView& v, const MissWs& ws, uint32_t batch, uint32_t seg, uint32_t w0,
+                                               uint32_t n_win, SettleCounts* cnt) {
+  constexpr uint32_t kPairs = 2;  // with eight wavefronts per SIMD; 4 at four per SIMD: 96 us instead of 63 (83k new ids)
   const uint32_t lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
-  const uint32_t wave = (blockIdx.x * 256 + threadIdx.x) >> 6, n_waves = (gridDim.x * 256) >> 6;
-  for (uint32_t u0 = wave * 2; u0 < n_unique; u0 += n_waves * 2) {
-    const uint32_t u = u0 + half;
-    const bool act = u < n_unique;
-    uint32_t set = 0, my_i = 0, rank = 0, nw = 0;
-    if (act) {
-      set = ws.u_set[u];
-      my_i = ws.u_i[u];
-      nw = ways_of(v, set);
-      const unsigned long long hv = ws.heads[mix32(set) & ws.headmask];
-      int32_t cur = (hv >> 32) == batch ? static_cast<int32_t>(static_cast<uint32_t>(hv)) : -1;
-      while (cur >= 0) {
-        if (ws.u_set[cur] == set && ws.u_i[cur] < my_i) ++rank;
-        cur = ws.u_next[cur];
-      }
-    }
-    uint32_t tg = kEmpty, sp = 0;
-    const bool way_ok = act && l32 < nw;
-    if (way_ok) {
-      tg = v.tags[static_cast<uint64_t>(set) * v.w_max + l32];
-      sp = v.stamps[static_cast<uint64_t>(set) * v.w_max + l32];
-    }
-    const bool cand = way_ok && (tg == kEmpty || (!refill && sp < batch));
-    const unsigned long long key =
-        !cand ? ~0ull : (tg == kEmpty ? l32 : ((1ull << 40) | (static_cast<unsigned long long>(sp) << 5) | l32));
-    uint32_t pos = 0;
-    for (uint32_t j = 0; j < 32; ++j) {
-      const unsigned long long kj = static_cast<unsigned long long>(shfl64(static_cast<int64_t>(key), half * 32 + j));
-      pos += (kj < key) ? 1u : 0u;
-    }
-    const unsigned long long vm = __ballot(cand && pos == rank);
-    const uint32_t mine = half ? static_cast<uint32_t>(vm >> 32) : static_cast<uint32_t>(vm);
-    const int32_t way = mine ? __ffs(mine) - 1 : -1;
-    const uint32_t victim_tag = __shfl(tg, half * 32 + (way >= 0 ? way : 0), kWave);
-    if (act && l32 == 0 && refill) {
-      ws.u_way[u] = way;
-      if (way >= 0) atomicAdd(&v.counters[ctr_index(kCtrInserted)], 1ull);
-    } else if (act && l32 == 0) {
-      ws.u_way[u] = way;
-      atomicAdd(&v.counters[ctr_index(kCtrUnique)], 1ull);
-      if (way >= 0) {
-        atomicAdd(&v.counters[ctr_index(kCtrInserted)], 1ull);
-        if (victim_tag != kEmpty) atomicAdd(&v.counters[ctr_index(kCtrEvicted)], 1ull);
-      } else {
-        atomicAdd(&v.counters[ctr_index(kCtrBypassed)], 1ull);
-      }
+  const uint32_t u0 = seg * ws.seg + w0;
+  const uint32_t here = n_win - w0 < kQuarter ? n_win - w0 : kQuarter;
+  // lane k: the rank of new id k = how many of its set's new ids occur earlier in the batch
+  uint4 rec = make_uint4(0, 0, 0, 0);
+  uint32_t rank = 0;
+  if (lane < here) {
+    rec = ws.rec[u0 + lane];
+    const uint32_t my_i = 0xFFFFFFFFu - static_cast<uint32_t>(ws.hents[rec.w].val);
+    uint32_t cur = static_cast<uint32_t>(ws.heads[mix32(rec.y) & ws.headmask]);
+    while (cur != kEmpty) {
+      const uint4 r = ws.rec[cur];
+      if (r.y == rec.y && cur != u0 + lane)
+        rank += (0xFFFFFFFFu - static_cast<uint32_t>(ws.hents[r.w].val)) < my_i ? 1u : 0u;
+      cur = r.z;
     }
   }
-}
-
-// every missing lookup, duplicates included, learns the staging row of its id
-__global__ __launch_bounds__(256) void miss_resolve(MissWs ws, const int64_t* __restrict__ ids, uint32_t batch) {
-  const uint32_t n_miss = ws.ctr[0];
-  for (uint32_t m = blockIdx.x * 256 + threadIdx.x; m < n_miss; m += gridDim.x * 256) {
-    const uint32_t i = ws.miss_list[m];
-    const uint32_t h = dedupe_slot(ws, batch, static_cast<uint32_t>(ids[i]), false);
-    ws.loc[i] = -(static_cast<int64_t>(ws.hslot_u[h]) + 3);
-  }
-}
-
-// Apply the decisions: new tag and stamp, then one read of the row from the pinned host
-// table (zero-copy over PCIe) into the staging row and, if inserted, into the pool slot.
-// With `refill` nobody waits for the row: it is fetched only if it enters the cache, and not staged.
-__global__ __launch_bounds__(256) void miss_apply_fetch(EmbView v, MissWs ws, uint32_t batch, bool refill) {
-  const uint32_t n_unique = ws.ctr[2];
-  const uint32_t lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
-  const uint32_t wave = (blockIdx.x * 256 + threadIdx.x) >> 6, n_waves = (gridDim.x * 256) >> 6;
   const uint32_t chunks = v.row_bytes / 16;
-  for (uint32_t u0 = wave * 2; u0 < n_unique; u0 += n_waves * 2) {
-    const uint32_t u = u0 + half;
-    if (u >= n_unique) continue;
-    const uint32_t id32 = ws.u_id[u], set = ws.u_set[u];
-    const int32_t way = ws.u_way[u];
-    if (refill && way < 0) continue;
-    uint8_t* dst = nullptr;
-    if (way >= 0) {
-      dst = v.base + slot_offset(v, set, static_cast<uint32_t>(way));
-      if (l32 == 0) {
-        v.tags[static_cast<uint64_t>(set) * v.w_max + way] = id32;
-        v.stamps[static_cast<uint64_t>(set) * v.w_max + way] = batch;
+  for (uint32_t p0 = 0; p0 < here; p0 += 2 * kPairs) {  // half a wavefront per id, lane = way, kPairs ids per half in flight
+    uint32_t set[kPairs], id32[kPairs], rk[kPairs], nw[kPairs], tg[kPairs], sp[kPairs];
+    int way[kPairs];
+    bool act[kPairs];
+#pragma unroll
+    for (uint32_t q = 0; q < kPairs; ++q) {
+      const uint32_t src = p0 + 2 * q + half;
+      act[q] = src < here;
+      set[q] = __shfl(rec.y, src, kWave);
+      id32[q] = __shfl(rec.x, src, kWave);
+      rk[q] = __shfl(rank, src, kWave);
+      nw[q] = act[q] ? ways_of(v, set[q]) : 0;
+      tg[q] = 0;
+      sp[q] = 0;
+      if (l32 < nw[q]) {
+        tg[q] = v.tags[static_cast<uint64_t>(set[q]) * v.w_max + l32];
+        if (!REFILL) sp[q] = v.stamps[static_cast<uint64_t>(set[q]) * v.w_max + l32];
       }
     }
-    const uint8_t* src = v.table + static_cast<uint64_t>(id32) * v.row_bytes;
-    uint32_t src_chunks = chunks;
-    if (v.n_tables > 1) {  // the table whose range holds the id; its row may be narrower than a slot
-      uint32_t t = 0;
-      while (t + 1 < v.n_tables && v.tables[t + 1].base <= id32) ++t;
-      src = v.tables[t].ptr + (id32 - v.tables[t].base) * v.tables[t].row_bytes;
-      src_chunks = v.tables[t].row_bytes / 16;
+#pragma unroll
+    for (uint32_t q = 0; q < kPairs; ++q) {
+      const bool empty = l32 < nw[q] && tg[q] == kEmpty;
+      const unsigned long long em2 = __ballot(empty);
+      const uint32_t em = half ? static_cast<uint32_t>(em2 >> 32) : static_cast<uint32_t>(em2);
+      const uint32_t ne = __popc(em);
+      way[q] = -1;
+      bool evicts = false;
+      if (rk[q] < ne) {
+        way[q] = static_cast<int>(nth_bit(em, rk[q]));
+      } else if (!REFILL) {
+        // the (rank - empties)-th of the ways not stamped in this batch, by (stamp, way): least stamp after least stamp
+        bool cand = l32 < nw[q] && !empty && sp[q] < batch;
+        uint32_t r = rk[q] - ne;
+        for (;;) {
+          uint32_t least = cand ? sp[q] : 0xFFFFFFFFu;
+#pragma unroll
+          for (int o = 16; o > 0; o >>= 1) {
+            const uint32_t other = __shfl_xor(least, o, kWave);
+            least = other < least ? other : least;
+          }
+          const bool is_least = cand && sp[q] == least;
+          const unsigned long long m2 = __ballot(is_least);
+          const uint32_t m = half ? static_cast<uint32_t>(m2 >> 32) : static_cast<uint32_t>(m2);
+          if (m == 0) break;
+          const uint32_t c = __popc(m);
+          if (r < c) {
+            way[q] = static_cast<int>(nth_bit(m, r));
+            evicts = true;
+            break;
+          }
+          r -= c;
+          cand = cand && !is_least;
+        }
+      }
+      if (act[q] && l32 == 0) {
+        ws.u_way[u0 + p0 + 2 * q + half] = way[q];
+        cnt->unique += 1;
+        cnt->inserted += way[q] >= 0;
+        cnt->evicted += evicts;
+        cnt->bypassed += way[q] < 0;
+      }
     }
-    uint8_t* stg = ws.staging + static_cast<uint64_t>(u) * v.row_bytes;
+    // the rows enter their slots: from the staging rows, or (refill) straight from the host table
     for (uint32_t c = l32; c < chunks; c += 32) {
-      const uint4 val = c < src_chunks ? *reinterpret_cast<const uint4*>(src + 16 * c) : make_uint4(0, 0, 0, 0);
-      if (!refill) *reinterpret_cast<uint4*>(stg + 16 * c) = val;
-      if (dst) *reinterpret_cast<uint4*>(dst + 16 * c) = val;
+      uint4 val[kPairs];
+#pragma unroll
+      for (uint32_t q = 0; q < kPairs; ++q) {
+        const uint32_t src = p0 + 2 * q + half;
+        val[q] = make_uint4(0, 0, 0, 0);
+        if (way[q] < 0 || !act[q]) continue;
+        if (REFILL) {
+          uint32_t there;
+          const uint8_t* row = host_row(v, id32[q], &there);
+          if (c < there) val[q] = *reinterpret_cast<const uint4*>(row + 16 * c);
+        } else {
+          val[q] = *reinterpret_cast<const uint4*>(ws.staging + static_cast<uint64_t>(u0 + src) * v.row_bytes + 16 * c);
+        }
+      }
+#pragma unroll
+      for (uint32_t q = 0; q < kPairs; ++q)
+        if (way[q] >= 0 && act[q])
+          *reinterpret_cast<uint4*>(v.base + slot_offset(v, set[q], static_cast<uint32_t>(way[q])) + 16 * c) = val[q];
     }
   }
 }
 
-// Output rows that waited for a miss.
-__global__ __launch_bounds__(256) void emb_deferred_gather(EmbView v, MissWs ws, uint32_t bag,
-                                                           uint8_t* __restrict__ out) {
-  const uint32_t n_def = ws.ctr[1];
-  const uint32_t chunks = v.row_bytes / 16;
-  const uint32_t lpr = lanes_per_row(chunks);
-  const uint32_t gid = blockIdx.x * 256 + threadIdx.x;
-  const uint32_t sub = gid % lpr;
-  const uint32_t groups = gridDim.x * 256 / lpr;
-  for (uint32_t k = gid / lpr; k < n_def; k += groups) {
-    const uint64_t o = ws.def_list[k];
-    emit_row(v, ws, bag, lpr, sub, out + o * v.row_bytes,
-             [&](uint32_t f) { return ws.loc[o * bag + f]; });
+// Output rows of stretch `seg` that waited for a miss, quarter `part` of them.
+__device__ __forceinline__ void gather_waiting(const EmbView& v, const MissWs& ws, uint32_t bag, uint8_t* __restrict__ out,
+                                               uint32_t seg, uint32_t part, uint32_t n_def) {
+  const uint32_t lpr = lanes_per_row(v.row_bytes / 16), rows_per_pass = kWave / lpr;
+  const uint32_t lane = threadIdx.x & 63, sub = lane % lpr;
+  for (uint32_t k = part * rows_per_pass + lane / lpr; k < n_def; k += 4 * rows_per_pass) {
+    const uint64_t o = ws.def_list[seg * ws.seg + k];
+    emit_row(v, ws, bag, lpr, sub, out + o * v.row_bytes, [&](uint32_t f) { return ws.loc[o * bag + f]; });
   }
+}
+
+template <bool REFILL>
+__device__ __forceinline__ void settle_units(const EmbView& v, const MissWs& ws, uint32_t bag, uint8_t* __restrict__ out,
+                                             uint32_t n_seg, uint32_t batch) {
+  __shared__ uint32_t s_cnt[4];
+  if (threadIdx.x < 4) s_cnt[threadIdx.x] = 0;
+  __syncthreads();
+  const uint32_t wave = (blockIdx.x * 256 + threadIdx.x) >> 6, n_waves = (gridDim.x * 256) >> 6;
+  SettleCounts cnt{0, 0, 0, 0};
+  for (uint32_t unit = wave; unit < 4 * n_seg; unit += n_waves) {
+    const uint32_t seg = unit >> 2, part = unit & 3, both = ws.seg_cnt[seg];
+    const uint32_t n_win = both & 0xFFFFu, n_def = both >> 16;
+    for (uint32_t w0 = kQuarter * part; w0 < n_win; w0 += 4 * kQuarter)
+      settle_quarter<REFILL>(v, ws, batch, seg, w0, n_win, &cnt);
+    if (!REFILL) gather_waiting(v, ws, bag, out, seg, part, n_def);
+  }
+  if ((threadIdx.x & 31) == 0) {
+    if (cnt.unique) atomicAdd(&s_cnt[0], cnt.unique);
+    if (cnt.inserted) atomicAdd(&s_cnt[1], cnt.inserted);
+    if (cnt.evicted) atomicAdd(&s_cnt[2], cnt.evicted);
+    if (cnt.bypassed) atomicAdd(&s_cnt[3], cnt.bypassed);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    if (s_cnt[1]) atomicAdd(&v.counters[ctr_index(kCtrInserted)], static_cast<unsigned long long>(s_cnt[1]));
+    if (!REFILL) {
+      if (s_cnt[0]) atomicAdd(&v.counters[ctr_index(kCtrUnique)], static_cast<unsigned long long>(s_cnt[0]));
+      if (s_cnt[2]) atomicAdd(&v.counters[ctr_index(kCtrEvicted)], static_cast<unsigned long long>(s_cnt[2]));
+      if (s_cnt[3]) atomicAdd(&v.counters[ctr_index(kCtrBypassed)], static_cast<unsigned long long>(s_cnt[3]));
+    }
+  }
+}
+
+__device__ __forceinline__ void apply_units(const EmbView& v, const MissWs& ws, uint32_t n_seg, uint32_t batch) {
+  const uint32_t wave = (blockIdx.x * 256 + threadIdx.x) >> 6, n_waves = (gridDim.x * 256) >> 6, lane = threadIdx.x & 63;
+  for (uint32_t unit = wave; unit < 4 * n_seg; unit += n_waves) {
+    const uint32_t seg = unit >> 2, part = unit & 3, n_win = ws.seg_cnt[seg] & 0xFFFFu;
+    if (lane >= kQuarter) continue;
+    for (uint32_t k = kQuarter * part + lane; k < n_win; k += 4 * kQuarter) {
+      const uint32_t u = seg * ws.seg + k;
+      const int32_t way = ws.u_way[u];
+      if (way < 0) continue;
+      const uint4 rec = ws.rec[u];
+      v.tags[static_cast<uint64_t>(rec.y) * v.w_max + way] = rec.x;
+      v.stamps[static_cast<uint64_t>(rec.y) * v.w_max + way] = batch;
+    }
+  }
+}
+
+template <bool REFILL>
+__global__ __launch_bounds__(256, 8) void miss_settle(EmbView v, MissWs ws, uint32_t bag, uint8_t* __restrict__ out, uint32_t n_seg,
+                                                   uint32_t batch) {
+  if (*ws.any != batch) return;
+  settle_units<REFILL>(v, ws, bag, out, n_seg, batch);
+}
+
+__global__ __launch_bounds__(256) void miss_apply(EmbView v, MissWs ws, uint32_t n_seg, uint32_t batch) {
+  if (*ws.any != batch) return;
+  apply_units(v, ws, n_seg, batch);
+}
+
+// Both in one launch for batches of few stretches, where a launch costs as much as its work: at most kSettleBlocks
+// blocks of 256 threads, a sixteenth of the chip's wavefront slots, so that every block is resident whatever else
+// runs (kernels that do not wait for one another drain), and each waits until all have read the tags they need.  A
+// unit of work is settled and applied by the same wavefront: nothing else passes between blocks.
+constexpr uint32_t kSettleBlocks = 128;
+// Grids of the separate kernels: two rounds of resident blocks for a lookup (whose batch may well have no miss), more
+// for a refill, whose ids are mostly misses or come late in the list (the colder ones): with 1024 blocks the host
+// link idled for the first 0.4 ms of a 4M-id call.
+constexpr uint32_t kSettleGrid = 4096;
+constexpr uint32_t kRefillGrid = 8192;
+__global__ __launch_bounds__(256, 8) void miss_settle_apply(EmbView v, MissWs ws, uint32_t bag, uint8_t* __restrict__ out,
+                                                         uint32_t n_seg, uint32_t batch) {
+  if (*ws.any != batch) return;
+  settle_units<false>(v, ws, bag, out, n_seg, batch);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    __hip_atomic_fetch_add(ws.bar, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    while (__hip_atomic_load(ws.bar, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < gridDim.x) __builtin_amdgcn_s_sleep(1);
+  }
+  __syncthreads();
+  apply_units(v, ws, n_seg, batch);
 }
 
 // ---------------------------------------------------------------------------------------
 // Refill of empty ways (paper Sec. IV-B: new EMB capacity is filled with hot rows in the
-// background).  The probe only finds out which ids are not resident: half a wavefront per id,
-// lane = way, one coalesced read of the set's tag line; nothing is stamped and nothing is
-// written out.  The ids that are not resident then take the miss path with `refill` set.
+// background).  The probe only finds out which ids are not resident: nothing is stamped and
+// nothing is written out.  Eight lanes per id read its set's tag line as 16-byte words, 16 ids
+// in flight per wavefront and step; sets of fewer than 32 ways take four bytes per lane.
+// The ids that are not resident are claimed and settled like misses, on empty ways only.
+// Bound: HBM, 136 bytes per id, and the claims' random atomics: 4M ids, 0.66M of them not resident, 0.26 ms (11 ms when
+// every such id bumped one list counter).
 // ---------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void emb_refill_probe(EmbView v, MissWs ws, const int64_t* __restrict__ ids, uint32_t n) {
-  const uint32_t lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
-  const uint32_t wave = (blockIdx.x * 256 + threadIdx.x) >> 6, n_waves = (gridDim.x * 256) >> 6;
-  if (blockIdx.x == 0 && threadIdx.x < 3) ws.ctr_next[threadIdx.x] = 0;  // the next call's list counters
-  for (uint32_t i0 = wave * 2; i0 < n; i0 += n_waves * 2) {
-    const uint32_t i = i0 + half;
-    const int64_t id = i < n ? ids[i] : -1;
-    const bool valid = id >= 0 && static_cast<uint64_t>(id) < v.rows;
-    bool match = false;
-    if (valid) {
-      const uint32_t set = set_of(v, id);
-      if (l32 < ways_of(v, set)) match = v.tags[static_cast<uint64_t>(set) * v.w_max + l32] == static_cast<uint32_t>(id);
-    }
-    const unsigned long long m = __ballot(match);
-    const bool resident = (half ? static_cast<uint32_t>(m >> 32) : static_cast<uint32_t>(m)) != 0;
-    if (l32 == 0 && valid && !resident) ws.miss_list[atomicAdd(&ws.ctr[0], 1u)] = i;
+constexpr uint32_t kRefillRounds = 4;
+constexpr uint32_t kRefillPerBlock = 32 * kRefillRounds;
+__global__ __launch_bounds__(256) void emb_refill_probe(EmbView v, MissWs ws, IdSrc ids, uint32_t n, uint32_t batch) {
+  __shared__ uint2 s_miss[kRefillPerBlock];
+  __shared__ uint4 s_win[kRefillPerBlock];
+  __shared__ uint32_t s_n[3];
+  const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, grp = lane >> 3, j = lane & 7;
+  if (tid < 3) s_n[tid] = 0;
+  __syncthreads();
+  uint32_t idx[kRefillRounds], id32[kRefillRounds], nw[kRefillRounds];
+  uint64_t line[kRefillRounds];
+  int64_t id[kRefillRounds];
+  bool valid[kRefillRounds];
+  {
+    uint64_t at[kRefillRounds];
+#pragma unroll
+    for (uint32_t r = 0; r < kRefillRounds; ++r) at[r] = static_cast<uint64_t>(blockIdx.x) * kRefillPerBlock + (r * 4 + wave) * 8 + grp;
+    load_ids<kRefillRounds>(v, ids, at, n, id);
+#pragma unroll
+    for (uint32_t r = 0; r < kRefillRounds; ++r) idx[r] = static_cast<uint32_t>(at[r]);
   }
+#pragma unroll
+  for (uint32_t r = 0; r < kRefillRounds; ++r) {
+    valid[r] = id[r] >= 0 && static_cast<uint64_t>(id[r]) < v.rows;
+    id32[r] = static_cast<uint32_t>(id[r]);
+    const uint32_t set = valid[r] ? set_of(v, id[r]) : 0;
+    nw[r] = valid[r] ? ways_of(v, set) : 0;
+    line[r] = static_cast<uint64_t>(set) * v.w_max;
+  }
+  bool match[kRefillRounds];
+  if (v.w_max == 32) {
+    uint4 t[kRefillRounds];
+#pragma unroll
+    for (uint32_t r = 0; r < kRefillRounds; ++r) {
+      t[r] = make_uint4(0, 0, 0, 0);
+      if (4 * j < nw[r]) t[r] = *reinterpret_cast<const uint4*>(v.tags + line[r] + 4 * j);
+    }
+#pragma unroll
+    for (uint32_t r = 0; r < kRefillRounds; ++r)
+      match[r] = (4 * j < nw[r] && t[r].x == id32[r]) || (4 * j + 1 < nw[r] && t[r].y == id32[r]) ||
+                 (4 * j + 2 < nw[r] && t[r].z == id32[r]) || (4 * j + 3 < nw[r] && t[r].w == id32[r]);
+  } else {
+#pragma unroll
+    for (uint32_t r = 0; r < kRefillRounds; ++r) {
+      match[r] = false;
+      for (uint32_t w = j; w < nw[r]; w += 8) match[r] |= v.tags[line[r] + w] == id32[r];
+    }
+  }
+#pragma unroll
+  for (uint32_t r = 0; r < kRefillRounds; ++r) {
+    const unsigned long long m = __ballot(match[r]);
+    const bool resident = (m >> (8 * grp) & 0xFFull) != 0;
+    if (j == 0 && valid[r] && !resident) s_miss[atomicAdd(&s_n[0], 1u)] = make_uint2(idx[r], id32[r]);
+  }
+  __syncthreads();
+  miss_tail<false, false>(v, ws, batch, s_miss, s_n[0], s_win, &s_n[1], nullptr);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -813,19 +1016,6 @@ __global__ __launch_bounds__(256) void emb_shrink_sets(EmbView v, uint32_t old_f
   }
 }
 
-// (table, row) pairs -> global ids of the rows; -1 where the table or the row does not exist
-__global__ void emb_global_ids(EmbView v, const uint32_t* __restrict__ table_of, const int64_t* __restrict__ ids,
-                               uint32_t n, int64_t* __restrict__ gids) {
-  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-    const uint32_t t = table_of[i];
-    const int64_t id = ids[i];
-    int64_t gid = -1;
-    if (t < v.n_tables && id >= 0 && static_cast<uint64_t>(id) < v.tables[t].rows)
-      gid = static_cast<int64_t>(v.tables[t].base) + id;
-    gids[i] = gid;
-  }
-}
-
 // Measurement aid: what the memory system gives a gather.  Groups of LPR lanes read rows of LPR * 16 bytes picked by
 // a counter-based hash out of [base, base + n_rows rows), ROUNDS rows in flight per group, and (optionally) write
 // them out back to back.  No cache helps when the region is much larger than the caches.
@@ -884,12 +1074,13 @@ hipError_t launch_fill_u32(uint32_t* p, uint64_t n, uint32_t value, hipStream_t 
   return hipGetLastError();
 }
 
-hipError_t launch_emb_probe(const EmbView& v, const MissWs& ws, const int64_t* ids, uint32_t n, uint32_t bag,
-                            uint8_t* out, uint8_t* hit_flags, uint32_t batch, hipStream_t stream) {
+hipError_t launch_emb_probe(const EmbView& v, MissWs& ws, const IdSrc& ids, uint32_t n, uint32_t bag, uint8_t* out,
+                            uint8_t* hit_flags, uint32_t batch, hipStream_t stream) {
   if (n == 0) return hipSuccess;
+  const dim3 block(256);
   if (bag == 1 && v.w_max == 32 && v.row_bytes % 128 == 0 && v.row_bytes <= 1024) {
-    const uint32_t per_block = 32 * kW32Rounds;
-    const dim3 grid((n + per_block - 1) / per_block), block(256);
+    ws.seg = 32 * kW32Rounds;
+    const dim3 grid((n + ws.seg - 1) / ws.seg);
     switch (v.row_bytes / 128) {
 #define RACER_W32_CASE(P) \
   case P: hipLaunchKernelGGL(emb_probe_gather_w32<P>, grid, block, 0, stream, v, ws, ids, n, out, hit_flags, batch); break;
@@ -897,58 +1088,46 @@ hipError_t launch_emb_probe(const EmbView& v, const MissWs& ws, const int64_t* i
       RACER_W32_CASE(5) RACER_W32_CASE(6) RACER_W32_CASE(7) RACER_W32_CASE(8)
 #undef RACER_W32_CASE
     }
-    return hipGetLastError();
-  }
-  if ((bag == 2 || bag == 4 || bag == 8) && v.w_max == 32 && v.row_bytes % 128 == 0 && v.row_bytes <= 512) {
-    const dim3 grid((n + 127) / 128), block(256);  // 128 lookups per block
+  } else if ((bag == 2 || bag == 4 || bag == 8) && v.w_max == 32 && v.row_bytes % 128 == 0 && v.row_bytes <= 512) {
+    ws.seg = 128;
+    const dim3 grid((n + ws.seg - 1) / ws.seg);
     switch (v.row_bytes / 128) {
 #define RACER_W32_BAG_CASE(P) \
   case P: hipLaunchKernelGGL(emb_probe_gather_w32_bag<P>, grid, block, 0, stream, v, ws, ids, n, bag, out, hit_flags, batch); break;
       RACER_W32_BAG_CASE(1) RACER_W32_BAG_CASE(2) RACER_W32_BAG_CASE(3) RACER_W32_BAG_CASE(4)
 #undef RACER_W32_BAG_CASE
     }
-    return hipGetLastError();
+  } else {
+    const uint32_t lb = (64 / bag) * bag;
+    ws.seg = 4 * lb;
+    hipLaunchKernelGGL(emb_probe_gather, dim3((n + ws.seg - 1) / ws.seg), block, 0, stream, v, ws, ids, n, bag, lb, out, hit_flags, batch);
   }
-  const uint32_t lb = (64 / bag) * bag;
-  const uint32_t per_block = 4 * lb;
-  const uint32_t blocks = (n + per_block - 1) / per_block;
-  hipLaunchKernelGGL(emb_probe_gather, dim3(blocks), dim3(256), 0, stream, v, ws, ids, n, bag, lb, out, hit_flags, batch);
   return hipGetLastError();
 }
 
-hipError_t launch_emb_miss_path(const EmbView& v, const MissWs& ws, const int64_t* ids, uint32_t n, uint32_t bag,
-                                uint8_t* out, uint32_t batch, hipStream_t stream) {
+hipError_t launch_emb_miss_path(const EmbView& v, const MissWs& ws, uint32_t n, uint32_t bag, uint8_t* out, uint32_t batch,
+                                hipStream_t stream) {
   if (n == 0) return hipSuccess;
-  // the miss kernels size themselves from device counters; a modest grid keeps the
-  // no-miss case cheap and still saturates PCIe when a cold batch arrives
-  const uint32_t mblocks = n / 256 + 1 < 1024 ? n / 256 + 1 : 1024;
-  hipLaunchKernelGGL(miss_dedupe, dim3(mblocks), dim3(256), 0, stream, ws, ids, batch);
-  hipLaunchKernelGGL(miss_link, dim3(mblocks), dim3(256), 0, stream, v, ws, ids, batch);
-  hipLaunchKernelGGL(miss_decide, dim3(mblocks), dim3(256), 0, stream, v, ws, batch, false);
-  hipLaunchKernelGGL(miss_resolve, dim3(mblocks), dim3(256), 0, stream, ws, ids, batch);
-  hipLaunchKernelGGL(miss_apply_fetch, dim3(mblocks), dim3(256), 0, stream, v, ws, batch, false);
-  hipLaunchKernelGGL(emb_deferred_gather, dim3(mblocks), dim3(256), 0, stream, v, ws, bag, out);
+  const dim3 block(256);
+  const uint32_t n_seg = (n + ws.seg - 1) / ws.seg;
+  if (n_seg <= 4 * kSettleBlocks) {  // one launch, four units per wavefront at most
+    hipLaunchKernelGGL(miss_settle_apply, dim3(n_seg < kSettleBlocks ? n_seg : kSettleBlocks), block, 0, stream, v, ws, bag, out, n_seg, batch);
+  } else {
+    const dim3 grid(n_seg < kSettleGrid ? n_seg : kSettleGrid);  // four units (quarters of a stretch) per block and pass
+    hipLaunchKernelGGL(miss_settle<false>, grid, block, 0, stream, v, ws, bag, out, n_seg, batch);
+    hipLaunchKernelGGL(miss_apply, grid, block, 0, stream, v, ws, n_seg, batch);
+  }
   return hipGetLastError();
 }
 
-hipError_t launch_emb_global_ids(const EmbView& v, const uint32_t* table_of, const int64_t* ids, uint32_t n, int64_t* gids,
-                                 hipStream_t stream) {
+hipError_t launch_emb_refill(const EmbView& v, MissWs ws, const IdSrc& ids, uint32_t n, uint32_t batch, hipStream_t stream) {
   if (n == 0) return hipSuccess;
-  const uint32_t blocks = n / 256 + 1 < 2048 ? n / 256 + 1 : 2048;
-  hipLaunchKernelGGL(emb_global_ids, dim3(blocks), dim3(256), 0, stream, v, table_of, ids, n, gids);
-  return hipGetLastError();
-}
-
-hipError_t launch_emb_refill(const EmbView& v, const MissWs& ws, const int64_t* ids, uint32_t n, uint32_t batch,
-                             hipStream_t stream) {
-  if (n == 0) return hipSuccess;
-  const uint32_t pblocks = n / 8 + 1 < 2048 ? n / 8 + 1 : 2048;  // two ids per wavefront and pass
-  const uint32_t mblocks = n / 256 + 1 < 1024 ? n / 256 + 1 : 1024;
-  hipLaunchKernelGGL(emb_refill_probe, dim3(pblocks), dim3(256), 0, stream, v, ws, ids, n);
-  hipLaunchKernelGGL(miss_dedupe, dim3(mblocks), dim3(256), 0, stream, ws, ids, batch);
-  hipLaunchKernelGGL(miss_link, dim3(mblocks), dim3(256), 0, stream, v, ws, ids, batch);
-  hipLaunchKernelGGL(miss_decide, dim3(mblocks), dim3(256), 0, stream, v, ws, batch, true);
-  hipLaunchKernelGGL(miss_apply_fetch, dim3(mblocks), dim3(256), 0, stream, v, ws, batch, true);
+  ws.seg = kRefillPerBlock;
+  const uint32_t n_seg = (n + ws.seg - 1) / ws.seg;
+  const dim3 grid(n_seg < kRefillGrid ? n_seg : kRefillGrid), block(256);
+  hipLaunchKernelGGL(emb_refill_probe, dim3(n_seg), block, 0, stream, v, ws, ids, n, batch);
+  hipLaunchKernelGGL(miss_settle<true>, grid, block, 0, stream, v, ws, 1u, nullptr, n_seg, batch);
+  hipLaunchKernelGGL(miss_apply, grid, block, 0, stream, v, ws, n_seg, batch);
   return hipGetLastError();
 }
 

@@ -52,36 +52,46 @@ struct EmbView {
   unsigned long long* counters;
 };
 
-// Per-call scratch of the miss path.  ctr points at three zeroed words:
-// [0] misses listed, [1] deferred output rows, [2] unique misses.
-struct MissWs {
-  uint32_t* ctr;
-  uint32_t* ctr_next;       // the other parity's words, zeroed by the probe kernel
-  uint32_t* miss_list;      // lookup indices that missed
-  uint32_t* def_list;       // output rows that wait for a miss
-  int64_t* loc;             // per lookup of a deferred row: >=0 pool byte offset, -1 zero row, <=-3 staging row -(v+3)
-  unsigned long long* hkeys;  // id dedupe table: (batch << 32) | id
-  unsigned long long* hvals;  // (batch << 32) | (0xFFFFFFFF - first lookup index)
-  uint32_t* hslot_u;          // unique-miss number of the table slot
-  uint32_t hmask;
-  unsigned long long* heads;  // per-set chains of unique misses: (batch << 32) | unique number
-  uint32_t headmask;
-  uint32_t* u_i;
-  uint32_t* u_id;
-  uint32_t* u_set;
-  int32_t* u_next;
-  int32_t* u_way;
-  uint8_t* staging;         // [unique][row_bytes] rows fetched from the host table
+// Lookup ids: int64 row numbers, or (table, row) pairs when table_of is set.
+struct IdSrc {
+  const int64_t* ids;
+  const uint32_t* table_of;
 };
 
-hipError_t launch_emb_probe(const EmbView& v, const MissWs& ws, const int64_t* ids, uint32_t n, uint32_t bag,
-                            uint8_t* out, uint8_t* hit_flags, uint32_t batch, hipStream_t stream);
-hipError_t launch_emb_miss_path(const EmbView& v, const MissWs& ws, const int64_t* ids, uint32_t n, uint32_t bag,
-                                uint8_t* out, uint32_t batch, hipStream_t stream);
+// Entry of the dedupe table: key = (batch << 32) | id, val = (batch << 32) | (0xFFFFFFFF - first lookup index).
+struct HashEnt {
+  unsigned long long key, val;
+};
+
+// Scratch of the miss path.  A probe block lists what it finds in its own stretch of the lists: block b owns
+// [b * seg, (b + 1) * seg) of the per-lookup arrays.  Tables are keyed by the batch number, so nothing is cleared
+// between calls on one pool.
+struct MissWs {
+  uint32_t seg;             // lookups per probe block (set by the probe's launch)
+  uint32_t* any;            // = batch when some block of the batch had a miss
+  uint32_t* bar;            // arrivals at the settle kernel's barrier, zeroed by the probe
+  uint32_t* seg_cnt;        // per stretch: (waiting output rows << 16) | new ids
+  uint32_t* def_list;       // output rows that wait for a miss
+  int64_t* loc;             // per lookup of a waiting row: >=0 pool byte offset, -1 zero row, <=-3 dedupe slot -(v+3)
+  HashEnt* hents;
+  uint32_t* hslot_u;        // number of the new id in a dedupe slot
+  uint32_t hmask;
+  unsigned long long* heads;  // per-set chains of new ids: (batch << 32) | number
+  uint32_t headmask;
+  uint4* rec;               // per new id: id, set, next in the chain (0xFFFFFFFF: last), dedupe slot
+  int32_t* u_way;           // the way it takes, -1: none
+  uint8_t* staging;         // its row, fetched from the host table
+};
+
+// probe, hit gather, missing rows fetched into staging; sets ws.seg for the miss path that follows
+hipError_t launch_emb_probe(const EmbView& v, MissWs& ws, const IdSrc& ids, uint32_t n, uint32_t bag, uint8_t* out,
+                            uint8_t* hit_flags, uint32_t batch, hipStream_t stream);
+// cache insertion of the new ids and the output rows that waited for them
+hipError_t launch_emb_miss_path(const EmbView& v, const MissWs& ws, uint32_t n, uint32_t bag, uint8_t* out, uint32_t batch,
+                                hipStream_t stream);
 
 // refill of empty ways with `ids` (hottest first): probe, then the miss path restricted to empty ways
-hipError_t launch_emb_refill(const EmbView& v, const MissWs& ws, const int64_t* ids, uint32_t n, uint32_t batch,
-                             hipStream_t stream);
+hipError_t launch_emb_refill(const EmbView& v, MissWs ws, const IdSrc& ids, uint32_t n, uint32_t batch, hipStream_t stream);
 
 hipError_t launch_emb_shrink(const EmbView& v, uint32_t old_full, uint32_t old_part_sets,
                              hipStream_t stream);
@@ -92,10 +102,6 @@ hipError_t launch_fill_u32(uint32_t* p, uint64_t n, uint32_t value, hipStream_t 
 // written out back to back at `out` unless that is null
 hipError_t launch_random_row_reads(const void* base, uint64_t n_rows, uint32_t row_bytes, uint64_t n_reads, void* out,
                                    uint64_t seed, hipStream_t stream);
-
-// (table, row) pairs -> global ids (-1 for a table or row that does not exist)
-hipError_t launch_emb_global_ids(const EmbView& v, const uint32_t* table_of, const int64_t* ids, uint32_t n, int64_t* gids,
-                                 hipStream_t stream);
 
 // ---- HSTU -----------------------------------------------------------------------------
 struct HstuDims {

@@ -133,16 +133,17 @@ constexpr uint64_t kNoallocMaxLookups = RACER_NOALLOC_MAX_LOOKUPS;
 constexpr uint64_t kNoallocStagingBytes = RACER_NOALLOC_MAX_ROW_BYTES_TOTAL;
 constexpr uint64_t kNoallocHash = 2 * kNoallocMaxLookups;  // slots of the dedupe table and of the set-chain heads
 constexpr uint64_t align256(uint64_t x) { return (x + 255) & ~255ull; }
-constexpr uint64_t kOffCtr = 0;                                                   // 8 x u32
-constexpr uint64_t kOffMissList = 256;                                            // u32 [lookups]
-constexpr uint64_t kOffDefList = kOffMissList + align256(4 * kNoallocMaxLookups);  // u32 [lookups]
-constexpr uint64_t kOffLoc = kOffDefList + align256(4 * kNoallocMaxLookups);       // i64 [lookups]
-constexpr uint64_t kOffHkeys = kOffLoc + align256(8 * kNoallocMaxLookups);         // u64 [hash]
-constexpr uint64_t kOffHvals = kOffHkeys + align256(8 * kNoallocHash);             // u64 [hash]
-constexpr uint64_t kOffHeads = kOffHvals + align256(8 * kNoallocHash);             // u64 [hash]
-constexpr uint64_t kOffHslot = kOffHeads + align256(8 * kNoallocHash);             // u32 [hash]
-constexpr uint64_t kOffUi = kOffHslot + align256(4 * kNoallocHash);                // five u32 / i32 [lookups]
-constexpr uint64_t kOffStaging = kOffUi + 5 * align256(4 * kNoallocMaxLookups);
+// control words, dedupe table and chain heads come first, one after the other for the table size of the call, so that
+// one fill clears them
+constexpr uint64_t kOffHents = 256;
+constexpr uint64_t kClearBytes = sizeof(racer::HashEnt) + sizeof(unsigned long long);  // per table slot
+constexpr uint64_t kOffSegCnt = kOffHents + align256(kClearBytes * kNoallocHash);   // u32 [lookups / 64 + 2]
+constexpr uint64_t kOffDefList = kOffSegCnt + align256(4 * (kNoallocMaxLookups / 64 + 2));  // u32 [lookups]
+constexpr uint64_t kOffLoc = kOffDefList + align256(4 * kNoallocMaxLookups);        // i64 [lookups]
+constexpr uint64_t kOffHslot = kOffLoc + align256(8 * kNoallocMaxLookups);          // u32 [hash]
+constexpr uint64_t kOffRec = kOffHslot + align256(4 * kNoallocHash);                // uint4 [lookups]
+constexpr uint64_t kOffWay = kOffRec + align256(16 * kNoallocMaxLookups);           // i32 [lookups]
+constexpr uint64_t kOffStaging = kOffWay + align256(4 * kNoallocMaxLookups);
 constexpr uint64_t kScratchBytes = kOffStaging + kNoallocStagingBytes;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
@@ -180,16 +181,12 @@ struct racer_pool {
   // every table behind the pool (the first is pool_create's); the device copy exists once a second one was added
   std::vector<racer::TableDesc> tables;
   racer::TableDesc* d_tables = nullptr;
-  int64_t* gid_buf = nullptr;  // global ids of a multi-table lookup
-  uint64_t gid_cap = 0;
   Staging stage;
   uint32_t batch = 0;
   uint64_t ws_allocs = 0;  // device work-space (re)allocations so far (pool_reserve keeps later calls from adding any)
-  uint64_t launches = 0;  // emb_lookup calls that reached the device (selects the list-counter parity)
   hipStream_t last_stream = nullptr;
   // miss-path workspace, grown on demand
   uint64_t ws_cap = 0;
-  uint32_t* ws_ctr = nullptr;
   racer::MissWs ws{};
   // hstu workspace
   uint64_t hw_slot = 0;  // bytes of each of the six activation matrices of a step
@@ -272,12 +269,9 @@ struct ProfScope {
 
 void free_miss_ws(racer_pool* p) {
   racer::MissWs& w = p->ws;
-  (void)hipFree(p->ws_ctr);
-  (void)hipFree(w.miss_list); (void)hipFree(w.def_list); (void)hipFree(w.loc); (void)hipFree(w.hkeys); (void)hipFree(w.hvals);
-  (void)hipFree(w.hslot_u); (void)hipFree(w.heads); (void)hipFree(w.u_i); (void)hipFree(w.u_id); (void)hipFree(w.u_set);
-  (void)hipFree(w.u_next); (void)hipFree(w.u_way); (void)hipFree(w.staging);
+  (void)hipFree(w.any); (void)hipFree(w.seg_cnt); (void)hipFree(w.def_list); (void)hipFree(w.loc); (void)hipFree(w.hents);
+  (void)hipFree(w.hslot_u); (void)hipFree(w.heads); (void)hipFree(w.rec); (void)hipFree(w.u_way); (void)hipFree(w.staging);
   p->ws = racer::MissWs{};
-  p->ws_ctr = nullptr;
   p->ws_cap = 0;
 }
 
@@ -293,18 +287,15 @@ int32_t ensure_miss_ws(racer_pool* p, uint64_t n, hipStream_t stream) {
   p->ws_allocs += 1;
   racer::MissWs& w = p->ws;
   int32_t rc;
-  if ((rc = dev_alloc(&p->ws_ctr, 8, true, stream))) return rc;
-  if ((rc = dev_alloc(&w.miss_list, cap, false, stream))) return rc;
+  if ((rc = dev_alloc(&w.any, 64, true, stream))) return rc;
+  w.bar = w.any + 32;  // a cache line of its own
+  if ((rc = dev_alloc(&w.seg_cnt, cap / 64 + 2, false, stream))) return rc;
   if ((rc = dev_alloc(&w.def_list, cap, false, stream))) return rc;
   if ((rc = dev_alloc(&w.loc, cap, false, stream))) return rc;
-  if ((rc = dev_alloc(&w.hkeys, hsize, true, stream))) return rc;
-  if ((rc = dev_alloc(&w.hvals, hsize, true, stream))) return rc;
+  if ((rc = dev_alloc(&w.hents, hsize, true, stream))) return rc;
   if ((rc = dev_alloc(&w.hslot_u, hsize, false, stream))) return rc;
   if ((rc = dev_alloc(&w.heads, hsize, true, stream))) return rc;
-  if ((rc = dev_alloc(&w.u_i, cap, false, stream))) return rc;
-  if ((rc = dev_alloc(&w.u_id, cap, false, stream))) return rc;
-  if ((rc = dev_alloc(&w.u_set, cap, false, stream))) return rc;
-  if ((rc = dev_alloc(&w.u_next, cap, false, stream))) return rc;
+  if ((rc = dev_alloc(&w.rec, cap, false, stream))) return rc;
   if ((rc = dev_alloc(&w.u_way, cap, false, stream))) return rc;
   if ((rc = dev_alloc(&w.staging, cap * p->cfg.row_bytes, false, stream))) return rc;
   w.hmask = static_cast<uint32_t>(hsize - 1);
@@ -313,22 +304,8 @@ int32_t ensure_miss_ws(racer_pool* p, uint64_t n, hipStream_t stream) {
   return RACER_OK;
 }
 
-
 // The remaining work spaces grow on demand (a growth waits for the streams that may still use the old buffer);
 // pool_reserve sizes them all ahead of time.
-int32_t ensure_gid(racer_pool* p, uint64_t n) {  // global ids of a multi-table lookup
-  if (n <= p->gid_cap) return RACER_OK;
-  HIP_TRY(hipStreamSynchronize(p->last_stream));
-  if (p->gid_buf) HIP_TRY(hipFree(p->gid_buf));
-  p->gid_buf = nullptr;
-  p->gid_cap = 0;
-  const uint64_t cap = std::max<uint64_t>(n, 1024);
-  HIP_TRY(hipMalloc(reinterpret_cast<void**>(&p->gid_buf), cap * sizeof(int64_t)));
-  p->gid_cap = cap;
-  p->ws_allocs += 1;
-  return RACER_OK;
-}
-
 int32_t ensure_partials(racer_pool* p, uint64_t bytes, hipStream_t stream) {  // fp32 partials of split attention items
   if (bytes <= p->hp_cap) return RACER_OK;
   HIP_TRY(hipStreamSynchronize(p->last_stream));
@@ -456,7 +433,6 @@ int32_t pool_destroy(racer_pool_t* p) {
       }
     if (p->ev_fork) (void)hipEventDestroy(p->ev_fork);
     (void)hipFree(p->d_tables);
-    (void)hipFree(p->gid_buf);
     (void)hipFree(p->d_tags);
     (void)hipFree(p->d_stamps);
     (void)hipFree(p->d_emb_pages);
@@ -576,31 +552,36 @@ int32_t kv_seq_pin(racer_pool_t* p, uint64_t key) { return p ? p->host.pin(key) 
 int32_t kv_seq_unpin(racer_pool_t* p, uint64_t key) { return p ? p->host.unpin(key) : RACER_EINVAL; }
 int32_t kv_seq_release(racer_pool_t* p, uint64_t key) { return p ? p->host.release(key) : RACER_EINVAL; }
 
-int32_t emb_lookup(racer_pool_t* p, const int64_t* ids, uint64_t n, uint32_t bag, void* out, uint8_t* hit_flags, void* stream_v) {
-  if (!p || !p->device || !p->d_table) return RACER_EINVAL;
+}  // extern "C"
+
+namespace {
+
+// emb_lookup and emb_lookup_tables: `ids` names the rows, the rest is the same.
+int32_t lookup(racer_pool* p, const racer::IdSrc& ids, uint64_t n, uint32_t bag, void* out, uint8_t* hit_flags, hipStream_t stream) {
   if (bag == 0 || bag > 64 || n % bag != 0 || n >= 0xFFFFFFFFull) return RACER_EINVAL;
-  if (n && (!ids || !out)) return RACER_EINVAL;
-  hipStream_t stream = static_cast<hipStream_t>(stream_v);
+  if (n && (!ids.ids || !out)) return RACER_EINVAL;
   p->batch += 1;  // one call = one LRU batch, empty or not
   if (n == 0) return RACER_OK;
   int32_t rc = ensure_miss_ws(p, n, stream);
   if (rc) return rc;
-  racer::MissWs ws = p->ws;
-  ws.ctr = p->ws_ctr + 4 * (p->launches & 1);
-  ws.ctr_next = p->ws_ctr + 4 * ((p->launches + 1) & 1);
-  p->launches += 1;
   p->last_stream = stream;
+  const racer::EmbView v = p->view();
   {
     ProfScope t(p, RACER_PROF_EMB_GATHER, stream);
-    HIP_TRY(racer::launch_emb_probe(p->view(), ws, ids, static_cast<uint32_t>(n), bag, static_cast<uint8_t*>(out),
-                                    hit_flags, p->batch, stream));
+    HIP_TRY(racer::launch_emb_probe(v, p->ws, ids, static_cast<uint32_t>(n), bag, static_cast<uint8_t*>(out), hit_flags, p->batch, stream));
   }
-  {
-    ProfScope t(p, RACER_PROF_EMB_MISS, stream);
-    HIP_TRY(racer::launch_emb_miss_path(p->view(), ws, ids, static_cast<uint32_t>(n), bag, static_cast<uint8_t*>(out),
-                                        p->batch, stream));
-  }
+  ProfScope t(p, RACER_PROF_EMB_MISS, stream);
+  HIP_TRY(racer::launch_emb_miss_path(v, p->ws, static_cast<uint32_t>(n), bag, static_cast<uint8_t*>(out), p->batch, stream));
   return RACER_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+int32_t emb_lookup(racer_pool_t* p, const int64_t* ids, uint64_t n, uint32_t bag, void* out, uint8_t* hit_flags, void* stream_v) {
+  if (!p || !p->device || !p->d_table) return RACER_EINVAL;
+  return lookup(p, racer::IdSrc{ids, nullptr}, n, bag, out, hit_flags, static_cast<hipStream_t>(stream_v));
 }
 
 int32_t emb_lookup_noalloc(racer_pool_t* p, const int64_t* ids, uint64_t n, uint32_t bag, void* out, uint8_t* hit_flags,
@@ -622,35 +603,26 @@ int32_t emb_lookup_noalloc(racer_pool_t* p, const int64_t* ids, uint64_t n, uint
   uint64_t hsize = 2048;
   while (hsize < 2 * n) hsize <<= 1;  // <= kNoallocHash
   racer::MissWs ws{};
-  ws.ctr = reinterpret_cast<uint32_t*>(base + kOffCtr);
-  ws.ctr_next = ws.ctr + 4;
-  ws.miss_list = reinterpret_cast<uint32_t*>(base + kOffMissList);
+  ws.any = reinterpret_cast<uint32_t*>(base);
+  ws.bar = ws.any + 32;
+  ws.hents = reinterpret_cast<racer::HashEnt*>(base + kOffHents);
+  ws.heads = reinterpret_cast<unsigned long long*>(ws.hents + hsize);
+  ws.hmask = ws.headmask = static_cast<uint32_t>(hsize - 1);
+  ws.seg_cnt = reinterpret_cast<uint32_t*>(base + kOffSegCnt);
   ws.def_list = reinterpret_cast<uint32_t*>(base + kOffDefList);
   ws.loc = reinterpret_cast<int64_t*>(base + kOffLoc);
-  ws.hkeys = reinterpret_cast<unsigned long long*>(base + kOffHkeys);
-  ws.hvals = reinterpret_cast<unsigned long long*>(base + kOffHvals);
-  ws.heads = reinterpret_cast<unsigned long long*>(base + kOffHeads);
   ws.hslot_u = reinterpret_cast<uint32_t*>(base + kOffHslot);
-  ws.hmask = ws.headmask = static_cast<uint32_t>(hsize - 1);
-  const uint64_t list = align256(4 * kNoallocMaxLookups);
-  ws.u_i = reinterpret_cast<uint32_t*>(base + kOffUi);
-  ws.u_id = reinterpret_cast<uint32_t*>(base + kOffUi + list);
-  ws.u_set = reinterpret_cast<uint32_t*>(base + kOffUi + 2 * list);
-  ws.u_next = reinterpret_cast<int32_t*>(base + kOffUi + 3 * list);
-  ws.u_way = reinterpret_cast<int32_t*>(base + kOffUi + 4 * list);
+  ws.rec = reinterpret_cast<uint4*>(base + kOffRec);
+  ws.u_way = reinterpret_cast<int32_t*>(base + kOffWay);
   ws.staging = base + kOffStaging;
-  // The array keeps the last call's contents, whichever pool made it: the list counters and the three tables
-  // whose entries are told apart by the batch number must start at zero.  Fill kernels, so that the call can
-  // be captured into a graph.
-  HIP_TRY(racer::launch_fill_u32(ws.ctr, 8, 0u, stream));
-  HIP_TRY(racer::launch_fill_u32(reinterpret_cast<uint32_t*>(ws.hkeys), 2 * hsize, 0u, stream));
-  HIP_TRY(racer::launch_fill_u32(reinterpret_cast<uint32_t*>(ws.hvals), 2 * hsize, 0u, stream));
-  HIP_TRY(racer::launch_fill_u32(reinterpret_cast<uint32_t*>(ws.heads), 2 * hsize, 0u, stream));
+  // The array keeps the last call's contents, whichever pool made it: the two tables whose entries are told apart by
+  // the batch number must start at zero.  A fill kernel, so that the call can be captured into a graph.
+  HIP_TRY(racer::launch_fill_u32(ws.any, (kOffHents + kClearBytes * hsize) / 4, 0u, stream));
   p->last_stream = stream;
-  HIP_TRY(racer::launch_emb_probe(p->view(), ws, ids, static_cast<uint32_t>(n), bag, static_cast<uint8_t*>(out), hit_flags,
-                                  p->batch, stream));
-  HIP_TRY(racer::launch_emb_miss_path(p->view(), ws, ids, static_cast<uint32_t>(n), bag, static_cast<uint8_t*>(out), p->batch,
-                                      stream));
+  const racer::EmbView v = p->view();
+  HIP_TRY(racer::launch_emb_probe(v, ws, racer::IdSrc{ids, nullptr}, static_cast<uint32_t>(n), bag, static_cast<uint8_t*>(out),
+                                  hit_flags, p->batch, stream));
+  HIP_TRY(racer::launch_emb_miss_path(v, ws, static_cast<uint32_t>(n), bag, static_cast<uint8_t*>(out), p->batch, stream));
   return RACER_OK;
 }
 
@@ -685,11 +657,7 @@ int32_t emb_lookup_tables(racer_pool_t* p, const uint32_t* table_of, const int64
   if (!p || !p->device || !p->d_table) return RACER_EINVAL;
   if (n >= 0xFFFFFFFFull || (n && (!table_of || !ids))) return RACER_EINVAL;
   if (p->tables.size() < 2) return RACER_EINVAL;  // one table: emb_lookup
-  hipStream_t stream = static_cast<hipStream_t>(stream_v);
-  int32_t rc_g = ensure_gid(p, n);
-  if (rc_g) return rc_g;
-  HIP_TRY(racer::launch_emb_global_ids(p->view(), table_of, ids, static_cast<uint32_t>(n), p->gid_buf, stream));
-  return emb_lookup(p, p->gid_buf, n, bag, out, hit_flags, stream_v);
+  return lookup(p, racer::IdSrc{ids, table_of}, n, bag, out, hit_flags, static_cast<hipStream_t>(stream_v));
 }
 
 int32_t emb_refill(racer_pool_t* p, const int64_t* ids, uint64_t n, void* stream_v) {
@@ -700,13 +668,9 @@ int32_t emb_refill(racer_pool_t* p, const int64_t* ids, uint64_t n, void* stream
   if (n == 0) return RACER_OK;
   int32_t rc = ensure_miss_ws(p, n, stream);
   if (rc) return rc;
-  racer::MissWs ws = p->ws;
-  ws.ctr = p->ws_ctr + 4 * (p->launches & 1);
-  ws.ctr_next = p->ws_ctr + 4 * ((p->launches + 1) & 1);
-  p->launches += 1;
   p->last_stream = stream;
   ProfScope t(p, RACER_PROF_EMB_MISS, stream);
-  HIP_TRY(racer::launch_emb_refill(p->view(), ws, ids, static_cast<uint32_t>(n), p->batch, stream));
+  HIP_TRY(racer::launch_emb_refill(p->view(), p->ws, racer::IdSrc{ids, nullptr}, static_cast<uint32_t>(n), p->batch, stream));
   return RACER_OK;
 }
 
@@ -1058,7 +1022,6 @@ int32_t pool_reserve(racer_pool_t* p, const racer_hstu_t* m, const racer_reserve
   if (r->max_lookups) {
     if (r->max_lookups >= 0xFFFFFFFFull) return RACER_EINVAL;
     if ((rc = ensure_miss_ws(p, r->max_lookups, stream))) return rc;
-    if ((rc = ensure_gid(p, r->max_lookups))) return rc;
   }
   if (m && r->max_requests) {
     const racer_hstu_cfg& c = m->cfg;

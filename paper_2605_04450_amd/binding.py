@@ -152,15 +152,23 @@ def _dp(t):
     if t is None:
         return None
     if isinstance(t, np.ndarray):
-        return t.ctypes.data_as(C.c_void_p)
-    return C.c_void_p(t.data_ptr())
+        return t.ctypes.data
+    return t.data_ptr()
+
+
+_raw_stream = None  # the current stream's handle of a device without a stream object around it
 
 
 def _stream_ptr(stream):
+    global _raw_stream
     if stream is None:
-        import torch
-        return C.c_void_p(torch.cuda.current_stream().cuda_stream)
-    return C.c_void_p(stream if isinstance(stream, int) else stream.cuda_stream)
+        if _raw_stream is None:
+            import torch
+            torch.cuda.current_stream()  # initialises the device
+            get = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+            _raw_stream = (lambda: get(torch.cuda.current_device())) if get else (lambda: torch.cuda.current_stream().cuda_stream)
+        return _raw_stream()
+    return stream if isinstance(stream, int) else stream.cuda_stream
 
 
 def pool_create(dev_base, nbytes, page_size, row_bytes, elem, page_tokens, w_max=32, host_table=None, rows=0,

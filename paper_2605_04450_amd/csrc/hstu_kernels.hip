@@ -16,6 +16,9 @@
 //   [layer][K|V][head] blocks of page_tokens*d_h elements;
 //   a K block is [token][d_h]; a V block is stored transposed, [d_h][token], so that the
 //   second product's matrix operand (contraction over keys) is read key-contiguous.
+#include <type_traits>
+#include <utility>
+
 #include "kernels.h"
 
 namespace racer {
@@ -28,6 +31,8 @@ struct bf16_t { uint16_t bits; };
 struct half_t { uint16_t bits; };  // IEEE binary16 (the library's own intermediates)
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));  // like uint4, but a value that stays in registers
 
 __device__ __forceinline__ float bf2f(uint16_t b) { return __uint_as_float(static_cast<uint32_t>(b) << 16); }
 __device__ __forceinline__ uint16_t f2bf(float f) {
@@ -407,42 +412,46 @@ __global__ __launch_bounds__(256) void gemm_front_bf16(HstuDims hd, uint32_t lay
 }
 
 // ---------------------------------------------------------------------------------------
-// Fused layer halves for bf16 models with d = KD <= 256 (one kernel each, no normalised copy
-// of the activations in memory):
+// Fused layer halves for bf16 models of width KD = 64, 128, 256 or 512 (one kernel each, no normalised copy of the
+// activations in memory):
 //   FRONT: [U|V|Q|K] = SiLU(LN1(X) W1 + b1), U and Q*log2(e) to row-major buffers, K and V into
 //          the pages;
 //   BACK:  Y = X + (LN2(O) * U) W2 + b2.
 // (X, Q, K, V, Y are bf16; O, U, the normalised operand and the weight copies are half precision.)
-// A wavefront owns 32 token rows.  Their activations are loaded once (whole-line loads, dealt
-// out to the lanes through LDS), normalised in registers (a row is split over the two lanes
-// (g = 0, 1) that share the token: two cross-lane sums) and kept as the token-side MFMA operand
-// for the whole sweep over the output columns, KD/16 fragments of 8 elements.  The weights (stored transposed, [out][KD]) pass through LDS in
-// tiles of 32 output columns, double buffered with one barrier per tile; chunk c of tile row R
-// sits at chunk position c ^ (R & 7) so that the operand reads of eight neighbouring lanes
-// (eight rows, same c) hit different banks.  The product is taken as (W tile) x (X^T), so a
+// A wavefront owns 32 consecutive token rows, whichever requests they belong to.  Their activations are loaded once
+// (whole-line loads, dealt out to the lanes through LDS, 64 columns at a time), normalised in registers (a row is split
+// over the two lanes (g = 0, 1) that share the token: two cross-lane sums) and kept as the token-side MFMA operand
+// for the whole sweep over the output columns, KD/16 fragments of 8 elements.  The weights are stored in the order of
+// the MFMA operand (weight_fragments below), so a tile of 32 output columns is one contiguous piece that
+// global_load_lds copies into LDS as it is, double buffered, without passing through registers, and an operand read
+// is 64 lanes times 16 consecutive bytes.  The product is taken as (W tile) x (X^T), so a
 // lane ends up with one token and 16 output features (four runs of four); row-major outputs and
 // K rows pass through a wave-private LDS tile and leave as 16-byte stores, V^T leaves as
 // lane-coalesced 2-byte stores.
-// WPB = wavefronts per block (a block covers 32 * WPB rows of a row tile of up to 128 rows).
+// A tile's weights are fetched while the tile before it is multiplied, and waited for just before that tile's results
+// are stored: the wait (which counts loads and stores in issue order) then never covers stores just issued.
+// A block sweeps n_cb column tiles: all of them when there are rows enough to fill the chip, else the columns
+// are cut too, down to one tile a block (the launchers' rule).
 // ---------------------------------------------------------------------------------------
 struct LayerHalfArgs {
   HstuDims hd;
   uint32_t layer;
+  uint32_t row0, n_rows;   // the launch's rows
   const uint16_t* a_in;    // FRONT: X   BACK: O       [N][KD]
   const uint16_t* gate;    // BACK: U
   const float* ln_g;
   const float* ln_b;
-  const uint16_t* wt;      // [n_out][KD] of this layer
+  const uint16_t* wf;      // weight fragments of this layer
   const float* bias;       // [n_out]
   uint16_t* u;             // FRONT outputs
   uint16_t* q;
   KvView kv;
   const ReqDev* reqs;
+  const uint32_t* group_req;  // request of row row0 + 32 i, and behind the last one the last row's
   const int32_t* page_tables;
   const uint16_t* resid;   // BACK: X
   uint16_t* y;             // BACK output
-  const RowTile* row_tiles;
-  uint32_t col_blocks_per_split;  // 32-column tiles one block sweeps
+  uint32_t n_cb;           // 32-column tiles one block sweeps
 };
 
 __device__ __forceinline__ uint32_t pack2_bf16(float lo, float hi) {
@@ -451,7 +460,7 @@ __device__ __forceinline__ uint32_t pack2_bf16(float lo, float hi) {
   const v2f v = {lo, hi};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, v2bf));
 }
-__device__ __forceinline__ void unpack8(const uint4& a, float v[8]) {  // eight bf16
+__device__ __forceinline__ void unpack8(const u32x4& a, float v[8]) {  // eight bf16
   const uint32_t w[4] = {a.x, a.y, a.z, a.w};
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
@@ -459,7 +468,7 @@ __device__ __forceinline__ void unpack8(const uint4& a, float v[8]) {  // eight 
     v[2 * k + 1] = __uint_as_float(w[k] & 0xFFFF0000u);
   }
 }
-__device__ __forceinline__ void unpack8h(const uint4& a, float v[8]) {  // eight half-precision values
+__device__ __forceinline__ void unpack8h(const u32x4& a, float v[8]) {  // eight half-precision values
   const uint32_t w[4] = {a.x, a.y, a.z, a.w};
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
@@ -470,7 +479,7 @@ __device__ __forceinline__ void unpack8h(const uint4& a, float v[8]) {  // eight
 }
 // the rows a layer half normalises: the bf16 residual stream (front) or the half-precision attention output (back)
 template <bool FRONT>
-__device__ __forceinline__ void unpack_in(const uint4& a, float v[8]) {
+__device__ __forceinline__ void unpack_in(const u32x4& a, float v[8]) {
   if (FRONT) unpack8(a, v);
   else unpack8h(a, v);
 }
@@ -478,244 +487,257 @@ __device__ __forceinline__ void unpack_in(const uint4& a, float v[8]) {
 // Tells the compiler nothing about the value it returns: the unpacked fp32 copy of a row that an
 // earlier pass over the registers made cannot be kept alive for a later pass (it would double
 // the registers the row takes).
-__device__ __forceinline__ void forget(uint4& a) { asm volatile("" : "+v"(a.x), "+v"(a.y), "+v"(a.z), "+v"(a.w)); }
+__device__ __forceinline__ void forget(u32x4& a) { asm volatile("" : "+v"(a)); }
+
+// Copies 16 bytes per lane from base + voff (+ OFFSET) to the LDS address lds + 16 * lane (+ OFFSET) without passing
+// through registers; lds and base are the wavefront's.  The compiler does not know about the copy: the
+// wavefront waits for it with wait_vm, other wavefronts see it behind a barrier.  (With the builtin of the same
+// instruction the compiler waits for all outstanding copies before every LDS read.)
+__device__ __forceinline__ uint32_t lds_address(const void* p) {
+  return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const void*)p));
+}
+// (A memory instruction may read a scalar register only five wait states after a vector instruction, v_readfirstlane for
+// one, has written it.  The compiler keeps that distance for its own instructions but does not look into this one.)
+template <int OFFSET>
+__device__ __forceinline__ void copy_to_lds(const void* base, uint32_t voff) {
+  asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %0, %1 offset:%2" ::"v"(voff), "s"(base), "n"(OFFSET) : "memory");
+}
+__device__ __forceinline__ void set_lds_target(uint32_t lds) { asm volatile("s_mov_b32 m0, %0\n\ts_nop 0" ::"s"(lds) : "memory"); }
+template <int N>
+__device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+
+// f(0), f(1), .. f(N - 1) with constant arguments: unrolled whatever its size, so that the arrays it indexes are registers
+template <int... I, typename F>
+__device__ __forceinline__ void unrolled(std::integer_sequence<int, I...>, F f) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void unrolled(F f) {
+  unrolled(std::make_integer_sequence<int, N>{}, f);
+}
+
+constexpr uint32_t kMaxSweep = 1024;  // output columns a block sweeps at most
 
 template <int KD, bool FRONT, int WPB>
-__global__ __attribute__((amdgpu_flat_work_group_size(64 * WPB, 64 * WPB), amdgpu_waves_per_eu(3, 3))) void layer_half_fused(LayerHalfArgs a) {
-  constexpr int kSt = KD / 16;                 // MFMA steps over the contraction
-  constexpr int kTileChunks = 32 * KD / 8;     // 16-byte chunks of a weight tile
-  constexpr int kPerThread = kTileChunks / (64 * WPB);
-  constexpr int kRowChunks = KD / 8;
-  static_assert(kTileChunks % (64 * WPB) == 0, "weight tile must split evenly over the block");
-  __shared__ __attribute__((aligned(16))) uint16_t wtile[2][32 * KD];
-  const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5, li = lane & 31;
-  const RowTile rt = a.row_tiles[blockIdx.x / (4 / WPB)];
-  const uint32_t sub = blockIdx.x % (4 / WPB);
-  if (32 * WPB * sub >= rt.rows) return;  // this part of the row tile is empty
-  const uint32_t rloc = 32 * (WPB * sub + wave) + li;  // row inside the tile
-  const bool row_ok = rloc < rt.rows;
-  const uint64_t row = rt.row0 + (row_ok ? rloc : 0);
+__global__ __launch_bounds__(64 * WPB, KD <= 256 ? 3 : 2) void layer_half_fused(LayerHalfArgs a) {
+  constexpr int kSt = KD / 16;        // MFMA steps over the contraction
+  constexpr int kPieces = KD / 64;    // 64-column pieces of a row
+  constexpr int kTileBytes = kSt * 1024;
+  constexpr int kCopies = kSt / WPB;  // 1 KB copies of a weight tile per wavefront
+  static_assert(kSt % WPB == 0 && KD % 64 == 0, "a weight tile must split evenly over the block");
+  constexpr int kStageBytes = WPB * 4096;        // row dealing: 32 rows of 128 bytes per wavefront
+  // The output tile of a wavefront: 32 tokens x 32 16-bit features (FRONT) or fp32 ones, 16 at a time where the whole
+  // would keep a second block from the CU (BACK, KD = 512); rows padded by 16 bytes.
+  constexpr int kOutParts = !FRONT && KD > 256 ? 2 : 1;
+  constexpr int kOutRow = (FRONT ? 64 : 128 / kOutParts) + 16;  // bytes
+  constexpr int kOutBytes = WPB * 32 * kOutRow;
+  constexpr bool kStageInTile = kTileBytes >= kStageBytes;  // the dealing happens in the second weight buffer, else in the output tiles
+  __shared__ __attribute__((aligned(16))) uint8_t wtile[2][kTileBytes];
+  __shared__ __attribute__((aligned(16))) uint8_t otile[(kStageInTile ? 0 : kStageBytes) > kOutBytes ? kStageBytes : kOutBytes];
+  __shared__ __attribute__((aligned(16))) float lnp_own[kStageInTile ? 4 : 2 * KD];
+  __shared__ __attribute__((aligned(16))) float bias_s[FRONT ? kMaxSweep : KD];
+  // LayerNorm scale and shift: in the output tiles, which the sweep takes over, unless the row dealing is there
+  static_assert(!kStageInTile || 2 * KD * 4 <= kOutBytes, "LayerNorm parameters fit the output tiles");
+  float* lnp = kStageInTile ? reinterpret_cast<float*>(&otile[0]) : lnp_own;
+  const uint32_t tid = threadIdx.x, lane = tid & 63, g = lane >> 5, li = lane & 31;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t r0 = (blockIdx.x * WPB + wave) * 32;  // this wavefront's first row, counted from a.row0
   const HstuDims& hd = a.hd;
+  const uint32_t cb0 = blockIdx.y * a.n_cb, n_cb = a.n_cb;
+
+  const uint32_t wlds = __builtin_amdgcn_readfirstlane(lds_address(&wtile[0][0])) + wave * (kCopies * 1024);
+  auto fetch_w = [&](uint32_t cb, uint32_t buf) {
+    const uint8_t* src = reinterpret_cast<const uint8_t*>(a.wf) + static_cast<uint64_t>(cb) * kTileBytes + wave * (kCopies * 1024);
+#pragma unroll
+    for (int c = 0; c < kCopies; c += 4) {
+      set_lds_target(wlds + buf * kTileBytes + c * 1024);
+      copy_to_lds<0>(src + c * 1024, lane * 16);
+      if (kCopies > c + 1) copy_to_lds<1024>(src + c * 1024, lane * 16);
+      if (kCopies > c + 2) copy_to_lds<2048>(src + c * 1024, lane * 16);
+      if (kCopies > c + 3) copy_to_lds<3072>(src + c * 1024, lane * 16);
+    }
+  };
 
   // ---- activation rows: issue the loads ---------------------------------------------------------
-  // A wavefront's 32 rows come in with whole-line loads (a load instruction covers the same half of 64 / (KD/16)
-  // rows, 16 bytes per lane) and are dealt out to the operand layout (lane = token, 8 of every 16 elements)
-  // through LDS: half a row of each of the 32 rows at a time, in the wavefront's quarter of the weight tile
-  // buffers, which nothing uses before the first barrier below.  Chunk c of row r sits at c ^ (r mod chunks).
-  // Rows past the tile's end read its first row; their results are never stored.
-  constexpr int kHalfChunks = KD / 16;            // 16-byte chunks in half a row
-  constexpr int kRowsPerLoad = 64 / kHalfChunks;  // rows one wave-wide load covers
-  constexpr int kLoads = 32 / kRowsPerLoad;       // loads per half
-  static_assert(kSt % 2 == 0 && 64 % kHalfChunks == 0 && 32 % kRowsPerLoad == 0, "row staging layout");
-  const uint32_t stage_lr = lane / kHalfChunks, stage_lc = lane % kHalfChunks;
-  auto issue_rows = [&](const uint16_t* src, int h, uint4 (&v)[kLoads]) {
+  // One load instruction covers 128 bytes of eight rows.  A piece (64 columns of the 32 rows) is dealt out to the
+  // operand layout (lane = token, 8 of every 16 elements) through 4 KB of wave-private LDS; chunk c of row r sits at
+  // c ^ (r mod 8).  Rows past the end read the launch's first row; their results are never stored.
+  const uint32_t st_r = lane >> 3, st_c = lane & 7;
+  auto issue_piece = [&](const uint16_t* src, int p, u32x4 (&v)[4]) {
 #pragma unroll
-    for (int i = 0; i < kLoads; ++i) {
-      const uint32_t rl = 32 * (WPB * sub + wave) + kRowsPerLoad * i + stage_lr;
-      v[i] = *reinterpret_cast<const uint4*>(src + (rt.row0 + (rl < rt.rows ? rl : 0)) * KD + 8 * (kHalfChunks * h + stage_lc));
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t r = r0 + 8 * i + st_r;
+      v[i] = *reinterpret_cast<const u32x4*>(src + static_cast<uint64_t>(a.row0 + (r < a.n_rows ? r : 0)) * KD + 64 * p + 8 * st_c);
     }
   };
-  auto deal_rows = [&](const uint4 (&v)[kLoads], int h, uint4 (&dst)[kSt]) {
-    uint16_t* stage = &wtile[0][0] + wave * (32 * KD / 2);
+  uint8_t* stage = (kStageInTile ? &wtile[1][0] : &otile[0]) + wave * 4096;
+  auto deal_piece = [&](const u32x4 (&v)[4], auto& dst, auto at) {
 #pragma unroll
-    for (int i = 0; i < kLoads; ++i) {
-      const uint32_t r = kRowsPerLoad * i + stage_lr;
-      *reinterpret_cast<uint4*>(stage + r * (KD / 2) + 8 * (stage_lc ^ (r & (kHalfChunks - 1)))) = v[i];
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t r = 8 * i + st_r;
+      *reinterpret_cast<u32x4*>(stage + r * 128 + 16 * (st_c ^ (r & 7))) = v[i];
     }
 #pragma unroll
-    for (int s2 = 0; s2 < kSt / 2; ++s2)
-      dst[kSt / 2 * h + s2] =
-          *reinterpret_cast<const uint4*>(stage + li * (KD / 2) + 8 * ((2 * s2 + g) ^ (li & (kHalfChunks - 1))));
+    for (int s2 = 0; s2 < 4; ++s2) dst[at + s2] = *reinterpret_cast<const u32x4*>(stage + li * 128 + 16 * ((2 * s2 + g) ^ (li & 7)));
   };
-  uint4 va[kLoads], vb[kLoads];
-  issue_rows(a.a_in, 0, va);
-  issue_rows(a.a_in, 1, vb);
-  uint4 xr[kSt];  // this lane's half of its token's row: raw, then normalised (and gated) bf16
-  deal_rows(va, 0, xr);
-  if constexpr (!FRONT) issue_rows(a.gate, 0, va);
-  deal_rows(vb, 1, xr);
-  if constexpr (!FRONT) issue_rows(a.gate, 1, vb);
+  u32x4 xr[kSt];  // this lane's half of its token's row: raw, then normalised (and gated) half precision
+  {
+    u32x4 raw[kPieces][4];
+    unrolled<kPieces>([&](auto p) { issue_piece(a.a_in, p, raw[p]); });
+    fetch_w(cb0, 0);
+    unrolled<kPieces>([&](auto p) { deal_piece(raw[p], xr, std::integral_constant<int, 4 * p>{}); });
+  }
+  u32x4 gate0[4], gate1[4];  // BACK: the gate rows follow two pieces at a time
+  if constexpr (!FRONT) {
+    issue_piece(a.gate, 0, gate0);
+    if (kPieces > 1) issue_piece(a.gate, 1, gate1);
+  }
+  for (uint32_t i = tid; i < KD; i += 64 * WPB) {
+    lnp[i] = a.ln_g[i];
+    lnp[KD + i] = a.ln_b[i];
+  }
+  for (uint32_t i = tid; i < n_cb * 32; i += 64 * WPB) bias_s[i] = a.bias[cb0 * 32 + i];
 
   // ---- where this lane's token goes (these dependent loads fly during the LayerNorm) ----------------
-  const uint8_t* page_ptr = nullptr;  // FRONT: start of the token's page (nullptr: bad page id)
+  const bool row_ok = r0 + li < a.n_rows;
+  const uint8_t* page_ptr = nullptr;  // FRONT: start of the token's page (nullptr: no such row, or a bad page id)
   uint32_t tok = 0;
-  if (FRONT) {
-    const ReqDev rq = a.reqs[rt.req];
-    const uint32_t pos = rq.prefix_len + static_cast<uint32_t>(row - rq.x_off);
-    uint32_t pi;
-    split_token(hd, pos, &pi, &tok);
-    if (row_ok) {
-      const int32_t page = a.page_tables[rq.page_table_off + pi];
-      if (page < 0 || static_cast<uint32_t>(page) >= a.kv.n_pages) {
-        if (blockIdx.y == 0 && g == 0) atomicAdd(&a.kv.counters[ctr_index(kCtrBadPages)], 1ull);
-      } else {
-        page_ptr = a.kv.base + static_cast<uint64_t>(page) * a.kv.page_size;
-      }
+  if (FRONT && row_ok) {
+    const uint32_t row = a.row0 + r0 + li, grp = r0 / 32;
+    uint32_t lo = a.group_req[grp], hi = a.group_req[grp + 1];
+    while (lo < hi) {  // the last request that starts at or before the row
+      const uint32_t mid = (lo + hi + 1) / 2;
+      if (a.reqs[mid].x_off <= row) lo = mid;
+      else hi = mid - 1;
     }
+    const ReqDev rq = a.reqs[lo];
+    uint32_t pi;
+    split_token(hd, rq.prefix_len + (row - rq.x_off), &pi, &tok);
+    const int32_t page = a.page_tables[rq.page_table_off + pi];
+    if (page < 0 || static_cast<uint32_t>(page) >= a.kv.n_pages) {
+      if (blockIdx.y == 0 && g == 0) atomicAdd(&a.kv.counters[ctr_index(kCtrBadPages)], 1ull);
+    } else {
+      page_ptr = a.kv.base + static_cast<uint64_t>(page) * a.kv.page_size;
+    }
+  }
+
+  // ---- normalise, keep as MFMA operand -----------------------------------------------------------
+  {
+    float s = 0.0f;
+    unrolled<kSt>([&](auto st) {
+      float v[8];
+      unpack_in<FRONT>(xr[st], v);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) s += v[e];
+    });
+    s += __shfl_xor(s, 32, 64);
+    const float mean = s / KD;
+    float qq = 0.0f;
+    unrolled<kSt>([&](auto st) { forget(xr[st]); });
+    unrolled<kSt>([&](auto st) {
+      float v[8];
+      unpack_in<FRONT>(xr[st], v);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) qq += (v[e] - mean) * (v[e] - mean);
+    });
+    qq += __shfl_xor(qq, 32, 64);
+    const float rstd = 1.0f / sqrtf(qq / KD + hd.eps);
+    __syncthreads();  // lnp is visible
+    unrolled<kSt>([&](auto st) { forget(xr[st]); });
+    unrolled<kPieces>([&](auto p) {
+      u32x4 gr[4];
+      if constexpr (!FRONT) {
+        if constexpr (p % 2 == 1) {
+          deal_piece(gate1, gr, std::integral_constant<int, 0>{});
+          if (p + 2 < kPieces) issue_piece(a.gate, p + 2, gate1);
+        } else {
+          deal_piece(gate0, gr, std::integral_constant<int, 0>{});
+          if (p + 2 < kPieces) issue_piece(a.gate, p + 2, gate0);
+        }
+      }
+      unrolled<4>([&](auto s2) {
+        constexpr int st = 4 * p + s2;
+        float v[8], gg[8], bb[8];
+        unpack_in<FRONT>(xr[st], v);
+        load8(lnp + 16 * st + 8 * g, gg);
+        load8(lnp + KD + 16 * st + 8 * g, bb);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = (v[e] - mean) * rstd * gg[e] + bb[e];
+        if constexpr (!FRONT) {
+          float uv[8];
+          unpack8h(gr[s2], uv);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v[e] *= uv[e];
+        }
+        xr[st] = u32x4{pack2_f16(v[0], v[1]), pack2_f16(v[2], v[3]), pack2_f16(v[4], v[5]), pack2_f16(v[6], v[7])};
+        // the result is pinned down here and memory operations may not pass: the LDS reads of later
+        // steps stay behind this step's arithmetic instead of piling up in registers
+        forget(xr[st]);
+        asm volatile("" ::: "memory");
+      });
+    });
   }
 
   // Row-major outputs leave through a wave-private LDS tile that turns "one token, four runs of four
   // features per lane" into 16-byte pieces: lane l then stores features 8 (l % 4) .. + 8 of the tokens
-  // l / 4 and l / 4 + 16 of its wavefront, so four lanes cover 64 contiguous bytes of a row.
-  const bool wave_has_rows = 32 * (WPB * sub + wave) < rt.rows;
+  // l / 4 and l / 4 + 16 of its wavefront, so four lanes cover 64 contiguous bytes of a row (with the tile in two
+  // parts: features 8 (l % 2) of token l / 2, then the same of the other 16 features).
+  constexpr int kStores = 2;
+  auto store_row = [&](int h2) { return kOutParts == 1 ? (lane >> 2) + 16 * h2 : lane >> 1; };
+  auto store_col = [&](int h2) { return kOutParts == 1 ? lane & 3 : (lane & 1) + 2 * h2; };
   bool ok2[2];
   uint64_t row2[2];
   uint8_t* kdst2[2] = {nullptr, nullptr};  // FRONT: K row of the token inside its page, before the head offset
 #pragma unroll
   for (int h2 = 0; h2 < 2; ++h2) {
-    const uint32_t rl = 32 * (WPB * sub + wave) + (lane >> 2) + 16 * h2;
-    ok2[h2] = rl < rt.rows;
-    row2[h2] = rt.row0 + (ok2[h2] ? rl : 0);
-    if (FRONT && ok2[h2]) {
-      const ReqDev rq = a.reqs[rt.req];
-      const uint32_t pos = rq.prefix_len + static_cast<uint32_t>(row2[h2] - rq.x_off);
-      uint32_t pi, tk;
-      split_token(hd, pos, &pi, &tk);
-      const int32_t page = a.page_tables[rq.page_table_off + pi];
-      if (page >= 0 && static_cast<uint32_t>(page) < a.kv.n_pages)
-        kdst2[h2] = a.kv.base + static_cast<uint64_t>(page) * a.kv.page_size + static_cast<uint64_t>(tk) * 128;
+    const uint32_t rl = store_row(h2);
+    ok2[h2] = r0 + rl < a.n_rows;
+    row2[h2] = a.row0 + (ok2[h2] ? r0 + rl : 0);
+    if (FRONT) {
+      const uint64_t mine = reinterpret_cast<uint64_t>(page_ptr);
+      const uint32_t lo = __shfl(static_cast<uint32_t>(mine), rl, 64), hi = __shfl(static_cast<uint32_t>(mine >> 32), rl, 64);
+      const uint32_t tk = __shfl(tok, rl, 64);
+      const uint64_t pp = (static_cast<uint64_t>(hi) << 32) | lo;
+      if (pp) kdst2[h2] = reinterpret_cast<uint8_t*>(pp) + static_cast<uint64_t>(tk) * 128;
     }
   }
-  // ---- activations: load, normalise, keep as MFMA operand ----------------------------------
-  __shared__ __attribute__((aligned(16))) float lnp[4][KD];  // LayerNorm scale and shift in the first two rows
-  for (uint32_t i = tid; i < KD; i += 64 * WPB) {
-    lnp[0][i] = a.ln_g[i];
-    lnp[1][i] = a.ln_b[i];
-  }
-  {
-    uint4 gr[FRONT ? 1 : kSt];  // BACK: the gate row
-    if constexpr (!FRONT) {
-      deal_rows(va, 0, gr);
-      deal_rows(vb, 1, gr);
-    }
-    float s = 0.0f;
-#pragma unroll
-    for (int st = 0; st < kSt; ++st) {
-      float v[8];
-      unpack_in<FRONT>(xr[st], v);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) s += v[e];
-    }
-    s += __shfl_xor(s, 32, 64);
-    const float mean = s / KD;
-    float qq = 0.0f;
-#pragma unroll
-    for (int st = 0; st < kSt; ++st) forget(xr[st]);
-#pragma unroll
-    for (int st = 0; st < kSt; ++st) {
-      float v[8];
-      unpack_in<FRONT>(xr[st], v);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) qq += (v[e] - mean) * (v[e] - mean);
-    }
-    qq += __shfl_xor(qq, 32, 64);
-    const float rstd = 1.0f / sqrtf(qq / KD + hd.eps);
-    __syncthreads();  // lnp is visible
-#pragma unroll
-    for (int st = 0; st < kSt; ++st) forget(xr[st]);
-#pragma unroll
-    for (int st = 0; st < kSt; ++st) {
-      float v[8], gg[8], bb[8];
-      unpack_in<FRONT>(xr[st], v);
-      load8(&lnp[0][16 * st + 8 * g], gg);
-      load8(&lnp[1][16 * st + 8 * g], bb);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = (v[e] - mean) * rstd * gg[e] + bb[e];
-      if (!FRONT) {
-        float uv[8];
-        unpack8h(gr[st], uv);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] *= uv[e];
-      }
-      xr[st] = make_uint4(pack2_f16(v[0], v[1]), pack2_f16(v[2], v[3]), pack2_f16(v[4], v[5]), pack2_f16(v[6], v[7]));
-      // the result is pinned down here and memory operations may not pass: the LDS reads of later
-      // steps stay behind this step's arithmetic instead of piling up in registers
-      forget(xr[st]);
-      asm volatile("" ::: "memory");
-
-    }
-  }
-  // The LayerNorm parameters are done with; their LDS space takes this block's slice of the bias (at most
-  // 4 KD columns per block).  Nothing inside the sweep below may read global memory for immediate use: the
-  // wait for such a load also waits for every store and every weight prefetch issued before it.
-  const uint32_t cb0 = blockIdx.y * a.col_blocks_per_split, n_cb = a.col_blocks_per_split;
-  float* bias_s = &lnp[0][0];
-  __syncthreads();
-  for (uint32_t i = tid; i < n_cb * 32; i += 64 * WPB) bias_s[i] = a.bias[cb0 * 32 + i];
-
-  constexpr int kOutStride = FRONT ? 40 : 72;  // 16-bit units per token row of the tile: 32 bf16 or 32 fp32, padded
-  __shared__ __attribute__((aligned(16))) uint16_t otile[WPB][32 * kOutStride];
-  uint16_t* ot = otile[wave];
+  uint8_t* ot = &otile[0] + wave * (32 * kOutRow);
 
   // ---- sweep over the output columns ----------------------------------------------------------
-  // weight tiles travel global -> registers -> LDS, two tiles ahead of their use (two register sets;
-  // named members and spelled-out steps, so that they are registers whatever the optimiser's unrolling order)
-  struct WSet { uint4 c0, c1, c2, c3; };
-  static_assert(kPerThread == 2 || kPerThread == 4, "a thread stages two or four chunks of a weight tile");
-  const uint4 zero4 = make_uint4(0, 0, 0, 0);
-  WSet wregA{zero4, zero4, zero4, zero4}, wregB{zero4, zero4, zero4, zero4};
-  auto fetch_w = [&](WSet& wr, uint32_t cb) {
-    const uint4* src = reinterpret_cast<const uint4*>(a.wt + static_cast<uint64_t>(cb) * 32 * KD) + tid;
-    wr.c0 = src[0];
-    wr.c1 = src[64 * WPB];
-    if (kPerThread == 4) {
-      wr.c2 = src[2 * 64 * WPB];
-      wr.c3 = src[3 * 64 * WPB];
+  wait_vm<0>();
+  for (uint32_t k = 0; k < n_cb; ++k) {
+    const uint32_t cb = cb0 + k, n0 = cb * 32;
+    __syncthreads();  // tile k is in LDS, and every wavefront is done with tile k - 1, whose buffer takes tile k + 1
+    if (k + 1 < n_cb) fetch_w(cb + 1, (k + 1) & 1);
+    if (r0 >= a.n_rows) {  // a wavefront without rows only helps to fetch
+      wait_vm<0>();
+      continue;
     }
-  };
-  auto put_w = [&](const uint4& v, uint32_t it, uint16_t* dst) {
-    const uint32_t c = tid + 64 * WPB * it, R = c / kRowChunks, ch = c % kRowChunks;
-    *reinterpret_cast<uint4*>(dst + R * KD + 8 * (ch ^ (R & 7))) = v;
-  };
-  auto commit_w = [&](const WSet& wr, uint16_t* dst) {
-    put_w(wr.c0, 0, dst);
-    put_w(wr.c1, 1, dst);
-    if (kPerThread == 4) {
-      put_w(wr.c2, 2, dst);
-      put_w(wr.c3, 3, dst);
-    }
-  };
-  uint32_t swz[4];  // element offset of chunk 2 j + g (j < 4) inside this lane's tile row
+    u32x4 res[2];  // BACK: the residual pieces this lane adds at its two stores
+    if (!FRONT) {
 #pragma unroll
-  for (uint32_t j = 0; j < 4; ++j) swz[j] = li * KD + 8 * ((2 * j + g) ^ (li & 7));
-
-  // BACK: the residual pieces a lane adds at its two stores, fetched one tile ahead (the wait for them then
-  // covers the stores of the tile before, not those just issued)
-  struct RSet { uint4 r0, r1; };
-  // (row2 of a lane without a row points at the tile's first row, so the loads need no condition)
-  auto fetch_resid = [&](RSet& rs, uint32_t cb) {
-    if (FRONT) return;
-    rs.r0 = *reinterpret_cast<const uint4*>(a.resid + row2[0] * KD + cb * 32 + 8 * (lane & 3));
-    rs.r1 = *reinterpret_cast<const uint4*>(a.resid + row2[1] * KD + cb * 32 + 8 * (lane & 3));
-  };
-
-  // Prefetches are issued unconditionally (past the end they fetch the last tile again): the compiler sizes
-  // each wait by the memory operations that every path issues after the awaited one, and a prefetch under a
-  // condition would make it wait for the stores just issued as well.
-  const uint32_t cb_last = cb0 + n_cb - 1;
-  // one 32-column tile: product, epilogue, stores
-  auto compute = [&](const uint16_t* wb, uint32_t cb, const RSet& res, RSet& res_next) {
-    const uint32_t n0 = cb * 32;
-    fetch_resid(res_next, cb < cb_last ? cb + 1 : cb_last);
+      for (int h2 = 0; h2 < 2; ++h2) res[h2] = *reinterpret_cast<const u32x4*>(a.resid + row2[h2] * KD + n0 + 8 * store_col(h2));
+    }
     f32x16 acc;
     // acc[e]: feature n0 + 8*(e/4) + 4*g + e%4 of this lane's token; the bias is the starting value
 #pragma unroll
     for (int r4 = 0; r4 < 4; ++r4) {
-      const float4 b = *reinterpret_cast<const float4*>(bias_s + (cb - cb0) * 32 + 8 * r4 + 4 * g);
+      const float4 b = *reinterpret_cast<const float4*>(bias_s + k * 32 + 8 * r4 + 4 * g);
       acc[4 * r4] = b.x; acc[4 * r4 + 1] = b.y; acc[4 * r4 + 2] = b.z; acc[4 * r4 + 3] = b.w;
     }
+    const uint8_t* wb = wtile[k & 1] + lane * 16;
 #pragma unroll
     for (int st = 0; st < kSt; ++st) {
-      const f16x8 wf = __builtin_bit_cast(f16x8, *reinterpret_cast<const uint4*>(wb + swz[st & 3] + 64 * (st >> 2)));
+      const f16x8 wf = __builtin_bit_cast(f16x8, *reinterpret_cast<const u32x4*>(wb + st * 1024));
       acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wf, __builtin_bit_cast(f16x8, xr[st]), acc, 0, 0, 0);
     }
-    if (!wave_has_rows) return;
     if (FRONT) {
       const uint32_t which = n0 / KD, c0 = n0 % KD;  // 0: U, 1: V, 2: Q, 3: K
       float z[16];
 #pragma unroll
       for (int e = 0; e < 16; ++e) z[e] = acc[e] * __builtin_amdgcn_rcpf(1.0f + __expf(-acc[e]));
       if (which == 1) {
+        wait_vm<0>();
         // V block [64][page_tokens]: the 32 lanes of a half-wave write 32 consecutive tokens of one feature
         if (page_ptr) {
           const uint32_t head = c0 / 64, cc = c0 % 64 + 4 * g;
@@ -724,65 +746,53 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64 * WPB, 64 * WPB), amdgp
           for (int e = 0; e < 16; ++e)
             dst[static_cast<uint64_t>(cc + 8 * (e / 4) + e % 4) * hd.pt] = static_cast<uint16_t>(pack2_bf16(z[e], 0.0f));
         }
-        return;
+        continue;
       }
       const float sc = which == 2 ? 1.4426950408889634f : 1.0f;  // the attention kernel wants q * log2(e)
 #pragma unroll
       for (int r4 = 0; r4 < 4; ++r4)
-        *reinterpret_cast<uint2*>(ot + li * kOutStride + 8 * r4 + 4 * g) =
+        *reinterpret_cast<uint2*>(ot + li * kOutRow + 16 * r4 + 8 * g) =
             which == 0  // U is the library's own (half precision); Q and K are bf16
                 ? make_uint2(pack2_f16(z[4 * r4], z[4 * r4 + 1]), pack2_f16(z[4 * r4 + 2], z[4 * r4 + 3]))
                 : make_uint2(pack2_bf16(z[4 * r4] * sc, z[4 * r4 + 1] * sc), pack2_bf16(z[4 * r4 + 2] * sc, z[4 * r4 + 3] * sc));
+      u32x4 v2[2];
+#pragma unroll
+      for (int h2 = 0; h2 < 2; ++h2) v2[h2] = *reinterpret_cast<const u32x4*>(ot + ((lane >> 2) + 16 * h2) * kOutRow + 16 * (lane & 3));
+      wait_vm<0>();
 #pragma unroll
       for (int h2 = 0; h2 < 2; ++h2) {
-        const uint4 v = *reinterpret_cast<const uint4*>(ot + ((lane >> 2) + 16 * h2) * kOutStride + 8 * (lane & 3));
         if (which == 3) {  // K block [token][64]
           if (kdst2[h2])
-            *reinterpret_cast<uint4*>(kdst2[h2] + kv_block_offset(hd, a.layer, 0, c0 / 64, 2) + (c0 % 64 + 8 * (lane & 3)) * 2) = v;
+            *reinterpret_cast<u32x4*>(kdst2[h2] + kv_block_offset(hd, a.layer, 0, c0 / 64, 2) + (c0 % 64 + 8 * (lane & 3)) * 2) = v2[h2];
         } else if (ok2[h2]) {
-          *reinterpret_cast<uint4*>((which == 0 ? a.u : a.q) + row2[h2] * KD + c0 + 8 * (lane & 3)) = v;
+          *reinterpret_cast<u32x4*>((which == 0 ? a.u : a.q) + row2[h2] * KD + c0 + 8 * (lane & 3)) = v2[h2];
         }
       }
     } else {
-      float* otf = reinterpret_cast<float*>(ot);
+      // a store takes 8 features of a token: four lanes a row, or two with half the features at a time
+      wait_vm<0>();
+      unrolled<kOutParts>([&](auto part) {
+        constexpr int kRuns = 4 / kOutParts;  // runs of four features per lane and part
 #pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4)
-        *reinterpret_cast<float4*>(otf + li * (kOutStride / 2) + 8 * r4 + 4 * g) =
-            make_float4(acc[4 * r4], acc[4 * r4 + 1], acc[4 * r4 + 2], acc[4 * r4 + 3]);
+        for (int r4 = 0; r4 < kRuns; ++r4)
+          *reinterpret_cast<f32x4*>(ot + li * kOutRow + 32 * r4 + 16 * g) =
+              f32x4{acc[4 * (kRuns * part + r4)], acc[4 * (kRuns * part + r4) + 1], acc[4 * (kRuns * part + r4) + 2], acc[4 * (kRuns * part + r4) + 3]};
 #pragma unroll
-      for (int h2 = 0; h2 < 2; ++h2) {
-        const float* src = otf + ((lane >> 2) + 16 * h2) * (kOutStride / 2) + 8 * (lane & 3);
-        const float4 p0 = *reinterpret_cast<const float4*>(src), p1 = *reinterpret_cast<const float4*>(src + 4);
-        if (!ok2[h2]) continue;
-        const uint64_t at = row2[h2] * KD + n0 + 8 * (lane & 3);
-        float xv[8];
-        unpack8(h2 == 0 ? res.r0 : res.r1, xv);
-        *reinterpret_cast<uint4*>(a.y + at) = make_uint4(pack2_bf16(xv[0] + p0.x, xv[1] + p0.y), pack2_bf16(xv[2] + p0.z, xv[3] + p0.w),
-                                                        pack2_bf16(xv[4] + p1.x, xv[5] + p1.y), pack2_bf16(xv[6] + p1.z, xv[7] + p1.w));
-      }
+        for (int h2 = 0; h2 < kStores / kOutParts; ++h2) {
+          constexpr int at0 = part * (kStores / kOutParts);
+          const uint8_t* src = ot + store_row(at0 + h2) * kOutRow + 32 * (store_col(at0 + h2) % (4 / kOutParts));
+          f32x4 p0 = *reinterpret_cast<const f32x4*>(src), p1 = *reinterpret_cast<const f32x4*>(src + 16);
+          // all lanes have read before any lane goes on to write the next part: the reads must not sink into the branch
+          asm volatile("" : "+v"(p0), "+v"(p1));
+          if (!ok2[at0 + h2]) continue;
+          float xv[8];
+          unpack8(res[at0 + h2], xv);
+          *reinterpret_cast<u32x4*>(a.y + row2[at0 + h2] * KD + n0 + 8 * store_col(at0 + h2)) =
+              u32x4{pack2_bf16(xv[0] + p0.x, xv[1] + p0.y), pack2_bf16(xv[2] + p0.z, xv[3] + p0.w),
+                    pack2_bf16(xv[4] + p1.x, xv[5] + p1.y), pack2_bf16(xv[6] + p1.z, xv[7] + p1.w)};
+        }
+      });
     }
-  };
-
-  RSet resA{zero4, zero4}, resB{zero4, zero4};
-  auto tile_at = [&](uint32_t k) { return cb0 + k < cb_last ? cb0 + k : cb_last; };
-  fetch_resid(resA, cb0);
-  fetch_w(wregA, cb0);
-  fetch_w(wregB, tile_at(1));
-  asm volatile("" ::: "memory");  // keeps the issue order: the waits inside the loop are sized by it
-  commit_w(wregA, wtile[0]);
-  asm volatile("" ::: "memory");
-  fetch_w(wregA, tile_at(2));
-  asm volatile("" ::: "memory");
-  for (uint32_t k = 0; k < n_cb; k += 2) {  // n_cb is even (the launchers check it)
-    // tile k is visible, and every wave is done with tile k-1, whose buffer takes tile k+1
-    __syncthreads();
-    commit_w(wregB, wtile[1]);
-    fetch_w(wregB, tile_at(k + 3));
-    compute(wtile[0], cb0 + k, resA, resB);
-    __syncthreads();
-    commit_w(wregA, wtile[0]);  // after the last pair: a copy of the last tile that nobody reads
-    fetch_w(wregA, tile_at(k + 4));
-    compute(wtile[1], cb0 + k + 1, resB, resA);
   }
 }
 
@@ -1427,6 +1437,22 @@ __global__ void transpose_kernel(const T* __restrict__ w, T* __restrict__ wt, ui
     if (bx + yy < cols && by + threadIdx.x < rows) wt[static_cast<uint64_t>(bx + yy) * rows + by + threadIdx.x] = tile[threadIdx.x][yy];
 }
 
+// Copy of a bf16 weight matrix [rows][cols] in half precision, in the order in which the fused layer halves use it as
+// an MFMA operand: for every 32 columns and 16 rows one piece of 64 lanes x 8 elements, lane (g, i) holding column i
+// and rows 8 g .. 8 g + 7 (exact unless a weight is below 2^-14 in magnitude).
+__global__ __launch_bounds__(256) void weight_fragments(const uint16_t* __restrict__ w, uint16_t* __restrict__ wf, uint32_t rows, uint32_t cols) {
+  const uint64_t n = static_cast<uint64_t>(rows) * cols / 8;  // one thread: the 8 elements of one lane
+  for (uint64_t t = blockIdx.x * 256ull + threadIdx.x; t < n; t += gridDim.x * 256ull) {
+    const uint32_t lane = t & 63, g = lane >> 5, li = lane & 31;
+    const uint64_t piece = t >> 6;
+    const uint32_t st = piece % (rows / 16), cb = piece / (rows / 16);
+    uint16_t v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = f2h(bf2f(w[static_cast<uint64_t>(16 * st + 8 * g + e) * cols + 32 * cb + li]));
+    *reinterpret_cast<uint4*>(wf + 8 * t) = make_uint4(v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16));
+  }
+}
+
 // transposed copy of a bf16 weight matrix in half precision (exact unless a weight is below 2^-14 in magnitude)
 __global__ void transpose_bf16_to_f16(const uint16_t* __restrict__ w, uint16_t* __restrict__ wt, uint32_t rows, uint32_t cols) {
   __shared__ uint16_t tile[32][33];
@@ -1470,10 +1496,34 @@ hipError_t launch_layernorm(const HstuDims& hd, const void* x, const float* g, c
   return hipGetLastError();
 }
 
-bool layer_halves_fused(const HstuDims& hd) { return hd.elem == 1 && (hd.d == 128 || hd.d == 256); }
+bool layer_halves_fused(const HstuDims& hd) { return hd.elem == 1 && (hd.d == 64 || hd.d == 128 || hd.d == 256 || hd.d == 512); }
+
+// How many column tiles a block of a layer half sweeps: all of them if the row tiles alone give every CU two blocks
+// (the rows are then read and normalised once), else the sweep is halved until they do, down to one tile.
+static uint32_t tiles_per_block(uint32_t row_tiles, uint32_t col_tiles) {
+  uint32_t splits = col_tiles > kMaxSweep / 32 ? col_tiles / (kMaxSweep / 32) : 1;
+  while (splits < col_tiles && row_tiles * splits < 512) splits *= 2;
+  return col_tiles / splits;
+}
+
+template <bool FRONT>
+static hipError_t launch_layer_half(LayerHalfArgs& a, uint32_t col_tiles, hipStream_t stream) {
+  constexpr uint32_t kRows = 128;  // per block
+  const uint32_t row_tiles = (a.n_rows + kRows - 1) / kRows;
+  a.n_cb = tiles_per_block(row_tiles, col_tiles);
+  const dim3 grid(row_tiles, col_tiles / a.n_cb), block(256);
+  switch (a.hd.d) {
+    case 64: hipLaunchKernelGGL((layer_half_fused<64, FRONT, 4>), grid, block, 0, stream, a); break;
+    case 128: hipLaunchKernelGGL((layer_half_fused<128, FRONT, 4>), grid, block, 0, stream, a); break;
+    case 256: hipLaunchKernelGGL((layer_half_fused<256, FRONT, 4>), grid, block, 0, stream, a); break;
+    case 512: hipLaunchKernelGGL((layer_half_fused<512, FRONT, 4>), grid, block, 0, stream, a); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
 
 hipError_t launch_layer_front_fused(const HstuDims& hd, uint32_t layer, const void* x, const float* ln_g,
-                                    const float* ln_b, const void* w1t, const float* b1, void* u, void* q,
+                                    const float* ln_b, const void* w1f, const float* b1, void* u, void* q,
                                     const KvView& kv, const StepLists& sl, const int32_t* page_tables,
                                     hipStream_t stream) {
   if (sl.N == 0) return hipSuccess;
@@ -1481,50 +1531,40 @@ hipError_t launch_layer_front_fused(const HstuDims& hd, uint32_t layer, const vo
   LayerHalfArgs a{};
   a.hd = hd;
   a.layer = layer;
+  a.row0 = sl.row0;
+  a.n_rows = sl.N;
   a.a_in = static_cast<const uint16_t*>(x);
   a.ln_g = ln_g;
   a.ln_b = ln_b;
-  a.wt = static_cast<const uint16_t*>(w1t);
+  a.wf = static_cast<const uint16_t*>(w1f);
   a.bias = b1;
   a.u = static_cast<uint16_t*>(u);
   a.q = static_cast<uint16_t*>(q);
   a.kv = kv;
   a.reqs = sl.reqs;
+  a.group_req = sl.group_req;
   a.page_tables = page_tables;
-  a.row_tiles = sl.row_tiles;
-  // A block sweeps all 4 d output columns of its rows, so that the rows are read and normalised once; only a launch
-  // with too few row tiles to fill a third of the chip's block slots is cut into the column halves U|V and Q|K.
-  const uint32_t kSplit = sl.n_row_tiles >= 256 ? 1 : 2;
-  a.col_blocks_per_split = 4 * hd.d / 32 / kSplit;
-  if (a.col_blocks_per_split % 2 != 0) return hipErrorInvalidValue;  // the sweep takes column tiles in pairs
-  const dim3 grid(sl.n_row_tiles, kSplit), block(256);
-  if (hd.d == 256) hipLaunchKernelGGL((layer_half_fused<256, true, 4>), grid, block, 0, stream, a);
-  else hipLaunchKernelGGL((layer_half_fused<128, true, 4>), grid, block, 0, stream, a);
-  return hipGetLastError();
+  return launch_layer_half<true>(a, 4 * hd.d / 32, stream);
 }
 
 hipError_t launch_layer_back_fused(const HstuDims& hd, const void* o, const void* u, const float* ln_g,
-                                   const float* ln_b, const void* w2t, const float* b2, const void* x, void* y,
+                                   const float* ln_b, const void* w2f, const float* b2, const void* x, void* y,
                                    const StepLists& sl, hipStream_t stream) {
   if (sl.N == 0) return hipSuccess;
   if (!layer_halves_fused(hd)) return hipErrorInvalidValue;
   LayerHalfArgs a{};
   a.hd = hd;
+  a.row0 = sl.row0;
+  a.n_rows = sl.N;
   a.a_in = static_cast<const uint16_t*>(o);
   a.gate = static_cast<const uint16_t*>(u);
   a.ln_g = ln_g;
   a.ln_b = ln_b;
-  a.wt = static_cast<const uint16_t*>(w2t);
+  a.wf = static_cast<const uint16_t*>(w2f);
   a.bias = b2;
   a.resid = static_cast<const uint16_t*>(x);
   a.y = static_cast<uint16_t*>(y);
-  a.row_tiles = sl.row_tiles;
-  a.col_blocks_per_split = hd.d / 32;
-  if (a.col_blocks_per_split % 2 != 0) return hipErrorInvalidValue;  // the sweep takes column tiles in pairs
-  const dim3 grid(sl.n_row_tiles, 1), block(256);
-  if (hd.d == 256) hipLaunchKernelGGL((layer_half_fused<256, false, 4>), grid, block, 0, stream, a);
-  else hipLaunchKernelGGL((layer_half_fused<128, false, 4>), grid, block, 0, stream, a);
-  return hipGetLastError();
+  return launch_layer_half<false>(a, hd.d / 32, stream);
 }
 
 hipError_t launch_gemm_front(const HstuDims& hd, uint32_t layer, const void* xn, const void* w1, const float* b1,
@@ -1613,10 +1653,13 @@ hipError_t launch_scale_q(const void* in, void* out, uint64_t n, hipStream_t str
   return hipGetLastError();
 }
 
-hipError_t launch_transpose_weights(const void* w, void* wt, uint32_t rows, uint32_t cols, uint32_t elem,
+hipError_t launch_transpose_weights(const void* w, void* wt, uint32_t rows, uint32_t cols, uint32_t elem, bool fragments,
                                     hipStream_t stream) {
   const dim3 grid((cols + 31) / 32, (rows + 31) / 32), block(32, 8);
-  if (elem == 1)  // bf16 in, half precision out
+  if (fragments)  // bf16 in, half precision out
+    hipLaunchKernelGGL(weight_fragments, dim3((rows * cols / 8 + 255) / 256), dim3(256), 0, stream,
+                       static_cast<const uint16_t*>(w), static_cast<uint16_t*>(wt), rows, cols);
+  else if (elem == 1)
     hipLaunchKernelGGL(transpose_bf16_to_f16, grid, block, 0, stream, static_cast<const uint16_t*>(w),
                        static_cast<uint16_t*>(wt), rows, cols);
   else

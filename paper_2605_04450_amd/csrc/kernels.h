@@ -123,7 +123,6 @@ struct KvView {
   unsigned long long* counters;
 };
 
-constexpr uint32_t kAttnQueries = 256;
 constexpr uint32_t kAttnMaxItemPages = 1024;  // page-table entries one attention item may span
 
 // One attention work item: q_block (128) queries of one request against the key tiles [kt_begin, kt_end)
@@ -164,10 +163,12 @@ struct StepLists {
   const AttnGroup* groups;   // query tiles that were split
   const RowTile* row_tiles;  // projection tiles, none crosses a request
   uint32_t n_row_tiles;
+  const uint32_t* group_req; // request of rows row0, row0 + 32, .. and, behind the last of these, of the last row
   float* partials;           // [slot][head][q_block][64]
   uint32_t n_items, n_groups;
   uint32_t q_block;          // queries per item
   uint32_t B, N;
+  uint32_t row0;             // first of the N new-token rows these lists are about
 };
 
 // One pass over every request's timestamps (max_seq: the longest request's prefix + new tokens): ts_ordered, which
@@ -186,16 +187,16 @@ hipError_t launch_gemm_front(const HstuDims& hd, uint32_t layer, const void* xn,
                              const int32_t* page_tables, hipStream_t stream);
 hipError_t launch_gemm_back(const HstuDims& hd, const void* g, const void* w2t, const float* b2,
                             const void* x, void* y, uint32_t N, hipStream_t stream);
-// bf16 models with d = 128 or 256: LayerNorm, projection and epilogue of a layer half in one kernel
-// (front: X -> U, Q*log2(e), K/V pages; back: O, U, X -> Y); weights transposed as for the GEMMs.
-// In bf16 models U, O, the normalised matrices and the transposed weights (launch_transpose_weights) are half precision.
+// bf16 models with d = 64, 128, 256 or 512: LayerNorm, projection and epilogue of a layer half in one kernel
+// (front: X -> U, Q*log2(e), K/V pages; back: O, U, X -> Y); weights as fragments.
+// In bf16 models U, O, the normalised matrices and the library's weight copies (launch_transpose_weights) are half precision.
 bool layer_halves_fused(const HstuDims& hd);
 hipError_t launch_layer_front_fused(const HstuDims& hd, uint32_t layer, const void* x, const float* ln_g,
-                                    const float* ln_b, const void* w1t, const float* b1, void* u, void* q,
+                                    const float* ln_b, const void* w1f, const float* b1, void* u, void* q,
                                     const KvView& kv, const StepLists& sl, const int32_t* page_tables,
                                     hipStream_t stream);
 hipError_t launch_layer_back_fused(const HstuDims& hd, const void* o, const void* u, const float* ln_g,
-                                   const float* ln_b, const void* w2t, const float* b2, const void* x, void* y,
+                                   const float* ln_b, const void* w2f, const float* b2, const void* x, void* y,
                                    const StepLists& sl, hipStream_t stream);
 // o_half (bf16 models): the output is written in half precision (the step's own matrix between the attention and the
 // second LayerNorm) instead of bf16 (what a caller of the attention alone gets)
@@ -208,7 +209,8 @@ hipError_t launch_attention_reduce(const HstuDims& hd, const StepLists& sl, void
 // q must already be multiplied by log2(e) (launch_gemm_front stores it that way)
 hipError_t launch_scale_bias(const float* in, float* out, uint64_t n, hipStream_t stream);
 hipError_t launch_scale_q(const void* in, void* out, uint64_t n, hipStream_t stream);
-hipError_t launch_transpose_weights(const void* w, void* wt, uint32_t rows, uint32_t cols, uint32_t elem,
+// fragments: in the operand order of the fused layer halves instead of transposed (bf16 models of those widths)
+hipError_t launch_transpose_weights(const void* w, void* wt, uint32_t rows, uint32_t cols, uint32_t elem, bool fragments,
                                     hipStream_t stream);
 
 }  // namespace racer

@@ -234,8 +234,9 @@ struct racer_pool {
 struct racer_hstu {
   racer_hstu_cfg cfg;
   racer_hstu_weights w;
-  void* w1t = nullptr;  // bf16 models: [L][4d][d], the MFMA kernels want output-major weights; half precision copies
-  void* w2t = nullptr;  // [L][d][d]
+  // bf16 models: half-precision copies of W1 and W2, as operand fragments for the fused layer halves, else output-major
+  void* w1t = nullptr;
+  void* w2t = nullptr;
   float* pos_s = nullptr;   // bf16 models: pos and time tables times log2(e), as the attention kernel wants them
   float* time_s = nullptr;
 };
@@ -699,14 +700,15 @@ int32_t hstu_model_create(const racer_hstu_cfg* cfg, const racer_hstu_weights* w
   m->w = *w;
   if (cfg->elem == RACER_ELEM_BF16) {
     const uint64_t d = cfg->d;
+    const bool fused = racer::layer_halves_fused(racer::HstuDims{cfg->L, cfg->d, cfg->H, cfg->d / cfg->H, cfg->elem});
     hipError_t e = hipMalloc(&m->w1t, cfg->L * d * 4 * d * 2);
     if (e == hipSuccess) e = hipMalloc(&m->w2t, cfg->L * d * d * 2);
     for (uint32_t l = 0; l < cfg->L && e == hipSuccess; ++l) {
       e = racer::launch_transpose_weights(static_cast<const uint16_t*>(w->w1) + l * d * 4 * d,
-                                          static_cast<uint16_t*>(m->w1t) + l * d * 4 * d, cfg->d, 4 * cfg->d, 1, nullptr);
+                                          static_cast<uint16_t*>(m->w1t) + l * d * 4 * d, cfg->d, 4 * cfg->d, 1, fused, nullptr);
       if (e == hipSuccess)
         e = racer::launch_transpose_weights(static_cast<const uint16_t*>(w->w2) + l * d * d,
-                                            static_cast<uint16_t*>(m->w2t) + l * d * d, cfg->d, cfg->d, 1, nullptr);
+                                            static_cast<uint16_t*>(m->w2t) + l * d * d, cfg->d, cfg->d, 1, fused, nullptr);
     }
     const uint64_t n_pos_all = static_cast<uint64_t>(cfg->L) * cfg->H * cfg->n_pos;
     const uint64_t n_time_all = static_cast<uint64_t>(cfg->L) * cfg->H * cfg->n_time;
@@ -766,9 +768,9 @@ StepBounds step_bounds(uint64_t B, uint64_t N, uint64_t max_seq, uint32_t H, uin
   const uint64_t chunk_cap = std::max<uint64_t>(1, (static_cast<uint64_t>(racer::kAttnMaxItemPages) - 2) * page_tokens / 64 * 4 / 5);
   const uint64_t items = Q + std::max<uint64_t>(2048 / H + 1, V / chunk_cap + 1);
   StepBounds b;
-  b.list_bytes = sizeof(racer::ReqDev) * (B + 1) + 4 * (N + 1) + sizeof(racer::AttnItem) * items +
+  b.list_bytes = sizeof(racer::ReqDev) * (B + 1) + 4 * (N + 1) + 4 * (N / 32 + 2 * kMaxRuns) + sizeof(racer::AttnItem) * items +
                  (sizeof(racer::AttnGroup) + sizeof(racer::RowTile)) * (Q + 1) +
-                 sizeof(racer::AttnWork) * racer::kXcds * items * H + 6 * 256;
+                 sizeof(racer::AttnWork) * racer::kXcds * items * H + 7 * 256;
   b.partial_bytes = items * H * 128 * 64 * sizeof(float);
   b.partial_bytes += b.partial_bytes / 4;
   return b;
@@ -844,6 +846,13 @@ int32_t prepare_step(racer_pool* p, racer_hstu* m, const racer_hstu_req* reqs, u
     }
     while (k < n_runs) { run_begin[k] = std::max(run_begin[k - 1] + 1, B - (n_runs - k)); ++k; }
     run_begin[n_runs] = B;
+    for (uint32_t run = 0; run < n_runs; ++run) {
+      const uint64_t row_end = run_begin[run + 1] < B ? reqs[run_begin[run + 1]].x_off : N;
+      if (row_end == reqs[run_begin[run]].x_off) {  // a run without new tokens: one pipeline
+        n_runs = 1;
+        run_begin[1] = B;
+      }
+    }
   }
   auto run_of = [&](uint32_t req) {
     uint32_t k = 0;
@@ -924,19 +933,39 @@ int32_t prepare_step(racer_pool* p, racer_hstu* m, const racer_hstu_req* reqs, u
   }
 
   const uint64_t bytes_reqs = sizeof(racer::ReqDev) * std::max<uint32_t>(B, 1);
-  const uint64_t bytes_rows = sizeof(uint32_t) * std::max<uint64_t>(N, 1);
+  const bool fp32 = c.elem != RACER_ELEM_BF16;
+  const bool fused = racer::layer_halves_fused(racer::HstuDims{c.L, c.d, c.H, c.d / c.H, c.elem});
+  const uint64_t bytes_rows = fp32 ? sizeof(uint32_t) * std::max<uint64_t>(N, 1) : 0;  // row -> request: the fp32 kernels
   const uint64_t bytes_items = sizeof(racer::AttnItem) * std::max<size_t>(items.size(), 1);
   const uint64_t bytes_groups = sizeof(racer::AttnGroup) * std::max<size_t>(groups.size(), 1);
-  std::vector<racer::RowTile> row_tiles;
-  for (uint32_t r = 0; r < B; ++r)
-    for (uint32_t t0 = 0; t0 < reqs[r].new_len; t0 += 128)
-      row_tiles.push_back({static_cast<uint32_t>(reqs[r].x_off) + t0, std::min<uint32_t>(128, reqs[r].new_len - t0), r, 0});
+  std::vector<racer::RowTile> row_tiles;  // bf16 models whose layer halves are not fused
+  if (!fp32 && !fused)
+    for (uint32_t r = 0; r < B; ++r)
+      for (uint32_t t0 = 0; t0 < reqs[r].new_len; t0 += 128)
+        row_tiles.push_back({static_cast<uint32_t>(reqs[r].x_off) + t0, std::min<uint32_t>(128, reqs[r].new_len - t0), r, 0});
+  // fused layer halves: the request of every 32nd row of a run, and of the run's last row
+  std::vector<uint32_t> group_req;
+  size_t group_begin[kMaxRuns] = {};
+  if (fused)
+    for (uint32_t run = 0; run < n_runs; ++run) {
+      group_begin[run] = group_req.size();
+      uint64_t next = run_begin[run] < B ? reqs[run_begin[run]].x_off : N;
+      uint32_t last = run_begin[run];
+      for (uint32_t r = run_begin[run]; r < run_begin[run + 1]; ++r) {
+        const uint64_t end = reqs[r].x_off + reqs[r].new_len;
+        if (reqs[r].new_len) last = r;
+        for (; next < end; next += 32) group_req.push_back(r);
+      }
+      group_req.push_back(last);
+    }
+  const uint64_t bytes_group_req = sizeof(uint32_t) * std::max<size_t>(group_req.size(), 1);
   const uint64_t bytes_row_tiles = sizeof(racer::RowTile) * std::max<size_t>(row_tiles.size(), 1);
   const uint64_t bytes_work = sizeof(racer::AttnWork) * std::max<size_t>(work.size(), 1);
   const uint64_t off_rows = (bytes_reqs + 255) & ~255ull, off_items = (off_rows + bytes_rows + 255) & ~255ull;
   const uint64_t off_groups = (off_items + bytes_items + 255) & ~255ull;
   const uint64_t off_row_tiles = (off_groups + bytes_groups + 255) & ~255ull;
-  const uint64_t off_work = (off_row_tiles + bytes_row_tiles + 255) & ~255ull;
+  const uint64_t off_group_req = (off_row_tiles + bytes_row_tiles + 255) & ~255ull;
+  const uint64_t off_work = (off_group_req + bytes_group_req + 255) & ~255ull;
   const uint64_t total = off_work + bytes_work;
   {
     int32_t rc_l = ensure_lists(p, total, total * 2);
@@ -951,8 +980,10 @@ int32_t prepare_step(racer_pool* p, racer_hstu* m, const racer_hstu_req* reqs, u
   for (uint32_t r = 0; r < B; ++r) {
     hr[r] = racer::ReqDev{reqs[r].prefix_len, reqs[r].new_len, static_cast<uint32_t>(reqs[r].page_table_off),
                           static_cast<uint32_t>(reqs[r].ts_off), static_cast<uint32_t>(reqs[r].x_off), (ts && N) ? 1u : 0u /* cleared by the check */};
-    for (uint32_t i = 0; i < reqs[r].new_len; ++i) hrow[reqs[r].x_off + i] = r;
+    if (fp32)
+      for (uint32_t i = 0; i < reqs[r].new_len; ++i) hrow[reqs[r].x_off + i] = r;
   }
+  if (!group_req.empty()) std::memcpy(hbuf + off_group_req, group_req.data(), sizeof(uint32_t) * group_req.size());
   if (!items.empty()) std::memcpy(hbuf + off_items, items.data(), sizeof(racer::AttnItem) * items.size());
   if (!groups.empty()) std::memcpy(hbuf + off_groups, groups.data(), sizeof(racer::AttnGroup) * groups.size());
   if (!row_tiles.empty()) std::memcpy(hbuf + off_row_tiles, row_tiles.data(), sizeof(racer::RowTile) * row_tiles.size());
@@ -984,6 +1015,8 @@ int32_t prepare_step(racer_pool* p, racer_hstu* m, const racer_hstu_req* reqs, u
   ctx->sl.q_block = q_block;
   ctx->sl.row_tiles = reinterpret_cast<const racer::RowTile*>(p->hl_dev + off_row_tiles);
   ctx->sl.n_row_tiles = static_cast<uint32_t>(row_tiles.size());
+  ctx->sl.group_req = reinterpret_cast<const uint32_t*>(p->hl_dev + off_group_req);
+  ctx->sl.row0 = 0;
   ctx->sl.B = B;
   ctx->sl.N = static_cast<uint32_t>(N);
   ctx->n_runs = n_runs;
@@ -1005,6 +1038,9 @@ int32_t prepare_step(racer_pool* p, racer_hstu* m, const racer_hstu_req* reqs, u
       ctx->run_row0[run] = run_begin[run] < B ? static_cast<uint32_t>(reqs[run_begin[run]].x_off) : static_cast<uint32_t>(N);
       const uint64_t row_end = run_begin[run + 1] < B ? reqs[run_begin[run + 1]].x_off : N;
       ctx->run_rows[run] = static_cast<uint32_t>(row_end - ctx->run_row0[run]);
+      h.group_req = ctx->sl.group_req + group_begin[run];
+      h.row0 = ctx->run_row0[run];
+      h.N = ctx->run_rows[run];
     }
   }
   return RACER_OK;
@@ -1045,7 +1081,7 @@ int32_t hstu_step(racer_pool_t* p, racer_hstu_t* m, const racer_hstu_req* reqs, 
   // A large bf16 batch runs as several pipelines, one per run of requests, all but the first on streams of the
   // pool's own: requests share nothing inside a step, and the workgroups of one pipeline's kernel fill the slots
   // that another's leaves idle towards its end.  Not while kernels are being timed (their durations would overlap).
-  const bool fused = c.elem == RACER_ELEM_BF16 && (c.d == 128 || c.d == 256);
+  const bool fused = racer::layer_halves_fused(racer::HstuDims{c.L, c.d, c.H, c.d / c.H, c.elem});
   uint64_t n_tokens = 0, n_pairs = 0;
   for (uint32_t r = 0; r < B; ++r) {
     n_tokens += reqs[r].new_len;
@@ -1071,9 +1107,7 @@ int32_t hstu_step(racer_pool_t* p, racer_hstu_t* m, const racer_hstu_req* reqs, 
   const bool bf16 = c.elem == RACER_ELEM_BF16;
   const uint64_t w1_layer = d * 4 * d * ctx.esize, w2_layer = d * d * ctx.esize;
   const uint32_t n_runs = ctx.n_runs;
-  bool split = n_runs > 1;
-  for (uint32_t run = 0; split && run < n_runs; ++run)
-    if (ctx.run[run].n_row_tiles == 0 || ctx.run[run].n_work == 0) split = false;  // a run without new tokens
+  const bool split = n_runs > 1;
   if (split) {  // the other pipelines start behind everything the caller's stream holds so far (lists included)
     if ((rc = ensure_step_streams(p, n_runs - 1))) return rc;
     HIP_TRY(hipEventRecord(p->ev_fork, stream));

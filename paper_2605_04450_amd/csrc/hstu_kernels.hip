@@ -496,11 +496,19 @@ __device__ __forceinline__ void forget(u32x4& a) { asm volatile("" : "+v"(a)); }
 __device__ __forceinline__ uint32_t lds_address(const void* p) {
   return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const void*)p));
 }
+__device__ __forceinline__ const uint8_t* in_scalar(const uint8_t* p) {  // a pointer all lanes agree on, in scalar registers
+  const uint64_t a = reinterpret_cast<uint64_t>(p);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(a)), hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(a >> 32));
+  return reinterpret_cast<const uint8_t*>((static_cast<uint64_t>(hi) << 32) | lo);
+}
 // (A memory instruction may read a scalar register only five wait states after a vector instruction, v_readfirstlane for
 // one, has written it.  The compiler keeps that distance for its own instructions but does not look into this one.)
 template <int OFFSET>
 __device__ __forceinline__ void copy_to_lds(const void* base, uint32_t voff) {
   asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %0, %1 offset:%2" ::"v"(voff), "s"(base), "n"(OFFSET) : "memory");
+}
+__device__ __forceinline__ void copy_to_lds_from(const void* src) {  // from an address of each lane's own
+  asm volatile("global_load_lds_dwordx4 %0, off" ::"v"(src) : "memory");
 }
 __device__ __forceinline__ void set_lds_target(uint32_t lds) { asm volatile("s_mov_b32 m0, %0\n\ts_nop 0" ::"s"(lds) : "memory"); }
 template <int N>
@@ -863,10 +871,10 @@ __global__ __launch_bounds__(256) void attention_f32(HstuDims hd, uint32_t layer
 }
 
 // ---------------------------------------------------------------------------------------
-// bf16 paged attention on MFMA, d_h = 64.  A block of four wavefronts owns 128 * NQB consecutive
-// queries of one request and one head (32 * NQB per wavefront, as NQB 32-query groups) and walks
-// a range of key tiles (64 keys), staging K [key][d_h] and V^T [d_h][key] of the tile in
-// LDS through the page table (tile k+1 is fetched into registers while tile k is used).
+// bf16 paged attention on MFMA, d_h = 64.  A block of four wavefronts owns 128 consecutive
+// queries of one request and one head (32 per wavefront) and walks
+// a range of key tiles (64 keys), K [key][d_h] and V^T [d_h][key] of the tile in
+// LDS, copied there through the page table while the tile before it is used.
 // Each wavefront computes S^T = K Q^T (keys x queries, so a lane ends up holding one query
 // and 16 keys), applies bias, SiLU and the causal mask in registers, and feeds the bf16
 // result straight back as the second operand of O^T += V^T P^T: the accumulator layout of
@@ -883,33 +891,43 @@ __global__ __launch_bounds__(256) void attention_f32(HstuDims hd, uint32_t layer
 //   - the positional bias is Toeplitz: the window of the (reversed, scaled) table that a key
 //     tile needs sits in LDS, in four copies shifted by one element each so that every lane
 //     can read its 8 consecutive entries as aligned 16-byte words, and initialises the score
-//     accumulators, so adding it costs no arithmetic;
+//     accumulators, so adding it costs no arithmetic; from one tile to the next the window moves by 64 entries,
+//     which replace the oldest ones of a ring;
 //   - time gaps are taken from 32-bit timestamps relative to the request's first one; for a
 //     32x32 block whose smallest and largest gap fall into the same log2 bucket (most blocks
 //     away from the diagonal) the time bias is one scalar; if they fall into adjacent
 //     buckets it is a compare-and-select per score; other blocks take the bucket per score;
 //     requests spanning >= 2^31 s (or models with more than 32 buckets) use 64-bit gaps;
 //   - the causal select is applied only in blocks that touch the diagonal.
+//
+// What the vector unit has to do is fixed by that (about 680 of its cycles per 32x32 block, 256 of the matrix unit), so
+// the rest is to keep it fed: the copies to LDS pass through no registers, which leaves the 128 that four wavefronts
+// per SIMD allow, and the block needs 40 KB of LDS, so that four are resident per CU.  With tiles staged through registers
+// (168 of them, 48 KB, three per SIMD) a launch over 195M (query, key) pairs, d = 256, took 0.382 ms, now 0.333
+// (600 TFLOP/s); over 32 x 512 queries behind 16 384 keys, d = 512, 0.971 ms, now 0.849 (657 TFLOP/s).
 // ---------------------------------------------------------------------------------------
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
-constexpr uint32_t kPosWinMax = 320;  // 256 queries + 64 keys - 1 distances per tile, padded
-
-struct AttnTile {  // one staged key tile
-  uint16_t Ks[64][64 + kLdsPad];
-  uint16_t Vs[64][64 + kLdsPad];
-  uint32_t tk[64];             // key timestamps relative to the request's first one
-  // copy s holds window entry x at [s][4 + x - s]; a copy is 32 bytes (mod 128) long, which spreads the
-  // 16-byte reads of eight neighbouring lanes (two per copy) over all LDS banks
-  float pos[4][kPosWinMax + 8];
-};
+constexpr uint32_t kAttnQ = 128;     // queries per block
+constexpr uint32_t kPosRing = 256;   // a tile needs 191 distances, the next one 64 new ones
+constexpr uint32_t kPosMirror = 24;  // the first entries once more behind the end: a lane reads up to 24 from its first
 
 struct AttnShared {
-  AttnTile tile[2];  // tile k is consumed from one half while tile k+1 is written into the other
+  // two staged key tiles: K [key][d_h] and V^T [d_h][key], 64 rows of 128 bytes each; chunk c (16 bytes) of row r sits
+  // at c ^ (r mod 8), which spreads the operand reads of eight neighbouring lanes over all banks
+  uint8_t kv[2][2][8192];
+  // copy s holds entry x of the positional window at (x - s) mod kPosRing, so that any 8 consecutive entries can be
+  // read as aligned 16-byte words of one of the copies; a copy is 96 bytes (mod 128) long, which spreads the
+  // reads of eight neighbouring lanes (two per copy) over all banks
+  float pos[4][kPosRing + kPosMirror];
+  uint32_t tk[2][64];  // key timestamps of the staged tiles relative to the request's first one
   float time[64];
-  float rtime[32];   // rtime[c] = time bias of a gap with c leading zero bits (32-bit gaps, n_time <= 32)
+  float rtime[32];     // rtime[c] = time bias of a gap with c leading zero bits (32-bit gaps, n_time <= 32)
   int32_t pages[kAttnMaxItemPages];  // page ids of the item's key range (-1: outside the pool)
 };
+static_assert(sizeof(AttnShared) <= 40960, "four blocks per CU");
+
+__device__ const uint4 kZeroChunk = {0, 0, 0, 0};  // what keys without a page are copied from
 
 __device__ __forceinline__ uint32_t bucket_u32(uint32_t dt, uint32_t n_time) {
   const uint32_t b = dt > 1 ? 31u - static_cast<uint32_t>(__clz(static_cast<int>(dt))) : 0u;
@@ -929,11 +947,10 @@ __device__ __forceinline__ float silu_log2(float y) {
   return y * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-y));
 }
 
-// NQB = 32-query groups per wavefront (1: 128 queries per block, three resident blocks per CU).
 // OHALF: the output goes out in half precision (the step's own matrix between the attention and the second
 // LayerNorm) instead of bf16 (what a caller of the attention alone gets).
-template <int NQB, bool OHALF>
-__global__ __launch_bounds__(256, NQB == 1 ? 3 : 2) void attention_bf16_mfma(HstuDims hd, uint32_t layer, const uint16_t* __restrict__ q,
+template <bool OHALF>
+__global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint32_t layer, const uint16_t* __restrict__ q,
                                                               const float* __restrict__ pos,
                                                               const float* __restrict__ time, KvView kv,
                                                               const ReqDev* __restrict__ reqs,
@@ -943,17 +960,17 @@ __global__ __launch_bounds__(256, NQB == 1 ? 3 : 2) void attention_bf16_mfma(Hst
                                                               const int32_t* __restrict__ page_tables,
                                                               const long long* __restrict__ ts,
                                                               uint16_t* __restrict__ o) {
-  constexpr uint32_t kQ = 128 * NQB;     // queries per block
-  constexpr uint32_t kPosWin = kQ + 64;  // distances a tile can need (kQ + 63), padded
   __shared__ __attribute__((aligned(16))) AttnShared sm;
-  const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5, li = lane & 31;
+  const uint32_t tid = threadIdx.x, lane = tid & 63, g = lane >> 5, li = lane & 31;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const AttnWork wk = work[blockIdx.x];
   if (wk.item == kNoWork) return;  // padding of a die's list
   const AttnItem item = items[wk.item];
-  const uint32_t r = item.req, qt = item.qt, h = wk.head;
-  const ReqDev rq = reqs[r];
-  const uint32_t P = rq.prefix_len, T = rq.new_len, S = P + T;
-  const uint32_t q0 = qt * kQ;  // first query (index among the new tokens) of the block
+  auto scalar = [](uint32_t x) { return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(x)); };  // all lanes agree on it
+  const uint32_t h = scalar(wk.head);
+  const ReqDev rq = reqs[item.req];
+  const uint32_t P = scalar(rq.prefix_len), T = scalar(rq.new_len), S = P + T;
+  const uint32_t q0 = item.qt * kAttnQ;  // first query (index among the new tokens) of the block
   const long long* tsr = ts + rq.ts_off;
   const long long ts_base = tsr[0];
   const long long span = tsr[S - 1] - ts_base;
@@ -966,45 +983,42 @@ __global__ __launch_bounds__(256, NQB == 1 ? 3 : 2) void attention_bf16_mfma(Hst
   }
   const float* pos_h = pos + (static_cast<uint64_t>(layer) * hd.H + h) * hd.n_pos;
 
-  // per 32-query group qb of this wavefront
-  uint32_t ql[NQB], p[NQB], grp_first[NQB], grp_last[NQB], tq[NQB], tq_first[NQB], tq_last[NQB];
-  bool q_ok[NQB], grp_active[NQB];
-  long long ts_q[NQB];
-  bf16x8 qf[NQB][4];  // Q^T operand: lane (g, li) holds query li, d_h elements 16*st + 8*g .. +8
-  f32x16 oacc[NQB][2];
-#pragma unroll
-  for (int qb = 0; qb < NQB; ++qb) {
-    ql[qb] = 32 * NQB * wave + 32 * qb + li;  // query index inside the block
-    const uint32_t qi = q0 + ql[qb];
-    q_ok[qb] = qi < T;
-    p[qb] = P + qi;
-    const uint32_t first = q0 + 32 * NQB * wave + 32 * qb;
-    grp_active[qb] = first < T;
-    grp_first[qb] = P + first;
-    grp_last[qb] = P + (first + 31 < T - 1 ? first + 31 : T - 1);
-    ts_q[qb] = q_ok[qb] ? tsr[p[qb]] : ts_base;
-    tq[qb] = static_cast<uint32_t>(ts_q[qb] - ts_base);
-    uint32_t a = 0, b = 0;
-    if (grp_active[qb]) {
-      a = static_cast<uint32_t>(tsr[grp_first[qb]] - ts_base);
-      b = static_cast<uint32_t>(tsr[grp_last[qb]] - ts_base);
-    }
-    tq_first[qb] = __builtin_amdgcn_readfirstlane(a);
-    tq_last[qb] = __builtin_amdgcn_readfirstlane(b);
-#pragma unroll
-    for (int st = 0; st < 4; ++st) {
-      uint4 val = make_uint4(0, 0, 0, 0);
-      if (q_ok[qb]) val = *reinterpret_cast<const uint4*>(q + static_cast<uint64_t>(rq.x_off + qi) * hd.d + h * 64 + 16 * st + 8 * g);
-      qf[qb][st] = __builtin_bit_cast(bf16x8, val);
-    }
-#pragma unroll
-    for (int b2 = 0; b2 < 2; ++b2)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) oacc[qb][b2][e] = 0.0f;
+  // A wavefront takes 32 queries and all keys of a tile.  With at most 64 queries in the block, the wavefronts are
+  // paired instead: each pair takes 32 queries, one of it the first and the other the second half of every tile, and their
+  // sums are added at the end, so that no SIMD idles (128 requests of 64 queries: 122 -> 108 us).
+  const bool paired = T - q0 <= 64;
+  const uint32_t grp = paired ? wave & 1 : wave;
+  const uint32_t sb_first = paired ? wave >> 1 : 0, sb_last = paired ? wave >> 1 : 1;
+  const uint32_t ql = 32 * grp + li;  // query index inside the block
+  const uint32_t qi = q0 + ql;
+  const bool q_ok = qi < T;
+  const uint32_t p = P + qi;
+  const uint32_t first = q0 + 32 * grp;
+  const bool grp_active = first < T;
+  const uint32_t grp_first = P + first, grp_last = P + (first + 31 < T - 1 ? first + 31 : T - 1);
+  const uint32_t tq = static_cast<uint32_t>((q_ok ? tsr[p] : ts_base) - ts_base);
+  uint32_t tq_first = 0, tq_last = 0;
+  if (grp_active) {
+    tq_first = static_cast<uint32_t>(tsr[grp_first] - ts_base);
+    tq_last = static_cast<uint32_t>(tsr[grp_last] - ts_base);
   }
+  tq_first = __builtin_amdgcn_readfirstlane(tq_first);
+  tq_last = __builtin_amdgcn_readfirstlane(tq_last);
+  bf16x8 qf[4];  // Q^T operand: lane (g, li) holds query li, d_h elements 16*st + 8*g .. +8
+#pragma unroll
+  for (int st = 0; st < 4; ++st) {
+    u32x4 val = {0, 0, 0, 0};
+    if (q_ok) val = *reinterpret_cast<const u32x4*>(q + static_cast<uint64_t>(rq.x_off + qi) * hd.d + h * 64 + 16 * st + 8 * g);
+    qf[st] = __builtin_bit_cast(bf16x8, val);
+  }
+  f32x16 oacc[2];
+#pragma unroll
+  for (int b2 = 0; b2 < 2; ++b2)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) oacc[b2][e] = 0.0f;
 
   const uint64_t koff = kv_block_offset(hd, layer, 0, h, 2), voff = kv_block_offset(hd, layer, 1, h, 2);
-  const uint32_t kt_begin = item.kt_begin, kt_end = item.kt_end;
+  const uint32_t kt_begin = scalar(item.kt_begin), kt_end = scalar(item.kt_end);
   // the item's slice of the page table goes to LDS once, so that a tile fetch is a single
   // global round trip instead of two dependent ones
   uint32_t page0, unused_ip;
@@ -1022,327 +1036,298 @@ __global__ __launch_bounds__(256, NQB == 1 ? 3 : 2) void attention_bf16_mfma(Hst
       sm.pages[i] = pg;
     }
   }
+  // Positional window: entry x = (key - first key of the item) + (127 - query in the block) holds the (reversed, scaled)
+  // bias of distance pos_top - x.  Negative distances belong to keys after the query, which the causal select removes.
+  const int32_t pos_top = static_cast<int32_t>(P + q0 + kAttnQ - 1 - kt_begin * 64);
+  auto pos_at = [&](uint32_t x) {
+    int32_t i = pos_top - static_cast<int32_t>(x);
+    i = i < 0 ? 0 : (i > static_cast<int32_t>(hd.n_pos) - 1 ? static_cast<int32_t>(hd.n_pos) - 1 : i);
+    return pos_h[i];
+  };
+  auto pos_put = [&](uint32_t x, float v) {
+#pragma unroll
+    for (uint32_t s = 0; s < 4; ++s) {
+      const uint32_t at = (x - s) & (kPosRing - 1);
+      sm.pos[s][at] = v;
+      if (at < kPosMirror) sm.pos[s][kPosRing + at] = v;
+    }
+  };
+  auto tile_time = [&](uint32_t j) { return j < S ? static_cast<uint32_t>(tsr[j] - ts_base) : 0u; };
+  if (tid < 191) pos_put(tid, pos_at(tid));
+  if (tid >= 192) sm.tk[0][tid - 192] = tile_time(kt_begin * 64 + tid - 192);
   __syncthreads();
 
-  // registers that carry the next tile from global memory to LDS
-  uint4 kreg[2], vreg[2];
-  uint32_t treg = 0;
-  float preg[2] = {0.0f, 0.0f};
-  // thread-constant byte offsets of its two K and two V^T chunks inside a tile that lies in one page
+  // A tile is copied global -> LDS without passing through registers, four 1 KB copies per wavefront: two of K, two of V^T.
+  // A lane's 16 bytes of copy i: LDS row 16 * wave + 8 * i + r with r = lane / 8, chunk position lane % 8.  LDS row R of K
+  // holds key R with bits 2 and 3 swapped: the 8 keys a lane holds after the first product are then consecutive, and the
+  // matching V^T operand is one 16-byte read.
+  const uint32_t r8 = lane >> 3, part = (lane & 7) ^ r8;
+  const uint32_t krow = 16 * wave + (r8 & 3) + 8 * (r8 >> 2);  // + 4 i
+  const uint32_t vrow = 16 * wave + r8;                        // + 8 i
+  const uint32_t kconst = krow * 128 + part * 16, vconst = (vrow * hd.pt + part * 8) * 2;
   const bool one_page_tiles = hd.pt_shift < 32 && hd.pt >= 64;
-  uint32_t kconst[2], vconst[2];
-#pragma unroll
-  for (int it = 0; it < 2; ++it) {
-    const uint32_t c = tid + 256 * it, row = c >> 3, part = c & 7;
-    kconst[it] = row * 128 + part * 16;
-    vconst[it] = (row * hd.pt + part * 8) * 2;
-  }
-  const int32_t pos_top = static_cast<int32_t>(P + q0 + kQ - 1);  // window entry m of tile j0 is pos[pos_top - j0 - m]
-  auto fetch = [&](uint32_t kt) {
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(&sm.kv[0][0][0])) + wave * 2048;
+  auto fetch = [&](uint32_t kt, uint32_t buf) {
     const uint32_t j0 = kt * 64;
-    bool done = false;
+    const uint32_t lds = lds0 + buf * 16384;
     if (one_page_tiles && j0 + 64 <= S) {
-      // the whole tile sits in one page and inside the sequence: one scalar base, no per-thread arithmetic
       const int32_t page = __builtin_amdgcn_readfirstlane(sm.pages[(j0 >> hd.pt_shift) - page0]);
-      if (page >= 0) {
+      if (page >= 0) {  // the whole tile sits in one page and inside the sequence: scalar bases, no per-lane arithmetic
         const uint32_t tb = j0 & (hd.pt - 1);
         const uint8_t* pb = kv.base + static_cast<uint64_t>(page) * kv.page_size;
-        const uint8_t* kbase = pb + koff + static_cast<uint64_t>(tb) * 128;
-        const uint8_t* vbase = pb + voff + static_cast<uint64_t>(tb) * 2;
-#pragma unroll
-        for (int it = 0; it < 2; ++it) {
-          kreg[it] = *reinterpret_cast<const uint4*>(kbase + kconst[it]);
-          vreg[it] = *reinterpret_cast<const uint4*>(vbase + vconst[it]);
-        }
-        done = true;
+        const uint8_t* kbase = in_scalar(pb + koff + static_cast<uint64_t>(tb) * 128);
+        const uint8_t* vbase = in_scalar(pb + voff + static_cast<uint64_t>(tb) * 2);
+        set_lds_target(lds);
+        copy_to_lds<0>(kbase, kconst);
+        set_lds_target(lds + 1024);
+        copy_to_lds<0>(kbase + 512, kconst);
+        set_lds_target(lds + 8192);
+        copy_to_lds<0>(vbase, vconst);
+        set_lds_target(lds + 8192 + 1024);
+        copy_to_lds<0>(vbase + 16 * hd.pt, vconst);
+        return;
       }
     }
-    if (!done) {
+    auto page_of = [&](uint32_t j, uint32_t* ip) -> const uint8_t* {
+      if (j >= S) return nullptr;
+      uint32_t pi;
+      split_token(hd, j, &pi, ip);
+      const int32_t page = sm.pages[pi - page0];
+      return page >= 0 ? kv.base + static_cast<uint64_t>(page) * kv.page_size : nullptr;
+    };
+    const uint8_t* zero = reinterpret_cast<const uint8_t*>(&kZeroChunk);
 #pragma unroll
-      for (int it = 0; it < 2; ++it) {
-        const uint32_t c = tid + 256 * it, row = c >> 3, part = c & 7;
-        // K: row = key, part = 8 d_h elements
-        kreg[it] = make_uint4(0, 0, 0, 0);
-        const uint32_t j = j0 + row;
-        if (j < S) {
-          uint32_t pi, ip;
-          split_token(hd, j, &pi, &ip);
-          const int32_t page = sm.pages[pi - page0];
-          if (page >= 0)
-            kreg[it] = *reinterpret_cast<const uint4*>(kv.base + static_cast<uint64_t>(page) * kv.page_size + koff +
-                                                       (static_cast<uint64_t>(ip) * 64 + part * 8) * 2);
-        }
-        // V^T: row = d_h element, part = 8 consecutive keys (inside one page: page_tokens % 8 == 0)
-        vreg[it] = make_uint4(0, 0, 0, 0);
-        const uint32_t jv = j0 + part * 8;
-        if (jv < S) {
-          uint32_t pi, ip;
-          split_token(hd, jv, &pi, &ip);
-          const int32_t page = sm.pages[pi - page0];
-          if (page >= 0) {
-            uint4 vval = *reinterpret_cast<const uint4*>(kv.base + static_cast<uint64_t>(page) * kv.page_size + voff +
-                                                         (static_cast<uint64_t>(row) * hd.pt + ip) * 2);
-            if (jv + 8 > S) {  // keys past the end of the sequence hold whatever the page held before
-              uint32_t w[4] = {vval.x, vval.y, vval.z, vval.w};
-#pragma unroll
-              for (int e = 0; e < 8; ++e)
-                if (jv + e >= S) w[e >> 1] &= (e & 1) ? 0x0000FFFFu : 0xFFFF0000u;
-              vval = make_uint4(w[0], w[1], w[2], w[3]);
-            }
-            vreg[it] = vval;
-          }
-        }
-      }
+    for (uint32_t i = 0; i < 2; ++i) {
+      uint32_t ip = 0;
+      const uint8_t* pb = page_of(j0 + krow + 4 * i, &ip);
+      const uint8_t* src = pb ? pb + koff + static_cast<uint64_t>(ip) * 128 + part * 16 : zero;
+      set_lds_target(lds + i * 1024);
+      copy_to_lds_from(src);
     }
-    // window of the reversed positional table (already scaled by log2 e); entries with a negative
-    // distance belong to keys after the query, which the causal select removes
+    uint32_t ip = 0;  // V^T: 8 consecutive keys inside one page (page_tokens % 8 == 0)
+    const uint8_t* pb = page_of(j0 + part * 8, &ip);
 #pragma unroll
-    for (int it = 0; it < 2; ++it) {
-      const uint32_t m = tid + 256 * it;
-      if (m < kPosWin) {
-        int32_t i = pos_top - static_cast<int32_t>(j0) - static_cast<int32_t>(m);
-        i = i < 0 ? 0 : (i > static_cast<int32_t>(hd.n_pos) - 1 ? static_cast<int32_t>(hd.n_pos) - 1 : i);
-        preg[it] = pos_h[i];
-      }
+    for (uint32_t i = 0; i < 2; ++i) {
+      const uint8_t* src = pb ? pb + voff + (static_cast<uint64_t>(vrow + 8 * i) * hd.pt + ip) * 2 : zero;
+      set_lds_target(lds + 8192 + i * 1024);
+      copy_to_lds_from(src);
     }
-    if (tid < 64) treg = (j0 + tid < S) ? static_cast<uint32_t>(tsr[j0 + tid] - ts_base) : 0u;
   };
-  auto commit = [&](AttnTile& t) {
+  // Behind the copies: keys past the end of the sequence that share a chunk of V^T with the last ones hold whatever the
+  // page held before, and are cleared by the lane that copied them.
+  auto fetched = [&](uint32_t kt, uint32_t buf) {
+    wait_vm<0>();
+    const uint32_t j0 = kt * 64;
+    if (j0 + 64 <= S || (S & 7) == 0) return;
+    if (j0 + part * 8 < S && j0 + part * 8 + 8 > S) {
 #pragma unroll
-    for (int it = 0; it < 2; ++it) {
-      const uint32_t c = tid + 256 * it, row = c >> 3, part = c & 7;
-      // key row r is stored at row perm(r) (bits 2 and 3 swapped): the first product then reads
-      // consecutive LDS rows, which the row padding keeps free of bank conflicts
-      *reinterpret_cast<uint4*>(&t.Ks[(row & 0x33) | ((row & 8) >> 1) | ((row & 4) << 1)][part * 8]) = kreg[it];
-      *reinterpret_cast<uint4*>(&t.Vs[row][part * 8]) = vreg[it];
-      if (c < kPosWin) {
+      for (uint32_t i = 0; i < 2; ++i) {
+        u32x4* c = reinterpret_cast<u32x4*>(&sm.kv[buf][1][wave * 2048 + i * 1024 + lane * 16]);
+        u32x4 v = *c;
 #pragma unroll
-        for (uint32_t s = 0; s < 4; ++s) t.pos[s][4 + c - s] = preg[it];  // copy s = window shifted by s
+        for (uint32_t e = 0; e < 8; ++e)
+          if (j0 + part * 8 + e >= S) v[e >> 1] &= (e & 1) ? 0x0000FFFFu : 0xFFFF0000u;
+        *c = v;
       }
     }
-    if (tid < 64) t.tk[tid] = treg;
   };
 
-  // first and last key timestamp of the two 32-key halves of a tile, through the scalar unit
-  // (read-only), one tile ahead; indices are clamped to the sequence
-  auto tile_times = [&](uint32_t kt, uint32_t out[4]) {
-    const uint32_t j0 = kt * 64;
+  // operand reads: row li (+ 32) of a tile, chunk 2 * st + g
+  uint32_t chunk_off[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const uint32_t j = j0 + 32 * (k >> 1) + 31 * (k & 1);
-      out[k] = static_cast<uint32_t>(tsr[j < S ? j : S - 1] - ts_base);
-    }
-  };
-  uint32_t tkb[4], tkb_next[4] = {0, 0, 0, 0};
-  fetch(kt_begin);
-  tile_times(kt_begin, tkb);
-  commit(sm.tile[0]);
-  if (kt_begin + 1 < kt_end) fetch(kt_begin + 1);
-  uint32_t cur = 0;
-  for (uint32_t kt = kt_begin; kt < kt_end; ++kt, cur ^= 1) {
-    const uint32_t j0 = kt * 64;
-    AttnTile& tl = sm.tile[cur];
-    // one barrier per tile: tile kt is visible, and every wave is done with tile kt-1, whose
-    // half now takes tile kt+1 (in registers since the previous iteration)
+  for (uint32_t st = 0; st < 4; ++st) chunk_off[st] = li * 128 + 16 * ((2 * st + g) ^ (li & 7));
+  const uint32_t pos_c0 = 8 * g + 127 - ql;  // the lane's first window entry of the item's first half tile
+  const float* pos_copy = sm.pos[pos_c0 & 3];
+
+  fetch(kt_begin, 0);
+  fetched(kt_begin, 0);
+  for (uint32_t kt = kt_begin; kt < kt_end; ++kt) {
+    const uint32_t j0 = kt * 64, t = kt - kt_begin, buf = t & 1;
+    // one barrier per tile: tile kt is in LDS, and every wavefront is done with tile kt - 1, whose half takes tile kt + 1
     __syncthreads();
-    if (kt != kt_begin) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) tkb[k] = tkb_next[k];
+    const bool more = kt + 1 < kt_end;
+    uint32_t side = 0;  // wavefront 0: the next tile's 64 window entries, wavefront 1: its timestamps
+    if (more) {
+      if (wave == 0) side = __float_as_uint(pos_at(64 * t + 191 + lane));
+      if (wave == 1) side = tile_time(j0 + 64 + lane);
+      fetch(kt + 1, buf ^ 1);
     }
-    if (kt + 1 < kt_end) {
-      commit(sm.tile[cur ^ 1]);
-      tile_times(kt + 1, tkb_next);
-      if (kt + 2 < kt_end) fetch(kt + 2);  // its global loads fly while this tile is consumed
+    const uint8_t* ks = &sm.kv[buf][0][0];
+    const uint8_t* vs = &sm.kv[buf][1][0];
+    // first and last key time of the two halves
+    uint32_t tkb[4] = {0, 0, 0, 0};
+    if (fast) {
+      const uint32_t mine = sm.tk[buf][lane];
+      tkb[0] = __builtin_amdgcn_readlane(mine, 0);
+      tkb[1] = __builtin_amdgcn_readlane(mine, 31);
+      tkb[2] = __builtin_amdgcn_readlane(mine, 32);
+      tkb[3] = __builtin_amdgcn_readlane(mine, 63);
     }
-
-    {
-      // operands are read from LDS right where they are consumed: holding all of them across
-      // the epilogue would push the kernel past 256 registers
-      auto k_frag = [&](int sb, int st) {
-        return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(&tl.Ks[32 * sb + li][16 * st + 8 * g]));
-      };
-      auto v_frag = [&](int sb, int s2, int db) {
-        return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(&tl.Vs[32 * db + li][32 * sb + 16 * s2 + 8 * g]));
-      };
-      // S^T = K Q^T on top of the positional bias: lane's window entries m0 .. m0+7 and m0+16 .. m0+23
-      auto scores_begin = [&](int qb, int sb) {
-        const uint32_t m0 = (kQ - 1) - ql[qb] + 32 * sb + 8 * g;
-        const float* pw = &tl.pos[m0 & 3][4 + (m0 & ~3u)];
-        const float4 w0 = *reinterpret_cast<const float4*>(pw), w1 = *reinterpret_cast<const float4*>(pw + 4);
-        const float4 w2 = *reinterpret_cast<const float4*>(pw + 16), w3 = *reinterpret_cast<const float4*>(pw + 20);
-        f32x16 sacc;
-        sacc[0] = w0.x; sacc[1] = w0.y; sacc[2] = w0.z; sacc[3] = w0.w;
-        sacc[4] = w1.x; sacc[5] = w1.y; sacc[6] = w1.z; sacc[7] = w1.w;
-        sacc[8] = w2.x; sacc[9] = w2.y; sacc[10] = w2.z; sacc[11] = w2.w;
-        sacc[12] = w3.x; sacc[13] = w3.y; sacc[14] = w3.z; sacc[15] = w3.w;
-        return sacc;
-      };
-      // bias, SiLU, mask -> bf16 pairs.  sacc[e]: key kb + 16*(e/8) + 8*g + e%8, query li of group qb;
-      // y = (q.k + pos) * log2 e
-      auto epilogue = [&](int qb, int sb, const f32x16& sacc, uint32_t pk[8]) {
-        const uint32_t kb = j0 + 32 * sb;
-        const bool diag = kb + 31 > grp_first[qb];
-        int mode = 2;  // 0: one time bias for the block, 1: two adjacent buckets, 2: bucket per score (+ mask)
-        float c_lo = 0.0f, c_hi = 0.0f;
-        uint32_t thr = 0;
-        if (fast && !diag) {
-          const uint32_t tk_first = tkb[2 * sb], tk_last = tkb[2 * sb + 1];
-          const uint32_t bmin = bucket_u32(tq_first[qb] - tk_last, hd.n_time);
-          const uint32_t bmax = bucket_u32(tq_last[qb] - tk_first, hd.n_time);
-          c_lo = sm.time[bmin];
-          if (bmin == bmax) {
-            mode = 0;
-          } else if (bmax == bmin + 1) {
-            mode = 1;
-            c_hi = sm.time[bmax];
-            thr = 2u << bmin;  // gaps >= 2^(bmin+1) belong to the upper bucket
-          }
-        }
-        if (mode == 0) {
+    auto k_frag = [&](int sb, int st) { return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(ks + sb * 4096 + chunk_off[st])); };
+    auto v_frag = [&](int sb, int s2, int db) {
+      return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(vs + db * 4096 + chunk_off[2 * sb + s2]));
+    };
+    // S^T = K Q^T on top of the positional bias: lane's window entries x0 .. x0+7 and x0+16 .. x0+23
+    auto scores_begin = [&](int sb) {
+      const float* pw = pos_copy + (((pos_c0 & ~3u) + 64 * t + 32 * sb) & (kPosRing - 1));
+      const f32x4 w0 = *reinterpret_cast<const f32x4*>(pw), w1 = *reinterpret_cast<const f32x4*>(pw + 4);
+      const f32x4 w2 = *reinterpret_cast<const f32x4*>(pw + 16), w3 = *reinterpret_cast<const f32x4*>(pw + 20);
+      f32x16 sacc;
 #pragma unroll
-          for (int e = 0; e < 16; e += 2)
-            pk[e >> 1] = pack_bf16x2(silu_log2(sacc[e] + c_lo), silu_log2(sacc[e + 1] + c_lo));
-          return;
-        }
-        if (fast) {
-          // eight scores at a time: the lane's key timestamps (all below 2^31) come as two 16-byte reads
-          const uint4* tkp = reinterpret_cast<const uint4*>(&tl.tk[32 * sb + 8 * g]);
-          const int32_t lim_t = tq[qb] >= thr ? static_cast<int32_t>(tq[qb] - thr) : -1;
-          const int lim = static_cast<int>(p[qb]) - static_cast<int>(kb) - 8 * static_cast<int>(g);  // visible: key offset <= lim
-#pragma unroll
-          for (int hf = 0; hf < 2; ++hf) {
-            const uint4 t0 = tkp[4 * hf], t1 = tkp[4 * hf + 1];
-            const uint32_t tkl[8] = {t0.x, t0.y, t0.z, t0.w, t1.x, t1.y, t1.z, t1.w};
-            float a[8];
-            if (mode == 1) {
-              // gap >= thr  <=>  key time <= query time - thr (never, if that is negative)
-#pragma unroll
-              for (int e = 0; e < 8; ++e)
-                a[e] = silu_log2(sacc[8 * hf + e] + (static_cast<int32_t>(tkl[e]) <= lim_t ? c_hi : c_lo));
-            } else {
-              // bucket per score through the table indexed by the gap's leading zero count; a key after
-              // the query gives a wrapped gap, whose (valid) table entry the causal select discards
-#pragma unroll
-              for (int e = 0; e < 8; ++e) {
-                const uint32_t gap = tq[qb] - tkl[e];
-                a[e] = silu_log2(sacc[8 * hf + e] + sm.rtime[__clz(static_cast<int>(gap > 1 ? gap : 1))]);
-              }
-              if (diag) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) a[e] = 16 * hf + e <= lim ? a[e] : 0.0f;
-              }
-            }
-#pragma unroll
-            for (int e = 0; e < 8; e += 2) pk[4 * hf + (e >> 1)] = pack_bf16x2(a[e], a[e + 1]);
-          }
-          return;
-        }
-        float a[16];
-        {
-          // 64-bit gaps (requests spanning 2^31 s or more, or more than 32 buckets)
-          const int lim = static_cast<int>(p[qb]) - static_cast<int>(kb) - 8 * static_cast<int>(g);
-#pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            const int off = 16 * (e / 8) + (e % 8);
-            const uint32_t jl = 32 * sb + off + 8 * g;
-            const uint32_t bkt = time_bucket(ts_q[qb] - (j0 + jl < S ? tsr[j0 + jl] : ts_base), hd.n_time);
-            const float v = silu_log2(sacc[e] + sm.time[bkt]);
-            a[e] = off <= lim ? v : 0.0f;
-          }
-        }
-#pragma unroll
-        for (int e = 0; e < 16; e += 2) pk[e >> 1] = pack_bf16x2(a[e], a[e + 1]);
-      };
-      // O^T += V^T P^T; the P^T operand of step s2 = elements 8*s2 .. 8*s2+7: keys kb + 16*s2 + 8*g + 0..7
-      auto accumulate = [&](int qb, int sb, const uint32_t pk[8]) {
-#pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2) {
-          const bf16x8 pf = __builtin_bit_cast(bf16x8, make_uint4(pk[4 * s2], pk[4 * s2 + 1], pk[4 * s2 + 2], pk[4 * s2 + 3]));
-#pragma unroll
-          for (int db = 0; db < 2; ++db)
-            oacc[qb][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_frag(sb, s2, db), pf, oacc[qb][db], 0, 0, 0);
-        }
-      };
-      // which (query group, sub-block) pairs hold at least one visible (query, key) pair
-      auto visible = [&](int qb, int sb) { return grp_active[qb] && j0 + 32 * sb <= grp_last[qb]; };
-      if (NQB == 1 && visible(0, 1)) {
-        // both sub-blocks are visible: the two score chains are issued interleaved, and each
-        // sub-block's second product runs while the other's epilogue executes
-        f32x16 s0 = scores_begin(0, 0), s1 = scores_begin(0, 1);
-#pragma unroll
-        for (int st = 0; st < 4; ++st) {
-          s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_frag(0, st), qf[0][st], s0, 0, 0, 0);
-          s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_frag(1, st), qf[0][st], s1, 0, 0, 0);
-        }
-        uint32_t pk0[8], pk1[8];
-        epilogue(0, 0, s0, pk0);
-        accumulate(0, 0, pk0);
-        epilogue(0, 1, s1, pk1);
-        accumulate(0, 1, pk1);
-      } else {
-#pragma unroll
-        for (int sb = 0; sb < 2; ++sb) {
-          if (NQB == 2 && visible(0, sb) && visible(NQB - 1, sb) && j0 + 32 * sb <= grp_last[0]) {
-            // both query groups see the sub-block: same interleaving over the groups
-            f32x16 s0 = scores_begin(0, sb), s1 = scores_begin(NQB - 1, sb);
-#pragma unroll
-            for (int st = 0; st < 4; ++st) {
-              const bf16x8 kf = k_frag(sb, st);
-              s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[0][st], s0, 0, 0, 0);
-              s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[NQB - 1][st], s1, 0, 0, 0);
-            }
-            uint32_t pk0[8], pk1[8];
-            epilogue(0, sb, s0, pk0);
-            accumulate(0, sb, pk0);
-            epilogue(NQB - 1, sb, s1, pk1);
-            accumulate(NQB - 1, sb, pk1);
-          } else {
-#pragma unroll
-            for (int qb = 0; qb < NQB; ++qb) {
-              if (!visible(qb, sb)) continue;
-              f32x16 s0 = scores_begin(qb, sb);
-#pragma unroll
-              for (int st = 0; st < 4; ++st) s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_frag(sb, st), qf[qb][st], s0, 0, 0, 0);
-              uint32_t pk0[8];
-              epilogue(qb, sb, s0, pk0);
-              accumulate(qb, sb, pk0);
-            }
-          }
+      for (int e = 0; e < 4; ++e) {
+        sacc[e] = w0[e];
+        sacc[4 + e] = w1[e];
+        sacc[8 + e] = w2[e];
+        sacc[12 + e] = w3[e];
+      }
+      return sacc;
+    };
+    // bias, SiLU, mask -> bf16 pairs.  sacc[e]: key kb + 16*(e/8) + 8*g + e%8, query li;
+    // y = (q.k + pos) * log2 e
+    auto epilogue = [&](int sb, const f32x16& sacc, uint32_t (&pk)[8]) {
+      const uint32_t kb = j0 + 32 * sb;
+      const bool diag = kb + 31 > grp_first;
+      int mode = 2;  // 0: one time bias for the block, 1: two adjacent buckets, 2: bucket per score (+ mask)
+      float c_lo = 0.0f, c_hi = 0.0f;
+      uint32_t thr = 0;
+      if (fast && !diag) {
+        const uint32_t bmin = bucket_u32(tq_first - tkb[2 * sb + 1], hd.n_time);
+        const uint32_t bmax = bucket_u32(tq_last - tkb[2 * sb], hd.n_time);
+        c_lo = sm.time[bmin];
+        if (bmin == bmax) {
+          mode = 0;
+        } else if (bmax == bmin + 1) {
+          mode = 1;
+          c_hi = sm.time[bmax];
+          thr = 2u << bmin;  // gaps >= 2^(bmin+1) belong to the upper bucket
         }
       }
+      if (mode == 0) {
+#pragma unroll
+        for (int e = 0; e < 16; e += 2)
+          pk[e >> 1] = pack_bf16x2(silu_log2(sacc[e] + c_lo), silu_log2(sacc[e + 1] + c_lo));
+        return;
+      }
+      const int lim = static_cast<int>(p) - static_cast<int>(kb) - 8 * static_cast<int>(g);  // visible: key offset <= lim
+      if (fast) {
+        // eight scores at a time: the lane's key timestamps (all below 2^31) come as two 16-byte reads
+        const u32x4* tkp = reinterpret_cast<const u32x4*>(&sm.tk[buf][32 * sb + 8 * g]);
+        const int32_t lim_t = tq >= thr ? static_cast<int32_t>(tq - thr) : -1;
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+          const u32x4 t0 = tkp[4 * hf], t1 = tkp[4 * hf + 1];
+          const uint32_t tkl[8] = {t0.x, t0.y, t0.z, t0.w, t1.x, t1.y, t1.z, t1.w};
+          float a[8];
+          if (mode == 1) {
+            // gap >= thr  <=>  key time <= query time - thr (never, if that is negative)
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+              a[e] = silu_log2(sacc[8 * hf + e] + (static_cast<int32_t>(tkl[e]) <= lim_t ? c_hi : c_lo));
+          } else {
+            // bucket per score through the table indexed by the gap's leading zero count; a key after
+            // the query gives a wrapped gap, whose (valid) table entry the causal select discards
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              const uint32_t gap = tq - tkl[e];
+              a[e] = silu_log2(sacc[8 * hf + e] + sm.rtime[__clz(static_cast<int>(gap > 1 ? gap : 1))]);
+            }
+            if (diag) {
+#pragma unroll
+              for (int e = 0; e < 8; ++e) a[e] = 16 * hf + e <= lim ? a[e] : 0.0f;
+            }
+          }
+#pragma unroll
+          for (int e = 0; e < 8; e += 2) pk[4 * hf + (e >> 1)] = pack_bf16x2(a[e], a[e + 1]);
+        }
+        return;
+      }
+      // 64-bit gaps (requests spanning 2^31 s or more or with decreasing timestamps, or more than 32 buckets)
+      const long long ts_q = q_ok ? tsr[p] : ts_base;
+#pragma unroll
+      for (int e = 0; e < 16; e += 2) {
+        float a[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const int off = 16 * ((e + k) / 8) + ((e + k) % 8);
+          const uint32_t jl = 32 * sb + off + 8 * g;
+          const uint32_t bkt = time_bucket(ts_q - (j0 + jl < S ? tsr[j0 + jl] : ts_base), hd.n_time);
+          const float v = silu_log2(sacc[e + k] + sm.time[bkt]);
+          a[k] = off <= lim ? v : 0.0f;
+        }
+        pk[e >> 1] = pack_bf16x2(a[0], a[1]);
+      }
+    };
+    // O^T += V^T P^T; the P^T operand of step s2 = elements 8*s2 .. 8*s2+7: keys kb + 16*s2 + 8*g + 0..7
+    auto accumulate = [&](int sb, const uint32_t (&pk)[8]) {
+#pragma unroll
+      for (int s2 = 0; s2 < 2; ++s2) {
+        const bf16x8 pf = __builtin_bit_cast(bf16x8, u32x4{pk[4 * s2], pk[4 * s2 + 1], pk[4 * s2 + 2], pk[4 * s2 + 3]});
+#pragma unroll
+        for (int db = 0; db < 2; ++db)
+          oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_frag(sb, s2, db), pf, oacc[db], 0, 0, 0);
+      }
+    };
+#pragma unroll
+    for (uint32_t sb = 0; sb < 2; ++sb) {
+      if (sb < sb_first || sb > sb_last || !grp_active || j0 + 32 * sb > grp_last) continue;  // the wavefront's, and some pair visible
+      f32x16 s = scores_begin(sb);
+#pragma unroll
+      for (int st = 0; st < 4; ++st) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_frag(sb, st), qf[st], s, 0, 0, 0);
+      uint32_t pk[8];
+      epilogue(sb, s, pk);
+      accumulate(sb, pk);
+    }
+    if (more) {
+      fetched(kt + 1, buf ^ 1);
+      if (wave == 0) pos_put(64 * t + 191 + lane, __uint_as_float(side));
+      if (wave == 1) sm.tk[buf ^ 1][lane] = side;
     }
   }
-  // oacc[qb][db][e]: d_h element 32*db + 8*(e/4) + 4*g + e%4 of the lane's query; undo the log2 e scaling, apply 1/n
-  const float sc = hd.inv_n * kLn2;
+  if (paired) {  // the second half tiles' sums join the first ones'
+    __syncthreads();
+    float* xs = reinterpret_cast<float*>(&sm.kv[0][0][0]) + grp * (32 * 64) + lane * 4;  // [e / 4][lane][4] per group
+    if (wave >= 2) {
 #pragma unroll
-  for (int qb = 0; qb < NQB; ++qb) {
-    if (item.slot != kDirect) {
-      // part of a split query tile: fp32 partial [slot][head][query][d_h], summed by attention_reduce
-      float* prow = partials + ((static_cast<uint64_t>(item.slot) * hd.H + h) * kQ + ql[qb]) * 64;
-#pragma unroll
-      for (int db = 0; db < 2; ++db)
-#pragma unroll
-        for (int e4 = 0; e4 < 4; ++e4)
-          *reinterpret_cast<float4*>(prow + 32 * db + 8 * e4 + 4 * g) =
-              make_float4(oacc[qb][db][4 * e4] * sc, oacc[qb][db][4 * e4 + 1] * sc, oacc[qb][db][4 * e4 + 2] * sc,
-                          oacc[qb][db][4 * e4 + 3] * sc);
-    } else if (q_ok[qb]) {
-      uint16_t* orow = o + static_cast<uint64_t>(rq.x_off + q0 + ql[qb]) * hd.d + h * 64;
-#pragma unroll
-      for (int db = 0; db < 2; ++db)
-#pragma unroll
-        for (int e4 = 0; e4 < 4; ++e4) {
-          uint2 w;
-          if (OHALF) {
-            w.x = pack2_f16(oacc[qb][db][4 * e4] * sc, oacc[qb][db][4 * e4 + 1] * sc);
-            w.y = pack2_f16(oacc[qb][db][4 * e4 + 2] * sc, oacc[qb][db][4 * e4 + 3] * sc);
-          } else {
-            w.x = pack_bf16x2(oacc[qb][db][4 * e4] * sc, oacc[qb][db][4 * e4 + 1] * sc);
-            w.y = pack_bf16x2(oacc[qb][db][4 * e4 + 2] * sc, oacc[qb][db][4 * e4 + 3] * sc);
-          }
-          *reinterpret_cast<uint2*>(orow + 32 * db + 8 * e4 + 4 * g) = w;
-        }
+      for (int k = 0; k < 8; ++k)
+        *reinterpret_cast<f32x4*>(xs + 256 * k) = f32x4{oacc[k >> 2][4 * (k & 3)], oacc[k >> 2][4 * (k & 3) + 1], oacc[k >> 2][4 * (k & 3) + 2], oacc[k >> 2][4 * (k & 3) + 3]};
     }
+    __syncthreads();
+    if (wave >= 2) return;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(xs + 256 * k);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) oacc[k >> 2][4 * (k & 3) + e] += v[e];
+    }
+  }
+  // oacc[db][e]: d_h element 32*db + 8*(e/4) + 4*g + e%4 of the lane's query; undo the log2 e scaling, apply 1/n
+  const float sc = hd.inv_n * kLn2;
+  if (item.slot != kDirect) {
+    // part of a split query tile: fp32 partial [slot][head][query][d_h], summed by attention_reduce
+    if (!q_ok) return;
+    float* prow = partials + ((static_cast<uint64_t>(item.slot) * hd.H + h) * kAttnQ + ql) * 64;
+#pragma unroll
+    for (int db = 0; db < 2; ++db)
+#pragma unroll
+      for (int e4 = 0; e4 < 4; ++e4)
+        *reinterpret_cast<f32x4*>(prow + 32 * db + 8 * e4 + 4 * g) =
+            f32x4{oacc[db][4 * e4] * sc, oacc[db][4 * e4 + 1] * sc, oacc[db][4 * e4 + 2] * sc, oacc[db][4 * e4 + 3] * sc};
+  } else if (q_ok) {
+    uint16_t* orow = o + static_cast<uint64_t>(rq.x_off + qi) * hd.d + h * 64;
+#pragma unroll
+    for (int db = 0; db < 2; ++db)
+#pragma unroll
+      for (int e4 = 0; e4 < 4; ++e4) {
+        uint2 w;
+        if (OHALF) {
+          w.x = pack2_f16(oacc[db][4 * e4] * sc, oacc[db][4 * e4 + 1] * sc);
+          w.y = pack2_f16(oacc[db][4 * e4 + 2] * sc, oacc[db][4 * e4 + 3] * sc);
+        } else {
+          w.x = pack_bf16x2(oacc[db][4 * e4] * sc, oacc[db][4 * e4 + 1] * sc);
+          w.y = pack_bf16x2(oacc[db][4 * e4 + 2] * sc, oacc[db][4 * e4 + 3] * sc);
+        }
+        *reinterpret_cast<uint2*>(orow + 32 * db + 8 * e4 + 4 * g) = w;
+      }
   }
 }
 
@@ -1607,11 +1592,11 @@ hipError_t launch_attention(const HstuDims& hd, uint32_t layer, const void* q, c
   if (hd.elem == 1) {
     if (sl.q_block != 128) return hipErrorInvalidValue;  // the work items are cut for 128-query blocks
     if (o_half)
-      hipLaunchKernelGGL((attention_bf16_mfma<1, true>), dim3(sl.n_work), dim3(256), 0, stream, hd, layer,
+      hipLaunchKernelGGL((attention_bf16_mfma<true>), dim3(sl.n_work), dim3(256), 0, stream, hd, layer,
                          static_cast<const uint16_t*>(q), pos, time, kv, sl.reqs, sl.items, sl.work, sl.partials, page_tables,
                          reinterpret_cast<const long long*>(ts), static_cast<uint16_t*>(o));
     else
-      hipLaunchKernelGGL((attention_bf16_mfma<1, false>), dim3(sl.n_work), dim3(256), 0, stream, hd, layer,
+      hipLaunchKernelGGL((attention_bf16_mfma<false>), dim3(sl.n_work), dim3(256), 0, stream, hd, layer,
                          static_cast<const uint16_t*>(q), pos, time, kv, sl.reqs, sl.items, sl.work, sl.partials, page_tables,
                          reinterpret_cast<const long long*>(ts), static_cast<uint16_t*>(o));
   } else {

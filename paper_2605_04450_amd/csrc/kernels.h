@@ -123,7 +123,7 @@ struct KvView {
   unsigned long long* counters;
 };
 
-constexpr uint32_t kAttnMaxItemPages = 1024;  // page-table entries one attention item may span
+constexpr uint32_t kAttnMaxItemPages = 640;  // page-table entries one attention item may span
 
 // One attention work item: q_block (128) queries of one request against the key tiles [kt_begin, kt_end)
 // (64 keys each).  A query tile whose key range was cut into several items accumulates

@@ -1,0 +1,44 @@
+"""GPU parity of the paged attention at the edges of its tiles: query tiles of up to 64 queries (paired wavefronts), of 65
+and more, sequences that end inside a 16-byte run of keys, pages smaller than a key tile and not a power of two, items of one
+and of several key tiles."""
+import numpy as np
+import pytest
+import torch
+
+from tests.test_gpu_hstu import Case, assert_close
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d,pt", [(64, 64), (128, 16), (128, 8), (256, 64), (128, 24), (512, 128)])
+@pytest.mark.parametrize("prefix,new", [
+    ([0, 0, 0, 0, 0, 0], [1, 31, 32, 33, 63, 64]),
+    ([0, 0, 0, 0], [65, 127, 128, 129]),
+    ([1, 63, 64, 65, 200], [1, 64, 32, 63, 7]),         # short appends behind cached keys
+    ([509, 700, 1003], [64, 65, 3]),                    # several key tiles and items
+])
+def test_query_and_key_tile_edges(d, pt, prefix, new):
+    c = Case(11, 1, d, d // 64, pt, True, 300, 16, 1024.0, 640)
+    total = [p + n for p, n in zip(prefix, new)]
+    reqs, pts, ts, x = c.inputs([0] * len(new), total)
+    # the cached part through a first step, the new part through a second one
+    if any(prefix):
+        offs = np.concatenate([[0], np.cumsum(prefix)])
+        first = [(0, p, r[2], r[3], int(o)) for p, r, o in zip(prefix, reqs, offs)]
+        xa = np.concatenate([x[r[4]: r[4] + p] for p, r in zip(prefix, reqs)])
+        assert_close(c.run_gpu(first, pts, ts, xa), c.run_oracle(first, pts, ts, xa), True, "cached part")
+    offs = np.concatenate([[0], np.cumsum(new)])
+    second = [(p, n, r[2], r[3], int(o)) for p, n, r, o in zip(prefix, new, reqs, offs)]
+    xb = np.concatenate([x[r[4] + p: r[4] + p + n] for p, n, r in zip(prefix, new, reqs)])
+    assert_close(c.run_gpu(second, pts, ts, xb), c.run_oracle(second, pts, ts, xb), True, "new part")
+    assert c.pool.stats()["bad_pages"] == 0
+    c.close()
+
+
+@pytest.mark.parametrize("pt", [16, 64])
+def test_values_behind_the_end_of_a_sequence_do_not_matter(pt):
+    c = Case(12, 1, 128, 2, pt, True, 256, 16, 256.0, 64)
+    reqs, pts, ts, x = c.inputs([0, 0], [101, 67])
+    c.pool.mem.view(torch.int16).fill_(0x7FC0)  # NaN everywhere
+    assert_close(c.run_gpu(reqs, pts, ts, x), c.run_oracle(reqs, pts, ts, x), True, "NaN behind the end")
+    c.close()

@@ -100,7 +100,7 @@ int32_t pool_destroy(racer_pool_t* pool);
 int32_t pool_set_split(racer_pool_t* pool, double emb_frac, void* stream, double* achieved);
 
 /* pool_reserve: size the library's work spaces once.  The miss path's lists, the step's activation matrices,
- * work lists, partial outputs, pinned staging buffers and the step's streams otherwise grow on demand, and a
+ * work lists, partial outputs and pinned staging buffers otherwise grow on demand, and a
  * growth (hipFree + hipMalloc, after waiting for the streams that use the old buffer) stalls the device in the
  * middle of serving.  After pool_reserve, no call whose sizes stay within *r allocates (pool_stats.ws_allocs
  * stays constant).  model (may be NULL: EMB calls only) fixes width, heads, element type and page tokens of the
@@ -248,11 +248,7 @@ int32_t hstu_model_destroy(racer_hstu_t* model);
  * written into the request's pages at positions prefix_len.., then every new token attends
  * to positions 0..its own through the page table.  Page ids outside the pool are skipped
  * and counted in bad_pages.  The work is ordered on `stream` as usual: what the caller
- * queues behind the call sees the finished outputs.  Inside, a bf16 batch of 32 768 or more
- * new tokens, or 2^26 or more (query, key) pairs, runs as three pipelines over three runs of requests, two of
- * them on streams of the pool's own (default priority) that fork from `stream` at the start
- * and join it at the end; results do not depend on it.  While racer_prof_enable is on,
- * the step runs as one pipeline so that kernel durations do not overlap.
+ * queues behind the call sees the finished outputs.
  * Errors: RACER_EINVAL (shape mismatch with the pool, offsets beyond n_page_entries),
  * RACER_ENOMEM/RACER_EHIP (workspace). */
 int32_t hstu_step(racer_pool_t* pool, racer_hstu_t* model, const racer_hstu_req* reqs, uint32_t B,

@@ -436,7 +436,7 @@ __global__ __launch_bounds__(256) void gemm_front_bf16(HstuDims hd, uint32_t lay
 struct LayerHalfArgs {
   HstuDims hd;
   uint32_t layer;
-  uint32_t row0, n_rows;   // the launch's rows
+  uint32_t n_rows;
   const uint16_t* a_in;    // FRONT: X   BACK: O       [N][KD]
   const uint16_t* gate;    // BACK: U
   const float* ln_g;
@@ -447,7 +447,7 @@ struct LayerHalfArgs {
   uint16_t* q;
   KvView kv;
   const ReqDev* reqs;
-  const uint32_t* group_req;  // request of row row0 + 32 i, and behind the last one the last row's
+  const uint32_t* group_req;  // request of row 32 i, and behind the last one the last row's
   const int32_t* page_tables;
   const uint16_t* resid;   // BACK: X
   uint16_t* y;             // BACK output
@@ -549,7 +549,7 @@ __global__ __launch_bounds__(64 * WPB, KD <= 256 ? 3 : 2) void layer_half_fused(
   float* lnp = kStageInTile ? reinterpret_cast<float*>(&otile[0]) : lnp_own;
   const uint32_t tid = threadIdx.x, lane = tid & 63, g = lane >> 5, li = lane & 31;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const uint32_t r0 = (blockIdx.x * WPB + wave) * 32;  // this wavefront's first row, counted from a.row0
+  const uint32_t r0 = (blockIdx.x * WPB + wave) * 32;  // this wavefront's first row
   const HstuDims& hd = a.hd;
   const uint32_t cb0 = blockIdx.y * a.n_cb, n_cb = a.n_cb;
 
@@ -569,13 +569,13 @@ __global__ __launch_bounds__(64 * WPB, KD <= 256 ? 3 : 2) void layer_half_fused(
   // ---- activation rows: issue the loads ---------------------------------------------------------
   // One load instruction covers 128 bytes of eight rows.  A piece (64 columns of the 32 rows) is dealt out to the
   // operand layout (lane = token, 8 of every 16 elements) through 4 KB of wave-private LDS; chunk c of row r sits at
-  // c ^ (r mod 8).  Rows past the end read the launch's first row; their results are never stored.
+  // c ^ (r mod 8).  Rows past the end read the first row; their results are never stored.
   const uint32_t st_r = lane >> 3, st_c = lane & 7;
   auto issue_piece = [&](const uint16_t* src, int p, u32x4 (&v)[4]) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const uint32_t r = r0 + 8 * i + st_r;
-      v[i] = *reinterpret_cast<const u32x4*>(src + static_cast<uint64_t>(a.row0 + (r < a.n_rows ? r : 0)) * KD + 64 * p + 8 * st_c);
+      v[i] = *reinterpret_cast<const u32x4*>(src + static_cast<uint64_t>(r < a.n_rows ? r : 0) * KD + 64 * p + 8 * st_c);
     }
   };
   uint8_t* stage = (kStageInTile ? &wtile[1][0] : &otile[0]) + wave * 4096;
@@ -611,7 +611,7 @@ __global__ __launch_bounds__(64 * WPB, KD <= 256 ? 3 : 2) void layer_half_fused(
   const uint8_t* page_ptr = nullptr;  // FRONT: start of the token's page (nullptr: no such row, or a bad page id)
   uint32_t tok = 0;
   if (FRONT && row_ok) {
-    const uint32_t row = a.row0 + r0 + li, grp = r0 / 32;
+    const uint32_t row = r0 + li, grp = r0 / 32;
     uint32_t lo = a.group_req[grp], hi = a.group_req[grp + 1];
     while (lo < hi) {  // the last request that starts at or before the row
       const uint32_t mid = (lo + hi + 1) / 2;
@@ -700,7 +700,7 @@ __global__ __launch_bounds__(64 * WPB, KD <= 256 ? 3 : 2) void layer_half_fused(
   for (int h2 = 0; h2 < 2; ++h2) {
     const uint32_t rl = store_row(h2);
     ok2[h2] = r0 + rl < a.n_rows;
-    row2[h2] = a.row0 + (ok2[h2] ? r0 + rl : 0);
+    row2[h2] = ok2[h2] ? r0 + rl : 0;
     if (FRONT) {
       const uint64_t mine = reinterpret_cast<uint64_t>(page_ptr);
       const uint32_t lo = __shfl(static_cast<uint32_t>(mine), rl, 64), hi = __shfl(static_cast<uint32_t>(mine >> 32), rl, 64);
@@ -953,7 +953,7 @@ template <bool OHALF>
 __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint32_t layer, const uint16_t* __restrict__ q,
                                                               const float* __restrict__ pos,
                                                               const float* __restrict__ time, KvView kv,
-                                                              const ReqDev* __restrict__ reqs,
+                                                              const uint32_t* __restrict__ ts_marks, uint32_t epoch,
                                                               const AttnItem* __restrict__ items,
                                                               const AttnWork* __restrict__ work,
                                                               float* __restrict__ partials,
@@ -968,14 +968,13 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
   const AttnItem item = items[wk.item];
   auto scalar = [](uint32_t x) { return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(x)); };  // all lanes agree on it
   const uint32_t h = scalar(wk.head);
-  const ReqDev rq = reqs[item.req];
-  const uint32_t P = scalar(rq.prefix_len), T = scalar(rq.new_len), S = P + T;
+  const uint32_t P = scalar(item.prefix_len), T = scalar(item.new_len), S = P + T;
   const uint32_t q0 = item.qt * kAttnQ;  // first query (index among the new tokens) of the block
-  const long long* tsr = ts + rq.ts_off;
+  const long long* tsr = ts + item.ts_off;
   const long long ts_base = tsr[0];
   const long long span = tsr[S - 1] - ts_base;
   // 32-bit times relative to the request's first: only for requests whose timestamps never decrease
-  const bool fast = hd.n_time <= 32 && rq.ts_ordered != 0 && span >= 0 && span < (1ll << 31);
+  const bool fast = hd.n_time <= 32 && ts_marks[item.req] != epoch && span >= 0 && span < (1ll << 31);
   if (tid < 64) sm.time[tid] = tid < hd.n_time ? time[(static_cast<uint64_t>(layer) * hd.H + h) * hd.n_time + tid] : 0.0f;
   if (tid >= 64 && tid < 96) {
     const uint32_t bkt = 95 - tid;  // floor(log2(gap)) of a gap with tid - 64 leading zeros
@@ -1008,7 +1007,7 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
 #pragma unroll
   for (int st = 0; st < 4; ++st) {
     u32x4 val = {0, 0, 0, 0};
-    if (q_ok) val = *reinterpret_cast<const u32x4*>(q + static_cast<uint64_t>(rq.x_off + qi) * hd.d + h * 64 + 16 * st + 8 * g);
+    if (q_ok) val = *reinterpret_cast<const u32x4*>(q + static_cast<uint64_t>(item.x_off + qi) * hd.d + h * 64 + 16 * st + 8 * g);
     qf[st] = __builtin_bit_cast(bf16x8, val);
   }
   f32x16 oacc[2];
@@ -1028,7 +1027,7 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
     uint32_t page_last;
     split_token(hd, last_key, &page_last, &unused_ip);
     for (uint32_t i = tid; i <= page_last - page0 && i < kAttnMaxItemPages; i += 256) {
-      int32_t pg = page_tables[rq.page_table_off + page0 + i];
+      int32_t pg = page_tables[item.page_table_off + page0 + i];
       if (pg < 0 || static_cast<uint32_t>(pg) >= kv.n_pages) {
         atomicAdd(&kv.counters[ctr_index(kCtrBadPages)], 1ull);
         pg = -1;
@@ -1313,7 +1312,7 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
         *reinterpret_cast<f32x4*>(prow + 32 * db + 8 * e4 + 4 * g) =
             f32x4{oacc[db][4 * e4] * sc, oacc[db][4 * e4 + 1] * sc, oacc[db][4 * e4 + 2] * sc, oacc[db][4 * e4 + 3] * sc};
   } else if (q_ok) {
-    uint16_t* orow = o + static_cast<uint64_t>(rq.x_off + qi) * hd.d + h * 64;
+    uint16_t* orow = o + static_cast<uint64_t>(item.x_off + qi) * hd.d + h * 64;
 #pragma unroll
     for (int db = 0; db < 2; ++db)
 #pragma unroll
@@ -1375,12 +1374,10 @@ __global__ __launch_bounds__(256) void attention_reduce(HstuDims hd, uint32_t q_
 }
 
 // Are a request's timestamps non-decreasing?  Block (c, r) looks at tokens 2048 c + 1 .. 2048 (c + 1) of request r
-// (eight per thread, all loads independent).  The host sets ts_ordered to 1; the first block that finds a decrease
-// clears it and counts the request.
+// (eight per thread, all loads independent).  The first block that finds a decrease marks and counts the request.
 constexpr uint32_t kTsChunk = 2048;
-__global__ __launch_bounds__(256) void check_timestamps(ReqDev* __restrict__ reqs, uint32_t B,
-                                                        const long long* __restrict__ ts,
-                                                        unsigned long long* __restrict__ counters) {
+__device__ __forceinline__ void check_timestamps(const ReqDev* reqs, uint32_t B, uint32_t* __restrict__ marks, uint32_t epoch,
+                                                 const long long* __restrict__ ts, unsigned long long* __restrict__ counters) {
   for (uint32_t r = blockIdx.y; r < B; r += gridDim.y) {  // (the grid's second dimension stops at 65 535)
     const uint32_t S = reqs[r].prefix_len + reqs[r].new_len;
     const uint32_t j0 = blockIdx.x * kTsChunk + 1;
@@ -1393,10 +1390,23 @@ __global__ __launch_bounds__(256) void check_timestamps(ReqDev* __restrict__ req
       if (j < S) bad |= t[j] < t[j - 1];
     }
     if (__syncthreads_or(bad) && threadIdx.x == 0) {
-      if (atomicExch(&reqs[r].ts_ordered, 0u) == 1u) atomicAdd(&counters[ctr_index(kCtrUnorderedTs)], 1ull);
+      if (atomicExch(&marks[r], epoch) != epoch) atomicAdd(&counters[ctr_index(kCtrUnorderedTs)], 1ull);
     }
   }
 }
+__global__ __launch_bounds__(256) void begin_step(const ReqDev* __restrict__ reqs, uint32_t B, uint32_t* __restrict__ marks, uint32_t epoch,
+                                                  const long long* __restrict__ ts, unsigned long long* __restrict__ counters) {
+  check_timestamps(reqs, B, marks, epoch, ts, counters);
+}
+// The same for a small step, whose lists (the requests first) come as an argument: no copy engine, no staging buffer to
+// wait for (10 us of host time and 5 us of the stream's a step).
+__global__ __launch_bounds__(256) void begin_step_with_lists(ListArg arg, uint4* __restrict__ dst, uint32_t n16, uint32_t B,
+                                                             uint32_t* __restrict__ marks, uint32_t epoch,
+                                                             const long long* __restrict__ ts, unsigned long long* __restrict__ counters) {
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < n16) dst[threadIdx.x] = reinterpret_cast<const uint4*>(arg.bytes)[threadIdx.x];
+  check_timestamps(reinterpret_cast<const ReqDev*>(arg.bytes), B, marks, epoch, ts, counters);
+}
+static_assert(kListArgBytes / 16 <= 256, "one 16-byte word of the lists per thread");
 
 __global__ void scale_f32(const float* __restrict__ in, float* __restrict__ out, uint64_t n, float s) {
   for (uint64_t k = blockIdx.x * static_cast<uint64_t>(blockDim.x) + threadIdx.x; k < n;
@@ -1516,7 +1526,6 @@ hipError_t launch_layer_front_fused(const HstuDims& hd, uint32_t layer, const vo
   LayerHalfArgs a{};
   a.hd = hd;
   a.layer = layer;
-  a.row0 = sl.row0;
   a.n_rows = sl.N;
   a.a_in = static_cast<const uint16_t*>(x);
   a.ln_g = ln_g;
@@ -1539,7 +1548,6 @@ hipError_t launch_layer_back_fused(const HstuDims& hd, const void* o, const void
   if (!layer_halves_fused(hd)) return hipErrorInvalidValue;
   LayerHalfArgs a{};
   a.hd = hd;
-  a.row0 = sl.row0;
   a.n_rows = sl.N;
   a.a_in = static_cast<const uint16_t*>(o);
   a.gate = static_cast<const uint16_t*>(u);
@@ -1593,11 +1601,11 @@ hipError_t launch_attention(const HstuDims& hd, uint32_t layer, const void* q, c
     if (sl.q_block != 128) return hipErrorInvalidValue;  // the work items are cut for 128-query blocks
     if (o_half)
       hipLaunchKernelGGL((attention_bf16_mfma<true>), dim3(sl.n_work), dim3(256), 0, stream, hd, layer,
-                         static_cast<const uint16_t*>(q), pos, time, kv, sl.reqs, sl.items, sl.work, sl.partials, page_tables,
+                         static_cast<const uint16_t*>(q), pos, time, kv, sl.ts_marks, sl.epoch, sl.items, sl.work, sl.partials, page_tables,
                          reinterpret_cast<const long long*>(ts), static_cast<uint16_t*>(o));
     else
       hipLaunchKernelGGL((attention_bf16_mfma<false>), dim3(sl.n_work), dim3(256), 0, stream, hd, layer,
-                         static_cast<const uint16_t*>(q), pos, time, kv, sl.reqs, sl.items, sl.work, sl.partials, page_tables,
+                         static_cast<const uint16_t*>(q), pos, time, kv, sl.ts_marks, sl.epoch, sl.items, sl.work, sl.partials, page_tables,
                          reinterpret_cast<const long long*>(ts), static_cast<uint16_t*>(o));
   } else {
     const uint32_t items = sl.N * hd.H;
@@ -1615,11 +1623,18 @@ hipError_t launch_attention_reduce(const HstuDims& hd, const StepLists& sl, void
   return hipGetLastError();
 }
 
-hipError_t launch_check_timestamps(ReqDev* reqs, uint32_t B, uint32_t max_seq, const int64_t* ts,
-                                   unsigned long long* counters, hipStream_t stream) {
-  if (B == 0 || max_seq < 2) return hipSuccess;
-  hipLaunchKernelGGL(check_timestamps, dim3((max_seq - 1 + kTsChunk - 1) / kTsChunk, B < 65535 ? B : 65535), dim3(256), 0,
-                     stream, reqs, B, reinterpret_cast<const long long*>(ts), counters);
+hipError_t launch_begin_step(const StepLists& sl, uint32_t max_seq, const int64_t* ts, unsigned long long* counters, const ListArg* arg,
+                             uint8_t* list_dst, uint64_t list_bytes, hipStream_t stream) {
+  if (!arg && max_seq < 2) return hipSuccess;
+  const uint32_t chunks = max_seq < 2 ? 1 : (max_seq - 1 + kTsChunk - 1) / kTsChunk;
+  const dim3 grid(chunks, sl.B < 65535 ? sl.B : 65535), block(256);
+  const long long* t = reinterpret_cast<const long long*>(ts);
+  uint32_t* marks = const_cast<uint32_t*>(sl.ts_marks);
+  if (arg)
+    hipLaunchKernelGGL(begin_step_with_lists, grid, block, 0, stream, *arg, reinterpret_cast<uint4*>(list_dst),
+                       static_cast<uint32_t>((list_bytes + 15) / 16), sl.B, marks, sl.epoch, t, counters);
+  else
+    hipLaunchKernelGGL(begin_step, grid, block, 0, stream, sl.reqs, sl.B, marks, sl.epoch, t, counters);
   return hipGetLastError();
 }
 

@@ -113,7 +113,6 @@ struct HstuDims {
 struct ReqDev {  // device copy of one request
   uint32_t prefix_len, new_len;
   uint32_t page_table_off, ts_off, x_off;
-  uint32_t ts_ordered;  // 1 from the host, cleared by the timestamp check if the request's timestamps decrease somewhere
 };
 
 struct KvView {
@@ -130,7 +129,8 @@ constexpr uint32_t kAttnMaxItemPages = 640;  // page-table entries one attention
 // through fp32 partial slots (slot .. slot + chunks - 1) that a reduction pass adds up in
 // order; an item that covers its whole key range writes the output directly (slot = kDirect).
 struct AttnItem {
-  uint32_t req, qt, kt_begin, kt_end, slot, pad;
+  uint32_t prefix_len, new_len, page_table_off, ts_off, x_off;  // of the request
+  uint32_t req, qt, kt_begin, kt_end, slot;
 };
 struct AttnGroup {
   uint32_t req, qt, slot0, chunks;
@@ -156,6 +156,8 @@ struct RowTile {
 // row -> request map and work lists built on the host for one step
 struct StepLists {
   const ReqDev* reqs;        // [B]
+  const uint32_t* ts_marks;  // [B] = epoch where the request's timestamps decrease somewhere
+  uint32_t epoch;
   const uint32_t* row_req;   // [N] request of each new-token row
   const AttnItem* items;     // grouped by (request, key chunk)
   const AttnWork* work;      // [n_work] workgroup -> (item, head), die-interleaved
@@ -163,21 +165,26 @@ struct StepLists {
   const AttnGroup* groups;   // query tiles that were split
   const RowTile* row_tiles;  // projection tiles, none crosses a request
   uint32_t n_row_tiles;
-  const uint32_t* group_req; // request of rows row0, row0 + 32, .. and, behind the last of these, of the last row
+  const uint32_t* group_req; // request of rows 0, 32, .. and, behind the last of these, of the last row
   float* partials;           // [slot][head][q_block][64]
-  uint32_t n_items, n_groups;
+  uint32_t n_groups;
   uint32_t q_block;          // queries per item
   uint32_t B, N;
-  uint32_t row0;             // first of the N new-token rows these lists are about
 };
 
-// One pass over every request's timestamps (max_seq: the longest request's prefix + new tokens): ts_ordered, which
-// the host has set to 1, is cleared for each request whose timestamps decrease somewhere, and the number of such
-// requests is added to the kCtrUnorderedTs counter.  The attention kernels take their 32-bit
-// relative-time paths only for ordered requests (an unordered one gets the general 64-bit gaps, where a negative gap
-// falls into bucket 0).
-hipError_t launch_check_timestamps(ReqDev* reqs, uint32_t B, uint32_t max_seq, const int64_t* ts,
-                                   unsigned long long* counters, hipStream_t stream);
+// Lists of up to this size are handed to the kernel that begins a step as an argument.
+constexpr uint32_t kListArgBytes = 3072;
+struct ListArg {
+  alignas(16) uint8_t bytes[kListArgBytes];
+};
+
+// Begins a step: one pass over every request's timestamps (max_seq: the longest request's prefix + new tokens); a request
+// whose timestamps decrease somewhere is marked with the step's epoch and counted in kCtrUnorderedTs.  The
+// attention kernels take their 32-bit relative-time paths only for ordered requests (an unordered one gets the general
+// 64-bit gaps, where a negative gap falls into bucket 0).  With `arg` the kernel first writes the lists out of its
+// argument to list_dst (the check then reads the requests there), else they are on the device already.
+hipError_t launch_begin_step(const StepLists& sl, uint32_t max_seq, const int64_t* ts, unsigned long long* counters, const ListArg* arg,
+                             uint8_t* list_dst, uint64_t list_bytes, hipStream_t stream);
 
 hipError_t launch_layernorm(const HstuDims& hd, const void* x, const float* g, const float* b,
                             const void* gate /*nullable: multiply by gate rows*/, void* y, uint32_t N,

@@ -167,6 +167,23 @@ int32_t scratch_address(uint8_t** out) {
 
 }  // namespace
 
+// Host-side arrays of prepare_step, kept from call to call for their memory.
+struct StepScratch {
+  struct QTile { uint32_t req, qt, n_kt, n_ch, slot0; };
+  struct Unit { uint32_t item0, n_items; uint64_t weight; };
+  std::vector<QTile> qtiles;
+  std::vector<Unit> units;
+  std::vector<uint32_t> order;
+  std::vector<racer::AttnItem> items;
+  std::vector<racer::AttnGroup> groups;
+  std::vector<racer::RowTile> row_tiles;
+  std::vector<racer::AttnWork> die_list[racer::kXcds];
+  void clear() {
+    qtiles.clear(); units.clear(); items.clear(); groups.clear(); row_tiles.clear();
+    for (auto& l : die_list) l.clear();
+  }
+};
+
 struct racer_pool {
   racer::HostPool host;
   racer_pool_cfg cfg;
@@ -196,9 +213,10 @@ struct racer_pool {
   uint64_t hp_cap = 0;  // fp32 partial outputs of split attention items
   uint8_t* hp_dev = nullptr;
   Staging hstage;
-  // further streams of a step that runs as several pipelines (default priority), with the fork and join events
-  hipStream_t aux_stream[3] = {nullptr, nullptr, nullptr};
-  hipEvent_t ev_fork = nullptr, ev_join[3] = {nullptr, nullptr, nullptr};
+  StepScratch step;
+  uint32_t step_epoch = 0;  // number of the step: a request with unordered timestamps is marked with it
+  uint32_t* ts_marks = nullptr;
+  uint64_t ts_marks_cap = 0;
   // optional per-kernel-class timing with events on the caller's stream
   struct ProfMark { hipEvent_t a, b; int kind; };
   bool prof_on = false;
@@ -346,14 +364,18 @@ int32_t ensure_hstu_ws(racer_pool* p, uint64_t slot, hipStream_t stream) {
   return RACER_OK;
 }
 
-// The step's further streams and its fork / join events.
-int32_t ensure_step_streams(racer_pool* p, uint32_t n_aux) {
-  if (!p->ev_fork) HIP_TRY(hipEventCreateWithFlags(&p->ev_fork, hipEventDisableTiming));
-  for (uint32_t k = 0; k < n_aux; ++k) {
-    if (p->aux_stream[k]) continue;
-    HIP_TRY(hipStreamCreateWithFlags(&p->aux_stream[k], hipStreamNonBlocking));
-    HIP_TRY(hipEventCreateWithFlags(&p->ev_join[k], hipEventDisableTiming));
-  }
+// The marks of requests whose timestamps decrease somewhere (the number of the step that found it; 0: none).
+int32_t ensure_ts_marks(racer_pool* p, uint64_t B, hipStream_t stream) {
+  if (B <= p->ts_marks_cap) return RACER_OK;
+  HIP_TRY(hipStreamSynchronize(p->last_stream));
+  if (p->ts_marks) HIP_TRY(hipFree(p->ts_marks));
+  p->ts_marks = nullptr;
+  p->ts_marks_cap = 0;
+  const uint64_t cap = std::max<uint64_t>(B, 256);
+  int32_t rc = dev_alloc(&p->ts_marks, cap, true, stream);
+  if (rc) return rc;
+  p->ts_marks_cap = cap;
+  p->ws_allocs += 1;
   return RACER_OK;
 }
 
@@ -426,13 +448,6 @@ int32_t pool_destroy(racer_pool_t* p) {
       (void)hipEventDestroy(m.b);
     }
     for (hipEvent_t e : p->prof_spare) (void)hipEventDestroy(e);
-    for (int k = 0; k < 3; ++k)
-      if (p->aux_stream[k]) {
-        (void)hipStreamSynchronize(p->aux_stream[k]);
-        (void)hipStreamDestroy(p->aux_stream[k]);
-        (void)hipEventDestroy(p->ev_join[k]);
-      }
-    if (p->ev_fork) (void)hipEventDestroy(p->ev_fork);
     (void)hipFree(p->d_tables);
     (void)hipFree(p->d_tags);
     (void)hipFree(p->d_stamps);
@@ -441,6 +456,7 @@ int32_t pool_destroy(racer_pool_t* p) {
     (void)hipFree(p->hw_buf);
     (void)hipFree(p->hl_dev);
     (void)hipFree(p->hp_dev);
+    (void)hipFree(p->ts_marks);
   }
   delete p;
   return RACER_OK;
@@ -740,35 +756,24 @@ int32_t hstu_model_destroy(racer_hstu_t* m) {
 
 namespace {
 
-// a step with fewer new tokens than this runs as one pipeline (its kernels do not fill the chip twice over)
-#ifndef RACER_SPLIT_MIN_TOKENS
-#define RACER_SPLIT_MIN_TOKENS 32768
-#endif
-constexpr uint64_t kSplitMinTokens = RACER_SPLIT_MIN_TOKENS;
-// ... or with fewer (query, key) pairs than this (a few new tokens against long cached prefixes are a large step too)
-#ifndef RACER_SPLIT_MIN_PAIRS
-#define RACER_SPLIT_MIN_PAIRS (64ull << 20)
-#endif
-constexpr uint64_t kSplitMinPairs = RACER_SPLIT_MIN_PAIRS;
-#ifndef RACER_STEP_RUNS
-#define RACER_STEP_RUNS 3
-#endif
-constexpr uint32_t kMaxRuns = 4;
-constexpr uint32_t kStepRuns = RACER_STEP_RUNS;  // pipelines of a large step
-static_assert(kStepRuns >= 2 && kStepRuns <= kMaxRuns, "pipelines per step");
-
 // Upper bounds of a step's list bytes and partial-output bytes for up to B requests, N new tokens and sequences of up
 // to max_seq tokens (pool_reserve sizes the work spaces with them; prepare_step's own sizes never exceed them).
 // Q query tiles (128 new tokens of one request), V visits of 64-key tiles; a query tile is cut into at most
-// n_kt / chunk + 1 items, and the chunk is at least V * H / 2048 tiles unless the item's page-table slice caps it.
+// n_kt / chunk + 1 items, and the chunk is at least V * H / kAttnItemsWanted tiles unless the item's page-table slice
+// caps it, and at least kAttnMinChunk.
+constexpr uint64_t kAttnItemsWanted = 2048;  // two rounds of the chip's 256 x 4 resident blocks
+constexpr uint32_t kAttnMinChunk = 8;
+uint32_t attn_chunk_cap(uint32_t page_tokens) {  // an item's slice of the page table (a chunk and a quarter at most) must fit the kernel's LDS copy
+  return std::max<uint32_t>(1, static_cast<uint32_t>((static_cast<uint64_t>(racer::kAttnMaxItemPages) - 2) * page_tokens / 64 * 4 / 5));
+}
 struct StepBounds { uint64_t list_bytes, partial_bytes; };
 StepBounds step_bounds(uint64_t B, uint64_t N, uint64_t max_seq, uint32_t H, uint32_t page_tokens) {
   const uint64_t Q = N / 128 + B;
   const uint64_t V = Q * (max_seq / 64 + 1);
-  const uint64_t chunk_cap = std::max<uint64_t>(1, (static_cast<uint64_t>(racer::kAttnMaxItemPages) - 2) * page_tokens / 64 * 4 / 5);
-  const uint64_t items = Q + std::max<uint64_t>(2048 / H + 1, V / chunk_cap + 1);
+  const uint64_t by_chunk = std::min<uint64_t>(kAttnItemsWanted / H + 1, V / kAttnMinChunk + 1);
+  const uint64_t items = Q + std::max<uint64_t>(by_chunk, V / attn_chunk_cap(page_tokens) + 1);
   StepBounds b;
-  b.list_bytes = sizeof(racer::ReqDev) * (B + 1) + 4 * (N + 1) + 4 * (N / 32 + 2 * kMaxRuns) + sizeof(racer::AttnItem) * items +
+  b.list_bytes = sizeof(racer::ReqDev) * (B + 1) + 4 * (N + 1) + 4 * (N / 32 + B + 2) + sizeof(racer::AttnItem) * items +
                  (sizeof(racer::AttnGroup) + sizeof(racer::RowTile)) * (Q + 1) +
                  sizeof(racer::AttnWork) * racer::kXcds * items * H + 7 * 256;
   b.partial_bytes = items * H * 128 * 64 * sizeof(float);
@@ -779,24 +784,21 @@ StepBounds step_bounds(uint64_t B, uint64_t N, uint64_t max_seq, uint32_t H, uin
 struct StepCtx {
   racer::HstuDims hd;
   racer::KvView kv;
-  racer::StepLists sl;       // the whole batch
-  racer::StepLists run[kMaxRuns];  // with a split: consecutive runs of requests, each with lists of its own
-  uint32_t run_row0[kMaxRuns] = {}, run_rows[kMaxRuns] = {};  // a run's new-token rows
-  uint32_t n_runs = 1;             // 1: no split
+  racer::StepLists sl;
   uint64_t esize;
+  bool fused;  // layer halves in one kernel each
 };
 
-// Validate the requests, build the row->request map and the attention work lists, ship them
-// to the device on `stream`.  With `want_split` the batch is also cut into kStepRuns runs of requests with about
-// equal attention work, each with its own work list, groups and row tiles (pipelines that touch disjoint rows,
-// pages and partial slots), if it has at least as many requests as pipelines.
+// Validate the requests, build the attention work lists and the row -> request maps, ship them to the device on
+// `stream`, and have the timestamps looked at.
 int32_t prepare_step(racer_pool* p, racer_hstu* m, const racer_hstu_req* reqs, uint32_t B, uint64_t n_page_entries,
-                     const int64_t* ts, hipStream_t stream, StepCtx* ctx, bool want_split = false) {
+                     const int64_t* ts, hipStream_t stream, StepCtx* ctx) {
   const racer_hstu_cfg& c = m->cfg;
   if (!p->device || c.page_tokens != p->cfg.page_tokens || c.elem != p->cfg.elem) return RACER_EINVAL;
   const uint64_t esize = c.elem == RACER_ELEM_BF16 ? 2 : 4;
   if (static_cast<uint64_t>(c.page_tokens) * 2 * c.L * c.d * esize != p->page_size) return RACER_EINVAL;
   uint64_t N = 0;
+  uint32_t longest = 0;
   for (uint32_t r = 0; r < B; ++r) {
     const racer_hstu_req& q = reqs[r];
     const uint64_t S = static_cast<uint64_t>(q.prefix_len) + q.new_len;
@@ -805,8 +807,22 @@ int32_t prepare_step(racer_pool* p, racer_hstu* m, const racer_hstu_req* reqs, u
     if (q.x_off != N) return RACER_EINVAL;  // rows are packed request after request
     if (q.page_table_off >= (1ull << 32) || q.ts_off >= (1ull << 32) || S >= (1ull << 31)) return RACER_EINVAL;
     N += q.new_len;
+    longest = std::max(longest, static_cast<uint32_t>(S));
   }
   if (N >= (1ull << 31) || B >= (1u << 24)) return RACER_EINVAL;
+  const bool fp32 = c.elem != RACER_ELEM_BF16;
+  ctx->esize = esize;
+  uint32_t pt_shift = 32;
+  for (uint32_t b = 0; b < 32; ++b)
+    if ((1u << b) == c.page_tokens) pt_shift = b;
+  ctx->hd = racer::HstuDims{c.L, c.d, c.H, c.d / c.H, c.elem, c.page_tokens, c.n_pos, c.n_time, 1.0f / c.n_scale, c.eps, pt_shift};
+  ctx->kv = racer::KvView{p->base, p->page_size, static_cast<uint32_t>(p->host.n_pages()), p->d_counters};
+  ctx->fused = racer::layer_halves_fused(ctx->hd);
+  racer::StepLists& sl = ctx->sl;
+  sl = racer::StepLists{};
+  sl.B = B;
+  sl.N = static_cast<uint32_t>(N);
+  if (N == 0) return RACER_OK;
 
   // Attention work items.  The score matrix of a request is a staircase: late query tiles see
   // many more key tiles than early ones, and one long request would otherwise set the
@@ -814,235 +830,152 @@ int32_t prepare_step(racer_pool* p, racer_hstu* m, const racer_hstu_req* reqs, u
   // that about two items per resident block slot exist; a short tail joins the chunk before
   // it), which also makes the items of different query tiles with the same chunk index read
   // exactly the same keys.
+  StepScratch& w = p->step;
+  w.clear();
   const uint32_t q_block = 128;
-  struct QTile { uint32_t req, qt, n_kt, n_ch, slot0; };
-  std::vector<QTile> qtiles;
   uint64_t visits = 0;
-  for (uint32_t r = 0; r < B; ++r) {
-    const uint32_t T = reqs[r].new_len;
-    for (uint32_t qt = 0; qt * q_block < T; ++qt) {
-      const uint64_t last = static_cast<uint64_t>(reqs[r].prefix_len) + std::min<uint64_t>(qt * q_block + q_block - 1, T - 1);
-      qtiles.push_back({r, qt, static_cast<uint32_t>(last / 64 + 1), 0, 0});
-      visits += last / 64 + 1;
-    }
-  }
-  // run_begin[k] = first request of run k; a cut is placed where the visits so far come closest to k / n_runs of all
-  uint32_t n_runs = 1, run_begin[kMaxRuns + 1] = {0, B, B, B, B};
-  if (want_split && B >= kStepRuns) {
-    n_runs = kStepRuns;
-    uint64_t acc = 0;
-    size_t qi = 0;
-    uint32_t k = 1;
-    for (uint32_t r = 0; r < B && k < n_runs; ++r) {
-      const uint64_t before = acc;
-      while (qi < qtiles.size() && qtiles[qi].req == r) acc += qtiles[qi++].n_kt;
-      const uint64_t target = visits * k / n_runs;
-      if (acc >= target) {  // the cut goes before or after request r, whichever is closer; runs stay non-empty
-        uint32_t cut = (acc - target <= target - before) ? r + 1 : r;
-        cut = std::max(cut, run_begin[k - 1] + 1);
-        cut = std::min(cut, B - (n_runs - k));
-        run_begin[k++] = cut;
+  if (!fp32)
+    for (uint32_t r = 0; r < B; ++r) {
+      const uint32_t T = reqs[r].new_len;
+      for (uint32_t qt = 0; qt * q_block < T; ++qt) {
+        const uint64_t last = static_cast<uint64_t>(reqs[r].prefix_len) + std::min<uint64_t>(qt * q_block + q_block - 1, T - 1);
+        w.qtiles.push_back({r, qt, static_cast<uint32_t>(last / 64 + 1), 0, 0});
+        visits += last / 64 + 1;
       }
     }
-    while (k < n_runs) { run_begin[k] = std::max(run_begin[k - 1] + 1, B - (n_runs - k)); ++k; }
-    run_begin[n_runs] = B;
-    for (uint32_t run = 0; run < n_runs; ++run) {
-      const uint64_t row_end = run_begin[run + 1] < B ? reqs[run_begin[run + 1]].x_off : N;
-      if (row_end == reqs[run_begin[run]].x_off) {  // a run without new tokens: one pipeline
-        n_runs = 1;
-        run_begin[1] = B;
-      }
-    }
-  }
-  auto run_of = [&](uint32_t req) {
-    uint32_t k = 0;
-    while (k + 1 < n_runs && req >= run_begin[k + 1]) ++k;
-    return k;
-  };
-  const uint64_t block_slots = 1024;  // about 256 CUs x resident blocks
-  uint32_t chunk = static_cast<uint32_t>(std::max<uint64_t>(8, (visits * c.H + 2 * block_slots - 1) / (2 * block_slots)));
-  // an item's slice of the page table (a chunk and a quarter at most) must fit the kernel's LDS copy
-  const uint32_t chunk_cap = static_cast<uint32_t>((static_cast<uint64_t>(racer::kAttnMaxItemPages) - 2) * c.page_tokens / 64 * 4 / 5);
-  chunk = std::min(chunk, std::max<uint32_t>(1, chunk_cap));
-  std::vector<racer::AttnGroup> groups;
+  uint32_t chunk = static_cast<uint32_t>(std::max<uint64_t>(kAttnMinChunk, (visits * c.H + kAttnItemsWanted - 1) / kAttnItemsWanted));
+  chunk = std::min(chunk, attn_chunk_cap(c.page_tokens));
   uint32_t n_slots = 0;
-  for (QTile& t : qtiles) {
+  for (StepScratch::QTile& t : w.qtiles) {
     t.n_ch = t.n_kt / chunk;
     if (t.n_ch == 0 || t.n_kt % chunk > chunk / 4) ++t.n_ch;
     if (t.n_ch > 1) {
       t.slot0 = n_slots;
-      groups.push_back({t.req, t.qt, n_slots, t.n_ch});
+      w.groups.push_back({t.req, t.qt, n_slots, t.n_ch});
       n_slots += t.n_ch;
     }
   }
   // units: the items of one request with the same chunk index, for one head
-  struct Unit { uint32_t item0, n_items, req; uint64_t weight; };
-  std::vector<racer::AttnItem> items;
-  std::vector<Unit> units;
-  for (size_t q0 = 0; q0 < qtiles.size();) {
+  for (size_t q0 = 0; q0 < w.qtiles.size();) {
     size_t q1 = q0;
     uint32_t max_ch = 0;
-    while (q1 < qtiles.size() && qtiles[q1].req == qtiles[q0].req) max_ch = std::max(max_ch, qtiles[q1++].n_ch);
+    while (q1 < w.qtiles.size() && w.qtiles[q1].req == w.qtiles[q0].req) max_ch = std::max(max_ch, w.qtiles[q1++].n_ch);
+    const racer_hstu_req& rq = reqs[w.qtiles[q0].req];
     for (uint32_t k = 0; k < max_ch; ++k) {
-      Unit u{static_cast<uint32_t>(items.size()), 0, qtiles[q0].req, 0};
+      StepScratch::Unit u{static_cast<uint32_t>(w.items.size()), 0, 0};
       for (size_t q = q0; q < q1; ++q) {
-        const QTile& t = qtiles[q];
+        const StepScratch::QTile& t = w.qtiles[q];
         if (k >= t.n_ch) continue;
         const uint32_t b = k * chunk, e = k + 1 == t.n_ch ? t.n_kt : b + chunk;
-        items.push_back({t.req, t.qt, b, e, t.n_ch > 1 ? t.slot0 + k : racer::kDirect, 0});
+        w.items.push_back({rq.prefix_len, rq.new_len, static_cast<uint32_t>(rq.page_table_off), static_cast<uint32_t>(rq.ts_off),
+                           static_cast<uint32_t>(rq.x_off), t.req, t.qt, b, e, t.n_ch > 1 ? t.slot0 + k : racer::kDirect});
         u.weight += e - b;
       }
-      u.n_items = static_cast<uint32_t>(items.size()) - u.item0;
-      units.push_back(u);
+      u.n_items = static_cast<uint32_t>(w.items.size()) - u.item0;
+      w.units.push_back(u);
     }
     q0 = q1;
   }
   // heaviest unit first onto the least loaded die; a die's list keeps that order, so its last
   // workgroups are the short ones
-  std::vector<uint32_t> order(units.size());
-  for (uint32_t i = 0; i < order.size(); ++i) order[i] = i;
-  std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) { return units[a].weight > units[b].weight; });
-  // (with a split: one set of die lists per run of requests, laid out one after the other)
-  std::vector<racer::AttnWork> die_list[kMaxRuns][racer::kXcds];
-  uint64_t die_load[kMaxRuns][racer::kXcds] = {};
-  for (uint32_t ui : order) {
-    const uint32_t run = run_of(units[ui].req);
+  w.order.resize(w.units.size());
+  for (uint32_t i = 0; i < w.order.size(); ++i) w.order[i] = i;
+  std::sort(w.order.begin(), w.order.end(), [&](uint32_t a, uint32_t b) {
+    return w.units[a].weight != w.units[b].weight ? w.units[a].weight > w.units[b].weight : a < b;
+  });
+  uint64_t die_load[racer::kXcds] = {};
+  size_t die_len = 0;
+  for (uint32_t ui : w.order)
     for (uint32_t h = 0; h < c.H; ++h) {
       uint32_t best = 0;
       for (uint32_t x = 1; x < racer::kXcds; ++x)
-        if (die_load[run][x] < die_load[run][best]) best = x;
-      die_load[run][best] += units[ui].weight;
-      for (uint32_t i = 0; i < units[ui].n_items; ++i) die_list[run][best].push_back({units[ui].item0 + i, h});
+        if (die_load[x] < die_load[best]) best = x;
+      die_load[best] += w.units[ui].weight;
+      for (uint32_t i = 0; i < w.units[ui].n_items; ++i) w.die_list[best].push_back({w.units[ui].item0 + i, h});
+      die_len = std::max(die_len, w.die_list[best].size());
     }
-  }
-  std::vector<racer::AttnWork> work;
-  size_t work_begin[kMaxRuns + 1] = {};
-  for (uint32_t run = 0; run < n_runs; ++run) {
-    size_t die_len = 0;
-    for (uint32_t x = 0; x < racer::kXcds; ++x) die_len = std::max(die_len, die_list[run][x].size());
-    work_begin[run] = work.size();
-    work.resize(work.size() + die_len * racer::kXcds, racer::AttnWork{racer::kNoWork, 0});
-    for (uint32_t x = 0; x < racer::kXcds; ++x)
-      for (size_t i = 0; i < die_list[run][x].size(); ++i) work[work_begin[run] + i * racer::kXcds + x] = die_list[run][x][i];
-  }
-  work_begin[n_runs] = work.size();
+  const size_t n_work = die_len * racer::kXcds;
   const uint64_t partial_bytes = static_cast<uint64_t>(n_slots) * c.H * q_block * 64 * sizeof(float);
-  {
-    int32_t rc_p = ensure_partials(p, partial_bytes + partial_bytes / 4, stream);
-    if (rc_p) return rc_p;
-  }
-
-  const uint64_t bytes_reqs = sizeof(racer::ReqDev) * std::max<uint32_t>(B, 1);
-  const bool fp32 = c.elem != RACER_ELEM_BF16;
-  const bool fused = racer::layer_halves_fused(racer::HstuDims{c.L, c.d, c.H, c.d / c.H, c.elem});
-  const uint64_t bytes_rows = fp32 ? sizeof(uint32_t) * std::max<uint64_t>(N, 1) : 0;  // row -> request: the fp32 kernels
-  const uint64_t bytes_items = sizeof(racer::AttnItem) * std::max<size_t>(items.size(), 1);
-  const uint64_t bytes_groups = sizeof(racer::AttnGroup) * std::max<size_t>(groups.size(), 1);
-  std::vector<racer::RowTile> row_tiles;  // bf16 models whose layer halves are not fused
-  if (!fp32 && !fused)
+  int32_t rc = ensure_partials(p, partial_bytes + partial_bytes / 4, stream);
+  if (rc) return rc;
+  if (!fp32 && !ctx->fused)
     for (uint32_t r = 0; r < B; ++r)
       for (uint32_t t0 = 0; t0 < reqs[r].new_len; t0 += 128)
-        row_tiles.push_back({static_cast<uint32_t>(reqs[r].x_off) + t0, std::min<uint32_t>(128, reqs[r].new_len - t0), r, 0});
-  // fused layer halves: the request of every 32nd row of a run, and of the run's last row
-  std::vector<uint32_t> group_req;
-  size_t group_begin[kMaxRuns] = {};
-  if (fused)
-    for (uint32_t run = 0; run < n_runs; ++run) {
-      group_begin[run] = group_req.size();
-      uint64_t next = run_begin[run] < B ? reqs[run_begin[run]].x_off : N;
-      uint32_t last = run_begin[run];
-      for (uint32_t r = run_begin[run]; r < run_begin[run + 1]; ++r) {
-        const uint64_t end = reqs[r].x_off + reqs[r].new_len;
-        if (reqs[r].new_len) last = r;
-        for (; next < end; next += 32) group_req.push_back(r);
-      }
-      group_req.push_back(last);
-    }
-  const uint64_t bytes_group_req = sizeof(uint32_t) * std::max<size_t>(group_req.size(), 1);
-  const uint64_t bytes_row_tiles = sizeof(racer::RowTile) * std::max<size_t>(row_tiles.size(), 1);
-  const uint64_t bytes_work = sizeof(racer::AttnWork) * std::max<size_t>(work.size(), 1);
-  const uint64_t off_rows = (bytes_reqs + 255) & ~255ull, off_items = (off_rows + bytes_rows + 255) & ~255ull;
-  const uint64_t off_groups = (off_items + bytes_items + 255) & ~255ull;
-  const uint64_t off_row_tiles = (off_groups + bytes_groups + 255) & ~255ull;
-  const uint64_t off_group_req = (off_row_tiles + bytes_row_tiles + 255) & ~255ull;
-  const uint64_t off_work = (off_group_req + bytes_group_req + 255) & ~255ull;
-  const uint64_t total = off_work + bytes_work;
-  {
-    int32_t rc_l = ensure_lists(p, total, total * 2);
-    if (rc_l) return rc_l;
-  }
-  uint8_t* hbuf;
-  int which;
-  int32_t rc = p->hstage.acquire(total, &hbuf, &which);
-  if (rc) return rc;
-  racer::ReqDev* hr = reinterpret_cast<racer::ReqDev*>(hbuf);
-  uint32_t* hrow = reinterpret_cast<uint32_t*>(hbuf + off_rows);
-  for (uint32_t r = 0; r < B; ++r) {
+        w.row_tiles.push_back({static_cast<uint32_t>(reqs[r].x_off) + t0, std::min<uint32_t>(128, reqs[r].new_len - t0), r, 0});
+
+  // one block of memory for all lists
+  const uint64_t n_groups32 = ctx->fused ? (N + 31) / 32 + 1 : 0;
+  uint64_t total = 0;
+  auto place = [&](uint64_t bytes) {
+    const uint64_t at = total;
+    total = (total + bytes + 15) & ~15ull;
+    return at;
+  };
+  const uint64_t off_reqs = place(sizeof(racer::ReqDev) * B);
+  const uint64_t off_rows = place(fp32 ? sizeof(uint32_t) * N : 0);  // row -> request: the fp32 kernels
+  const uint64_t off_items = place(sizeof(racer::AttnItem) * w.items.size());
+  const uint64_t off_groups = place(sizeof(racer::AttnGroup) * w.groups.size());
+  const uint64_t off_row_tiles = place(sizeof(racer::RowTile) * w.row_tiles.size());
+  const uint64_t off_group_req = place(sizeof(uint32_t) * n_groups32);  // request of every 32nd row, and of the last one
+  const uint64_t off_work = place(sizeof(racer::AttnWork) * n_work);
+  if ((rc = ensure_lists(p, total, total * 2)) || (rc = ensure_ts_marks(p, B, stream))) return rc;
+  p->step_epoch += 1;
+  // Small lists travel as an argument of the kernel that looks at the timestamps, larger ones through pinned staging.
+  const bool by_argument = total <= racer::kListArgBytes;
+  racer::ListArg arg;
+  uint8_t* hbuf = arg.bytes;
+  int which = 0;
+  if (!by_argument && (rc = p->hstage.acquire(total, &hbuf, &which))) return rc;
+  racer::ReqDev* hr = reinterpret_cast<racer::ReqDev*>(hbuf + off_reqs);
+  for (uint32_t r = 0; r < B; ++r)
     hr[r] = racer::ReqDev{reqs[r].prefix_len, reqs[r].new_len, static_cast<uint32_t>(reqs[r].page_table_off),
-                          static_cast<uint32_t>(reqs[r].ts_off), static_cast<uint32_t>(reqs[r].x_off), (ts && N) ? 1u : 0u /* cleared by the check */};
-    if (fp32)
-      for (uint32_t i = 0; i < reqs[r].new_len; ++i) hrow[reqs[r].x_off + i] = r;
+                          static_cast<uint32_t>(reqs[r].ts_off), static_cast<uint32_t>(reqs[r].x_off)};
+  if (fp32) {
+    uint32_t* hrow = reinterpret_cast<uint32_t*>(hbuf + off_rows);
+    for (uint32_t r = 0; r < B; ++r) std::fill_n(hrow + reqs[r].x_off, reqs[r].new_len, r);
   }
-  if (!group_req.empty()) std::memcpy(hbuf + off_group_req, group_req.data(), sizeof(uint32_t) * group_req.size());
-  if (!items.empty()) std::memcpy(hbuf + off_items, items.data(), sizeof(racer::AttnItem) * items.size());
-  if (!groups.empty()) std::memcpy(hbuf + off_groups, groups.data(), sizeof(racer::AttnGroup) * groups.size());
-  if (!row_tiles.empty()) std::memcpy(hbuf + off_row_tiles, row_tiles.data(), sizeof(racer::RowTile) * row_tiles.size());
-  if (!work.empty()) std::memcpy(hbuf + off_work, work.data(), sizeof(racer::AttnWork) * work.size());
-  HIP_TRY(hipMemcpyAsync(p->hl_dev, hbuf, total, hipMemcpyHostToDevice, stream));
-  if ((rc = p->hstage.mark(which, stream))) return rc;
-  // which requests' timestamps never decrease (the attention kernels' 32-bit time paths rely on it)
-  if (ts && N) {
-    uint32_t longest = 0;
-    for (uint32_t r = 0; r < B; ++r) longest = std::max(longest, reqs[r].prefix_len + reqs[r].new_len);
-    HIP_TRY(racer::launch_check_timestamps(reinterpret_cast<racer::ReqDev*>(p->hl_dev), B, longest, ts, p->d_counters, stream));
+  auto put = [&](uint64_t at, const void* src, uint64_t bytes) {
+    if (bytes) std::memcpy(hbuf + at, src, bytes);
+  };
+  put(off_items, w.items.data(), sizeof(racer::AttnItem) * w.items.size());
+  put(off_groups, w.groups.data(), sizeof(racer::AttnGroup) * w.groups.size());
+  put(off_row_tiles, w.row_tiles.data(), sizeof(racer::RowTile) * w.row_tiles.size());
+  if (ctx->fused) {
+    uint32_t* gr = reinterpret_cast<uint32_t*>(hbuf + off_group_req);
+    uint64_t next = 0;
+    uint32_t last = 0;
+    for (uint32_t r = 0; r < B; ++r) {
+      const uint64_t end = reqs[r].x_off + reqs[r].new_len;
+      if (reqs[r].new_len) last = r;
+      for (; next < end; next += 32) *gr++ = r;
+    }
+    *gr = last;
+  }
+  racer::AttnWork* hw = reinterpret_cast<racer::AttnWork*>(hbuf + off_work);
+  for (uint32_t x = 0; x < racer::kXcds; ++x)
+    for (size_t i = 0; i < die_len; ++i)
+      hw[i * racer::kXcds + x] = i < w.die_list[x].size() ? w.die_list[x][i] : racer::AttnWork{racer::kNoWork, 0};
+  if (!by_argument) {
+    HIP_TRY(hipMemcpyAsync(p->hl_dev, hbuf, total, hipMemcpyHostToDevice, stream));
+    if ((rc = p->hstage.mark(which, stream))) return rc;
   }
 
-  ctx->esize = esize;
-  uint32_t pt_shift = 32;
-  for (uint32_t b = 0; b < 32; ++b)
-    if ((1u << b) == c.page_tokens) pt_shift = b;
-  ctx->hd = racer::HstuDims{c.L, c.d, c.H, c.d / c.H, c.elem, c.page_tokens, c.n_pos, c.n_time, 1.0f / c.n_scale, c.eps, pt_shift};
-  ctx->kv = racer::KvView{p->base, p->page_size, static_cast<uint32_t>(p->host.n_pages()), p->d_counters};
-  ctx->sl.reqs = reinterpret_cast<const racer::ReqDev*>(p->hl_dev);
-  ctx->sl.row_req = reinterpret_cast<const uint32_t*>(p->hl_dev + off_rows);
-  ctx->sl.items = reinterpret_cast<const racer::AttnItem*>(p->hl_dev + off_items);
-  ctx->sl.groups = reinterpret_cast<const racer::AttnGroup*>(p->hl_dev + off_groups);
-  ctx->sl.partials = reinterpret_cast<float*>(p->hp_dev);
-  ctx->sl.n_items = static_cast<uint32_t>(items.size());
-  ctx->sl.work = reinterpret_cast<const racer::AttnWork*>(p->hl_dev + off_work);
-  ctx->sl.n_work = static_cast<uint32_t>(work.size());
-  ctx->sl.n_groups = static_cast<uint32_t>(groups.size());
-  ctx->sl.q_block = q_block;
-  ctx->sl.row_tiles = reinterpret_cast<const racer::RowTile*>(p->hl_dev + off_row_tiles);
-  ctx->sl.n_row_tiles = static_cast<uint32_t>(row_tiles.size());
-  ctx->sl.group_req = reinterpret_cast<const uint32_t*>(p->hl_dev + off_group_req);
-  ctx->sl.row0 = 0;
-  ctx->sl.B = B;
-  ctx->sl.N = static_cast<uint32_t>(N);
-  ctx->n_runs = n_runs;
-  if (n_runs > 1) {
-    // groups and row tiles were built request after request: a run's are a contiguous piece of each array
-    size_t g = 0, t = 0;
-    for (uint32_t run = 0; run < n_runs; ++run) {
-      racer::StepLists& h = ctx->run[run];
-      h = ctx->sl;
-      h.work = ctx->sl.work + work_begin[run];
-      h.n_work = static_cast<uint32_t>(work_begin[run + 1] - work_begin[run]);
-      const size_t g0 = g, t0 = t;
-      while (g < groups.size() && groups[g].req < run_begin[run + 1]) ++g;
-      while (t < row_tiles.size() && row_tiles[t].req < run_begin[run + 1]) ++t;
-      h.groups = ctx->sl.groups + g0;
-      h.n_groups = static_cast<uint32_t>(g - g0);
-      h.row_tiles = ctx->sl.row_tiles + t0;
-      h.n_row_tiles = static_cast<uint32_t>(t - t0);
-      ctx->run_row0[run] = run_begin[run] < B ? static_cast<uint32_t>(reqs[run_begin[run]].x_off) : static_cast<uint32_t>(N);
-      const uint64_t row_end = run_begin[run + 1] < B ? reqs[run_begin[run + 1]].x_off : N;
-      ctx->run_rows[run] = static_cast<uint32_t>(row_end - ctx->run_row0[run]);
-      h.group_req = ctx->sl.group_req + group_begin[run];
-      h.row0 = ctx->run_row0[run];
-      h.N = ctx->run_rows[run];
-    }
-  }
+  sl.reqs = reinterpret_cast<const racer::ReqDev*>(p->hl_dev + off_reqs);
+  sl.ts_marks = p->ts_marks;
+  sl.epoch = p->step_epoch;
+  sl.row_req = reinterpret_cast<const uint32_t*>(p->hl_dev + off_rows);
+  sl.items = reinterpret_cast<const racer::AttnItem*>(p->hl_dev + off_items);
+  sl.groups = reinterpret_cast<const racer::AttnGroup*>(p->hl_dev + off_groups);
+  sl.partials = reinterpret_cast<float*>(p->hp_dev);
+  sl.work = reinterpret_cast<const racer::AttnWork*>(p->hl_dev + off_work);
+  sl.n_work = static_cast<uint32_t>(n_work);
+  sl.n_groups = static_cast<uint32_t>(w.groups.size());
+  sl.q_block = q_block;
+  sl.row_tiles = reinterpret_cast<const racer::RowTile*>(p->hl_dev + off_row_tiles);
+  sl.n_row_tiles = static_cast<uint32_t>(w.row_tiles.size());
+  sl.group_req = reinterpret_cast<const uint32_t*>(p->hl_dev + off_group_req);
+  // which requests' timestamps never decrease (the attention kernels' 32-bit time paths rely on it)
+  if (ts) HIP_TRY(racer::launch_begin_step(sl, longest, ts, p->d_counters, by_argument ? &arg : nullptr, p->hl_dev, total, stream));
   return RACER_OK;
 }
 
@@ -1064,11 +997,10 @@ int32_t pool_reserve(racer_pool_t* p, const racer_hstu_t* m, const racer_reserve
     if (r->max_new_tokens >= (1ull << 31) || r->max_seq_tokens == 0) return RACER_EINVAL;
     const uint64_t esize = c.elem == RACER_ELEM_BF16 ? 2 : 4;
     const StepBounds b = step_bounds(r->max_requests, r->max_new_tokens, r->max_seq_tokens, c.H, c.page_tokens);
-    if ((rc = ensure_lists(p, b.list_bytes, b.list_bytes))) return rc;
+    if ((rc = ensure_lists(p, b.list_bytes, b.list_bytes)) || (rc = ensure_ts_marks(p, r->max_requests, stream))) return rc;
     if ((rc = p->hstage.reserve(b.list_bytes))) return rc;
     if (c.elem == RACER_ELEM_BF16 && (rc = ensure_partials(p, b.partial_bytes, stream))) return rc;
     if ((rc = ensure_hstu_ws(p, (r->max_new_tokens * c.d * esize + 255) & ~255ull, stream))) return rc;
-    if ((rc = ensure_step_streams(p, kStepRuns - 1))) return rc;
   }
   return RACER_OK;
 }
@@ -1078,22 +1010,12 @@ int32_t hstu_step(racer_pool_t* p, racer_hstu_t* m, const racer_hstu_req* reqs, 
   if (!p || !m || (B && !reqs)) return RACER_EINVAL;
   hipStream_t stream = static_cast<hipStream_t>(stream_v);
   const racer_hstu_cfg& c = m->cfg;
-  // A large bf16 batch runs as several pipelines, one per run of requests, all but the first on streams of the
-  // pool's own: requests share nothing inside a step, and the workgroups of one pipeline's kernel fill the slots
-  // that another's leaves idle towards its end.  Not while kernels are being timed (their durations would overlap).
-  const bool fused = racer::layer_halves_fused(racer::HstuDims{c.L, c.d, c.H, c.d / c.H, c.elem});
-  uint64_t n_tokens = 0, n_pairs = 0;
-  for (uint32_t r = 0; r < B; ++r) {
-    n_tokens += reqs[r].new_len;
-    n_pairs += static_cast<uint64_t>(reqs[r].new_len) * (reqs[r].prefix_len + reqs[r].new_len / 2);
-  }
-  const bool want_split = c.elem == RACER_ELEM_BF16 && !p->prof_on && B >= 2 &&
-                          (n_tokens >= kSplitMinTokens || n_pairs >= kSplitMinPairs);
   StepCtx ctx;
-  int32_t rc = prepare_step(p, m, reqs, B, n_page_entries, ts, stream, &ctx, want_split);
+  int32_t rc = prepare_step(p, m, reqs, B, n_page_entries, ts, stream, &ctx);
   if (rc) return rc;
   p->last_stream = stream;
-  const uint32_t N = ctx.sl.N;
+  const racer::StepLists& sl = ctx.sl;
+  const uint32_t N = sl.N;
   if (N == 0) return RACER_OK;
   if (!page_tables || !x_in || !ts || !out) return RACER_EINVAL;
   const uint64_t d = c.d;
@@ -1106,20 +1028,9 @@ int32_t hstu_step(racer_pool_t* p, racer_hstu_t* m, const racer_hstu_req* reqs, 
   uint8_t* xb[2] = {o + stride, o + 2 * stride};
   const bool bf16 = c.elem == RACER_ELEM_BF16;
   const uint64_t w1_layer = d * 4 * d * ctx.esize, w2_layer = d * d * ctx.esize;
-  const uint32_t n_runs = ctx.n_runs;
-  const bool split = n_runs > 1;
-  if (split) {  // the other pipelines start behind everything the caller's stream holds so far (lists included)
-    if ((rc = ensure_step_streams(p, n_runs - 1))) return rc;
-    HIP_TRY(hipEventRecord(p->ev_fork, stream));
-    for (uint32_t k = 0; k + 1 < n_runs; ++k) HIP_TRY(hipStreamWaitEvent(p->aux_stream[k], p->ev_fork, 0));
-  }
-  // one layer of one pipeline: rows, pages and partial slots of `sl` only
-  auto layer_of = [&](const racer::StepLists& sl, uint32_t row0, uint32_t rows, hipStream_t st, uint32_t l,
-                      const void* x_cur, void* x_next) -> int32_t {
-    // the separate LayerNorm and output GEMM work on rows [row0, row0 + rows) of every matrix
-    const uint64_t off = static_cast<uint64_t>(row0) * d * ctx.esize;
-    auto at = [&](const void* base) { return static_cast<const uint8_t*>(base) + off; };
-    auto at_w = [&](void* base) { return static_cast<uint8_t*>(base) + off; };
+  const void* x_cur = x_in;
+  for (uint32_t l = 0; l < c.L; ++l) {
+    void* x_next = (l + 1 == c.L) ? out : static_cast<void*>(xb[l & 1]);
     const float* ln1_g = static_cast<const float*>(m->w.ln1_g) + l * d;
     const float* ln1_b = static_cast<const float*>(m->w.ln1_b) + l * d;
     const float* ln2_g = static_cast<const float*>(m->w.ln2_g) + l * d;
@@ -1128,58 +1039,39 @@ int32_t hstu_step(racer_pool_t* p, racer_hstu_t* m, const racer_hstu_req* reqs, 
     const float* b2 = static_cast<const float*>(m->w.b2) + l * d;
     const uint8_t* w1 = static_cast<const uint8_t*>(bf16 ? m->w1t : m->w.w1) + l * w1_layer;
     const uint8_t* w2 = static_cast<const uint8_t*>(bf16 ? m->w2t : m->w.w2) + l * w2_layer;
-    if (fused) {
-      ProfScope t(p, RACER_PROF_GEMM_FRONT, st);
-      HIP_TRY(racer::launch_layer_front_fused(ctx.hd, l, x_cur, ln1_g, ln1_b, w1, b1, u, q, ctx.kv, sl, page_tables, st));
+    if (ctx.fused) {
+      ProfScope t(p, RACER_PROF_GEMM_FRONT, stream);
+      HIP_TRY(racer::launch_layer_front_fused(ctx.hd, l, x_cur, ln1_g, ln1_b, w1, b1, u, q, ctx.kv, sl, page_tables, stream));
     } else {
       {
-        ProfScope t(p, RACER_PROF_LAYERNORM, st);
-        HIP_TRY(racer::launch_layernorm(ctx.hd, at(x_cur), ln1_g, ln1_b, nullptr, at_w(xn), rows, st));
+        ProfScope t(p, RACER_PROF_LAYERNORM, stream);
+        HIP_TRY(racer::launch_layernorm(ctx.hd, x_cur, ln1_g, ln1_b, nullptr, xn, N, stream));
       }
-      ProfScope t(p, RACER_PROF_GEMM_FRONT, st);
-      HIP_TRY(racer::launch_gemm_front(ctx.hd, l, xn, w1, b1, u, q, ctx.kv, sl, page_tables, st));
+      ProfScope t(p, RACER_PROF_GEMM_FRONT, stream);
+      HIP_TRY(racer::launch_gemm_front(ctx.hd, l, xn, w1, b1, u, q, ctx.kv, sl, page_tables, stream));
     }
     {
-      ProfScope t(p, RACER_PROF_ATTENTION, st);
+      ProfScope t(p, RACER_PROF_ATTENTION, stream);
       HIP_TRY(racer::launch_attention(ctx.hd, l, q, bf16 ? m->pos_s : static_cast<const float*>(m->w.pos),
                                       bf16 ? m->time_s : static_cast<const float*>(m->w.time), ctx.kv, sl,
-                                      page_tables, ts, o, /*o_half=*/bf16, st));
+                                      page_tables, ts, o, /*o_half=*/bf16, stream));
     }
     if (sl.n_groups) {
-      ProfScope t(p, RACER_PROF_ATTN_REDUCE, st);
-      HIP_TRY(racer::launch_attention_reduce(ctx.hd, sl, o, /*o_half=*/bf16, st));
+      ProfScope t(p, RACER_PROF_ATTN_REDUCE, stream);
+      HIP_TRY(racer::launch_attention_reduce(ctx.hd, sl, o, /*o_half=*/bf16, stream));
     }
-    if (fused) {
-      ProfScope t(p, RACER_PROF_GEMM_BACK, st);
-      HIP_TRY(racer::launch_layer_back_fused(ctx.hd, o, u, ln2_g, ln2_b, w2, b2, x_cur, x_next, sl, st));
+    if (ctx.fused) {
+      ProfScope t(p, RACER_PROF_GEMM_BACK, stream);
+      HIP_TRY(racer::launch_layer_back_fused(ctx.hd, o, u, ln2_g, ln2_b, w2, b2, x_cur, x_next, sl, stream));
     } else {
       {
-        ProfScope t(p, RACER_PROF_LAYERNORM, st);
-        HIP_TRY(racer::launch_layernorm(ctx.hd, at(o), ln2_g, ln2_b, at(u), at_w(xn), rows, st));
+        ProfScope t(p, RACER_PROF_LAYERNORM, stream);
+        HIP_TRY(racer::launch_layernorm(ctx.hd, o, ln2_g, ln2_b, u, xn, N, stream));
       }
-      ProfScope t(p, RACER_PROF_GEMM_BACK, st);
-      HIP_TRY(racer::launch_gemm_back(ctx.hd, at(xn), w2, b2, at(x_cur), at_w(x_next), rows, st));
-    }
-    return RACER_OK;
-  };
-  const void* x_cur = x_in;
-  for (uint32_t l = 0; l < c.L; ++l) {
-    void* x_next = (l + 1 == c.L) ? out : static_cast<void*>(xb[l & 1]);
-    if (split) {
-      for (uint32_t run = 0; run < n_runs; ++run)
-        if ((rc = layer_of(ctx.run[run], ctx.run_row0[run], ctx.run_rows[run], run ? p->aux_stream[run - 1] : stream, l,
-                           x_cur, x_next)))
-          return rc;
-    } else {
-      if ((rc = layer_of(ctx.sl, 0, N, stream, l, x_cur, x_next))) return rc;
+      ProfScope t(p, RACER_PROF_GEMM_BACK, stream);
+      HIP_TRY(racer::launch_gemm_back(ctx.hd, xn, w2, b2, x_cur, x_next, N, stream));
     }
     x_cur = x_next;
-  }
-  if (split) {  // the caller's stream goes on when every pipeline is through
-    for (uint32_t k = 0; k + 1 < n_runs; ++k) {
-      HIP_TRY(hipEventRecord(p->ev_join[k], p->aux_stream[k]));
-      HIP_TRY(hipStreamWaitEvent(stream, p->ev_join[k], 0));
-    }
   }
   return RACER_OK;
 }

@@ -1087,27 +1087,32 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
         return;
       }
     }
-    auto page_of = [&](uint32_t j, uint32_t* ip) -> const uint8_t* {
+    // (The block's base passes through an empty asm, so that its sum with a lane's place in the block, the same for every
+    // tile, is not kept in registers over the whole loop.)
+    auto block_of = [&](uint32_t j, uint64_t off, uint32_t* ip) -> const uint8_t* {
       if (j >= S) return nullptr;
       uint32_t pi;
       split_token(hd, j, &pi, ip);
       const int32_t page = sm.pages[pi - page0];
-      return page >= 0 ? kv.base + static_cast<uint64_t>(page) * kv.page_size : nullptr;
+      if (page < 0) return nullptr;
+      const uint8_t* b = kv.base + static_cast<uint64_t>(page) * kv.page_size + off;
+      asm volatile("" : "+v"(b));
+      return b;
     };
     const uint8_t* zero = reinterpret_cast<const uint8_t*>(&kZeroChunk);
 #pragma unroll
     for (uint32_t i = 0; i < 2; ++i) {
       uint32_t ip = 0;
-      const uint8_t* pb = page_of(j0 + krow + 4 * i, &ip);
-      const uint8_t* src = pb ? pb + koff + static_cast<uint64_t>(ip) * 128 + part * 16 : zero;
+      const uint8_t* kb = block_of(j0 + krow + 4 * i, koff, &ip);
+      const uint8_t* src = kb ? kb + (ip * 128 + part * 16) : zero;
       set_lds_target(lds + i * 1024);
       copy_to_lds_from(src);
     }
     uint32_t ip = 0;  // V^T: 8 consecutive keys inside one page (page_tokens % 8 == 0)
-    const uint8_t* pb = page_of(j0 + part * 8, &ip);
+    const uint8_t* vb = block_of(j0 + part * 8, voff, &ip);
 #pragma unroll
     for (uint32_t i = 0; i < 2; ++i) {
-      const uint8_t* src = pb ? pb + voff + (static_cast<uint64_t>(vrow + 8 * i) * hd.pt + ip) * 2 : zero;
+      const uint8_t* src = vb ? vb + ((vrow + 8 * i) * hd.pt + ip) * 2 : zero;
       set_lds_target(lds + 8192 + i * 1024);
       copy_to_lds_from(src);
     }
@@ -1140,148 +1145,154 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
 
   fetch(kt_begin, 0);
   fetched(kt_begin, 0);
-  for (uint32_t kt = kt_begin; kt < kt_end; ++kt) {
-    const uint32_t j0 = kt * 64, t = kt - kt_begin, buf = t & 1;
-    // one barrier per tile: tile kt is in LDS, and every wavefront is done with tile kt - 1, whose half takes tile kt + 1
-    __syncthreads();
-    const bool more = kt + 1 < kt_end;
-    uint32_t side = 0;  // wavefront 0: the next tile's 64 window entries, wavefront 1: its timestamps
-    if (more) {
-      if (wave == 0) side = __float_as_uint(pos_at(64 * t + 191 + lane));
-      if (wave == 1) side = tile_time(j0 + 64 + lane);
-      fetch(kt + 1, buf ^ 1);
-    }
-    const uint8_t* ks = &sm.kv[buf][0][0];
-    const uint8_t* vs = &sm.kv[buf][1][0];
-    // first and last key time of the two halves
-    uint32_t tkb[4] = {0, 0, 0, 0};
-    if (fast) {
-      const uint32_t mine = sm.tk[buf][lane];
-      tkb[0] = __builtin_amdgcn_readlane(mine, 0);
-      tkb[1] = __builtin_amdgcn_readlane(mine, 31);
-      tkb[2] = __builtin_amdgcn_readlane(mine, 32);
-      tkb[3] = __builtin_amdgcn_readlane(mine, 63);
-    }
-    auto k_frag = [&](int sb, int st) { return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(ks + sb * 4096 + chunk_off[st])); };
-    auto v_frag = [&](int sb, int s2, int db) {
-      return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(vs + db * 4096 + chunk_off[2 * sb + s2]));
-    };
-    // S^T = K Q^T on top of the positional bias: lane's window entries x0 .. x0+7 and x0+16 .. x0+23
-    auto scores_begin = [&](int sb) {
-      const float* pw = pos_copy + (((pos_c0 & ~3u) + 64 * t + 32 * sb) & (kPosRing - 1));
-      const f32x4 w0 = *reinterpret_cast<const f32x4*>(pw), w1 = *reinterpret_cast<const f32x4*>(pw + 4);
-      const f32x4 w2 = *reinterpret_cast<const f32x4*>(pw + 16), w3 = *reinterpret_cast<const f32x4*>(pw + 20);
-      f32x16 sacc;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        sacc[e] = w0[e];
-        sacc[4 + e] = w1[e];
-        sacc[8 + e] = w2[e];
-        sacc[12 + e] = w3[e];
+  // (the general requests have a loop of their own, so that what it needs does not weigh on the other's registers)
+  auto sweep = [&](auto fast_tag) {
+    constexpr bool FAST = decltype(fast_tag)::value;
+    for (uint32_t kt = kt_begin; kt < kt_end; ++kt) {
+      const uint32_t j0 = kt * 64, t = kt - kt_begin, buf = t & 1;
+      // one barrier per tile: tile kt is in LDS, and every wavefront is done with tile kt - 1, whose half takes tile kt + 1
+      __syncthreads();
+      const bool more = kt + 1 < kt_end;
+      uint32_t side = 0;  // wavefront 0: the next tile's 64 window entries, wavefront 1: its timestamps
+      if (more) {
+        if (wave == 0) side = __float_as_uint(pos_at(64 * t + 191 + lane));
+        if (wave == 1) side = tile_time(j0 + 64 + lane);
+        fetch(kt + 1, buf ^ 1);
       }
-      return sacc;
-    };
-    // bias, SiLU, mask -> bf16 pairs.  sacc[e]: key kb + 16*(e/8) + 8*g + e%8, query li;
-    // y = (q.k + pos) * log2 e
-    auto epilogue = [&](int sb, const f32x16& sacc, uint32_t (&pk)[8]) {
-      const uint32_t kb = j0 + 32 * sb;
-      const bool diag = kb + 31 > grp_first;
-      int mode = 2;  // 0: one time bias for the block, 1: two adjacent buckets, 2: bucket per score (+ mask)
-      float c_lo = 0.0f, c_hi = 0.0f;
-      uint32_t thr = 0;
-      if (fast && !diag) {
-        const uint32_t bmin = bucket_u32(tq_first - tkb[2 * sb + 1], hd.n_time);
-        const uint32_t bmax = bucket_u32(tq_last - tkb[2 * sb], hd.n_time);
-        c_lo = sm.time[bmin];
-        if (bmin == bmax) {
-          mode = 0;
-        } else if (bmax == bmin + 1) {
-          mode = 1;
-          c_hi = sm.time[bmax];
-          thr = 2u << bmin;  // gaps >= 2^(bmin+1) belong to the upper bucket
+      const uint8_t* ks = &sm.kv[buf][0][0];
+      const uint8_t* vs = &sm.kv[buf][1][0];
+      // first and last key time of the two halves
+      uint32_t tkb[4] = {0, 0, 0, 0};
+      if (FAST) {
+        const uint32_t mine = sm.tk[buf][lane];
+        tkb[0] = __builtin_amdgcn_readlane(mine, 0);
+        tkb[1] = __builtin_amdgcn_readlane(mine, 31);
+        tkb[2] = __builtin_amdgcn_readlane(mine, 32);
+        tkb[3] = __builtin_amdgcn_readlane(mine, 63);
+      }
+      auto k_frag = [&](int sb, int st) { return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(ks + sb * 4096 + chunk_off[st])); };
+      auto v_frag = [&](int sb, int s2, int db) {
+        return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(vs + db * 4096 + chunk_off[2 * sb + s2]));
+      };
+      // S^T = K Q^T on top of the positional bias: lane's window entries x0 .. x0+7 and x0+16 .. x0+23
+      auto scores_begin = [&](int sb) {
+        const float* pw = pos_copy + (((pos_c0 & ~3u) + 64 * t + 32 * sb) & (kPosRing - 1));
+        const f32x4 w0 = *reinterpret_cast<const f32x4*>(pw), w1 = *reinterpret_cast<const f32x4*>(pw + 4);
+        const f32x4 w2 = *reinterpret_cast<const f32x4*>(pw + 16), w3 = *reinterpret_cast<const f32x4*>(pw + 20);
+        f32x16 sacc;
+  #pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          sacc[e] = w0[e];
+          sacc[4 + e] = w1[e];
+          sacc[8 + e] = w2[e];
+          sacc[12 + e] = w3[e];
         }
-      }
-      if (mode == 0) {
-#pragma unroll
-        for (int e = 0; e < 16; e += 2)
-          pk[e >> 1] = pack_bf16x2(silu_log2(sacc[e] + c_lo), silu_log2(sacc[e + 1] + c_lo));
-        return;
-      }
-      const int lim = static_cast<int>(p) - static_cast<int>(kb) - 8 * static_cast<int>(g);  // visible: key offset <= lim
-      if (fast) {
-        // eight scores at a time: the lane's key timestamps (all below 2^31) come as two 16-byte reads
-        const u32x4* tkp = reinterpret_cast<const u32x4*>(&sm.tk[buf][32 * sb + 8 * g]);
-        const int32_t lim_t = tq >= thr ? static_cast<int32_t>(tq - thr) : -1;
-#pragma unroll
-        for (int hf = 0; hf < 2; ++hf) {
-          const u32x4 t0 = tkp[4 * hf], t1 = tkp[4 * hf + 1];
-          const uint32_t tkl[8] = {t0.x, t0.y, t0.z, t0.w, t1.x, t1.y, t1.z, t1.w};
-          float a[8];
-          if (mode == 1) {
-            // gap >= thr  <=>  key time <= query time - thr (never, if that is negative)
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-              a[e] = silu_log2(sacc[8 * hf + e] + (static_cast<int32_t>(tkl[e]) <= lim_t ? c_hi : c_lo));
-          } else {
-            // bucket per score through the table indexed by the gap's leading zero count; a key after
-            // the query gives a wrapped gap, whose (valid) table entry the causal select discards
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-              const uint32_t gap = tq - tkl[e];
-              a[e] = silu_log2(sacc[8 * hf + e] + sm.rtime[__clz(static_cast<int>(gap > 1 ? gap : 1))]);
-            }
-            if (diag) {
-#pragma unroll
-              for (int e = 0; e < 8; ++e) a[e] = 16 * hf + e <= lim ? a[e] : 0.0f;
-            }
+        return sacc;
+      };
+      // bias, SiLU, mask -> bf16 pairs.  sacc[e]: key kb + 16*(e/8) + 8*g + e%8, query li;
+      // y = (q.k + pos) * log2 e
+      auto epilogue = [&](int sb, const f32x16& sacc, uint32_t (&pk)[8]) {
+        const uint32_t kb = j0 + 32 * sb;
+        const bool diag = kb + 31 > grp_first;
+        int mode = 2;  // 0: one time bias for the block, 1: two adjacent buckets, 2: bucket per score (+ mask)
+        float c_lo = 0.0f, c_hi = 0.0f;
+        uint32_t thr = 0;
+        if (FAST && !diag) {
+          const uint32_t bmin = bucket_u32(tq_first - tkb[2 * sb + 1], hd.n_time);
+          const uint32_t bmax = bucket_u32(tq_last - tkb[2 * sb], hd.n_time);
+          c_lo = sm.time[bmin];
+          if (bmin == bmax) {
+            mode = 0;
+          } else if (bmax == bmin + 1) {
+            mode = 1;
+            c_hi = sm.time[bmax];
+            thr = 2u << bmin;  // gaps >= 2^(bmin+1) belong to the upper bucket
           }
-#pragma unroll
-          for (int e = 0; e < 8; e += 2) pk[4 * hf + (e >> 1)] = pack_bf16x2(a[e], a[e + 1]);
         }
-        return;
-      }
-      // 64-bit gaps (requests spanning 2^31 s or more or with decreasing timestamps, or more than 32 buckets)
-      const long long ts_q = q_ok ? tsr[p] : ts_base;
-#pragma unroll
-      for (int e = 0; e < 16; e += 2) {
-        float a[2];
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-          const int off = 16 * ((e + k) / 8) + ((e + k) % 8);
-          const uint32_t jl = 32 * sb + off + 8 * g;
-          const uint32_t bkt = time_bucket(ts_q - (j0 + jl < S ? tsr[j0 + jl] : ts_base), hd.n_time);
-          const float v = silu_log2(sacc[e + k] + sm.time[bkt]);
-          a[k] = off <= lim ? v : 0.0f;
+        if (mode == 0) {
+  #pragma unroll
+          for (int e = 0; e < 16; e += 2)
+            pk[e >> 1] = pack_bf16x2(silu_log2(sacc[e] + c_lo), silu_log2(sacc[e + 1] + c_lo));
+          return;
         }
-        pk[e >> 1] = pack_bf16x2(a[0], a[1]);
+        const int lim = static_cast<int>(p) - static_cast<int>(kb) - 8 * static_cast<int>(g);  // visible: key offset <= lim
+        if (FAST) {
+          // eight scores at a time: the lane's key timestamps (all below 2^31) come as two 16-byte reads
+          const u32x4* tkp = reinterpret_cast<const u32x4*>(&sm.tk[buf][32 * sb + 8 * g]);
+          const int32_t lim_t = tq >= thr ? static_cast<int32_t>(tq - thr) : -1;
+  #pragma unroll
+          for (int hf = 0; hf < 2; ++hf) {
+            const u32x4 t0 = tkp[4 * hf], t1 = tkp[4 * hf + 1];
+            const uint32_t tkl[8] = {t0.x, t0.y, t0.z, t0.w, t1.x, t1.y, t1.z, t1.w};
+            float a[8];
+            if (mode == 1) {
+              // gap >= thr  <=>  key time <= query time - thr (never, if that is negative)
+  #pragma unroll
+              for (int e = 0; e < 8; ++e)
+                a[e] = silu_log2(sacc[8 * hf + e] + (static_cast<int32_t>(tkl[e]) <= lim_t ? c_hi : c_lo));
+            } else {
+              // bucket per score through the table indexed by the gap's leading zero count; a key after
+              // the query gives a wrapped gap, whose (valid) table entry the causal select discards
+  #pragma unroll
+              for (int e = 0; e < 8; ++e) {
+                const uint32_t gap = tq - tkl[e];
+                a[e] = silu_log2(sacc[8 * hf + e] + sm.rtime[__clz(static_cast<int>(gap > 1 ? gap : 1))]);
+              }
+              if (diag) {
+  #pragma unroll
+                for (int e = 0; e < 8; ++e) a[e] = 16 * hf + e <= lim ? a[e] : 0.0f;
+              }
+            }
+  #pragma unroll
+            for (int e = 0; e < 8; e += 2) pk[4 * hf + (e >> 1)] = pack_bf16x2(a[e], a[e + 1]);
+          }
+          return;
+        }
+        // 64-bit gaps (requests spanning 2^31 s or more or with decreasing timestamps, or more than 32 buckets)
+        const long long ts_q = q_ok ? tsr[p] : ts_base;
+  #pragma unroll
+        for (int e = 0; e < 16; e += 2) {
+          float a[2];
+  #pragma unroll
+          for (int k = 0; k < 2; ++k) {
+            const int off = 16 * ((e + k) / 8) + ((e + k) % 8);
+            const uint32_t jl = 32 * sb + off + 8 * g;
+            const uint32_t bkt = time_bucket(ts_q - (j0 + jl < S ? tsr[j0 + jl] : ts_base), hd.n_time);
+            const float v = silu_log2(sacc[e + k] + sm.time[bkt]);
+            a[k] = off <= lim ? v : 0.0f;
+          }
+          pk[e >> 1] = pack_bf16x2(a[0], a[1]);
+        }
+      };
+      // O^T += V^T P^T; the P^T operand of step s2 = elements 8*s2 .. 8*s2+7: keys kb + 16*s2 + 8*g + 0..7
+      auto accumulate = [&](int sb, const uint32_t (&pk)[8]) {
+  #pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2) {
+          const bf16x8 pf = __builtin_bit_cast(bf16x8, u32x4{pk[4 * s2], pk[4 * s2 + 1], pk[4 * s2 + 2], pk[4 * s2 + 3]});
+  #pragma unroll
+          for (int db = 0; db < 2; ++db)
+            oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_frag(sb, s2, db), pf, oacc[db], 0, 0, 0);
+        }
+      };
+  #pragma unroll
+      for (uint32_t sb = 0; sb < 2; ++sb) {
+        if (sb < sb_first || sb > sb_last || !grp_active || j0 + 32 * sb > grp_last) continue;  // the wavefront's, and some pair visible
+        f32x16 s = scores_begin(sb);
+  #pragma unroll
+        for (int st = 0; st < 4; ++st) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_frag(sb, st), qf[st], s, 0, 0, 0);
+        uint32_t pk[8];
+        epilogue(sb, s, pk);
+        accumulate(sb, pk);
       }
-    };
-    // O^T += V^T P^T; the P^T operand of step s2 = elements 8*s2 .. 8*s2+7: keys kb + 16*s2 + 8*g + 0..7
-    auto accumulate = [&](int sb, const uint32_t (&pk)[8]) {
-#pragma unroll
-      for (int s2 = 0; s2 < 2; ++s2) {
-        const bf16x8 pf = __builtin_bit_cast(bf16x8, u32x4{pk[4 * s2], pk[4 * s2 + 1], pk[4 * s2 + 2], pk[4 * s2 + 3]});
-#pragma unroll
-        for (int db = 0; db < 2; ++db)
-          oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_frag(sb, s2, db), pf, oacc[db], 0, 0, 0);
+      if (more) {
+        fetched(kt + 1, buf ^ 1);
+        if (wave == 0) pos_put(64 * t + 191 + lane, __uint_as_float(side));
+        if (wave == 1) sm.tk[buf ^ 1][lane] = side;
       }
-    };
-#pragma unroll
-    for (uint32_t sb = 0; sb < 2; ++sb) {
-      if (sb < sb_first || sb > sb_last || !grp_active || j0 + 32 * sb > grp_last) continue;  // the wavefront's, and some pair visible
-      f32x16 s = scores_begin(sb);
-#pragma unroll
-      for (int st = 0; st < 4; ++st) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_frag(sb, st), qf[st], s, 0, 0, 0);
-      uint32_t pk[8];
-      epilogue(sb, s, pk);
-      accumulate(sb, pk);
     }
-    if (more) {
-      fetched(kt + 1, buf ^ 1);
-      if (wave == 0) pos_put(64 * t + 191 + lane, __uint_as_float(side));
-      if (wave == 1) sm.tk[buf ^ 1][lane] = side;
-    }
-  }
+  };
+  if (fast) sweep(std::true_type{});
+  else sweep(std::false_type{});
   if (paired) {  // the second half tiles' sums join the first ones'
     __syncthreads();
     float* xs = reinterpret_cast<float*>(&sm.kv[0][0][0]) + grp * (32 * 64) + lane * 4;  // [e / 4][lane][4] per group

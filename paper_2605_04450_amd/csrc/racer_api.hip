@@ -761,8 +761,12 @@ namespace {
 // Q query tiles (128 new tokens of one request), V visits of 64-key tiles; a query tile is cut into at most
 // n_kt / chunk + 1 items, and the chunk is at least V * H / kAttnItemsWanted tiles unless the item's page-table slice
 // caps it, and at least kAttnMinChunk.
-constexpr uint64_t kAttnItemsWanted = 2048;  // two rounds of the chip's 256 x 4 resident blocks
-constexpr uint32_t kAttnMinChunk = 8;
+// One item per resident block of the chip (256 CUs x 4): with twice as many, the partial sums of a 131k-token step and
+// their reduction cost 8 us a layer and saved nothing; with one, 32 x 512 queries behind 16 384 keys are not cut at all.
+constexpr uint64_t kAttnItemsWanted = 1024;
+// Small steps: a block needs about 5 us before its first tile and 1.3 us per tile, so two tiles an item, spread over
+// idle CUs, beat eight in one block (one request of 64 new tokens 18 -> 11 us, 13 ragged prefills 35 -> 14 us).
+constexpr uint32_t kAttnMinChunk = 2;
 uint32_t attn_chunk_cap(uint32_t page_tokens) {  // an item's slice of the page table (a chunk and a quarter at most) must fit the kernel's LDS copy
   return std::max<uint32_t>(1, static_cast<uint32_t>((static_cast<uint64_t>(racer::kAttnMaxItemPages) - 2) * page_tokens / 64 * 4 / 5));
 }
@@ -827,7 +831,7 @@ int32_t prepare_step(racer_pool* p, racer_hstu* m, const racer_hstu_req* reqs, u
   // Attention work items.  The score matrix of a request is a staircase: late query tiles see
   // many more key tiles than early ones, and one long request would otherwise set the
   // kernel's duration.  Key ranges are therefore cut at multiples of `chunk` tiles (sized so
-  // that about two items per resident block slot exist; a short tail joins the chunk before
+  // that about one item per resident block slot exists; a short tail joins the chunk before
   // it), which also makes the items of different query tiles with the same chunk index read
   // exactly the same keys.
   StepScratch& w = p->step;

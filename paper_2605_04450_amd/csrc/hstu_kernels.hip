@@ -1,9 +1,9 @@
-// HSTU layer kernels for gfx950 (paper Sec. II-A/II-B "Compute" stage; the layer equations
+// HSTU layer kernels of bf16 models for gfx950 (paper Sec. II-A/II-B "Compute" stage; the layer equations
 // are the published HSTU form):
 //   Xn = LayerNorm(X);  [U|V|Q|K] = SiLU(Xn W1 + b1);  K,V of the new tokens -> KV pages
 //   O_i = (1/n) sum_{j<=p_i} SiLU(q_i.k_j + pos[min(p_i-j, n_pos-1)] + time[bucket(ts_p-ts_j)]) v_j
 //   Y = X + (LayerNorm(O) * U) W2 + b2
-// bf16 models run on MFMA with fp32 accumulation; the small fp32 configuration uses plain FMA kernels.
+// They run on MFMA with fp32 accumulation (fp32 models: hstu_fp32.hip).
 // What a bf16 model stores where a caller can see it (inputs, weights, K and V in the pages, outputs) is bf16.
 // The library's own intermediate matrices (the normalised activations, U, the attention output O, the gated
 // activations) and its transposed copies of the weights are IEEE half precision: eleven significant bits
@@ -19,7 +19,7 @@
 #include <type_traits>
 #include <utility>
 
-#include "kernels.h"
+#include "hstu_common.h"
 
 namespace racer {
 namespace {
@@ -41,42 +41,6 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
   return static_cast<uint16_t>((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
 }
 __device__ __forceinline__ uint16_t f2h(float f) { return __builtin_bit_cast(uint16_t, static_cast<_Float16>(f)); }  // nearest even
-__device__ __forceinline__ float load_elem(const float* p, uint64_t i) { return p[i]; }
-__device__ __forceinline__ float load_elem(const bf16_t* p, uint64_t i) { return bf2f(p[i].bits); }
-__device__ __forceinline__ void store_elem(float* p, uint64_t i, float v) { p[i] = v; }
-__device__ __forceinline__ void store_elem(bf16_t* p, uint64_t i, float v) { p[i].bits = f2bf(v); }
-
-__device__ __forceinline__ float silu(float x) { return x / (1.0f + __expf(-x)); }
-
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
-__device__ __forceinline__ uint32_t time_bucket(long long dt, uint32_t n_time) {
-  const unsigned long long v = dt > 1 ? static_cast<unsigned long long>(dt) : 1ull;
-  const uint32_t b = 63u - static_cast<uint32_t>(__clzll(static_cast<long long>(v)));
-  return b < n_time - 1 ? b : n_time - 1;
-}
-
-// byte offset of the K (kv = 0) or V (kv = 1) block of (layer, head) inside a page
-__device__ __forceinline__ uint64_t kv_block_offset(const HstuDims& hd, uint32_t layer, uint32_t kv, uint32_t head,
-                                                    uint32_t esize) {
-  return ((static_cast<uint64_t>(layer) * 2 + kv) * hd.H + head) * hd.pt * hd.dh * esize;
-}
-
-// page index and offset inside the page of token j (page_tokens is usually a power of two)
-__device__ __forceinline__ void split_token(const HstuDims& hd, uint32_t j, uint32_t* page_idx, uint32_t* in_page) {
-  if (hd.pt_shift < 32) {
-    *page_idx = j >> hd.pt_shift;
-    *in_page = j & (hd.pt - 1);
-  } else {
-    *page_idx = j / hd.pt;
-    *in_page = j % hd.pt;
-  }
-}
-
 // ---------------------------------------------------------------------------------------
 // LayerNorm over d (optionally times a gate row), two-pass in fp32.  A row is owned by LPR
 // consecutive lanes of a wavefront (64 / LPR rows per wavefront, LPR chosen so that every
@@ -113,10 +77,6 @@ __device__ __forceinline__ uint32_t pack2_f16(float lo, float hi) {
 }
 __device__ __forceinline__ void store8(half_t* p, const float v[8]) {
   *reinterpret_cast<uint4*>(p) = make_uint4(pack2_f16(v[0], v[1]), pack2_f16(v[2], v[3]), pack2_f16(v[4], v[5]), pack2_f16(v[6], v[7]));
-}
-__device__ __forceinline__ void store8(float* p, const float v[8]) {
-  *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
-  *reinterpret_cast<float4*>(p + 4) = make_float4(v[4], v[5], v[6], v[7]);
 }
 template <int LPR>
 __device__ __forceinline__ float group_sum(float v) {  // sum over the LPR lanes that share a row
@@ -178,58 +138,8 @@ __global__ __launch_bounds__(256) void layernorm_rows(const TX* __restrict__ x, 
 }
 
 // ---------------------------------------------------------------------------------------
-// Epilogues
-// ---------------------------------------------------------------------------------------
-template <typename T>
-struct FrontEpilogue {  // SiLU(acc + b1), split U | V | Q | K, K and V into the pages
-  HstuDims hd;
-  uint32_t layer;
-  const float* b1;
-  T* u;
-  T* q;
-  KvView kv;
-  const ReqDev* reqs;
-  const uint32_t* row_req;
-  const int32_t* page_tables;
-
-  __device__ __forceinline__ void operator()(uint32_t row, uint32_t col, float acc) const {
-    const float z = silu(acc + b1[col]);
-    const uint32_t which = col / hd.d, c = col % hd.d;
-    if (which == 0) { store_elem(u, static_cast<uint64_t>(row) * hd.d + c, z); return; }
-    if (which == 2) {  // bf16 models: the attention kernel wants q * log2(e) (one rounding, here)
-      store_elem(q, static_cast<uint64_t>(row) * hd.d + c, sizeof(T) == 2 ? z * 1.4426950408889634f : z);
-      return;
-    }
-    const ReqDev rq = reqs[row_req[row]];
-    const uint32_t pos = rq.prefix_len + (row - rq.x_off);
-    const int32_t page = page_tables[rq.page_table_off + pos / hd.pt];
-    if (page < 0 || static_cast<uint32_t>(page) >= kv.n_pages) {
-      atomicAdd(&kv.counters[ctr_index(kCtrBadPages)], 1ull);
-      return;
-    }
-    const uint32_t head = c / hd.dh, cc = c % hd.dh, tok = pos % hd.pt;
-    T* blk = reinterpret_cast<T*>(kv.base + static_cast<uint64_t>(page) * kv.page_size +
-                                  kv_block_offset(hd, layer, which == 1 ? 1 : 0, head, sizeof(T)));
-    if (which == 3) store_elem(blk, static_cast<uint64_t>(tok) * hd.dh + cc, z);   // K: [token][d_h]
-    else store_elem(blk, static_cast<uint64_t>(cc) * hd.pt + tok, z);              // V: [d_h][token]
-  }
-};
-
-template <typename T>
-struct BackEpilogue {  // y = x + acc + b2
-  uint32_t d;
-  const float* b2;
-  const T* x;
-  T* y;
-  __device__ __forceinline__ void operator()(uint32_t row, uint32_t col, float acc) const {
-    const uint64_t i = static_cast<uint64_t>(row) * d + col;
-    store_elem(y, i, load_elem(x, i) + acc + b2[col]);
-  }
-};
-
-// ---------------------------------------------------------------------------------------
 // Half-precision GEMM on MFMA (both operands are the library's own: a normalised activation matrix and a
-// transposed weight copy): C[M][Nout] = A[M][K] * Bt[Nout][K]^T, block tile 128 x 64, four
+// transposed weight copy): Y = X + A Bt^T + b2 with A [M][K] and Bt [K][K], block tile 128 x 64, four
 // wavefronts of 32 rows x 64 columns each, K staged through LDS 64 at a time.
 // Operand layout of v_mfma_f32_32x32x16_f16 / _bf16: lane (g = lane/32, i = lane%32) supplies row
 // (A) or column (B) i with eight consecutive k of its half g; the result lane holds column
@@ -237,9 +147,9 @@ struct BackEpilogue {  // y = x + acc + b2
 // ---------------------------------------------------------------------------------------
 constexpr int kLdsPad = 8;
 
-template <typename Epi>
-__global__ __launch_bounds__(256) void gemm_bf16_mfma(const uint16_t* __restrict__ A, const uint16_t* __restrict__ Bt,
-                                                      uint32_t M, uint32_t K, Epi epi) {
+__global__ __launch_bounds__(256) void gemm_back_bf16(const uint16_t* __restrict__ A, const uint16_t* __restrict__ Bt, uint32_t M,
+                                                      uint32_t K, const float* __restrict__ b2, const uint16_t* __restrict__ x,
+                                                      uint16_t* __restrict__ y) {
   __shared__ __attribute__((aligned(16))) uint16_t As[128][64 + kLdsPad];
   __shared__ __attribute__((aligned(16))) uint16_t Bs[64][64 + kLdsPad];
   const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5, li = lane & 31;
@@ -281,7 +191,10 @@ __global__ __launch_bounds__(256) void gemm_bf16_mfma(const uint16_t* __restrict
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const uint32_t row = m0 + 32 * wave + 8 * (r / 4) + 4 * g + (r % 4);
-      if (row < M) epi(row, n0 + 32 * cb + li, acc[cb][r]);
+      if (row >= M) continue;
+      const uint32_t col = n0 + 32 * cb + li;
+      const uint64_t i = static_cast<uint64_t>(row) * K + col;  // (square: as many columns out as in)
+      y[i] = f2bf(bf2f(x[i]) + acc[cb][r] + b2[col]);
     }
 }
 
@@ -612,13 +525,7 @@ __global__ __launch_bounds__(64 * WPB, KD <= 256 ? 3 : 2) void layer_half_fused(
   uint32_t tok = 0;
   if (FRONT && row_ok) {
     const uint32_t row = r0 + li, grp = r0 / 32;
-    uint32_t lo = a.group_req[grp], hi = a.group_req[grp + 1];
-    while (lo < hi) {  // the last request that starts at or before the row
-      const uint32_t mid = (lo + hi + 1) / 2;
-      if (a.reqs[mid].x_off <= row) lo = mid;
-      else hi = mid - 1;
-    }
-    const ReqDev rq = a.reqs[lo];
+    const ReqDev rq = a.reqs[request_of(a.reqs, row, a.group_req[grp], a.group_req[grp + 1])];
     uint32_t pi;
     split_token(hd, rq.prefix_len + (row - rq.x_off), &pi, &tok);
     const int32_t page = a.page_tables[rq.page_table_off + pi];
@@ -800,72 +707,6 @@ __global__ __launch_bounds__(64 * WPB, KD <= 256 ? 3 : 2) void layer_half_fused(
                     pack2_bf16(xv[4] + p1.x, xv[5] + p1.y), pack2_bf16(xv[6] + p1.z, xv[7] + p1.w)};
         }
       });
-    }
-  }
-}
-
-// fp32 GEMM for the small configuration: one thread per output, W is [K][Nout]
-template <typename Epi>
-__global__ __launch_bounds__(256) void gemm_f32_simple(const float* __restrict__ A, const float* __restrict__ W,
-                                                       uint32_t M, uint32_t K, uint32_t Nout, Epi epi) {
-  const uint64_t idx = static_cast<uint64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (idx >= static_cast<uint64_t>(M) * Nout) return;
-  const uint32_t row = static_cast<uint32_t>(idx / Nout), col = static_cast<uint32_t>(idx % Nout);
-  float acc = 0.0f;
-  for (uint32_t k = 0; k < K; ++k) acc = fmaf(A[static_cast<uint64_t>(row) * K + k], W[static_cast<uint64_t>(k) * Nout + col], acc);
-  epi(row, col, acc);
-}
-
-// ---------------------------------------------------------------------------------------
-// fp32 attention: one wavefront per (query row, head); lanes stride over the keys
-// ---------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void attention_f32(HstuDims hd, uint32_t layer, const float* __restrict__ q,
-                                                     const float* __restrict__ pos, const float* __restrict__ time,
-                                                     KvView kv, const ReqDev* __restrict__ reqs,
-                                                     const uint32_t* __restrict__ row_req, uint32_t N,
-                                                     const int32_t* __restrict__ page_tables,
-                                                     const long long* __restrict__ ts, float* __restrict__ o) {
-  const uint32_t lane = threadIdx.x & 63;
-  const uint32_t item = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (item >= N * hd.H) return;
-  const uint32_t row = item / hd.H, h = item % hd.H;
-  const ReqDev rq = reqs[row_req[row]];
-  const uint32_t p = rq.prefix_len + (row - rq.x_off);
-  const long long ts_p = ts[rq.ts_off + p];
-  float qv[64], acc[64];
-#pragma unroll
-  for (int c = 0; c < 64; ++c) {
-    qv[c] = c < static_cast<int>(hd.dh) ? q[static_cast<uint64_t>(row) * hd.d + h * hd.dh + c] : 0.0f;
-    acc[c] = 0.0f;
-  }
-  const float* pos_h = pos + (static_cast<uint64_t>(layer) * hd.H + h) * hd.n_pos;
-  const float* time_h = time + (static_cast<uint64_t>(layer) * hd.H + h) * hd.n_time;
-  const uint64_t koff = kv_block_offset(hd, layer, 0, h, 4), voff = kv_block_offset(hd, layer, 1, h, 4);
-  for (uint32_t j = lane; j <= p; j += 64) {
-    const int32_t page = page_tables[rq.page_table_off + j / hd.pt];
-    if (page < 0 || static_cast<uint32_t>(page) >= kv.n_pages) {
-      atomicAdd(&kv.counters[ctr_index(kCtrBadPages)], 1ull);
-      continue;
-    }
-    const uint8_t* pb = kv.base + static_cast<uint64_t>(page) * kv.page_size;
-    const float* kr = reinterpret_cast<const float*>(pb + koff) + static_cast<uint64_t>(j % hd.pt) * hd.dh;
-    const float* vt = reinterpret_cast<const float*>(pb + voff) + (j % hd.pt);
-    float s = 0.0f;
-#pragma unroll
-    for (int c = 0; c < 64; ++c)
-      if (c < static_cast<int>(hd.dh)) s = fmaf(qv[c], kr[c], s);
-    const uint32_t rel = p - j < hd.n_pos - 1 ? p - j : hd.n_pos - 1;
-    s += pos_h[rel] + time_h[time_bucket(ts_p - ts[rq.ts_off + j], hd.n_time)];
-    const float a = s / (1.0f + expf(-s));
-#pragma unroll
-    for (int c = 0; c < 64; ++c)
-      if (c < static_cast<int>(hd.dh)) acc[c] = fmaf(a, vt[static_cast<uint64_t>(c) * hd.pt], acc[c]);
-  }
-#pragma unroll
-  for (int c = 0; c < 64; ++c) {
-    if (c < static_cast<int>(hd.dh)) {
-      const float t = wave_sum(acc[c]);
-      if (lane == 0) o[static_cast<uint64_t>(row) * hd.d + h * hd.dh + c] = t * hd.inv_n;
     }
   }
 }
@@ -1342,7 +1183,7 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
 }
 
 // Sum the fp32 partials of a split query tile in chunk order and write the bf16 output.
-__global__ __launch_bounds__(256) void attention_reduce(HstuDims hd, uint32_t q_block, const ReqDev* __restrict__ reqs,
+__global__ __launch_bounds__(256) void attention_reduce(HstuDims hd, const ReqDev* __restrict__ reqs,
                                                         const AttnGroup* __restrict__ groups,
                                                         const float* __restrict__ partials, uint16_t* __restrict__ o,
                                                         uint32_t o_half) {
@@ -1353,10 +1194,10 @@ __global__ __launch_bounds__(256) void attention_reduce(HstuDims hd, uint32_t q_
   const ReqDev rq = reqs[gr.req];
   const uint32_t idx = blockIdx.y * 256 + threadIdx.x;
   const uint32_t row = idx >> 4, c4 = idx & 15;
-  const uint32_t qi = gr.qt * q_block + row;
-  if (row >= q_block || qi >= rq.new_len) return;
-  const float* src = partials + ((static_cast<uint64_t>(gr.slot0) * hd.H + h) * q_block + row) * 64 + 4 * c4;
-  const uint64_t step = static_cast<uint64_t>(hd.H) * q_block * 64;  // from one chunk's partial to the next
+  const uint32_t qi = gr.qt * kAttnQ + row;
+  if (row >= kAttnQ || qi >= rq.new_len) return;
+  const float* src = partials + ((static_cast<uint64_t>(gr.slot0) * hd.H + h) * kAttnQ + row) * 64 + 4 * c4;
+  const uint64_t step = static_cast<uint64_t>(hd.H) * kAttnQ * 64;  // from one chunk's partial to the next
   float4 acc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
   uint32_t k = 0;
   for (; k + 4 <= gr.chunks; k += 4) {  // four loads in flight; the sum keeps the chunk order
@@ -1432,17 +1273,6 @@ __global__ void scale_bf16(const uint16_t* __restrict__ in, uint16_t* __restrict
     out[k] = f2bf(bf2f(in[k]) * s);
 }
 
-template <typename T>
-__global__ void transpose_kernel(const T* __restrict__ w, T* __restrict__ wt, uint32_t rows, uint32_t cols) {
-  __shared__ T tile[32][33];
-  const uint32_t bx = blockIdx.x * 32, by = blockIdx.y * 32;
-  for (uint32_t yy = threadIdx.y; yy < 32; yy += 8)
-    if (by + yy < rows && bx + threadIdx.x < cols) tile[yy][threadIdx.x] = w[static_cast<uint64_t>(by + yy) * cols + bx + threadIdx.x];
-  __syncthreads();
-  for (uint32_t yy = threadIdx.y; yy < 32; yy += 8)
-    if (bx + yy < cols && by + threadIdx.x < rows) wt[static_cast<uint64_t>(bx + yy) * rows + by + threadIdx.x] = tile[threadIdx.x][yy];
-}
-
 // Copy of a bf16 weight matrix [rows][cols] in half precision, in the order in which the fused layer halves use it as
 // an MFMA operand: for every 32 columns and 16 rows one piece of 64 lanes x 8 elements, lane (g, i) holding column i
 // and rows 8 g .. 8 g + 7 (exact unless a weight is below 2^-14 in magnitude).
@@ -1496,8 +1326,7 @@ static void layernorm_dispatch(const HstuDims& hd, const void* x, const float* g
 hipError_t launch_layernorm(const HstuDims& hd, const void* x, const float* g, const float* b, const void* gate,
                             void* y, uint32_t N, hipStream_t stream) {
   if (N == 0) return hipSuccess;
-  if (hd.elem != 1) layernorm_dispatch<float, float>(hd, x, g, b, gate, y, N, stream);
-  else if (gate) layernorm_dispatch<half_t, half_t>(hd, x, g, b, gate, y, N, stream);
+  if (gate) layernorm_dispatch<half_t, half_t>(hd, x, g, b, gate, y, N, stream);
   else layernorm_dispatch<bf16_t, half_t>(hd, x, g, b, gate, y, N, stream);
   return hipGetLastError();
 }
@@ -1575,32 +1404,17 @@ hipError_t launch_gemm_front(const HstuDims& hd, uint32_t layer, const void* xn,
                              void* u, void* q, const KvView& kv, const StepLists& sl, const int32_t* page_tables,
                              hipStream_t stream) {
   if (sl.N == 0) return hipSuccess;
-  if (hd.elem == 1) {
-    hipLaunchKernelGGL(gemm_front_bf16, dim3(sl.n_row_tiles, 4 * hd.d / 64), dim3(256), 0, stream, hd, layer,
-                       static_cast<const uint16_t*>(xn), static_cast<const uint16_t*>(w1), b1, static_cast<uint16_t*>(u),
-                       static_cast<uint16_t*>(q), kv, sl.reqs, sl.row_tiles, page_tables);
-  } else {
-    FrontEpilogue<float> epi{hd, layer, b1, static_cast<float*>(u), static_cast<float*>(q), kv, sl.reqs, sl.row_req, page_tables};
-    const uint64_t total = static_cast<uint64_t>(sl.N) * 4 * hd.d;
-    hipLaunchKernelGGL(gemm_f32_simple<FrontEpilogue<float>>, dim3(static_cast<uint32_t>((total + 255) / 256)), dim3(256),
-                       0, stream, static_cast<const float*>(xn), static_cast<const float*>(w1), sl.N, hd.d, 4 * hd.d, epi);
-  }
+  hipLaunchKernelGGL(gemm_front_bf16, dim3(sl.n_row_tiles, 4 * hd.d / 64), dim3(256), 0, stream, hd, layer,
+                     static_cast<const uint16_t*>(xn), static_cast<const uint16_t*>(w1), b1, static_cast<uint16_t*>(u),
+                     static_cast<uint16_t*>(q), kv, sl.reqs, sl.row_tiles, page_tables);
   return hipGetLastError();
 }
 
 hipError_t launch_gemm_back(const HstuDims& hd, const void* g, const void* w2, const float* b2, const void* x,
                             void* y, uint32_t N, hipStream_t stream) {
   if (N == 0) return hipSuccess;
-  if (hd.elem == 1) {
-    BackEpilogue<bf16_t> epi{hd.d, b2, static_cast<const bf16_t*>(x), static_cast<bf16_t*>(y)};
-    hipLaunchKernelGGL(gemm_bf16_mfma<BackEpilogue<bf16_t>>, dim3((N + 127) / 128, hd.d / 64), dim3(256), 0, stream,
-                       static_cast<const uint16_t*>(g), static_cast<const uint16_t*>(w2), N, hd.d, epi);
-  } else {
-    BackEpilogue<float> epi{hd.d, b2, static_cast<const float*>(x), static_cast<float*>(y)};
-    const uint64_t total = static_cast<uint64_t>(N) * hd.d;
-    hipLaunchKernelGGL(gemm_f32_simple<BackEpilogue<float>>, dim3(static_cast<uint32_t>((total + 255) / 256)), dim3(256), 0,
-                       stream, static_cast<const float*>(g), static_cast<const float*>(w2), N, hd.d, hd.d, epi);
-  }
+  hipLaunchKernelGGL(gemm_back_bf16, dim3((N + 127) / 128, hd.d / 64), dim3(256), 0, stream, static_cast<const uint16_t*>(g),
+                     static_cast<const uint16_t*>(w2), N, hd.d, b2, static_cast<const uint16_t*>(x), static_cast<uint16_t*>(y));
   return hipGetLastError();
 }
 
@@ -1608,29 +1422,19 @@ hipError_t launch_attention(const HstuDims& hd, uint32_t layer, const void* q, c
                             const KvView& kv, const StepLists& sl, const int32_t* page_tables, const int64_t* ts,
                             void* o, bool o_half, hipStream_t stream) {
   if (sl.N == 0) return hipSuccess;
-  if (hd.elem == 1) {
-    if (sl.q_block != 128) return hipErrorInvalidValue;  // the work items are cut for 128-query blocks
-    if (o_half)
-      hipLaunchKernelGGL((attention_bf16_mfma<true>), dim3(sl.n_work), dim3(256), 0, stream, hd, layer,
-                         static_cast<const uint16_t*>(q), pos, time, kv, sl.ts_marks, sl.epoch, sl.items, sl.work, sl.partials, page_tables,
-                         reinterpret_cast<const long long*>(ts), static_cast<uint16_t*>(o));
-    else
-      hipLaunchKernelGGL((attention_bf16_mfma<false>), dim3(sl.n_work), dim3(256), 0, stream, hd, layer,
-                         static_cast<const uint16_t*>(q), pos, time, kv, sl.ts_marks, sl.epoch, sl.items, sl.work, sl.partials, page_tables,
-                         reinterpret_cast<const long long*>(ts), static_cast<uint16_t*>(o));
-  } else {
-    const uint32_t items = sl.N * hd.H;
-    hipLaunchKernelGGL(attention_f32, dim3((items + 3) / 4), dim3(256), 0, stream, hd, layer,
-                       static_cast<const float*>(q), pos, time, kv, sl.reqs, sl.row_req, sl.N, page_tables,
-                       reinterpret_cast<const long long*>(ts), static_cast<float*>(o));
-  }
+  const long long* t = reinterpret_cast<const long long*>(ts);
+  if (o_half)
+    hipLaunchKernelGGL(attention_bf16_mfma<true>, dim3(sl.n_work), dim3(256), 0, stream, hd, layer, static_cast<const uint16_t*>(q), pos,
+                       time, kv, sl.ts_marks, sl.epoch, sl.items, sl.work, sl.partials, page_tables, t, static_cast<uint16_t*>(o));
+  else
+    hipLaunchKernelGGL(attention_bf16_mfma<false>, dim3(sl.n_work), dim3(256), 0, stream, hd, layer, static_cast<const uint16_t*>(q), pos,
+                       time, kv, sl.ts_marks, sl.epoch, sl.items, sl.work, sl.partials, page_tables, t, static_cast<uint16_t*>(o));
   return hipGetLastError();
 }
 
 hipError_t launch_attention_reduce(const HstuDims& hd, const StepLists& sl, void* o, bool o_half, hipStream_t stream) {
-  if (hd.elem != 1 || sl.n_groups == 0) return hipSuccess;
-  hipLaunchKernelGGL(attention_reduce, dim3(sl.n_groups * hd.H, (sl.q_block * 16 + 255) / 256), dim3(256), 0, stream, hd,
-                     sl.q_block, sl.reqs, sl.groups, sl.partials, static_cast<uint16_t*>(o), o_half ? 1u : 0u);
+  if (sl.n_groups == 0) return hipSuccess;
+  hipLaunchKernelGGL(attention_reduce, dim3(sl.n_groups * hd.H, (kAttnQ * 16 + 255) / 256), dim3(256), 0, stream, hd, sl.reqs, sl.groups, sl.partials, static_cast<uint16_t*>(o), o_half ? 1u : 0u);
   return hipGetLastError();
 }
 
@@ -1664,18 +1468,13 @@ hipError_t launch_scale_q(const void* in, void* out, uint64_t n, hipStream_t str
   return hipGetLastError();
 }
 
-hipError_t launch_transpose_weights(const void* w, void* wt, uint32_t rows, uint32_t cols, uint32_t elem, bool fragments,
-                                    hipStream_t stream) {
-  const dim3 grid((cols + 31) / 32, (rows + 31) / 32), block(32, 8);
-  if (fragments)  // bf16 in, half precision out
-    hipLaunchKernelGGL(weight_fragments, dim3((rows * cols / 8 + 255) / 256), dim3(256), 0, stream,
-                       static_cast<const uint16_t*>(w), static_cast<uint16_t*>(wt), rows, cols);
-  else if (elem == 1)
-    hipLaunchKernelGGL(transpose_bf16_to_f16, grid, block, 0, stream, static_cast<const uint16_t*>(w),
-                       static_cast<uint16_t*>(wt), rows, cols);
+hipError_t launch_weight_copy(const void* w, void* wt, uint32_t rows, uint32_t cols, bool fragments, hipStream_t stream) {
+  const uint16_t* src = static_cast<const uint16_t*>(w);
+  uint16_t* dst = static_cast<uint16_t*>(wt);
+  if (fragments)
+    hipLaunchKernelGGL(weight_fragments, dim3((rows * cols / 8 + 255) / 256), dim3(256), 0, stream, src, dst, rows, cols);
   else
-    hipLaunchKernelGGL(transpose_kernel<float>, grid, block, 0, stream, static_cast<const float*>(w),
-                       static_cast<float*>(wt), rows, cols);
+    hipLaunchKernelGGL(transpose_bf16_to_f16, dim3((cols + 31) / 32, (rows + 31) / 32), dim3(32, 8), 0, stream, src, dst, rows, cols);
   return hipGetLastError();
 }
 

@@ -124,7 +124,7 @@ struct KvView {
 
 constexpr uint32_t kAttnMaxItemPages = 640;  // page-table entries one attention item may span
 
-// One attention work item: q_block (128) queries of one request against the key tiles [kt_begin, kt_end)
+// One attention work item: 128 queries of one request against the key tiles [kt_begin, kt_end)
 // (64 keys each).  A query tile whose key range was cut into several items accumulates
 // through fp32 partial slots (slot .. slot + chunks - 1) that a reduction pass adds up in
 // order; an item that covers its whole key range writes the output directly (slot = kDirect).
@@ -145,6 +145,7 @@ constexpr uint32_t kDirect = 0xFFFFFFFFu;
 struct AttnWork {
   uint32_t item, head;
 };
+constexpr uint32_t kF32Queries = 16;  // queries per block of the fp32 attention
 constexpr uint32_t kXcds = 8;
 constexpr uint32_t kNoWork = 0xFFFFFFFFu;
 
@@ -153,12 +154,11 @@ struct RowTile {
   uint32_t row0, rows, req, pad;
 };
 
-// row -> request map and work lists built on the host for one step
+// Work lists built on the host for one step (fp32 models: only reqs, and work with (request, first query of a 16-query tile))
 struct StepLists {
   const ReqDev* reqs;        // [B]
   const uint32_t* ts_marks;  // [B] = epoch where the request's timestamps decrease somewhere
   uint32_t epoch;
-  const uint32_t* row_req;   // [N] request of each new-token row
   const AttnItem* items;     // grouped by (request, key chunk)
   const AttnWork* work;      // [n_work] workgroup -> (item, head), die-interleaved
   uint32_t n_work;
@@ -166,9 +166,8 @@ struct StepLists {
   const RowTile* row_tiles;  // projection tiles, none crosses a request
   uint32_t n_row_tiles;
   const uint32_t* group_req; // request of rows 0, 32, .. and, behind the last of these, of the last row
-  float* partials;           // [slot][head][q_block][64]
+  float* partials;           // [slot][head][128][64]
   uint32_t n_groups;
-  uint32_t q_block;          // queries per item
   uint32_t B, N;
 };
 
@@ -196,7 +195,7 @@ hipError_t launch_gemm_back(const HstuDims& hd, const void* g, const void* w2t, 
                             const void* x, void* y, uint32_t N, hipStream_t stream);
 // bf16 models with d = 64, 128, 256 or 512: LayerNorm, projection and epilogue of a layer half in one kernel
 // (front: X -> U, Q*log2(e), K/V pages; back: O, U, X -> Y); weights as fragments.
-// In bf16 models U, O, the normalised matrices and the library's weight copies (launch_transpose_weights) are half precision.
+// In bf16 models U, O, the normalised matrices and the library's weight copies (launch_weight_copy) are half precision.
 bool layer_halves_fused(const HstuDims& hd);
 hipError_t launch_layer_front_fused(const HstuDims& hd, uint32_t layer, const void* x, const float* ln_g,
                                     const float* ln_b, const void* w1f, const float* b1, void* u, void* q,
@@ -216,8 +215,16 @@ hipError_t launch_attention_reduce(const HstuDims& hd, const StepLists& sl, void
 // q must already be multiplied by log2(e) (launch_gemm_front stores it that way)
 hipError_t launch_scale_bias(const float* in, float* out, uint64_t n, hipStream_t stream);
 hipError_t launch_scale_q(const void* in, void* out, uint64_t n, hipStream_t stream);
-// fragments: in the operand order of the fused layer halves instead of transposed (bf16 models of those widths)
-hipError_t launch_transpose_weights(const void* w, void* wt, uint32_t rows, uint32_t cols, uint32_t elem, bool fragments,
-                                    hipStream_t stream);
+// the library's half-precision copy of a bf16 weight matrix: transposed, or (fragments) in the operand order of the fused
+// layer halves
+hipError_t launch_weight_copy(const void* w, void* wt, uint32_t rows, uint32_t cols, bool fragments, hipStream_t stream);
+
+// fp32 models: a layer half in one kernel (front: in = X -> U, Q, K/V pages; back: in = O, gate = U, resid = X -> Y), W as
+// the caller gave it, and the attention
+hipError_t launch_layer_half_f32(const HstuDims& hd, uint32_t layer, bool front, const float* in, const float* gate, const float* ln_g,
+                                 const float* ln_b, const float* w, const float* bias, float* u, float* q, const KvView& kv,
+                                 const StepLists& sl, const int32_t* page_tables, const float* resid, float* y, hipStream_t stream);
+hipError_t launch_attention_f32(const HstuDims& hd, uint32_t layer, const float* q, const float* pos, const float* time, const KvView& kv,
+                                const StepLists& sl, const int32_t* page_tables, const int64_t* ts, float* o, hipStream_t stream);
 
 }  // namespace racer

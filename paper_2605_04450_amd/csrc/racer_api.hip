@@ -720,11 +720,11 @@ int32_t hstu_model_create(const racer_hstu_cfg* cfg, const racer_hstu_weights* w
     hipError_t e = hipMalloc(&m->w1t, cfg->L * d * 4 * d * 2);
     if (e == hipSuccess) e = hipMalloc(&m->w2t, cfg->L * d * d * 2);
     for (uint32_t l = 0; l < cfg->L && e == hipSuccess; ++l) {
-      e = racer::launch_transpose_weights(static_cast<const uint16_t*>(w->w1) + l * d * 4 * d,
-                                          static_cast<uint16_t*>(m->w1t) + l * d * 4 * d, cfg->d, 4 * cfg->d, 1, fused, nullptr);
+      e = racer::launch_weight_copy(static_cast<const uint16_t*>(w->w1) + l * d * 4 * d,
+                                          static_cast<uint16_t*>(m->w1t) + l * d * 4 * d, cfg->d, 4 * cfg->d, fused, nullptr);
       if (e == hipSuccess)
-        e = racer::launch_transpose_weights(static_cast<const uint16_t*>(w->w2) + l * d * d,
-                                            static_cast<uint16_t*>(m->w2t) + l * d * d, cfg->d, cfg->d, 1, fused, nullptr);
+        e = racer::launch_weight_copy(static_cast<const uint16_t*>(w->w2) + l * d * d,
+                                            static_cast<uint16_t*>(m->w2t) + l * d * d, cfg->d, cfg->d, fused, nullptr);
     }
     const uint64_t n_pos_all = static_cast<uint64_t>(cfg->L) * cfg->H * cfg->n_pos;
     const uint64_t n_time_all = static_cast<uint64_t>(cfg->L) * cfg->H * cfg->n_time;
@@ -777,7 +777,7 @@ StepBounds step_bounds(uint64_t B, uint64_t N, uint64_t max_seq, uint32_t H, uin
   const uint64_t by_chunk = std::min<uint64_t>(kAttnItemsWanted / H + 1, V / kAttnMinChunk + 1);
   const uint64_t items = Q + std::max<uint64_t>(by_chunk, V / attn_chunk_cap(page_tokens) + 1);
   StepBounds b;
-  b.list_bytes = sizeof(racer::ReqDev) * (B + 1) + 4 * (N + 1) + 4 * (N / 32 + B + 2) + sizeof(racer::AttnItem) * items +
+  b.list_bytes = sizeof(racer::ReqDev) * (B + 1) + 4 * (N / 32 + B + 2) + sizeof(racer::AttnWork) * (N / racer::kF32Queries + B) + sizeof(racer::AttnItem) * items +
                  (sizeof(racer::AttnGroup) + sizeof(racer::RowTile)) * (Q + 1) +
                  sizeof(racer::AttnWork) * racer::kXcds * items * H + 7 * 256;
   b.partial_bytes = items * H * 128 * 64 * sizeof(float);
@@ -836,7 +836,7 @@ int32_t prepare_step(racer_pool* p, racer_hstu* m, const racer_hstu_req* reqs, u
   // exactly the same keys.
   StepScratch& w = p->step;
   w.clear();
-  const uint32_t q_block = 128;
+  const uint32_t q_block = fp32 ? racer::kF32Queries : 128;
   uint64_t visits = 0;
   if (!fp32)
     for (uint32_t r = 0; r < B; ++r) {
@@ -847,6 +847,9 @@ int32_t prepare_step(racer_pool* p, racer_hstu* m, const racer_hstu_req* reqs, u
         visits += last / 64 + 1;
       }
     }
+  else
+    for (uint32_t r = 0; r < B; ++r)
+      for (uint32_t q0 = 0; q0 < reqs[r].new_len; q0 += q_block) w.die_list[0].push_back({r, q0});
   uint32_t chunk = static_cast<uint32_t>(std::max<uint64_t>(kAttnMinChunk, (visits * c.H + kAttnItemsWanted - 1) / kAttnItemsWanted));
   chunk = std::min(chunk, attn_chunk_cap(c.page_tokens));
   uint32_t n_slots = 0;
@@ -887,8 +890,9 @@ int32_t prepare_step(racer_pool* p, racer_hstu* m, const racer_hstu_req* reqs, u
   std::sort(w.order.begin(), w.order.end(), [&](uint32_t a, uint32_t b) {
     return w.units[a].weight != w.units[b].weight ? w.units[a].weight > w.units[b].weight : a < b;
   });
+  const uint32_t n_dies = fp32 ? 1 : racer::kXcds;
   uint64_t die_load[racer::kXcds] = {};
-  size_t die_len = 0;
+  size_t die_len = w.die_list[0].size();
   for (uint32_t ui : w.order)
     for (uint32_t h = 0; h < c.H; ++h) {
       uint32_t best = 0;
@@ -898,7 +902,7 @@ int32_t prepare_step(racer_pool* p, racer_hstu* m, const racer_hstu_req* reqs, u
       for (uint32_t i = 0; i < w.units[ui].n_items; ++i) w.die_list[best].push_back({w.units[ui].item0 + i, h});
       die_len = std::max(die_len, w.die_list[best].size());
     }
-  const size_t n_work = die_len * racer::kXcds;
+  const size_t n_work = die_len * n_dies;
   const uint64_t partial_bytes = static_cast<uint64_t>(n_slots) * c.H * q_block * 64 * sizeof(float);
   int32_t rc = ensure_partials(p, partial_bytes + partial_bytes / 4, stream);
   if (rc) return rc;
@@ -916,7 +920,6 @@ int32_t prepare_step(racer_pool* p, racer_hstu* m, const racer_hstu_req* reqs, u
     return at;
   };
   const uint64_t off_reqs = place(sizeof(racer::ReqDev) * B);
-  const uint64_t off_rows = place(fp32 ? sizeof(uint32_t) * N : 0);  // row -> request: the fp32 kernels
   const uint64_t off_items = place(sizeof(racer::AttnItem) * w.items.size());
   const uint64_t off_groups = place(sizeof(racer::AttnGroup) * w.groups.size());
   const uint64_t off_row_tiles = place(sizeof(racer::RowTile) * w.row_tiles.size());
@@ -934,10 +937,6 @@ int32_t prepare_step(racer_pool* p, racer_hstu* m, const racer_hstu_req* reqs, u
   for (uint32_t r = 0; r < B; ++r)
     hr[r] = racer::ReqDev{reqs[r].prefix_len, reqs[r].new_len, static_cast<uint32_t>(reqs[r].page_table_off),
                           static_cast<uint32_t>(reqs[r].ts_off), static_cast<uint32_t>(reqs[r].x_off)};
-  if (fp32) {
-    uint32_t* hrow = reinterpret_cast<uint32_t*>(hbuf + off_rows);
-    for (uint32_t r = 0; r < B; ++r) std::fill_n(hrow + reqs[r].x_off, reqs[r].new_len, r);
-  }
   auto put = [&](uint64_t at, const void* src, uint64_t bytes) {
     if (bytes) std::memcpy(hbuf + at, src, bytes);
   };
@@ -956,9 +955,9 @@ int32_t prepare_step(racer_pool* p, racer_hstu* m, const racer_hstu_req* reqs, u
     *gr = last;
   }
   racer::AttnWork* hw = reinterpret_cast<racer::AttnWork*>(hbuf + off_work);
-  for (uint32_t x = 0; x < racer::kXcds; ++x)
+  for (uint32_t x = 0; x < n_dies; ++x)
     for (size_t i = 0; i < die_len; ++i)
-      hw[i * racer::kXcds + x] = i < w.die_list[x].size() ? w.die_list[x][i] : racer::AttnWork{racer::kNoWork, 0};
+      hw[i * n_dies + x] = i < w.die_list[x].size() ? w.die_list[x][i] : racer::AttnWork{racer::kNoWork, 0};
   if (!by_argument) {
     HIP_TRY(hipMemcpyAsync(p->hl_dev, hbuf, total, hipMemcpyHostToDevice, stream));
     if ((rc = p->hstage.mark(which, stream))) return rc;
@@ -967,14 +966,12 @@ int32_t prepare_step(racer_pool* p, racer_hstu* m, const racer_hstu_req* reqs, u
   sl.reqs = reinterpret_cast<const racer::ReqDev*>(p->hl_dev + off_reqs);
   sl.ts_marks = p->ts_marks;
   sl.epoch = p->step_epoch;
-  sl.row_req = reinterpret_cast<const uint32_t*>(p->hl_dev + off_rows);
   sl.items = reinterpret_cast<const racer::AttnItem*>(p->hl_dev + off_items);
   sl.groups = reinterpret_cast<const racer::AttnGroup*>(p->hl_dev + off_groups);
   sl.partials = reinterpret_cast<float*>(p->hp_dev);
   sl.work = reinterpret_cast<const racer::AttnWork*>(p->hl_dev + off_work);
   sl.n_work = static_cast<uint32_t>(n_work);
   sl.n_groups = static_cast<uint32_t>(w.groups.size());
-  sl.q_block = q_block;
   sl.row_tiles = reinterpret_cast<const racer::RowTile*>(p->hl_dev + off_row_tiles);
   sl.n_row_tiles = static_cast<uint32_t>(w.row_tiles.size());
   sl.group_req = reinterpret_cast<const uint32_t*>(p->hl_dev + off_group_req);
@@ -1043,6 +1040,24 @@ int32_t hstu_step(racer_pool_t* p, racer_hstu_t* m, const racer_hstu_req* reqs, 
     const float* b2 = static_cast<const float*>(m->w.b2) + l * d;
     const uint8_t* w1 = static_cast<const uint8_t*>(bf16 ? m->w1t : m->w.w1) + l * w1_layer;
     const uint8_t* w2 = static_cast<const uint8_t*>(bf16 ? m->w2t : m->w.w2) + l * w2_layer;
+    if (!bf16) {
+      auto f = [](const void* v) { return static_cast<const float*>(v); };
+      auto fw = [](void* v) { return static_cast<float*>(v); };
+      {
+        ProfScope t(p, RACER_PROF_GEMM_FRONT, stream);
+        HIP_TRY(racer::launch_layer_half_f32(ctx.hd, l, true, f(x_cur), nullptr, ln1_g, ln1_b, f(w1), b1, fw(u), fw(q), ctx.kv, sl,
+                                             page_tables, nullptr, nullptr, stream));
+      }
+      {
+        ProfScope t(p, RACER_PROF_ATTENTION, stream);
+        HIP_TRY(racer::launch_attention_f32(ctx.hd, l, f(q), f(m->w.pos), f(m->w.time), ctx.kv, sl, page_tables, ts, fw(o), stream));
+      }
+      ProfScope t(p, RACER_PROF_GEMM_BACK, stream);
+      HIP_TRY(racer::launch_layer_half_f32(ctx.hd, l, false, f(o), f(u), ln2_g, ln2_b, f(w2), b2, nullptr, nullptr, ctx.kv, sl, page_tables,
+                                           f(x_cur), fw(x_next), stream));
+      x_cur = x_next;
+      continue;
+    }
     if (ctx.fused) {
       ProfScope t(p, RACER_PROF_GEMM_FRONT, stream);
       HIP_TRY(racer::launch_layer_front_fused(ctx.hd, l, x_cur, ln1_g, ln1_b, w1, b1, u, q, ctx.kv, sl, page_tables, stream));
@@ -1056,13 +1071,11 @@ int32_t hstu_step(racer_pool_t* p, racer_hstu_t* m, const racer_hstu_req* reqs, 
     }
     {
       ProfScope t(p, RACER_PROF_ATTENTION, stream);
-      HIP_TRY(racer::launch_attention(ctx.hd, l, q, bf16 ? m->pos_s : static_cast<const float*>(m->w.pos),
-                                      bf16 ? m->time_s : static_cast<const float*>(m->w.time), ctx.kv, sl,
-                                      page_tables, ts, o, /*o_half=*/bf16, stream));
+      HIP_TRY(racer::launch_attention(ctx.hd, l, q, m->pos_s, m->time_s, ctx.kv, sl, page_tables, ts, o, /*o_half=*/true, stream));
     }
     if (sl.n_groups) {
       ProfScope t(p, RACER_PROF_ATTN_REDUCE, stream);
-      HIP_TRY(racer::launch_attention_reduce(ctx.hd, sl, o, /*o_half=*/bf16, stream));
+      HIP_TRY(racer::launch_attention_reduce(ctx.hd, sl, o, /*o_half=*/true, stream));
     }
     if (ctx.fused) {
       ProfScope t(p, RACER_PROF_GEMM_BACK, stream);
@@ -1101,10 +1114,11 @@ int32_t hstu_attn_paged(racer_pool_t* p, racer_hstu_t* m, uint32_t layer, const 
   }
   {
     ProfScope t(p, RACER_PROF_ATTENTION, stream);
-    const bool bf16 = m->cfg.elem == RACER_ELEM_BF16;
-    HIP_TRY(racer::launch_attention(ctx.hd, layer, q, bf16 ? m->pos_s : static_cast<const float*>(m->w.pos),
-                                    bf16 ? m->time_s : static_cast<const float*>(m->w.time), ctx.kv, ctx.sl,
-                                    page_tables, ts, o, /*o_half=*/false, stream));
+    if (m->cfg.elem == RACER_ELEM_BF16)
+      HIP_TRY(racer::launch_attention(ctx.hd, layer, q, m->pos_s, m->time_s, ctx.kv, ctx.sl, page_tables, ts, o, /*o_half=*/false, stream));
+    else
+      HIP_TRY(racer::launch_attention_f32(ctx.hd, layer, static_cast<const float*>(q), static_cast<const float*>(m->w.pos),
+                                          static_cast<const float*>(m->w.time), ctx.kv, ctx.sl, page_tables, ts, static_cast<float*>(o), stream));
   }
   if (ctx.sl.n_groups) {
     ProfScope t(p, RACER_PROF_ATTN_REDUCE, stream);

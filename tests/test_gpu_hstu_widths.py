@@ -1,0 +1,27 @@
+"""GPU parity of hstu_step over model widths: fp32 models whose heads are not a multiple of four or 16 wide and whose rows do
+not fill a wavefront or a block, bf16 models whose layer halves are fused (64 .. 512) and not (192)."""
+import numpy as np
+import pytest
+
+from tests.test_gpu_hstu import Case, assert_close
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("bf16,d,H,pt", [
+    (False, 16, 1, 4), (False, 48, 16, 8), (False, 48, 3, 5), (False, 128, 2, 16), (False, 1024, 16, 16),
+    (True, 64, 1, 16), (True, 192, 3, 16), (True, 256, 4, 16), (True, 512, 8, 16),
+])
+def test_two_steps_with_ragged_lengths(bf16, d, H, pt):
+    first, more = [1, 15, 0, 33, 70], [16, 3, 17, 1, 90]
+    c = Case(21, 2, d, H, pt, bf16, 100, 16, 160.0, 128)
+    reqs, pts, ts, x = c.inputs([0] * 5, [a + b for a, b in zip(first, more)])
+    o1, o2 = np.concatenate([[0], np.cumsum(first)]), np.concatenate([[0], np.cumsum(more)])
+    one = [(0, a, r[2], r[3], int(o)) for a, r, o in zip(first, reqs, o1)]
+    two = [(a, b, r[2], r[3], int(o)) for a, b, r, o in zip(first, more, reqs, o2)]
+    xa = np.concatenate([x[r[4]: r[4] + a] for a, r in zip(first, reqs)])
+    xb = np.concatenate([x[r[4] + a: r[4] + a + b] for a, b, r in zip(first, more, reqs)])
+    assert_close(c.run_gpu(one, pts, ts, xa), c.run_oracle(one, pts, ts, xa), bf16, "width %d, step 1" % d)
+    assert_close(c.run_gpu(two, pts, ts, xb), c.run_oracle(two, pts, ts, xb), bf16, "width %d, step 2" % d)
+    assert c.pool.stats()["bad_pages"] == 0
+    c.close()

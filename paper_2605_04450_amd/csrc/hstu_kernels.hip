@@ -33,6 +33,7 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));  // like uint4, but a value that stays in registers
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ float bf2f(uint16_t b) { return __uint_as_float(static_cast<uint32_t>(b) << 16); }
 __device__ __forceinline__ uint16_t f2bf(float f) {
@@ -343,8 +344,12 @@ __global__ __launch_bounds__(256) void gemm_front_bf16(HstuDims hd, uint32_t lay
 // lane-coalesced 2-byte stores.
 // A tile's weights are fetched while the tile before it is multiplied, and waited for just before that tile's results
 // are stored: the wait (which counts loads and stores in issue order) then never covers stores just issued.
-// A block sweeps n_cb column tiles: all of them when there are rows enough to fill the chip, else the columns
-// are cut too, down to one tile a block (the launchers' rule).
+// A block sweeps all column tiles when there are rows enough to fill the chip, else the columns are cut too, down to one
+// tile a block (the launcher's rule).
+// What bounds it, d = 256, 130 432 rows: 0.31 GB leave the front half, and vector (43% of its cycles), matrix (26%) and
+// LDS (31%) work share the rest of the time: 126 us with three blocks per CU and the rows in uneven rounds, 118 with
+// four, which 40 KB of LDS and 128 registers allow (back half 68 -> 63 us); 145 000 rows, where the last round was
+// nearly empty: 140 -> 126 us and 70 -> 67.
 // ---------------------------------------------------------------------------------------
 struct LayerHalfArgs {
   HstuDims hd;
@@ -364,7 +369,9 @@ struct LayerHalfArgs {
   const int32_t* page_tables;
   const uint16_t* resid;   // BACK: X
   uint16_t* y;             // BACK output
-  uint32_t n_cb;           // 32-column tiles one block sweeps
+  // Row tiles [0, rows0) in blocks of cb0 32-column tiles each (one or two column ranges), then rows1 more in blocks of
+  // cb1; the ranges of a row tile lie rows0 (rows1) blocks apart, and rows1_inv = 2^31 / rows1, rounded up
+  uint32_t rows0, cb0, blocks0, rows1, cb1, rows1_inv;
 };
 
 __device__ __forceinline__ uint32_t pack2_bf16(float lo, float hi) {
@@ -437,21 +444,18 @@ __device__ __forceinline__ void unrolled(F f) {
   unrolled(std::make_integer_sequence<int, N>{}, f);
 }
 
-constexpr uint32_t kMaxSweep = 1024;  // output columns a block sweeps at most
+constexpr uint32_t kMaxSweep = 1024;  // output columns a block sweeps at most (a layer half has at most twice as many)
 
 template <int KD, bool FRONT, int WPB>
-__global__ __launch_bounds__(64 * WPB, KD <= 256 ? 3 : 2) void layer_half_fused(LayerHalfArgs a) {
+__global__ __launch_bounds__(64 * WPB, KD <= 256 ? 4 : 2) void layer_half_fused(LayerHalfArgs a) {
   constexpr int kSt = KD / 16;        // MFMA steps over the contraction
   constexpr int kPieces = KD / 64;    // 64-column pieces of a row
   constexpr int kTileBytes = kSt * 1024;
   constexpr int kCopies = kSt / WPB;  // 1 KB copies of a weight tile per wavefront
   static_assert(kSt % WPB == 0 && KD % 64 == 0, "a weight tile must split evenly over the block");
   constexpr int kStageBytes = WPB * 4096;        // row dealing: 32 rows of 128 bytes per wavefront
-  // The output tile of a wavefront: 32 tokens x 32 16-bit features (FRONT) or fp32 ones, 16 at a time where the whole
-  // would keep a second block from the CU (BACK, KD = 512); rows padded by 16 bytes.
-  constexpr int kOutParts = !FRONT && KD > 256 ? 2 : 1;
-  constexpr int kOutRow = (FRONT ? 64 : 128 / kOutParts) + 16;  // bytes
-  constexpr int kOutBytes = WPB * 32 * kOutRow;
+  constexpr uint32_t kOutTok = KD == 256 ? 16 : 32;  // tokens in a wavefront's output tile: with all 32 the fourth block would not fit the CU
+  constexpr int kOutBytes = WPB * kOutTok * 64;
   constexpr bool kStageInTile = kTileBytes >= kStageBytes;  // the dealing happens in the second weight buffer, else in the output tiles
   __shared__ __attribute__((aligned(16))) uint8_t wtile[2][kTileBytes];
   __shared__ __attribute__((aligned(16))) uint8_t otile[(kStageInTile ? 0 : kStageBytes) > kOutBytes ? kStageBytes : kOutBytes];
@@ -462,9 +466,13 @@ __global__ __launch_bounds__(64 * WPB, KD <= 256 ? 3 : 2) void layer_half_fused(
   float* lnp = kStageInTile ? reinterpret_cast<float*>(&otile[0]) : lnp_own;
   const uint32_t tid = threadIdx.x, lane = tid & 63, g = lane >> 5, li = lane & 31;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const uint32_t r0 = (blockIdx.x * WPB + wave) * 32;  // this wavefront's first row
+  const bool rest = blockIdx.x >= a.blocks0;
+  const uint32_t bx = rest ? blockIdx.x - a.blocks0 : blockIdx.x;
+  const uint32_t col = rest ? static_cast<uint32_t>(static_cast<uint64_t>(bx) * a.rows1_inv >> 31) : (bx >= a.rows0 ? 1 : 0);
+  const uint32_t n_cb = rest ? a.cb1 : a.cb0, cb0 = col * n_cb;
+  const uint32_t tile = rest ? a.rows0 + bx - col * a.rows1 : bx - col * a.rows0;
+  const uint32_t r0 = (tile * WPB + wave) * 32;  // this wavefront's first row
   const HstuDims& hd = a.hd;
-  const uint32_t cb0 = blockIdx.y * a.n_cb, n_cb = a.n_cb;
 
   const uint32_t wlds = __builtin_amdgcn_readfirstlane(lds_address(&wtile[0][0])) + wave * (kCopies * 1024);
   auto fetch_w = [&](uint32_t cb, uint32_t buf) {
@@ -508,11 +516,10 @@ __global__ __launch_bounds__(64 * WPB, KD <= 256 ? 3 : 2) void layer_half_fused(
     fetch_w(cb0, 0);
     unrolled<kPieces>([&](auto p) { deal_piece(raw[p], xr, std::integral_constant<int, 4 * p>{}); });
   }
-  u32x4 gate0[4], gate1[4];  // BACK: the gate rows follow two pieces at a time
-  if constexpr (!FRONT) {
-    issue_piece(a.gate, 0, gate0);
-    if (kPieces > 1) issue_piece(a.gate, 1, gate1);
-  }
+  // BACK: the gate rows follow, a piece or two ahead of their use (what the registers of the block count above allow)
+  constexpr int kGates = KD == 256 ? 1 : kPieces < 2 ? 1 : 2;
+  u32x4 gate[kGates][4];
+  if constexpr (!FRONT) unrolled<kGates>([&](auto p) { issue_piece(a.gate, p, gate[p]); });
   for (uint32_t i = tid; i < KD; i += 64 * WPB) {
     lnp[i] = a.ln_g[i];
     lnp[KD + i] = a.ln_b[i];
@@ -530,7 +537,7 @@ __global__ __launch_bounds__(64 * WPB, KD <= 256 ? 3 : 2) void layer_half_fused(
     split_token(hd, rq.prefix_len + (row - rq.x_off), &pi, &tok);
     const int32_t page = a.page_tables[rq.page_table_off + pi];
     if (page < 0 || static_cast<uint32_t>(page) >= a.kv.n_pages) {
-      if (blockIdx.y == 0 && g == 0) atomicAdd(&a.kv.counters[ctr_index(kCtrBadPages)], 1ull);
+      if (col == 0 && g == 0) atomicAdd(&a.kv.counters[ctr_index(kCtrBadPages)], 1ull);
     } else {
       page_ptr = a.kv.base + static_cast<uint64_t>(page) * a.kv.page_size;
     }
@@ -562,13 +569,8 @@ __global__ __launch_bounds__(64 * WPB, KD <= 256 ? 3 : 2) void layer_half_fused(
     unrolled<kPieces>([&](auto p) {
       u32x4 gr[4];
       if constexpr (!FRONT) {
-        if constexpr (p % 2 == 1) {
-          deal_piece(gate1, gr, std::integral_constant<int, 0>{});
-          if (p + 2 < kPieces) issue_piece(a.gate, p + 2, gate1);
-        } else {
-          deal_piece(gate0, gr, std::integral_constant<int, 0>{});
-          if (p + 2 < kPieces) issue_piece(a.gate, p + 2, gate0);
-        }
+        deal_piece(gate[p % kGates], gr, std::integral_constant<int, 0>{});
+        if (p + kGates < kPieces) issue_piece(a.gate, p + kGates, gate[p % kGates]);
       }
       unrolled<4>([&](auto s2) {
         constexpr int st = 4 * p + s2;
@@ -593,32 +595,41 @@ __global__ __launch_bounds__(64 * WPB, KD <= 256 ? 3 : 2) void layer_half_fused(
     });
   }
 
-  // Row-major outputs leave through a wave-private LDS tile that turns "one token, four runs of four
-  // features per lane" into 16-byte pieces: lane l then stores features 8 (l % 4) .. + 8 of the tokens
-  // l / 4 and l / 4 + 16 of its wavefront, so four lanes cover 64 contiguous bytes of a row (with the tile in two
-  // parts: features 8 (l % 2) of token l / 2, then the same of the other 16 features).
-  constexpr int kStores = 2;
-  auto store_row = [&](int h2) { return kOutParts == 1 ? (lane >> 2) + 16 * h2 : lane >> 1; };
-  auto store_col = [&](int h2) { return kOutParts == 1 ? lane & 3 : (lane & 1) + 2 * h2; };
-  bool ok2[2];
-  uint64_t row2[2];
-  uint8_t* kdst2[2] = {nullptr, nullptr};  // FRONT: K row of the token inside its page, before the head offset
+  // Row-major outputs leave through a wave-private LDS tile that turns "one token, four runs of four features per lane"
+  // into 16-byte pieces, kOutTok tokens at a time: lane l stores features 8 (l % 4) .. + 8 of tokens l / 4 and l / 4 + 16,
+  // so four lanes cover 64 contiguous bytes of a row (32 bytes: 4% slower).  Chunk c of row r sits at c ^ (r / 4 mod 4),
+  // so that the rows' 64 bytes cover all banks.
+  const uint32_t st_row = lane >> 2, st_col = lane & 3;
+  const bool st_ok[2] = {r0 + st_row < a.n_rows, r0 + st_row + 16 < a.n_rows};
+  const uint64_t st_off = static_cast<uint64_t>(r0 + st_row) * KD + 8 * st_col;
+  uint8_t* kdst[2] = {nullptr, nullptr};  // FRONT: this lane's 16 bytes of the tokens' K rows inside their pages, before the head's offset
+  if (FRONT) {
 #pragma unroll
-  for (int h2 = 0; h2 < 2; ++h2) {
-    const uint32_t rl = store_row(h2);
-    ok2[h2] = r0 + rl < a.n_rows;
-    row2[h2] = ok2[h2] ? r0 + rl : 0;
-    if (FRONT) {
-      const uint64_t mine = reinterpret_cast<uint64_t>(page_ptr);
-      const uint32_t lo = __shfl(static_cast<uint32_t>(mine), rl, 64), hi = __shfl(static_cast<uint32_t>(mine >> 32), rl, 64);
+    for (int h2 = 0; h2 < 2; ++h2) {
+      const uint64_t own = reinterpret_cast<uint64_t>(page_ptr);
+      const uint32_t rl = st_row + 16 * h2;
+      const uint32_t lo = __shfl(static_cast<uint32_t>(own), rl, 64), hi = __shfl(static_cast<uint32_t>(own >> 32), rl, 64);
       const uint32_t tk = __shfl(tok, rl, 64);
       const uint64_t pp = (static_cast<uint64_t>(hi) << 32) | lo;
-      if (pp) kdst2[h2] = reinterpret_cast<uint8_t*>(pp) + static_cast<uint64_t>(tk) * 128;
+      if (pp) kdst[h2] = reinterpret_cast<uint8_t*>(pp) + tk * 128 + 16 * st_col;
     }
   }
-  uint8_t* ot = &otile[0] + wave * (32 * kOutRow);
+  uint8_t* ot = &otile[0] + wave * (kOutTok * 64);
+  auto transposed = [&](const u32x2 (&run)[4], u32x4 (&v)[2]) {  // run[k]: this lane's features 8 k + 4 g .. + 4 of its token
+#pragma unroll
+    for (uint32_t h2 = 0; h2 < 2; ++h2) {
+      if (kOutTok == 32 ? h2 == 0 : li >> 4 == h2) {
+#pragma unroll
+        for (uint32_t r4 = 0; r4 < 4; ++r4)
+          *reinterpret_cast<u32x2*>(ot + (li % kOutTok) * 64 + 16 * (r4 ^ ((li >> 2) & 3)) + 8 * g) = run[r4];
+      }
+      v[h2] = *reinterpret_cast<const u32x4*>(ot + (st_row + (kOutTok - 16) * h2) * 64 + 16 * (st_col ^ ((st_row >> 2) & 3)));
+      asm volatile("" : "+v"(v[h2]));  // all lanes have read before any lane goes on to write the next part
+    }
+  };
 
   // ---- sweep over the output columns ----------------------------------------------------------
+  const uint64_t own_off = static_cast<uint64_t>(row_ok ? r0 + li : 0) * KD + 4 * g;  // BACK: the lane's first residual run
   wait_vm<0>();
   for (uint32_t k = 0; k < n_cb; ++k) {
     const uint32_t cb = cb0 + k, n0 = cb * 32;
@@ -628,10 +639,10 @@ __global__ __launch_bounds__(64 * WPB, KD <= 256 ? 3 : 2) void layer_half_fused(
       wait_vm<0>();
       continue;
     }
-    u32x4 res[2];  // BACK: the residual pieces this lane adds at its two stores
+    u32x2 res[4];  // BACK: the residual of this lane's token, four runs of four features
     if (!FRONT) {
 #pragma unroll
-      for (int h2 = 0; h2 < 2; ++h2) res[h2] = *reinterpret_cast<const u32x4*>(a.resid + row2[h2] * KD + n0 + 8 * store_col(h2));
+      for (int r4 = 0; r4 < 4; ++r4) res[r4] = *reinterpret_cast<const u32x2*>(a.resid + own_off + n0 + 8 * r4);
     }
     f32x16 acc;
     // acc[e]: feature n0 + 8*(e/4) + 4*g + e%4 of this lane's token; the bias is the starting value
@@ -664,49 +675,41 @@ __global__ __launch_bounds__(64 * WPB, KD <= 256 ? 3 : 2) void layer_half_fused(
         continue;
       }
       const float sc = which == 2 ? 1.4426950408889634f : 1.0f;  // the attention kernel wants q * log2(e)
+      u32x2 run[4];
 #pragma unroll
       for (int r4 = 0; r4 < 4; ++r4)
-        *reinterpret_cast<uint2*>(ot + li * kOutRow + 16 * r4 + 8 * g) =
-            which == 0  // U is the library's own (half precision); Q and K are bf16
-                ? make_uint2(pack2_f16(z[4 * r4], z[4 * r4 + 1]), pack2_f16(z[4 * r4 + 2], z[4 * r4 + 3]))
-                : make_uint2(pack2_bf16(z[4 * r4] * sc, z[4 * r4 + 1] * sc), pack2_bf16(z[4 * r4 + 2] * sc, z[4 * r4 + 3] * sc));
-      u32x4 v2[2];
-#pragma unroll
-      for (int h2 = 0; h2 < 2; ++h2) v2[h2] = *reinterpret_cast<const u32x4*>(ot + ((lane >> 2) + 16 * h2) * kOutRow + 16 * (lane & 3));
+        run[r4] = which == 0  // U is the library's own (half precision); Q and K are bf16
+                      ? u32x2{pack2_f16(z[4 * r4], z[4 * r4 + 1]), pack2_f16(z[4 * r4 + 2], z[4 * r4 + 3])}
+                      : u32x2{pack2_bf16(z[4 * r4] * sc, z[4 * r4 + 1] * sc), pack2_bf16(z[4 * r4 + 2] * sc, z[4 * r4 + 3] * sc)};
+      u32x4 v[2];
+      transposed(run, v);
       wait_vm<0>();
 #pragma unroll
       for (int h2 = 0; h2 < 2; ++h2) {
         if (which == 3) {  // K block [token][64]
-          if (kdst2[h2])
-            *reinterpret_cast<u32x4*>(kdst2[h2] + kv_block_offset(hd, a.layer, 0, c0 / 64, 2) + (c0 % 64 + 8 * (lane & 3)) * 2) = v2[h2];
-        } else if (ok2[h2]) {
-          *reinterpret_cast<u32x4*>((which == 0 ? a.u : a.q) + row2[h2] * KD + c0 + 8 * (lane & 3)) = v2[h2];
+          if (kdst[h2]) *reinterpret_cast<u32x4*>(kdst[h2] + kv_block_offset(hd, a.layer, 0, c0 / 64, 2) + (c0 % 64) * 2) = v[h2];
+        } else if (st_ok[h2]) {
+          *reinterpret_cast<u32x4*>((which == 0 ? a.u : a.q) + st_off + 16 * KD * h2 + c0) = v[h2];
         }
       }
     } else {
-      // a store takes 8 features of a token: four lanes a row, or two with half the features at a time
-      wait_vm<0>();
-      unrolled<kOutParts>([&](auto part) {
-        constexpr int kRuns = 4 / kOutParts;  // runs of four features per lane and part
+      u32x2 run[4];
 #pragma unroll
-        for (int r4 = 0; r4 < kRuns; ++r4)
-          *reinterpret_cast<f32x4*>(ot + li * kOutRow + 32 * r4 + 16 * g) =
-              f32x4{acc[4 * (kRuns * part + r4)], acc[4 * (kRuns * part + r4) + 1], acc[4 * (kRuns * part + r4) + 2], acc[4 * (kRuns * part + r4) + 3]};
+      for (int r4 = 0; r4 < 4; ++r4) {
+        float y[4];
 #pragma unroll
-        for (int h2 = 0; h2 < kStores / kOutParts; ++h2) {
-          constexpr int at0 = part * (kStores / kOutParts);
-          const uint8_t* src = ot + store_row(at0 + h2) * kOutRow + 32 * (store_col(at0 + h2) % (4 / kOutParts));
-          f32x4 p0 = *reinterpret_cast<const f32x4*>(src), p1 = *reinterpret_cast<const f32x4*>(src + 16);
-          // all lanes have read before any lane goes on to write the next part: the reads must not sink into the branch
-          asm volatile("" : "+v"(p0), "+v"(p1));
-          if (!ok2[at0 + h2]) continue;
-          float xv[8];
-          unpack8(res[at0 + h2], xv);
-          *reinterpret_cast<u32x4*>(a.y + row2[at0 + h2] * KD + n0 + 8 * store_col(at0 + h2)) =
-              u32x4{pack2_bf16(xv[0] + p0.x, xv[1] + p0.y), pack2_bf16(xv[2] + p0.z, xv[3] + p0.w),
-                    pack2_bf16(xv[4] + p1.x, xv[5] + p1.y), pack2_bf16(xv[6] + p1.z, xv[7] + p1.w)};
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t w = res[r4][e >> 1];
+          y[e] = __uint_as_float(e & 1 ? w & 0xFFFF0000u : w << 16) + acc[4 * r4 + e];
         }
-      });
+        run[r4] = u32x2{pack2_bf16(y[0], y[1]), pack2_bf16(y[2], y[3])};
+      }
+      u32x4 v[2];
+      transposed(run, v);
+      wait_vm<0>();
+#pragma unroll
+      for (int h2 = 0; h2 < 2; ++h2)
+        if (st_ok[h2]) *reinterpret_cast<u32x4*>(a.y + st_off + 16 * KD * h2 + n0) = v[h2];
     }
   }
 }
@@ -1333,20 +1336,24 @@ hipError_t launch_layernorm(const HstuDims& hd, const void* x, const float* g, c
 
 bool layer_halves_fused(const HstuDims& hd) { return hd.elem == 1 && (hd.d == 64 || hd.d == 128 || hd.d == 256 || hd.d == 512); }
 
-// How many column tiles a block of a layer half sweeps: all of them if the row tiles alone give every CU two blocks
-// (the rows are then read and normalised once), else the sweep is halved until they do, down to one tile.
-static uint32_t tiles_per_block(uint32_t row_tiles, uint32_t col_tiles) {
-  uint32_t splits = col_tiles > kMaxSweep / 32 ? col_tiles / (kMaxSweep / 32) : 1;
-  while (splits < col_tiles && row_tiles * splits < 512) splits *= 2;
-  return col_tiles / splits;
-}
-
+// How many column tiles a block of a layer half sweeps: all of them (kMaxSweep at most) as long as the row tiles fill the
+// chip's block slots (the rows are then read and normalised once), and fewer for the row tiles that are left over for a
+// last, partial round, so that this round is short and reaches every CU: the sweep is halved until there are 512 blocks,
+// down to one tile.  (Row tiles that fill no round are all left over.)
 template <bool FRONT>
 static hipError_t launch_layer_half(LayerHalfArgs& a, uint32_t col_tiles, hipStream_t stream) {
   constexpr uint32_t kRows = 128;  // per block
   const uint32_t row_tiles = (a.n_rows + kRows - 1) / kRows;
-  a.n_cb = tiles_per_block(row_tiles, col_tiles);
-  const dim3 grid(row_tiles, col_tiles / a.n_cb), block(256);
+  const uint32_t slots = 256 * (a.hd.d <= 256 ? 4 : 2);
+  uint32_t splits = col_tiles > kMaxSweep / 32 ? 2 : 1;
+  a.cb0 = col_tiles / splits;
+  a.rows1 = row_tiles % (slots / splits);
+  a.rows0 = row_tiles - a.rows1;
+  a.blocks0 = a.rows0 * splits;
+  while (splits < col_tiles && a.rows1 * splits < 512) splits *= 2;
+  a.cb1 = col_tiles / splits;
+  a.rows1_inv = a.rows1 ? (0x80000000u + a.rows1 - 1) / a.rows1 : 0;  // (exact quotients: rows1 < 1024, splits <= 64)
+  const dim3 grid(a.blocks0 + a.rows1 * splits), block(256);
   switch (a.hd.d) {
     case 64: hipLaunchKernelGGL((layer_half_fused<64, FRONT, 4>), grid, block, 0, stream, a); break;
     case 128: hipLaunchKernelGGL((layer_half_fused<128, FRONT, 4>), grid, block, 0, stream, a); break;

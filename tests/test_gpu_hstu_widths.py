@@ -25,3 +25,23 @@ def test_two_steps_with_ragged_lengths(bf16, d, H, pt):
     assert_close(c.run_gpu(two, pts, ts, xb), c.run_oracle(two, pts, ts, xb), bf16, "width %d, step 2" % d)
     assert c.pool.stats()["bad_pages"] == 0
     c.close()
+
+
+@pytest.mark.parametrize("d,rounds,rest", [(64, 131072, 1), (256, 131072, 5000), (512, 32768, 130), (512, 32768, 31000)])
+def test_more_rows_than_one_round_of_blocks(d, rounds, rest):
+    """Whole rounds of row tiles keep their columns together, the rest is cut: every copy of one request gets the same rows."""
+    T = 64
+    n = (rounds + rest + T - 1) // T
+    new = [T] * n
+    new[-1] = rounds + rest - T * (n - 1)
+    c = Case(22, 1, d, d // 64, 16, True, 100, 16, 64.0, (n * 6 + 31) // 32 * 32)
+    reqs, pts, ts, x = c.inputs([0] * n, new)
+    for r in reqs:
+        ts[r[3]:r[3] + r[1]] = ts[:r[1]]
+        x[r[4]:r[4] + r[1]] = x[:r[1]]
+    got = c.run_gpu(reqs, pts, ts, x)
+    ref = c.run_oracle(reqs[:1], pts, ts, x[:T])
+    assert_close(got[:T], ref, True, "first copy")
+    for r in reqs[1:]:
+        assert np.array_equal(got[r[4]:r[4] + r[1]], got[:r[1]]), r
+    c.close()

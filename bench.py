@@ -951,8 +951,7 @@ def main():
     ap.add_argument("--no-embheavy", action="store_true",
                     help="leave out the EMB-heavy lookups-only pass (the gather against HBM proper) that the default run appends")
     ap.add_argument("--one-pipeline", action="store_true",
-                    help="run the throughput pass as one pipeline as well (per-kernel events on): every kernel launch "
-                         "then covers the whole batch, which is what a per-kernel profile of the run needs")
+                    help="run the throughput pass with per-kernel events on as well")
     ap.add_argument("--copy-calib-mb", type=int, default=0,
                     help="after the timed region, run one plain device copy of this many MiB (a kernel of known "
                          "traffic against which HBM byte counters of a profiler run are scaled)")
@@ -1058,9 +1057,8 @@ def main():
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": "bf16" if c["bf16"] else "f32", "data": "synthetic",
         "ms_per_step_with_kernel_events": dt_events * 1e3 / args.steps,
-        "passes": {"throughput": "K steps as the library runs them (a batch of this size: three pipelines on three "
-                                 "streams)" if not args.one_pipeline else "K steps, one pipeline, kernel events on",
-                   "kernels": "the same K steps again as one pipeline with a HIP event before and after every kernel"},
+        "passes": {"throughput": "K steps" if not args.one_pipeline else "K steps, kernel events on",
+                   "kernels": "the same K steps again with a HIP event before and after every kernel"},
         "config": {"workload": c["desc"], "new_tokens_per_step": int(N), "requests": int(c["batch"]),
                    "emb_frac": c["alpha"], "causal_pairs_per_layer": pairs},
         "emb_gather": {"GBps": gather_gbs, "frac_of_hbm_peak": gather_gbs / PEAK_HBM_GBS,

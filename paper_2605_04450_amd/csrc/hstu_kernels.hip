@@ -16,6 +16,7 @@
 //   [layer][K|V][head] blocks of page_tokens*d_h elements;
 //   a K block is [token][d_h]; a V block is stored transposed, [d_h][token], so that the
 //   second product's matrix operand (contraction over keys) is read key-contiguous.
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -1231,13 +1232,15 @@ __global__ __launch_bounds__(256) void attention_reduce(HstuDims hd, const ReqDe
 // Are a request's timestamps non-decreasing?  Block (c, r) looks at tokens 2048 c + 1 .. 2048 (c + 1) of request r
 // (eight per thread, all loads independent).  The first block that finds a decrease marks and counts the request.
 constexpr uint32_t kTsChunk = 2048;
-__device__ __forceinline__ void check_timestamps(const ReqDev* reqs, uint32_t B, uint32_t* __restrict__ marks, uint32_t epoch,
+template <typename GetReq>
+__device__ __forceinline__ void check_timestamps(const GetReq& req, uint32_t B, uint32_t* __restrict__ marks, uint32_t epoch,
                                                  const long long* __restrict__ ts, unsigned long long* __restrict__ counters) {
   for (uint32_t r = blockIdx.y; r < B; r += gridDim.y) {  // (the grid's second dimension stops at 65 535)
-    const uint32_t S = reqs[r].prefix_len + reqs[r].new_len;
+    const ReqDev rq = req(r);
+    const uint32_t S = rq.prefix_len + rq.new_len;
     const uint32_t j0 = blockIdx.x * kTsChunk + 1;
     if (j0 >= S) continue;  // uniform over the block
-    const long long* t = ts + reqs[r].ts_off;
+    const long long* t = ts + rq.ts_off;
     bool bad = false;
 #pragma unroll
     for (uint32_t k = 0; k < kTsChunk / 256; ++k) {
@@ -1249,9 +1252,31 @@ __device__ __forceinline__ void check_timestamps(const ReqDev* reqs, uint32_t B,
     }
   }
 }
-__global__ __launch_bounds__(256) void begin_step(const ReqDev* __restrict__ reqs, uint32_t B, uint32_t* __restrict__ marks, uint32_t epoch,
-                                                  const long long* __restrict__ ts, unsigned long long* __restrict__ counters) {
-  check_timestamps(reqs, B, marks, epoch, ts, counters);
+// The lists (the requests first) lie in pinned host memory: the grid copies them to the device, 16 KB per block and pass
+// with every load in flight, while it checks the timestamps.  A copy command in front of the kernel took 13 us of the
+// stream (64 KB and more; 3.5 for less); the kernel takes the 7 us (128 x 3136 tokens) that it took without the copy: both are
+// bound by one round trip.  (Loads at system scope, one by one, would make it 147 us.  Plain ones see what the host wrote
+// before the launch, and the host waits for the kernel before it writes the buffer again.)
+constexpr uint32_t kCopyAhead = 4;
+__global__ __launch_bounds__(256) void begin_step(const uint4* __restrict__ src, uint4* __restrict__ dst, uint32_t n16, uint32_t B,
+                                                  uint32_t* __restrict__ marks, uint32_t epoch, const long long* __restrict__ ts,
+                                                  unsigned long long* __restrict__ counters) {
+  const uint64_t stride = static_cast<uint64_t>(gridDim.x) * gridDim.y * 256;
+  const uint64_t first = (static_cast<uint64_t>(blockIdx.y) * gridDim.x + blockIdx.x) * 256 + threadIdx.x;
+  for (uint64_t i0 = first; i0 < n16; i0 += kCopyAhead * stride) {
+    uint4 v[kCopyAhead];
+#pragma unroll
+    for (uint32_t k = 0; k < kCopyAhead; ++k) {
+      const uint64_t i = i0 + k * stride;
+      v[k] = i < n16 ? src[i] : make_uint4(0, 0, 0, 0);
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < kCopyAhead; ++k) {
+      const uint64_t i = i0 + k * stride;
+      if (i < n16) dst[i] = v[k];
+    }
+  }
+  if (ts) check_timestamps([&](uint32_t r) { return reinterpret_cast<const ReqDev*>(src)[r]; }, B, marks, epoch, ts, counters);
 }
 // The same for a small step, whose lists (the requests first) come as an argument: no copy engine, no staging buffer to
 // wait for (10 us of host time and 5 us of the stream's a step).
@@ -1259,7 +1284,7 @@ __global__ __launch_bounds__(256) void begin_step_with_lists(ListArg arg, uint4*
                                                              uint32_t* __restrict__ marks, uint32_t epoch,
                                                              const long long* __restrict__ ts, unsigned long long* __restrict__ counters) {
   if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < n16) dst[threadIdx.x] = reinterpret_cast<const uint4*>(arg.bytes)[threadIdx.x];
-  check_timestamps(reinterpret_cast<const ReqDev*>(arg.bytes), B, marks, epoch, ts, counters);
+  if (ts) check_timestamps([&](uint32_t r) { return reinterpret_cast<const ReqDev*>(arg.bytes)[r]; }, B, marks, epoch, ts, counters);
 }
 static_assert(kListArgBytes / 16 <= 256, "one 16-byte word of the lists per thread");
 
@@ -1446,17 +1471,19 @@ hipError_t launch_attention_reduce(const HstuDims& hd, const StepLists& sl, void
 }
 
 hipError_t launch_begin_step(const StepLists& sl, uint32_t max_seq, const int64_t* ts, unsigned long long* counters, const ListArg* arg,
-                             uint8_t* list_dst, uint64_t list_bytes, hipStream_t stream) {
-  if (!arg && max_seq < 2) return hipSuccess;
+                             const uint8_t* pinned, uint8_t* list_dst, uint64_t list_bytes, hipStream_t stream) {
   const uint32_t chunks = max_seq < 2 ? 1 : (max_seq - 1 + kTsChunk - 1) / kTsChunk;
-  const dim3 grid(chunks, sl.B < 65535 ? sl.B : 65535), block(256);
+  // blocks for the copy too, where the requests do not ask for as many
+  const uint64_t copy_rows = arg ? 0 : std::min<uint64_t>(1024, (list_bytes / (256 * 16 * kCopyAhead) + chunks - 1) / chunks);
+  const dim3 grid(chunks, static_cast<uint32_t>(std::max<uint64_t>(copy_rows, std::min<uint32_t>(sl.B, 65535)))), block(256);
   const long long* t = reinterpret_cast<const long long*>(ts);
   uint32_t* marks = const_cast<uint32_t*>(sl.ts_marks);
   if (arg)
     hipLaunchKernelGGL(begin_step_with_lists, grid, block, 0, stream, *arg, reinterpret_cast<uint4*>(list_dst),
                        static_cast<uint32_t>((list_bytes + 15) / 16), sl.B, marks, sl.epoch, t, counters);
   else
-    hipLaunchKernelGGL(begin_step, grid, block, 0, stream, sl.reqs, sl.B, marks, sl.epoch, t, counters);
+    hipLaunchKernelGGL(begin_step, grid, block, 0, stream, reinterpret_cast<const uint4*>(pinned),
+                       reinterpret_cast<uint4*>(list_dst), static_cast<uint32_t>(list_bytes / 16), sl.B, marks, sl.epoch, t, counters);
   return hipGetLastError();
 }
 

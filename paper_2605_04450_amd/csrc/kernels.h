@@ -180,10 +180,10 @@ struct ListArg {
 // Begins a step: one pass over every request's timestamps (max_seq: the longest request's prefix + new tokens); a request
 // whose timestamps decrease somewhere is marked with the step's epoch and counted in kCtrUnorderedTs.  The
 // attention kernels take their 32-bit relative-time paths only for ordered requests (an unordered one gets the general
-// 64-bit gaps, where a negative gap falls into bucket 0).  With `arg` the kernel first writes the lists out of its
-// argument to list_dst (the check then reads the requests there), else they are on the device already.
+// 64-bit gaps, where a negative gap falls into bucket 0).  The kernel also writes the lists (list_bytes, a multiple of 16)
+// to list_dst: out of its argument if there is one, else from pinned host memory.
 hipError_t launch_begin_step(const StepLists& sl, uint32_t max_seq, const int64_t* ts, unsigned long long* counters, const ListArg* arg,
-                             uint8_t* list_dst, uint64_t list_bytes, hipStream_t stream);
+                             const uint8_t* pinned, uint8_t* list_dst, uint64_t list_bytes, hipStream_t stream);
 
 hipError_t launch_layernorm(const HstuDims& hd, const void* x, const float* g, const float* b,
                             const void* gate /*nullable: multiply by gate rows*/, void* y, uint32_t N,

@@ -56,7 +56,7 @@ int32_t dev_alloc(T** p, uint64_t count, bool zero, hipStream_t stream) {
   return RACER_OK;
 }
 
-// Pinned staging that is written by the host and copied to the device asynchronously;
+// Pinned staging that is written by the host and copied to the device (or read by a kernel) asynchronously;
 // two buffers alternate so a call only ever waits for the copy issued two calls earlier.
 struct Staging {
   uint8_t* buf[2] = {nullptr, nullptr};
@@ -78,7 +78,7 @@ struct Staging {
       if (buf[k]) HIP_TRY(hipHostFree(buf[k]));
       buf[k] = nullptr;
       cap[k] = 0;
-      HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&buf[k]), bytes, hipHostMallocDefault));
+      HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&buf[k]), bytes, hipHostMallocCoherent));
       cap[k] = bytes;
       ++allocs;
     }
@@ -97,7 +97,7 @@ struct Staging {
       buf[k] = nullptr;
       cap[k] = 0;
       const uint64_t want = std::max<uint64_t>(bytes * 2, 1 << 16);
-      HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&buf[k]), want, hipHostMallocDefault));
+      HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&buf[k]), want, hipHostMallocCoherent));
       cap[k] = want;
       ++allocs;
     }
@@ -927,7 +927,7 @@ int32_t prepare_step(racer_pool* p, racer_hstu* m, const racer_hstu_req* reqs, u
   const uint64_t off_work = place(sizeof(racer::AttnWork) * n_work);
   if ((rc = ensure_lists(p, total, total * 2)) || (rc = ensure_ts_marks(p, B, stream))) return rc;
   p->step_epoch += 1;
-  // Small lists travel as an argument of the kernel that looks at the timestamps, larger ones through pinned staging.
+  // Small lists travel as an argument of the kernel that begins the step, larger ones it reads from pinned staging.
   const bool by_argument = total <= racer::kListArgBytes;
   racer::ListArg arg;
   uint8_t* hbuf = arg.bytes;
@@ -958,10 +958,6 @@ int32_t prepare_step(racer_pool* p, racer_hstu* m, const racer_hstu_req* reqs, u
   for (uint32_t x = 0; x < n_dies; ++x)
     for (size_t i = 0; i < die_len; ++i)
       hw[i * n_dies + x] = i < w.die_list[x].size() ? w.die_list[x][i] : racer::AttnWork{racer::kNoWork, 0};
-  if (!by_argument) {
-    HIP_TRY(hipMemcpyAsync(p->hl_dev, hbuf, total, hipMemcpyHostToDevice, stream));
-    if ((rc = p->hstage.mark(which, stream))) return rc;
-  }
 
   sl.reqs = reinterpret_cast<const racer::ReqDev*>(p->hl_dev + off_reqs);
   sl.ts_marks = p->ts_marks;
@@ -975,8 +971,9 @@ int32_t prepare_step(racer_pool* p, racer_hstu* m, const racer_hstu_req* reqs, u
   sl.row_tiles = reinterpret_cast<const racer::RowTile*>(p->hl_dev + off_row_tiles);
   sl.n_row_tiles = static_cast<uint32_t>(w.row_tiles.size());
   sl.group_req = reinterpret_cast<const uint32_t*>(p->hl_dev + off_group_req);
-  // which requests' timestamps never decrease (the attention kernels' 32-bit time paths rely on it)
-  if (ts) HIP_TRY(racer::launch_begin_step(sl, longest, ts, p->d_counters, by_argument ? &arg : nullptr, p->hl_dev, total, stream));
+  // the lists to the device, and which requests' timestamps never decrease (the attention kernels' 32-bit time paths rely on it)
+  HIP_TRY(racer::launch_begin_step(sl, longest, ts, p->d_counters, by_argument ? &arg : nullptr, hbuf, p->hl_dev, total, stream));
+  if (!by_argument && (rc = p->hstage.mark(which, stream))) return rc;
   return RACER_OK;
 }
 

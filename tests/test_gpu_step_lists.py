@@ -1,0 +1,26 @@
+"""GPU parity of steps whose work lists are a kernel argument (up to 3 KB) or read from pinned memory: sizes around the border,
+one request with long lists, many requests, each three times in a row with other requests (two buffers take turns)."""
+import numpy as np
+import pytest
+
+from tests.test_gpu_hstu import Case, assert_close
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("bf16,lens", [
+    (True, [5] * 20), (True, [5] * 24), (True, [5] * 28), (True, [5] * 32),  # 2.6 to 4 KB of lists with two heads
+    (True, [3000]), (True, [1] * 700), (False, [1] * 130), (False, [3] * 400),
+])
+def test_lists_by_argument_and_from_pinned_memory(bf16, lens):
+    d, H = (128, 2) if bf16 else (64, 2)
+    rng = np.random.default_rng(len(lens))
+    pages = (3 * (sum(lens) // 16 + 2 * len(lens)) + 31) // 32 * 32 + 32
+    c = Case(31, 1, d, H, 16, bf16, 100, 16, 64.0, pages)
+    batches = [c.inputs([0] * len(lens), [max(1, int(n * f)) for n in lens]) for f in (1.0, 0.7, 0.9)]
+    for reqs, pts, ts, x in batches:
+        s = reqs[rng.integers(len(reqs))]
+        ts[s[3]:s[3] + s[1]] = ts[s[3]:s[3] + s[1]][::-1].copy()  # one request whose timestamps may decrease
+        assert_close(c.run_gpu(reqs, pts, ts, x), c.run_oracle(reqs, pts, ts, x), bf16, "%d requests" % len(lens))
+    assert c.pool.stats()["bad_pages"] == 0
+    c.close()

@@ -162,9 +162,10 @@ int32_t emb_lookup(racer_pool_t* pool, const int64_t* ids, uint64_t n, uint32_t 
  *      about 10 MB, held until the process ends), and the call makes no hipMalloc / hipFree or other
  *      allocating call and creates no events (racer_prof does not see it).  Limits: n <=
  *      RACER_NOALLOC_MAX_LOOKUPS and n * row_bytes <= RACER_NOALLOC_MAX_ROW_BYTES_TOTAL, else RACER_ERANGE
- *      and nothing is done.  Every call on a GPU, whatever its pool, shares that GPU's array: calls that
- *      overlap on one GPU (two streams, two threads) race; calls ordered on one stream, or by the caller's own
- *      events, do not.  Must be called with the pool's GPU current. */
+ *      and nothing is done.  Every call on a GPU, whatever its pool, shares that GPU's array: calls must not
+ *      overlap on one GPU (two streams, two threads), or they clear each other's lists while these are walked, and
+ *      anything may follow, a kernel that never ends included; calls ordered on one stream, or by the caller's own
+ *      events, are safe.  Must be called with the pool's GPU current. */
 #define RACER_NOALLOC_MAX_LOOKUPS 16384ull
 #define RACER_NOALLOC_MAX_ROW_BYTES_TOTAL (8ull << 20)
 int32_t emb_lookup_noalloc(racer_pool_t* pool, const int64_t* ids, uint64_t n, uint32_t bag, void* out,

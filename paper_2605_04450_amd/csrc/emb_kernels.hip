@@ -262,7 +262,6 @@ __global__ __launch_bounds__(256) void emb_probe_gather(EmbView v, MissWs ws, Id
   __shared__ uint32_t s_cnt[3];
   const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (tid < 3) s_n[tid] = s_cnt[tid] = 0;
-  if (blockIdx.x == 0 && tid == 0) *ws.bar = 0;
   __syncthreads();
 
   const uint64_t i0 = (static_cast<uint64_t>(blockIdx.x) * 4 + wave) * lb;
@@ -403,7 +402,6 @@ __global__ __launch_bounds__(256) void emb_probe_gather_w32(EmbView v, MissWs ws
   __shared__ uint32_t s_cnt[3];
   const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, grp = lane >> 3, j = lane & 7;
   if (tid < 3) s_n[tid] = s_cnt[tid] = 0;
-  if (blockIdx.x == 0 && tid == 0) *ws.bar = 0;
   __syncthreads();
   const uint4* tags4 = reinterpret_cast<const uint4*>(v.tags);
   // The dependent memory steps (ids -> tag lines -> rows -> output) are each taken for all rounds at once:
@@ -511,7 +509,6 @@ __global__ __launch_bounds__(256, PASSES == 1 ? 6 : PASSES == 2 ? 5 : 4) void em
   __shared__ __attribute__((aligned(16))) uint32_t s_rows[4][8][kRowWords];
   const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, grp = lane >> 3, j = lane & 7;
   if (tid < 3) s_n[tid] = s_cnt[tid] = 0;
-  if (blockIdx.x == 0 && tid == 0) *ws.bar = 0;
   __syncthreads();
   const uint4* tags4 = reinterpret_cast<const uint4*>(v.tags);
   const bool bf16 = v.elem == 1;
@@ -644,12 +641,15 @@ __global__ __launch_bounds__(256, PASSES == 1 ? 6 : PASSES == 2 ? 5 : 4) void em
 
 // ---------------------------------------------------------------------------------------
 // Behind the probe: which way each new id takes (settle), the output rows that waited (gather), and the new tags and
-// stamps (apply).  A set's victim candidates are fixed once the probe has stamped the hits, so every new id works out
-// its own rank among the set's new ids and takes the candidate of that rank; tags are written only after all of them
-// have been read.  Units of work are quarters of a probe block's stretch of the lists; everything returns at once
-// when the batch had no miss.
+// stamps.  A set's victim candidates are fixed once the probe has stamped the hits; its new ids take them in the order
+// of their first lookups.  No block waits for another one: either every new id works out its own rank among its set's new
+// ids, and the tags are written by a second kernel, when all of them have been read (apply); or, in batches of few
+// stretches, where a launch costs as much as its work, one half wavefront settles all new ids of a set, tags included,
+// which nobody else then reads or writes.  Units of work are parts of a probe block's stretch of the lists; everything
+// returns at once when the batch had no miss.
 // ---------------------------------------------------------------------------------------
 constexpr uint32_t kQuarter = 16;  // new ids a wavefront takes at a time
+constexpr uint32_t kFew = 4;       // the same in batches of few stretches
 
 __device__ __forceinline__ uint32_t nth_bit(uint32_t m, uint32_t k) {  // position of the k-th set bit
   for (; k; --k) m &= m - 1;
@@ -657,6 +657,10 @@ __device__ __forceinline__ uint32_t nth_bit(uint32_t m, uint32_t k) {  // positi
 }
 
 struct SettleCounts { uint32_t unique, inserted, evicted, bypassed; };
+
+__device__ __forceinline__ uint32_t first_lookup(const MissWs& ws, uint32_t slot) {  // of the id in a dedupe slot
+  return 0xFFFFFFFFu - static_cast<uint32_t>(ws.hents[slot].val);
+}
 
 // New ids [w0, w0 + 16) of stretch `seg`, by one wavefront.  With REFILL only empty ways are candidates (a refill
 // never evicts), only insertions are counted, and an id that enters the cache is fetched from the host table here.
@@ -672,12 +676,12 @@ __device__ __forceinline__ void settle_quarter(const EmbView& v, const MissWs& w
   uint32_t rank = 0;
   if (lane < here) {
     rec = ws.rec[u0 + lane];
-    const uint32_t my_i = 0xFFFFFFFFu - static_cast<uint32_t>(ws.hents[rec.w].val);
+    const uint32_t my_i = first_lookup(ws, rec.w);
     uint32_t cur = static_cast<uint32_t>(ws.heads[mix32(rec.y) & ws.headmask]);
     while (cur != kEmpty) {
       const uint4 r = ws.rec[cur];
       if (r.y == rec.y && cur != u0 + lane)
-        rank += (0xFFFFFFFFu - static_cast<uint32_t>(ws.hents[r.w].val)) < my_i ? 1u : 0u;
+        rank += first_lookup(ws, r.w) < my_i ? 1u : 0u;
       cur = r.z;
     }
   }
@@ -768,31 +772,164 @@ __device__ __forceinline__ void settle_quarter(const EmbView& v, const MissWs& w
   }
 }
 
-// Output rows of stretch `seg` that waited for a miss, quarter `part` of them.
+// The sets whose earliest new id is among the new ids [w0, w0 + kFew) of stretch `seg`, by one wavefront: ways, rows, tags
+// and stamps of all new ids of these sets.
+__device__ __forceinline__ void settle_sets(const EmbView& v, const MissWs& ws, uint32_t batch, uint32_t seg, uint32_t w0,
+                                            uint32_t n_win, SettleCounts* cnt) {
+  constexpr uint32_t kFly = 2;  // rows in flight per half wavefront (4: no faster)
+  const uint32_t lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
+  const uint32_t u0 = seg * ws.seg + w0;
+  const uint32_t here = n_win - w0 < kFew ? n_win - w0 : kFew;
+  // lane k: is new id k the earliest of its set, and how many has the set?
+  uint4 rec = make_uint4(0, 0, 0, 0);
+  uint32_t my_i = 0, n_set = 0;
+  bool earliest = lane < here;
+  if (earliest) {
+    rec = ws.rec[u0 + lane];
+    my_i = first_lookup(ws, rec.w);
+    uint32_t cur = static_cast<uint32_t>(ws.heads[mix32(rec.y) & ws.headmask]);
+    while (cur != kEmpty) {
+      const uint4 r = ws.rec[cur];
+      if (r.y == rec.y) {
+        if (cur != u0 + lane && first_lookup(ws, r.w) < my_i) {
+          earliest = false;
+          break;
+        }
+        ++n_set;
+      }
+      cur = r.z;
+    }
+  }
+  const uint32_t chunks = v.row_bytes / 16;
+  unsigned long long owners = __ballot(earliest);
+  while (owners) {  // two sets at a time, half a wavefront each, lane = way; what follows is uniform over a half
+    const int src_a = __ffsll(owners) - 1;
+    owners &= owners - 1;
+    const int src_b = owners ? __ffsll(owners) - 1 : -1;
+    if (owners) owners &= owners - 1;
+    const int src = half ? src_b : src_a;
+    const bool act = src >= 0;
+    const uint32_t set = __shfl(rec.y, act ? src : 0, kWave), n_here = __shfl(n_set, act ? src : 0, kWave);
+    const uint32_t n_new = act ? n_here : 0, nw = act ? ways_of(v, set) : 0;
+    uint32_t tg = 0, sp = 0;
+    if (l32 < nw) {
+      tg = v.tags[static_cast<uint64_t>(set) * v.w_max + l32];
+      sp = v.stamps[static_cast<uint64_t>(set) * v.w_max + l32];
+    }
+    // lane l: the set's l-th new id by first lookup (lookup, number, id); the earliest is known, the others are sorted in
+    // as the chain is walked, beyond 32 the later ones drop out (a set has no more ways)
+    const uint32_t own_u = u0 + static_cast<uint32_t>(act ? src : 0);
+    uint32_t m_u = own_u, m_id = __shfl(rec.x, act ? src : 0, kWave), m_i = __shfl(my_i, act ? src : 0, kWave);
+    if (l32 != 0) m_i = kEmpty;
+    if (n_new > 1) {
+      uint32_t cur = static_cast<uint32_t>(ws.heads[mix32(set) & ws.headmask]);
+      uint4 r = ws.rec[cur];
+      for (;;) {
+        const uint4 next = r.z != kEmpty ? ws.rec[r.z] : r;  // on its way while this one is looked at
+        if (r.y == set && cur != own_u) {
+          const uint32_t i = first_lookup(ws, r.w);
+          const uint32_t up_i = __shfl_up(m_i, 1, 32), up_u = __shfl_up(m_u, 1, 32), up_id = __shfl_up(m_id, 1, 32);
+          if (m_i > i) {  // (never lane 0)
+            const bool at = up_i < i;
+            m_i = at ? i : up_i;
+            m_u = at ? cur : up_u;
+            m_id = at ? r.x : up_id;
+          }
+        }
+        if (r.z == kEmpty) break;
+        cur = r.z;
+        r = next;
+      }
+    }
+    // lane l: the way its id takes.  First the empty ways by number, then those not stamped in this batch by (stamp, way),
+    // least stamp after least stamp; none left: the id bypasses the cache.
+    auto own_half = [&](unsigned long long m) { return half ? static_cast<uint32_t>(m >> 32) : static_cast<uint32_t>(m); };
+    const bool empty = l32 < nw && tg == kEmpty;
+    bool cand = l32 < nw && !empty && sp < batch;
+    uint32_t pick = own_half(__ballot(empty)), taken = 0, my_way = 0;
+    const uint32_t n_empty = __popc(pick);
+    while (taken < n_new) {
+      if (!pick) {
+        uint32_t least = cand ? sp : 0xFFFFFFFFu;
+#pragma unroll
+        for (int o = 16; o > 0; o >>= 1) {
+          const uint32_t other = __shfl_xor(least, o, kWave);
+          least = other < least ? other : least;
+        }
+        const bool is_least = cand && sp == least;
+        pick = own_half(__ballot(is_least));
+        cand = cand && !is_least;
+        if (!pick) break;
+      }
+      if (l32 == taken) my_way = static_cast<uint32_t>(__ffs(pick)) - 1;
+      pick &= pick - 1;
+      ++taken;
+    }
+    if (l32 < taken) {
+      v.tags[static_cast<uint64_t>(set) * v.w_max + my_way] = m_id;
+      v.stamps[static_cast<uint64_t>(set) * v.w_max + my_way] = batch;
+    }
+    if (l32 == 0) {
+      cnt->unique += n_new;
+      cnt->inserted += taken;
+      cnt->evicted += taken > n_empty ? taken - n_empty : 0;
+      cnt->bypassed += n_new - taken;
+    }
+    // the rows enter their slots
+    for (uint32_t r0 = 0; r0 < taken; r0 += kFly) {
+      const uint8_t* from[kFly];
+      uint8_t* to[kFly];
+#pragma unroll
+      for (uint32_t q = 0; q < kFly; ++q) {
+        const uint32_t l = 32 * half + (r0 + q < taken ? r0 + q : r0);
+        const uint32_t u = __shfl(m_u, l, kWave), way = __shfl(my_way, l, kWave);
+        from[q] = ws.staging + static_cast<uint64_t>(u) * v.row_bytes;
+        to[q] = v.base + slot_offset(v, set, way);
+      }
+      for (uint32_t c = l32; c < chunks; c += 32) {
+        uint4 val[kFly];
+#pragma unroll
+        for (uint32_t q = 0; q < kFly; ++q) {
+          val[q] = make_uint4(0, 0, 0, 0);
+          if (r0 + q < taken) val[q] = *reinterpret_cast<const uint4*>(from[q] + 16 * c);
+        }
+#pragma unroll
+        for (uint32_t q = 0; q < kFly; ++q)
+          if (r0 + q < taken) *reinterpret_cast<uint4*>(to[q] + 16 * c) = val[q];
+      }
+    }
+  }
+}
+
+// Output rows of stretch `seg` that waited for a miss, part `part` of `parts`.
 __device__ __forceinline__ void gather_waiting(const EmbView& v, const MissWs& ws, uint32_t bag, uint8_t* __restrict__ out,
-                                               uint32_t seg, uint32_t part, uint32_t n_def) {
+                                               uint32_t seg, uint32_t part, uint32_t parts, uint32_t n_def) {
   const uint32_t lpr = lanes_per_row(v.row_bytes / 16), rows_per_pass = kWave / lpr;
   const uint32_t lane = threadIdx.x & 63, sub = lane % lpr;
-  for (uint32_t k = part * rows_per_pass + lane / lpr; k < n_def; k += 4 * rows_per_pass) {
+  for (uint32_t k = part * rows_per_pass + lane / lpr; k < n_def; k += parts * rows_per_pass) {
     const uint64_t o = ws.def_list[seg * ws.seg + k];
     emit_row(v, ws, bag, lpr, sub, out + o * v.row_bytes, [&](uint32_t f) { return ws.loc[o * bag + f]; });
   }
 }
 
-template <bool REFILL>
+// SETS: settle_sets, 16 units per stretch; else settle_quarter, four.
+template <bool REFILL, bool SETS>
 __device__ __forceinline__ void settle_units(const EmbView& v, const MissWs& ws, uint32_t bag, uint8_t* __restrict__ out,
                                              uint32_t n_seg, uint32_t batch) {
+  constexpr uint32_t kParts = SETS ? 16 : 4, kTake = SETS ? kFew : kQuarter;
   __shared__ uint32_t s_cnt[4];
   if (threadIdx.x < 4) s_cnt[threadIdx.x] = 0;
   __syncthreads();
   const uint32_t wave = (blockIdx.x * 256 + threadIdx.x) >> 6, n_waves = (gridDim.x * 256) >> 6;
   SettleCounts cnt{0, 0, 0, 0};
-  for (uint32_t unit = wave; unit < 4 * n_seg; unit += n_waves) {
-    const uint32_t seg = unit >> 2, part = unit & 3, both = ws.seg_cnt[seg];
+  for (uint32_t unit = wave; unit < kParts * n_seg; unit += n_waves) {
+    const uint32_t seg = unit / kParts, part = unit % kParts, both = ws.seg_cnt[seg];
     const uint32_t n_win = both & 0xFFFFu, n_def = both >> 16;
-    for (uint32_t w0 = kQuarter * part; w0 < n_win; w0 += 4 * kQuarter)
-      settle_quarter<REFILL>(v, ws, batch, seg, w0, n_win, &cnt);
-    if (!REFILL) gather_waiting(v, ws, bag, out, seg, part, n_def);
+    for (uint32_t w0 = kTake * part; w0 < n_win; w0 += kParts * kTake) {
+      if constexpr (SETS) settle_sets(v, ws, batch, seg, w0, n_win, &cnt);
+      else settle_quarter<REFILL>(v, ws, batch, seg, w0, n_win, &cnt);
+    }
+    if (!REFILL) gather_waiting(v, ws, bag, out, seg, part, kParts, n_def);
   }
   if ((threadIdx.x & 31) == 0) {
     if (cnt.unique) atomicAdd(&s_cnt[0], cnt.unique);
@@ -831,7 +968,7 @@ template <bool REFILL>
 __global__ __launch_bounds__(256, 8) void miss_settle(EmbView v, MissWs ws, uint32_t bag, uint8_t* __restrict__ out, uint32_t n_seg,
                                                    uint32_t batch) {
   if (*ws.any != batch) return;
-  settle_units<REFILL>(v, ws, bag, out, n_seg, batch);
+  settle_units<REFILL, false>(v, ws, bag, out, n_seg, batch);
 }
 
 __global__ __launch_bounds__(256) void miss_apply(EmbView v, MissWs ws, uint32_t n_seg, uint32_t batch) {
@@ -839,28 +976,23 @@ __global__ __launch_bounds__(256) void miss_apply(EmbView v, MissWs ws, uint32_t
   apply_units(v, ws, n_seg, batch);
 }
 
-// Both in one launch for batches of few stretches, where a launch costs as much as its work: at most kSettleBlocks
-// blocks of 256 threads, a sixteenth of the chip's wavefront slots, so that every block is resident whatever else
-// runs (kernels that do not wait for one another drain), and each waits until all have read the tags they need.  A
-// unit of work is settled and applied by the same wavefront: nothing else passes between blocks.
-constexpr uint32_t kSettleBlocks = 128;
+__global__ __launch_bounds__(256, 8) void miss_settle_sets(EmbView v, MissWs ws, uint32_t bag, uint8_t* __restrict__ out, uint32_t n_seg,
+                                                        uint32_t batch) {
+  if (*ws.any != batch) return;
+  settle_units<false, true>(v, ws, bag, out, n_seg, batch);
+}
+
+// Up to this many stretches (32 768 lookups of one row each) the sets are settled whole, in one launch.  512-byte rows,
+// 100 000 slots for 1M rows, whole lookup call: 1000 lookups 27 us, 32 768 149 us (with a settle kernel that waits for all of
+// its blocks before it writes tags: 32 and 198, and it hangs where the blocks do not all fit the chip at once); 65 536
+// lookups 266 us against 264 in two kernels, 262 144 902 against 857: then a set has 15 and more new ids, and one half
+// wavefront walks its chain and moves its rows while others idle.
+constexpr uint32_t kFewStretches = 512;
 // Grids of the separate kernels: two rounds of resident blocks for a lookup (whose batch may well have no miss), more
 // for a refill, whose ids are mostly misses or come late in the list (the colder ones): with 1024 blocks the host
 // link idled for the first 0.4 ms of a 4M-id call.
 constexpr uint32_t kSettleGrid = 4096;
 constexpr uint32_t kRefillGrid = 8192;
-__global__ __launch_bounds__(256, 8) void miss_settle_apply(EmbView v, MissWs ws, uint32_t bag, uint8_t* __restrict__ out,
-                                                         uint32_t n_seg, uint32_t batch) {
-  if (*ws.any != batch) return;
-  settle_units<false>(v, ws, bag, out, n_seg, batch);
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    __hip_atomic_fetch_add(ws.bar, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    while (__hip_atomic_load(ws.bar, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < gridDim.x) __builtin_amdgcn_s_sleep(1);
-  }
-  __syncthreads();
-  apply_units(v, ws, n_seg, batch);
-}
 
 // ---------------------------------------------------------------------------------------
 // Refill of empty ways (paper Sec. IV-B: new EMB capacity is filled with hot rows in the
@@ -1110,8 +1242,8 @@ hipError_t launch_emb_miss_path(const EmbView& v, const MissWs& ws, uint32_t n, 
   if (n == 0) return hipSuccess;
   const dim3 block(256);
   const uint32_t n_seg = (n + ws.seg - 1) / ws.seg;
-  if (n_seg <= 4 * kSettleBlocks) {  // one launch, four units per wavefront at most
-    hipLaunchKernelGGL(miss_settle_apply, dim3(n_seg < kSettleBlocks ? n_seg : kSettleBlocks), block, 0, stream, v, ws, bag, out, n_seg, batch);
+  if (n_seg <= kFewStretches) {
+    hipLaunchKernelGGL(miss_settle_sets, dim3(4 * n_seg), block, 0, stream, v, ws, bag, out, n_seg, batch);  // a unit per wavefront
   } else {
     const dim3 grid(n_seg < kSettleGrid ? n_seg : kSettleGrid);  // four units (quarters of a stretch) per block and pass
     hipLaunchKernelGGL(miss_settle<false>, grid, block, 0, stream, v, ws, bag, out, n_seg, batch);

@@ -69,7 +69,6 @@ struct HashEnt {
 struct MissWs {
   uint32_t seg;             // lookups per probe block (set by the probe's launch)
   uint32_t* any;            // = batch when some block of the batch had a miss
-  uint32_t* bar;            // arrivals at the settle kernel's barrier, zeroed by the probe
   uint32_t* seg_cnt;        // per stretch: (waiting output rows << 16) | new ids
   uint32_t* def_list;       // output rows that wait for a miss
   int64_t* loc;             // per lookup of a waiting row: >=0 pool byte offset, -1 zero row, <=-3 dedupe slot -(v+3)

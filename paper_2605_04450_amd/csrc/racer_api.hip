@@ -307,7 +307,6 @@ int32_t ensure_miss_ws(racer_pool* p, uint64_t n, hipStream_t stream) {
   racer::MissWs& w = p->ws;
   int32_t rc;
   if ((rc = dev_alloc(&w.any, 64, true, stream))) return rc;
-  w.bar = w.any + 32;  // a cache line of its own
   if ((rc = dev_alloc(&w.seg_cnt, cap / 64 + 2, false, stream))) return rc;
   if ((rc = dev_alloc(&w.def_list, cap, false, stream))) return rc;
   if ((rc = dev_alloc(&w.loc, cap, false, stream))) return rc;
@@ -621,7 +620,6 @@ int32_t emb_lookup_noalloc(racer_pool_t* p, const int64_t* ids, uint64_t n, uint
   while (hsize < 2 * n) hsize <<= 1;  // <= kNoallocHash
   racer::MissWs ws{};
   ws.any = reinterpret_cast<uint32_t*>(base);
-  ws.bar = ws.any + 32;
   ws.hents = reinterpret_cast<racer::HashEnt*>(base + kOffHents);
   ws.heads = reinterpret_cast<unsigned long long*>(ws.hents + hsize);
   ws.hmask = ws.headmask = static_cast<uint32_t>(hsize - 1);

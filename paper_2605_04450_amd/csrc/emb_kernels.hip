@@ -251,8 +251,11 @@ __device__ __forceinline__ void miss_tail(const EmbView& v, const MissWs& ws, ui
 // bags, at most 64): lane i owns lookup i, two lookups are probed per step with 32 lanes
 // reading one set's tag line each (128 B, coalesced), then rows are copied with
 // 16-byte lanes.  Misses and the output rows that must wait for them are staged in LDS.
+// What bounds it is the chain of a wavefront's loads, so all eight wavefronts per SIMD are needed.  A SIMD has 800 scalar
+// registers, handed out in sixteens, and a wavefront takes sixteen beyond those the compiler counts: with 88 only seven
+// fit (491 520 lookups: 64-byte rows 38 us instead of 29, pooled by 16, 512-byte rows, 69 instead of 52).
 // ---------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void emb_probe_gather(EmbView v, MissWs ws, IdSrc ids,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_num_sgpr(80))) void emb_probe_gather(EmbView v, MissWs ws, IdSrc ids,
                                                         uint32_t n, uint32_t bag, uint32_t lb,
                                                         uint8_t* __restrict__ out,
                                                         uint8_t* __restrict__ hit_flags, uint32_t batch) {

@@ -2,6 +2,9 @@
 import glob
 import os
 import re
+import subprocess
+
+import pytest
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2605_04450_amd", "csrc")
 
@@ -18,3 +21,20 @@ def test_no_block_waits_for_another_one():
         assert "s_sleep" not in code, name
         assert not re.search(r"\b(while|for)\s*\([^{};]*atomic", code), name
         assert not re.search(r"cooperative|grid\.sync", code), name
+
+
+@pytest.mark.parametrize("name", ["emb_kernels.hip", "hstu_kernels.hip", "hstu_fp32.hip"])
+def test_scalar_registers_leave_room_for_eight_wavefronts(name, tmp_path):
+    # 800 scalar registers per SIMD in sixteens, sixteen more per wavefront than the compiler counts: a kernel whose vector
+    # registers allow eight wavefronts (64 each) keeps them only with 80 scalar ones
+    asm = tmp_path / "kernels.s"
+    subprocess.run(["hipcc", "--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang",
+                    "-packed-fp32-ops", "-w", "--cuda-device-only", "-S", os.path.join(CSRC, name), "-o", str(asm)], check=True)
+    found = 0
+    for entry in re.split(r"\n  - \.agpr_count:", asm.read_text())[1:]:
+        field = lambda key: re.search(r"\.%s:\s+(\S+)" % key, entry).group(1)
+        vector = int(entry.split()[0]) + int(field("vgpr_count"))
+        found += 1
+        if vector <= 64:
+            assert int(field("sgpr_count")) <= 80, field("name")
+    assert found >= 5

@@ -242,6 +242,31 @@ __global__ __launch_bounds__(256) void attention_f32(HstuDims hd, uint32_t layer
       b.bias[e] = pos_h[rel];
     }
   };
+  // In the product a key that a query does not see counts with probability 0, which would still spoil the query's sum if
+  // the key's values are infinite or not numbers.  Such values are taken out here and added to the queries that see them.
+  auto take_out_odd = [&](f32x4 (&v)[NS], const f32x4& pr, uint32_t j0) {
+#pragma unroll
+    for (uint32_t s = 0; s < NS; ++s) {
+      f32x4 rest, is_odd;
+#pragma unroll
+      for (uint32_t e = 0; e < 4; ++e) {
+        const bool odd = v[s][e] * 0.0f != 0.0f;
+        rest[e] = odd ? v[s][e] : 0.0f;
+        is_odd[e] = odd ? 1.0f : 0.0f;
+        v[s][e] = odd ? 0.0f : v[s][e];
+      }
+#pragma unroll 1
+      for (uint32_t key = 0; key < 16; ++key) {
+        auto pick = [&](const f32x4& x) { return g == key / 4 ? (key & 2 ? (key & 1 ? x[3] : x[2]) : (key & 1 ? x[1] : x[0])) : 0.0f; };
+        const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+        const f32x4 part = __builtin_amdgcn_mfma_f32_16x16x4f32(pick(rest), pick(pr), zero, 0, 0, 0);
+        const f32x4 here = __builtin_amdgcn_mfma_f32_16x16x4f32(pick(is_odd), 1.0f, zero, 0, 0, 0);
+#pragma unroll
+        for (uint32_t r = 0; r < 4; ++r)
+          if (here[r] != 0.0f && j0 + key <= p) acc[s][r] += part[r];
+      }
+    }
+  };
   const uint32_t n_groups = last / 16 + 1;
   Group cur, next;
   if (wave < n_groups) fetch(16 * wave, cur);
@@ -258,6 +283,14 @@ __global__ __launch_bounds__(256) void attention_f32(HstuDims hd, uint32_t layer
     f32x4 pr;
 #pragma unroll
     for (uint32_t e = 0; e < 4; ++e) pr[e] = 16 * k + 4 * g + e <= p ? s4[e] / (1.0f + expf(-s4[e])) : 0.0f;
+    if (16 * k + 15 > rq.prefix_len + q0) {  // some query may not see some key
+      float odd = 0.0f;                      // stays 0 unless a value is infinite or not a number
+#pragma unroll
+      for (uint32_t s = 0; s < NS; ++s)
+#pragma unroll
+        for (uint32_t e = 0; e < 4; ++e) odd += cur.v[s][e] * 0.0f;
+      if (__any(odd != 0.0f)) take_out_odd(cur.v, pr, 16 * k);
+    }
 #pragma unroll
     for (uint32_t e = 0; e < 4; ++e)
 #pragma unroll

@@ -410,10 +410,10 @@ __device__ __forceinline__ void unpack_in(const u32x4& a, float v[8]) {
 // the registers the row takes).
 __device__ __forceinline__ void forget(u32x4& a) { asm volatile("" : "+v"(a)); }
 
-// Copies 16 bytes per lane from base + voff (+ OFFSET) to the LDS address lds + 16 * lane (+ OFFSET) without passing
-// through registers; lds and base are the wavefront's.  The compiler does not know about the copy: the
-// wavefront waits for it with wait_vm, other wavefronts see it behind a barrier.  (With the builtin of the same
-// instruction the compiler waits for all outstanding copies before every LDS read.)
+// Copies 16 bytes per lane from base + voff to the LDS address lds + 16 * lane without passing through registers; lds and
+// base are the wavefront's.  The compiler does not know about the copy: the wavefront waits for it with wait_vm, other
+// wavefronts see it behind a barrier.  (With the builtin of the same instruction the compiler waits for all outstanding
+// copies before every LDS read.)
 __device__ __forceinline__ uint32_t lds_address(const void* p) {
   return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const void*)p));
 }
@@ -422,16 +422,27 @@ __device__ __forceinline__ const uint8_t* in_scalar(const uint8_t* p) {  // a po
   const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(a)), hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(a >> 32));
   return reinterpret_cast<const uint8_t*>((static_cast<uint64_t>(hi) << 32) | lo);
 }
-// (A memory instruction may read a scalar register only five wait states after a vector instruction, v_readfirstlane for
-// one, has written it.  The compiler keeps that distance for its own instructions but does not look into this one.)
-template <int OFFSET>
-__device__ __forceinline__ void copy_to_lds(const void* base, uint32_t voff) {
-  asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %0, %1 offset:%2" ::"v"(voff), "s"(base), "n"(OFFSET) : "memory");
+// (The LDS address goes into m0, which the compiler may use for itself between any two statements: one statement writes it,
+// waits and copies.  The instruction needs one wait state behind a write of m0, and five behind a vector instruction,
+// v_readfirstlane for one, that has written its scalar base.  The compiler keeps that distance for its own instructions
+// but does not look into this one.)
+// (m0 is reserved: the compiler holds nothing there across statements unless it sees that nobody writes it, which is what
+// the clobber says.  The warning that it will not be saved is beside the point.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+template <int COPIES>  // one KB, or two that follow each other in both places (four in one statement: the back half at d = 256 spills)
+__device__ __forceinline__ void copy_to_lds(uint32_t lds, const void* base, uint32_t voff) {
+  static_assert(COPIES == 1 || COPIES == 2);
+  if constexpr (COPIES == 1)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory", "m0");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2\n\tglobal_load_lds_dwordx4 %1, %2 offset:1024"
+                 ::"s"(lds), "v"(voff), "s"(base) : "memory", "m0");
 }
-__device__ __forceinline__ void copy_to_lds_from(const void* src) {  // from an address of each lane's own
-  asm volatile("global_load_lds_dwordx4 %0, off" ::"v"(src) : "memory");
+__device__ __forceinline__ void copy_to_lds_from(uint32_t lds, const void* src) {  // from an address of each lane's own
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(src) : "memory", "m0");
 }
-__device__ __forceinline__ void set_lds_target(uint32_t lds) { asm volatile("s_mov_b32 m0, %0\n\ts_nop 0" ::"s"(lds) : "memory"); }
+#pragma clang diagnostic pop
 template <int N>
 __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 
@@ -453,7 +464,7 @@ __global__ __launch_bounds__(64 * WPB, KD <= 256 ? 4 : 2) void layer_half_fused(
   constexpr int kPieces = KD / 64;    // 64-column pieces of a row
   constexpr int kTileBytes = kSt * 1024;
   constexpr int kCopies = kSt / WPB;  // 1 KB copies of a weight tile per wavefront
-  static_assert(kSt % WPB == 0 && KD % 64 == 0, "a weight tile must split evenly over the block");
+  static_assert(kSt % WPB == 0 && KD % 64 == 0 && (kCopies == 1 || kCopies % 2 == 0), "a weight tile must split evenly over the block");
   constexpr int kStageBytes = WPB * 4096;        // row dealing: 32 rows of 128 bytes per wavefront
   constexpr uint32_t kOutTok = KD == 256 ? 16 : 32;  // tokens in a wavefront's output tile: with all 32 the fourth block would not fit the CU
   constexpr int kOutBytes = WPB * kOutTok * 64;
@@ -479,13 +490,8 @@ __global__ __launch_bounds__(64 * WPB, KD <= 256 ? 4 : 2) void layer_half_fused(
   auto fetch_w = [&](uint32_t cb, uint32_t buf) {
     const uint8_t* src = reinterpret_cast<const uint8_t*>(a.wf) + static_cast<uint64_t>(cb) * kTileBytes + wave * (kCopies * 1024);
 #pragma unroll
-    for (int c = 0; c < kCopies; c += 4) {
-      set_lds_target(wlds + buf * kTileBytes + c * 1024);
-      copy_to_lds<0>(src + c * 1024, lane * 16);
-      if (kCopies > c + 1) copy_to_lds<1024>(src + c * 1024, lane * 16);
-      if (kCopies > c + 2) copy_to_lds<2048>(src + c * 1024, lane * 16);
-      if (kCopies > c + 3) copy_to_lds<3072>(src + c * 1024, lane * 16);
-    }
+    for (int c = 0; c < kCopies; c += 2)
+      copy_to_lds<kCopies < 2 ? 1 : 2>(wlds + buf * kTileBytes + c * 1024, src + c * 1024, lane * 16);
   };
 
   // ---- activation rows: issue the loads ---------------------------------------------------------
@@ -921,14 +927,10 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
         const uint8_t* pb = kv.base + static_cast<uint64_t>(page) * kv.page_size;
         const uint8_t* kbase = in_scalar(pb + koff + static_cast<uint64_t>(tb) * 128);
         const uint8_t* vbase = in_scalar(pb + voff + static_cast<uint64_t>(tb) * 2);
-        set_lds_target(lds);
-        copy_to_lds<0>(kbase, kconst);
-        set_lds_target(lds + 1024);
-        copy_to_lds<0>(kbase + 512, kconst);
-        set_lds_target(lds + 8192);
-        copy_to_lds<0>(vbase, vconst);
-        set_lds_target(lds + 8192 + 1024);
-        copy_to_lds<0>(vbase + 16 * hd.pt, vconst);
+        copy_to_lds<1>(lds, kbase, kconst);
+        copy_to_lds<1>(lds + 1024, kbase + 512, kconst);
+        copy_to_lds<1>(lds + 8192, vbase, vconst);
+        copy_to_lds<1>(lds + 8192 + 1024, vbase + 16 * hd.pt, vconst);
         return;
       }
     }
@@ -950,16 +952,14 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
       uint32_t ip = 0;
       const uint8_t* kb = block_of(j0 + krow + 4 * i, koff, &ip);
       const uint8_t* src = kb ? kb + (ip * 128 + part * 16) : zero;
-      set_lds_target(lds + i * 1024);
-      copy_to_lds_from(src);
+      copy_to_lds_from(lds + i * 1024, src);
     }
     uint32_t ip = 0;  // V^T: 8 consecutive keys inside one page (page_tokens % 8 == 0)
     const uint8_t* vb = block_of(j0 + part * 8, voff, &ip);
 #pragma unroll
     for (uint32_t i = 0; i < 2; ++i) {
       const uint8_t* src = vb ? vb + ((vrow + 8 * i) * hd.pt + ip) * 2 : zero;
-      set_lds_target(lds + 8192 + i * 1024);
-      copy_to_lds_from(src);
+      copy_to_lds_from(lds + 8192 + i * 1024, src);
     }
   };
   // Behind the copies: keys past the end of the sequence that share a chunk of V^T with the last ones hold whatever the

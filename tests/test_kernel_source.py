@@ -23,6 +23,20 @@ def test_no_block_waits_for_another_one():
         assert not re.search(r"cooperative|grid\.sync", code), name
 
 
+def test_assembly_that_needs_m0_sets_it_and_says_so():
+    # the compiler may use m0 between any two statements: one that copies to LDS sets it itself, and names it as changed
+    found = 0
+    for name, code in sources():
+        for asm in re.findall(r"\basm\s+volatile\s*\((.*?)\)\s*;", code, flags=re.S):
+            if "m0" not in asm and "load_lds" not in asm:
+                continue
+            found += 1
+            text = "".join(re.findall(r'"((?:[^"\\]|\\.)*)"', asm.split("::")[0]))
+            assert re.match(r"s_mov_b32 m0, %0\\n\\ts_nop \d\\n\\tglobal_load_lds", text), (name, asm)
+            assert re.search(r':\s*[^:]*"m0"\s*$', asm), (name, asm)
+    assert found
+
+
 @pytest.mark.parametrize("name", ["emb_kernels.hip", "hstu_kernels.hip", "hstu_fp32.hip"])
 def test_scalar_registers_leave_room_for_eight_wavefronts(name, tmp_path):
     # 800 scalar registers per SIMD in sixteens, sixteen more per wavefront than the compiler counts: a kernel whose vector

@@ -950,8 +950,6 @@ def main():
     ap.add_argument("--no-cpu", action="store_true")
     ap.add_argument("--no-embheavy", action="store_true",
                     help="leave out the EMB-heavy lookups-only pass (the gather against HBM proper) that the default run appends")
-    ap.add_argument("--one-pipeline", action="store_true",
-                    help="run the throughput pass with per-kernel events on as well")
     ap.add_argument("--copy-calib-mb", type=int, default=0,
                     help="after the timed region, run one plain device copy of this many MiB (a kernel of known "
                          "traffic against which HBM byte counters of a profiler run are scaled)")
@@ -999,8 +997,6 @@ def main():
     # warm the EMB cache, then whole warm-up steps
     for k in range(c["warm_batches"]):
         B.emb_lookup(pool.h, wl["ids_dev"][k % 4], wl["x"], 1, None)
-    if args.one_pipeline:
-        B.racer_prof_enable(pool.h, 1)
     for k in range(args.warmup):
         one_step(wl, k, B)
     torch.cuda.synchronize()
@@ -1057,7 +1053,7 @@ def main():
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": "bf16" if c["bf16"] else "f32", "data": "synthetic",
         "ms_per_step_with_kernel_events": dt_events * 1e3 / args.steps,
-        "passes": {"throughput": "K steps" if not args.one_pipeline else "K steps, kernel events on",
+        "passes": {"throughput": "K steps",
                    "kernels": "the same K steps again with a HIP event before and after every kernel"},
         "config": {"workload": c["desc"], "new_tokens_per_step": int(N), "requests": int(c["batch"]),
                    "emb_frac": c["alpha"], "causal_pairs_per_layer": pairs},

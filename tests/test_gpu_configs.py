@@ -292,8 +292,8 @@ def test_mid_config_step_full_batch_short_and_longest_requests_against_oracle():
     rc, ref = oracle.hstu_step(cfg, w, sreqs, np.arange(s_pt, dtype=np.int32), kv, sx, sts)
     sg = np.concatenate([got[reqs[r][4]: reqs[r][4] + lens[r]] for r in take])
     parity.assert_close(sg, ref, True, "Mid, six shortest requests")
-    # the longest request of the batch (several thousand tokens: its query tiles are cut into key ranges, it
-    # is spread over the dies' work lists and sits in one of the three pipelines): the oracle serves it alone
+    # the longest request of the batch (several thousand tokens, spread over the dies' work lists): the oracle
+    # serves it alone
     r = int(np.argmax(lens))
     S = int(lens[r])
     assert S >= 4096

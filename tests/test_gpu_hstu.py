@@ -138,7 +138,7 @@ def test_bf16_long_sequences_use_split_key_ranges():
 @pytest.mark.parametrize("bf16,L,d,H,pt,first,more", [
     (False, 2, 64, 2, 16, [200, 77, 130], [60, 140, 1]),
     (True, 2, 128, 2, 16, [200, 77, 130], [60, 140, 1]),
-    # the width of the long-history configuration (d = 512, 8 heads): separate LayerNorm + GEMM kernels,
+    # the width of the long-history configuration (d = 512, 8 heads): the widest fused layer halves,
     # ragged lengths, row tiles with a tail, a request that gets nothing in the second step
     (True, 2, 512, 8, 64, [300, 129, 64, 1, 515], [70, 1, 130, 64, 0]),
 ])
@@ -283,16 +283,17 @@ MIXED = [3000, 1700, 4096, 2500, 64, 3900, 2048, 3333, 2900, 4000, 1500, 3800, 1
 
 @pytest.mark.parametrize("L,d,H,lens", [
     (2, 128, 2, MIXED),             # fused layer halves
-    (1, 512, 8, MIXED),             # separate LayerNorm + GEMM kernels
-    (1, 128, 2, [30000, 5, 3000]),  # one request holds nearly all the work: the cuts fall right behind it
-    (1, 128, 2, [20000, 15000]),    # fewer requests than pipelines: stays one pipeline
+    (1, 512, 8, MIXED),             # fused layer halves, two blocks per CU
+    (1, 192, 3, MIXED),             # separate LayerNorm + GEMM kernels
+    (1, 128, 2, [30000, 5, 3000]),  # one request holds nearly all the work
+    (1, 128, 2, [20000, 15000]),
     (1, 128, 2, [33000, 0, 0, 7]),  # requests without new tokens
 ])
-def test_pipelined_step_equals_the_single_pipeline_step_bit_for_bit(L, d, H, lens):
-    # A batch of 32 768 or more new tokens runs as three pipelines on three streams, unless kernels are being timed.
-    # Same work items, same chunking, same summation order: the outputs and the stored K,V must be identical,
-    # also when further work is queued on the caller's stream right behind the step.  (Parity of the pipelined
-    # step with the oracle: the full-size Mid test in test_gpu_configs.py.)
+def test_large_steps_repeat_bit_for_bit_timed_or_not_and_follow_the_oracle(L, d, H, lens):
+    # Same work items, same summation order: outputs and stored K,V are identical from run to run, whether kernels are
+    # timed (events between the launches) or not, also when further work is queued right behind the step.  Of every
+    # request the oracle serves the first tokens (no token sees a later one), and the end of the longest one agrees with the
+    # same request served alone, where its key ranges are cut at other places.
     c = Case(31, L, d, H, 64, True, 4096, 16, 4096.0, 1024)
     reqs, pts, ts, x = c.inputs([0] * len(lens), lens)
     xd = torch.from_numpy(x).to(Hn.DEV).to(torch.bfloat16)
@@ -312,24 +313,44 @@ def test_pipelined_step_equals_the_single_pipeline_step_bit_for_bit(L, d, H, len
     assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
     assert torch.equal(outs[0].view(torch.int16), outs[2].view(torch.int16))
     assert torch.equal(kvs[0], kvs[1]) and torch.equal(kvs[0], kvs[2])
+    got = outs[0].float().cpu().numpy()
+    check_request_heads(c, reqs, pts, ts, x, got, range(len(lens)), "large step, d = %d" % d)
+    r = int(np.argmax(lens))
+    (_, T, pto, tso, xo) = reqs[r]
+    alone = torch.empty_like(xd[:T])
+    assert B.hstu_step(c.pool.h, c.model.h, [(0, T, pto, tso, 0)], ptd, xd[xo:xo + T].contiguous(), tsd, alone) == B.OK
+    assert_close(got[xo:xo + T], alone.float().cpu().numpy(), True, "longest request against itself alone, d = %d" % d)
     c.close()
 
 
-def test_pipelined_step_random_batches_match_the_single_pipeline():
-    # random request counts and lengths (total 33k-60k new tokens, so the pipelines are used), one pool reused
-    # from batch to batch without waiting in between
+def check_request_heads(c, reqs, pts, ts, x, got, which, what, most=500):
+    """The first tokens of some requests of a prefill against the oracle, which serves these tokens alone."""
+    heads, rows, xo = [], [], 0
+    for r in which:
+        (P, T, pto, tso, at) = reqs[r]
+        n = min(T, most)
+        heads.append((0, n, pto, tso, xo))
+        rows += range(at, at + n)
+        xo += n
+    assert_close(got[rows], c.run_oracle(heads, pts, ts, x[rows]), c.bf16, what)
+
+
+def test_random_large_steps_back_to_back_repeat_and_follow_the_oracle():
+    # random request counts and lengths (33k to 60k new tokens), one pool and its list buffers reused from batch to batch
+    # without waiting in between, with and without events between the kernels
     c = Case(77, 1, 128, 2, 64, True, 2048, 16, 2048.0, 2048)
     rng = np.random.default_rng(5)
-    piped, serial = [], []
-    batches = []
+    plain, with_events = [], []
+    batches, host = [], []
     for b in range(10):
         n_req = int(rng.integers(3, 40))
         lens = rng.integers(1, 3000, size=n_req)
         lens = (lens * (rng.integers(33000, 60000) / lens.sum())).astype(np.int64) + 1
         reqs, pts, ts, x = c.inputs([0] * n_req, lens.tolist())
+        host.append((reqs, pts, ts, x))
         batches.append((reqs, torch.from_numpy(pts).to(Hn.DEV), torch.from_numpy(ts).to(Hn.DEV),
                         torch.from_numpy(x).to(Hn.DEV).to(torch.bfloat16)))
-    for timed, outs in ((0, piped), (1, serial)):
+    for timed, outs in ((0, plain), (1, with_events)):
         B.racer_prof_enable(c.pool.h, timed)
         for reqs, ptd, tsd, xd in batches:  # back to back: the next step's lists and kernels queue behind this one
             out = torch.empty_like(xd)
@@ -337,6 +358,8 @@ def test_pipelined_step_random_batches_match_the_single_pipeline():
             outs.append(out)
         torch.cuda.synchronize()
     B.racer_prof_enable(c.pool.h, 0)
-    for k, (a, b_) in enumerate(zip(piped, serial)):
+    for k, (a, b_) in enumerate(zip(plain, with_events)):
         assert torch.equal(a.view(torch.int16), b_.view(torch.int16)), k
+        reqs, pts, ts, x = host[k]
+        check_request_heads(c, reqs, pts, ts, x, a.float().cpu().numpy(), (0, len(reqs) // 2, len(reqs) - 1), "batch %d" % k)
     c.close()

@@ -1,5 +1,5 @@
 """GPU parity of hstu_step over model widths: fp32 models whose heads are not a multiple of four or 16 wide and whose rows do
-not fill a wavefront or a block, bf16 models whose layer halves are fused (64 .. 512) and not (192)."""
+not fill a wavefront or a block, bf16 models whose layer halves are fused (64 .. 512) and not (192, 320, above 512)."""
 import numpy as np
 import pytest
 
@@ -13,9 +13,19 @@ pytestmark = pytest.mark.gpu
     (True, 64, 1, 16), (True, 192, 3, 16), (True, 256, 4, 16), (True, 512, 8, 16),
 ])
 def test_two_steps_with_ragged_lengths(bf16, d, H, pt):
-    first, more = [1, 15, 0, 33, 70], [16, 3, 17, 1, 90]
-    c = Case(21, 2, d, H, pt, bf16, 100, 16, 160.0, 128)
-    reqs, pts, ts, x = c.inputs([0] * 5, [a + b for a, b in zip(first, more)])
+    two_steps(Case(21, 2, d, H, pt, bf16, 100, 16, 160.0, 128), [1, 15, 0, 33, 70], [16, 3, 17, 1, 90])
+
+
+@pytest.mark.parametrize("d,pt", [(192, 64), (192, 24), (320, 64), (576, 64), (1024, 16)])
+def test_separate_layernorm_and_gemm_kernels(d, pt):
+    """Widths without fused layer halves: several row tiles of 128 per request, a step of several row blocks of the output
+    product, rows of more than 512 elements (two chunks per lane), runs of eight tokens of V whole and across pages."""
+    two_steps(Case(23, 1, d, d // 64, pt, True, 600, 16, 600.0, 256), [300, 129, 64, 1, 515], [70, 1, 130, 64, 0])
+
+
+def two_steps(c, first, more):
+    d, bf16 = c.d, c.bf16
+    reqs, pts, ts, x = c.inputs([0] * len(first), [a + b for a, b in zip(first, more)])
     o1, o2 = np.concatenate([[0], np.cumsum(first)]), np.concatenate([[0], np.cumsum(more)])
     one = [(0, a, r[2], r[3], int(o)) for a, r, o in zip(first, reqs, o1)]
     two = [(a, b, r[2], r[3], int(o)) for a, b, r, o in zip(first, more, reqs, o2)]

@@ -6,8 +6,9 @@
 // They run on MFMA with fp32 accumulation (fp32 models: hstu_fp32.hip).
 // What a bf16 model stores where a caller can see it (inputs, weights, K and V in the pages, outputs) is bf16.
 // The library's own intermediate matrices (the normalised activations, U, the attention output O, the gated
-// activations) and its transposed copies of the weights are IEEE half precision: eleven significant bits
-// instead of eight at the same size and the same MFMA rate (v_mfma_f32_32x32x16_f16), which halves the
+// activations) and its copies of the weights (MFMA operand fragments for the fused layer halves, transposed for the other
+// widths) are IEEE half precision: eleven significant bits instead of eight at the same size and the same MFMA rate
+// (v_mfma_f32_32x32x16_f16), which halves the
 // distance to the fp64 oracle; a bf16 weight converts exactly.  Values of these matrices must stay below
 // 65504 in magnitude, which LayerNorm and the 1/n scaling ensure for any sane model.  The two attention
 // products take bf16 operands (Q, and K, V as the pages hold them).
@@ -347,10 +348,11 @@ __global__ __launch_bounds__(256) void gemm_front_bf16(HstuDims hd, uint32_t lay
 // are stored: the wait (which counts loads and stores in issue order) then never covers stores just issued.
 // A block sweeps all column tiles when there are rows enough to fill the chip, else the columns are cut too, down to one
 // tile a block (the launcher's rule).
-// What bounds it, d = 256, 130 432 rows: 0.31 GB leave the front half, and vector (43% of its cycles), matrix (26%) and
-// LDS (31%) work share the rest of the time: 126 us with three blocks per CU and the rows in uneven rounds, 118 with
-// four, which 40 KB of LDS and 128 registers allow (back half 68 -> 63 us); 145 000 rows, where the last round was
-// nearly empty: 140 -> 126 us and 70 -> 67.
+// What bounds it, d = 256, 131 440 rows: the front half moves 0.40 GB (0.34 of them its rows), and vector (51% of its
+// cycles), matrix (30%) and LDS (36%) work lie only partly on top of one another (28% of the time neither of the first two
+// runs); the back half moves 0.31 GB at 4.9 TB/s.  Three blocks per CU and the rows in uneven rounds 126 and 68 us, four,
+// which 40 KB of LDS and 128 registers allow, 119 to 123 and 61 to 64; 145 000 rows, where the last round was nearly
+// empty: 140 -> 126 us and 70 -> 67.
 // ---------------------------------------------------------------------------------------
 struct LayerHalfArgs {
   HstuDims hd;
@@ -751,11 +753,14 @@ __global__ __launch_bounds__(64 * WPB, KD <= 256 ? 4 : 2) void layer_half_fused(
 //     requests spanning >= 2^31 s (or models with more than 32 buckets) use 64-bit gaps;
 //   - the causal select is applied only in blocks that touch the diagonal.
 //
-// What the vector unit has to do is fixed by that (about 680 of its cycles per 32x32 block, 256 of the matrix unit), so
+// What the vector unit has to do is fixed by that (671 of its cycles per 32x32 block, 256 of the matrix unit), so
 // the rest is to keep it fed: the copies to LDS pass through no registers, which leaves the 128 that four wavefronts
 // per SIMD allow, and the block needs 40 KB of LDS, so that four are resident per CU.  With tiles staged through registers
-// (168 of them, 48 KB, three per SIMD) a launch over 195M (query, key) pairs, d = 256, took 0.382 ms, now 0.333
-// (600 TFLOP/s); over 32 x 512 queries behind 16 384 keys, d = 512, 0.971 ms, now 0.849 (657 TFLOP/s).
+// (168 of them, 48 KB, three per SIMD) a launch over 195M (query, key) pairs, d = 256, took 0.382 ms, now 0.335 to 0.365
+// depending on the card (550 to 596 TFLOP/s); over 32 x 512 queries behind 16 384 keys, d = 512, 0.971 ms, now 0.85 to 0.88
+// (635 to 657 TFLOP/s).  By the counters the vector unit is busy 74% of the time (55% before), one of the two units 88% (68%).
+// The 128 registers are 14 too few: 36 bytes of scratch a lane, stored once in front of the loop (39 MB of writes in the
+// first of these launches) and reloaded only in the path of tiles that lie in several pages or end a sequence.
 // ---------------------------------------------------------------------------------------
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;

@@ -829,8 +829,9 @@ int32_t prepare_step(racer_pool* p, racer_hstu* m, const racer_hstu_req* reqs, u
   // Attention work items.  The score matrix of a request is a staircase: late query tiles see
   // many more key tiles than early ones, and one long request would otherwise set the
   // kernel's duration.  Key ranges are therefore cut at multiples of `chunk` tiles (sized so
-  // that about one item per resident block slot exists; a short tail joins the chunk before
-  // it), which also makes the items of different query tiles with the same chunk index read
+  // that about one item per resident block slot exists; a remainder of up to a quarter of a chunk
+  // joins the chunk before it, so with chunks of two or three tiles every remainder is an item of its
+  // own), which also makes the items of different query tiles with the same chunk index read
   // exactly the same keys.
   StepScratch& w = p->step;
   w.clear();

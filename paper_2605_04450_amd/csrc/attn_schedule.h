@@ -1,0 +1,230 @@
+// Which attention workgroup of a step does what (host code).
+//
+// The score matrix of a request is a staircase: a query tile (128 new tokens) sees as many 64-key tiles as lie before its
+// last query.  A workgroup takes a range of one query tile's key tiles for one head, and as many are resident as the chip
+// has places for (kAttnPlaces per die); the others start as places become free.
+//   - Workgroup ids go round-robin over the chip's dies, each with an L2 of its own, so every die has a list.  Units of
+//     work that read the same keys of the same head go to one die, where they lie one behind the other, heaviest unit onto
+//     the least loaded die.
+//   - The units with the largest items come first, so that what starts last is small (64 users back with 64 tokens behind
+//     2048 and 64 new histories, where the long cached ones used to start last: 424 -> 355 us a launch).
+//   - If a query tile has clearly more than a place's share of the work, those with more than that are cut over their keys
+//     into pieces of it, and the pieces sorted by size.  They leave fp32 partial outputs that attention_reduce adds up in the
+//     order of the keys.
+// Tried instead and slower: one workgroup per place with a list dealt beforehand (places do not progress alike: 131k-token
+// prefill 327 -> 366 us, 349 with wavefront priorities by progress; 128 x 64 behind 3072 99 -> 104), or with items
+// taken from a queue per die (390 and 120 us: what a workgroup does between two items takes longer than a new one's start).
+// Pieces of 4/5, 3/5 or 2/5 of the share: 107, 100, 105 us instead of 97 for 128 x 64 behind 3072.
+#pragma once
+
+#include <algorithm>
+#include <cstdint>
+#include <iterator>
+#include <vector>
+
+namespace racer {
+
+constexpr uint32_t kXcds = 8;
+constexpr uint32_t kAttnPlaces = 128;  // workgroups resident per die: 32 CUs, four each
+constexpr uint32_t kAttnBlocks = kXcds * kAttnPlaces;
+constexpr uint32_t kAttnItemCost = 2;  // what an item costs besides its key tiles, in key tiles
+// Small steps: a workgroup needs about 3 us before its first tile and 1.1 us per tile, so two tiles an item, spread over
+// idle CUs, beat eight in one (one request of 64 new tokens 18 -> 11 us, 13 ragged prefills 35 -> 14 us).
+constexpr uint32_t kAttnMinTiles = 2;
+constexpr uint32_t kAttnMaxItemPages = 640;  // page-table entries one item may span
+
+struct ReqDev {  // device copy of one request
+  uint32_t prefix_len, new_len;
+  uint32_t page_table_off, ts_off, x_off;
+};
+
+// A query tile: 128 new tokens (or what is left of them) of one request
+struct AttnItem {
+  uint32_t prefix_len, new_len, page_table_off, ts_off, x_off;  // of the request
+  uint32_t req, qt;
+};
+
+// What one workgroup does: key tiles [kt_begin, kt_end) of a query tile for one head.  slot: where its fp32 partial output goes,
+// kDirect: it covers all keys and writes the output itself.
+struct AttnWork {
+  uint32_t item_head, kt_begin, kt_end, slot;  // item << 4 | head
+};
+constexpr uint32_t kDirect = 0xFFFFFFFFu;
+constexpr uint32_t kMaxHeads = 16;
+
+struct AttnGroup {  // a query tile and head whose partial outputs are slots slot0 .. slot0 + pieces - 1
+  uint32_t item_head, slot0, pieces;
+};
+
+// key tiles whose pages an item's slice of the page table can name
+inline uint32_t attn_page_cap(uint32_t page_tokens) {
+  return static_cast<uint32_t>(std::max<uint64_t>(1, std::min<uint64_t>(1u << 30, (kAttnMaxItemPages - 2) * static_cast<uint64_t>(page_tokens) / 64)));
+}
+
+// Upper bounds for up to B requests, N new tokens and sequences of up to max_seq tokens: query tiles, and entries of all lists
+struct AttnBounds { uint64_t items, work; };
+inline AttnBounds attn_bounds(uint64_t B, uint64_t N, uint64_t max_seq, uint32_t H, uint32_t page_tokens) {
+  const uint64_t q = N / 128 + B, visits = q * H * (max_seq / 64 + 1);
+  // one per query tile and head, and one more per cut: at a place's share, or at the page cap
+  const uint64_t cuts = std::min<uint64_t>(2 * kAttnBlocks, visits / kAttnMinTiles) + 2 * (visits / attn_page_cap(page_tokens));
+  return {q, q * H + cuts};
+}
+
+class AttnSchedule {
+ public:
+  std::vector<AttnItem> items;
+  std::vector<AttnWork> work;      // die x's list: entries [begin[x], begin[x + 1])
+  uint32_t begin[kXcds + 1] = {};
+  uint32_t blocks = 0;             // workgroups to launch
+  std::vector<AttnGroup> groups;
+  uint32_t n_slots = 0;
+
+  // Memory for steps within these bounds (touched, so that the first of them pays for none of it).
+  void reserve(const AttnBounds& b, uint32_t H) {
+    auto have = [](auto& v, uint64_t n) {
+      if (v.capacity() >= n) return;
+      v.resize(n);
+      v.clear();
+    };
+    have(items, b.items);
+    have(work, b.work);
+    have(sorted_, b.work);
+    have(groups, b.items * H);
+    have(atoms_, b.work / H + b.items);
+    have(units_, b.work / H + b.items);
+    have(die_, b.work + b.items * H);
+    have(slot0_, b.items * H);
+  }
+
+  void build(const ReqDev* reqs, uint32_t B, uint32_t H, uint32_t page_tokens) {
+    items.clear(); work.clear(); groups.clear(); atoms_.clear(); units_.clear();
+    n_slots = blocks = 0;
+    uint64_t total = 0;
+    uint32_t largest = 0;
+    for (uint32_t r = 0; r < B; ++r)
+      for (uint32_t q0 = 0; q0 < reqs[r].new_len; q0 += 128) {
+        const ReqDev& q = reqs[r];
+        items.push_back({q.prefix_len, q.new_len, q.page_table_off, q.ts_off, q.x_off, r, q0 / 128});
+        const uint32_t n = tiles_of(items.back());
+        total += n + kAttnItemCost;
+        largest = std::max(largest, n);
+      }
+    const uint32_t page_cap = attn_page_cap(page_tokens);
+    uint64_t share = std::max<uint64_t>(kAttnMinTiles + kAttnItemCost, (total * H + kAttnBlocks - 1) / kAttnBlocks);
+    // Cut at all?  Then into the smallest pieces that all places together can take, what the pieces cost included.
+    const bool cut = largest + kAttnItemCost > share + share / 4 || largest > page_cap;
+    if (cut)
+      for (;; share += 1 + share / 32) {
+        uint64_t all = 0;
+        for (const AttnItem& t : items) all += tiles_of(t) + kAttnItemCost * ((tiles_of(t) + share - kAttnItemCost - 1) / (share - kAttnItemCost));
+        if (all * H <= share * kAttnBlocks) break;
+      }
+    const uint32_t piece = static_cast<uint32_t>(std::min<uint64_t>(share - kAttnItemCost, page_cap));
+    const uint32_t whole = cut ? piece : 0xFFFFFFFFu;  // up to this size nothing is cut
+    // units: query tiles of one request (cut ones: their pieces with the same keys), and, of one that is a large part of
+    // the whole step, runs of them
+    for (uint32_t i0 = 0; i0 < items.size();) {
+      uint32_t i1 = i0, most = 0;
+      while (i1 < items.size() && items[i1].req == items[i0].req) most = std::max(most, pieces_of(tiles_of(items[i1++]), whole, piece, page_cap));
+      for (uint32_t k = 0; k < most; ++k) {
+        Unit u{0, 0, static_cast<uint32_t>(atoms_.size()), 0};
+        for (uint32_t i = i1; i-- > i0;) {  // the largest first
+          const uint32_t n = tiles_of(items[i]), pieces = pieces_of(n, whole, piece, page_cap);
+          if (k >= pieces) continue;
+          const uint32_t b = pieces > 1 ? k * piece : 0, e = k + 1 == pieces ? n : b + piece;
+          atoms_.push_back({i, b, e, pieces > 1});
+          u.weight += e - b + kAttnItemCost;
+          u.largest = std::max(u.largest, e - b);
+          ++u.n;
+          if (u.weight > total / (4 * kXcds)) {
+            units_.push_back(u);
+            u = Unit{0, 0, static_cast<uint32_t>(atoms_.size()), 0};
+          }
+        }
+        if (u.n) units_.push_back(u);
+      }
+      i0 = i1;
+    }
+    std::sort(units_.begin(), units_.end(), [](const Unit& a, const Unit& b) {
+      return a.largest != b.largest ? a.largest > b.largest : a.weight != b.weight ? a.weight > b.weight : a.atom0 < b.atom0;
+    });
+    uint64_t load[kXcds] = {};
+    uint32_t at[kXcds + 1] = {};  // entries of the dies before x, then where the next one of die x goes
+    die_.resize(units_.size() * H);
+    for (size_t u = 0; u < units_.size(); ++u)
+      for (uint32_t h = 0; h < H; ++h) {
+        uint32_t best = 0;
+        for (uint32_t x = 1; x < kXcds; ++x)
+          if (load[x] < load[best]) best = x;
+        load[best] += units_[u].weight;
+        at[best + 1] += units_[u].n;
+        die_[u * H + h] = static_cast<uint8_t>(best);
+      }
+    for (uint32_t x = 0; x < kXcds; ++x) {
+      blocks = std::max(blocks, kXcds * at[x + 1]);
+      at[x + 1] += at[x];
+    }
+    std::copy(at, at + kXcds + 1, begin);
+    work.resize(begin[kXcds]);
+    for (size_t u = 0; u < units_.size(); ++u)
+      for (uint32_t h = 0; h < H; ++h) {
+        uint32_t& to = at[die_[u * H + h]];
+        for (uint32_t a = 0; a < units_[u].n; ++a) {
+          const Atom& t = atoms_[units_[u].atom0 + a];
+          work[to++] = {t.item << 4 | h, t.kt_begin, t.kt_end, t.part ? 0 : kDirect};
+        }
+      }
+    if (!cut) return;
+    sorted_.resize(work.size());
+    for (uint32_t x = 0; x < kXcds; ++x) {  // by size, else in the order they have
+      count_.assign(whole + kAttnMinTiles + 1, 0);
+      auto place = [&](const AttnWork& w) -> uint32_t& { return count_[whole + kAttnMinTiles - (w.kt_end - w.kt_begin)]; };
+      for (uint32_t i = begin[x]; i < begin[x + 1]; ++i) ++place(work[i]);
+      uint32_t to = begin[x];
+      for (uint32_t& c : count_) {
+        const uint32_t n = c;
+        c = to;
+        to += n;
+      }
+      for (uint32_t i = begin[x]; i < begin[x + 1]; ++i) sorted_[place(work[i])++] = work[i];
+    }
+    work.swap(sorted_);
+    // slots of the partial outputs, those of a query tile and head in the order of the keys
+    slot0_.assign(items.size() * static_cast<uint64_t>(H), 0);
+    for (uint32_t i = 0; i < items.size(); ++i) {
+      const uint32_t n = pieces_of(tiles_of(items[i]), whole, piece, page_cap);
+      if (n < 2) continue;
+      for (uint32_t h = 0; h < H; ++h) {
+        groups.push_back({i << 4 | h, n_slots, n});
+        slot0_[static_cast<uint64_t>(i) * H + h] = n_slots;
+        n_slots += n;
+      }
+    }
+    for (AttnWork& w : work)
+      if (w.slot != kDirect) w.slot = slot0_[static_cast<uint64_t>(w.item_head >> 4) * H + (w.item_head & 15)] + w.kt_begin / piece;
+  }
+
+ private:
+  struct Atom { uint32_t item, kt_begin, kt_end; bool part; };
+  struct Unit { uint64_t weight; uint32_t largest, atom0, n; };
+  std::vector<Atom> atoms_;
+  std::vector<Unit> units_;
+  std::vector<uint8_t> die_;  // [unit][head]
+  std::vector<uint32_t> slot0_, count_;
+  std::vector<AttnWork> sorted_;
+
+  static uint32_t tiles_of(const AttnItem& t) {
+    const uint32_t last = t.prefix_len + std::min(t.qt * 128 + 127, t.new_len - 1);
+    return last / 64 + 1;
+  }
+  // How many pieces a query tile of n key tiles is cut into, at multiples of `piece`; a last piece of less than
+  // kAttnMinTiles joins the one before it.
+  static uint32_t pieces_of(uint32_t n, uint32_t whole, uint32_t piece, uint32_t page_cap) {
+    if (n <= whole) return 1;
+    uint32_t k = (n + piece - 1) / piece;
+    if (k > 1 && n - (k - 1) * piece < kAttnMinTiles && n - (k - 2) * piece <= page_cap) --k;
+    return k;
+  }
+};
+
+}  // namespace racer

@@ -161,14 +161,14 @@ template <int NS>
 __global__ __launch_bounds__(256) void attention_f32(HstuDims hd, uint32_t layer, const float* __restrict__ q,
                                                      const float* __restrict__ pos, const float* __restrict__ time,
                                                      KvView kv, const ReqDev* __restrict__ reqs,
-                                                     const AttnWork* __restrict__ work, const int32_t* __restrict__ page_tables,
+                                                     const F32Tile* __restrict__ tiles, const int32_t* __restrict__ page_tables,
                                                      const long long* __restrict__ ts, float* __restrict__ o) {
   __shared__ __attribute__((aligned(16))) f32x4 sums[3][NS][64];
   __shared__ float times[64];
   const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, li = lane & 15, h = blockIdx.y;
-  const AttnWork wk = work[blockIdx.x];
-  const ReqDev rq = reqs[wk.item];
-  const uint32_t q0 = wk.head;  // first query of the tile among the request's new tokens
+  const F32Tile tile = tiles[blockIdx.x];
+  const ReqDev rq = reqs[tile.req];
+  const uint32_t q0 = tile.q0;  // first query of the tile among the request's new tokens
   const uint32_t nq = rq.new_len - q0 < 16 ? rq.new_len - q0 : 16;
   const bool ok = li < nq;
   const uint32_t dh = hd.dh;
@@ -331,15 +331,15 @@ hipError_t launch_layer_half_f32(const HstuDims& hd, uint32_t layer, bool front,
 
 hipError_t launch_attention_f32(const HstuDims& hd, uint32_t layer, const float* q, const float* pos, const float* time, const KvView& kv,
                                 const StepLists& sl, const int32_t* page_tables, const int64_t* ts, float* o, hipStream_t stream) {
-  if (sl.n_work == 0) return hipSuccess;
+  if (sl.n_f32_tiles == 0) return hipSuccess;
   if (hd.dh > 64) return hipErrorInvalidValue;
-  const dim3 grid(sl.n_work, hd.H), block(256);
+  const dim3 grid(sl.n_f32_tiles, hd.H), block(256);
   const long long* t = reinterpret_cast<const long long*>(ts);
   switch ((hd.dh + 15) / 16) {
-    case 1: hipLaunchKernelGGL(attention_f32<1>, grid, block, 0, stream, hd, layer, q, pos, time, kv, sl.reqs, sl.work, page_tables, t, o); break;
-    case 2: hipLaunchKernelGGL(attention_f32<2>, grid, block, 0, stream, hd, layer, q, pos, time, kv, sl.reqs, sl.work, page_tables, t, o); break;
-    case 3: hipLaunchKernelGGL(attention_f32<3>, grid, block, 0, stream, hd, layer, q, pos, time, kv, sl.reqs, sl.work, page_tables, t, o); break;
-    default: hipLaunchKernelGGL(attention_f32<4>, grid, block, 0, stream, hd, layer, q, pos, time, kv, sl.reqs, sl.work, page_tables, t, o); break;
+    case 1: hipLaunchKernelGGL(attention_f32<1>, grid, block, 0, stream, hd, layer, q, pos, time, kv, sl.reqs, sl.f32_tiles, page_tables, t, o); break;
+    case 2: hipLaunchKernelGGL(attention_f32<2>, grid, block, 0, stream, hd, layer, q, pos, time, kv, sl.reqs, sl.f32_tiles, page_tables, t, o); break;
+    case 3: hipLaunchKernelGGL(attention_f32<3>, grid, block, 0, stream, hd, layer, q, pos, time, kv, sl.reqs, sl.f32_tiles, page_tables, t, o); break;
+    default: hipLaunchKernelGGL(attention_f32<4>, grid, block, 0, stream, hd, layer, q, pos, time, kv, sl.reqs, sl.f32_tiles, page_tables, t, o); break;
   }
   return hipGetLastError();
 }

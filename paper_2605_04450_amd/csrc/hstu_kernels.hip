@@ -814,16 +814,18 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
                                                               const AttnWork* __restrict__ work,
                                                               float* __restrict__ partials,
                                                               const int32_t* __restrict__ page_tables,
+                                                              AttnDies dies,
                                                               const long long* __restrict__ ts,
                                                               uint16_t* __restrict__ o) {
   __shared__ __attribute__((aligned(16))) AttnShared sm;
   const uint32_t tid = threadIdx.x, lane = tid & 63, g = lane >> 5, li = lane & 31;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const AttnWork wk = work[blockIdx.x];
-  if (wk.item == kNoWork) return;  // padding of a die's list
-  const AttnItem item = items[wk.item];
   auto scalar = [](uint32_t x) { return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(x)); };  // all lanes agree on it
-  const uint32_t h = scalar(wk.head);
+  const uint32_t die = blockIdx.x % kXcds, at = dies.begin[die] + blockIdx.x / kXcds;
+  if (at >= dies.begin[die + 1]) return;
+  const AttnWork wk = work[at];
+  const AttnItem item = items[wk.item_head >> 4];
+  const uint32_t h = scalar(wk.item_head & 15);
   const uint32_t P = scalar(item.prefix_len), T = scalar(item.new_len), S = P + T;
   const uint32_t q0 = item.qt * kAttnQ;  // first query (index among the new tokens) of the block
   const long long* tsr = ts + item.ts_off;
@@ -873,7 +875,7 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
     for (int e = 0; e < 16; ++e) oacc[b2][e] = 0.0f;
 
   const uint64_t koff = kv_block_offset(hd, layer, 0, h, 2), voff = kv_block_offset(hd, layer, 1, h, 2);
-  const uint32_t kt_begin = scalar(item.kt_begin), kt_end = scalar(item.kt_end);
+  const uint32_t kt_begin = scalar(wk.kt_begin), kt_end = scalar(wk.kt_end);
   // the item's slice of the page table goes to LDS once, so that a tile fetch is a single
   // global round trip instead of two dependent ones
   uint32_t page0, unused_ip;
@@ -899,17 +901,21 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
     i = i < 0 ? 0 : (i > static_cast<int32_t>(hd.n_pos) - 1 ? static_cast<int32_t>(hd.n_pos) - 1 : i);
     return pos_h[i];
   };
-  auto pos_put = [&](uint32_t x, float v) {
-#pragma unroll
-    for (uint32_t s = 0; s < 4; ++s) {
-      const uint32_t at = (x - s) & (kPosRing - 1);
-      sm.pos[s][at] = v;
-      if (at < kPosMirror) sm.pos[s][kPosRing + at] = v;
-    }
+  auto pos_put_copy = [&](uint32_t s, uint32_t x, float v) {
+    const uint32_t at = (x - s) & (kPosRing - 1);
+    sm.pos[s][at] = v;
+    if (at < kPosMirror) sm.pos[s][kPosRing + at] = v;
   };
-  auto tile_time = [&](uint32_t j) { return j < S ? static_cast<uint32_t>(tsr[j] - ts_base) : 0u; };
-  if (tid < 191) pos_put(tid, pos_at(tid));
-  if (tid >= 192) sm.tk[0][tid - 192] = tile_time(kt_begin * 64 + tid - 192);
+  // Key times: the low half as loaded, and what the tile keeps of it.  (Apart, so that nothing waits for the load where it
+  // is issued: there the wait held up the wavefront's copies of the tile by a round trip to memory.)
+  auto time_low = [&](uint32_t j) { return reinterpret_cast<const uint32_t*>(tsr)[2 * static_cast<uint64_t>(j < S ? j : S - 1)]; };
+  auto relative_time = [&](uint32_t j, uint32_t low) { return j < S ? low - static_cast<uint32_t>(ts_base) : 0u; };
+  if (tid < 191) {
+    const float v = pos_at(tid);
+#pragma unroll
+    for (uint32_t s = 0; s < 4; ++s) pos_put_copy(s, tid, v);
+  }
+  if (tid >= 192) sm.tk[0][tid - 192] = relative_time(kt_begin * 64 + tid - 192, time_low(kt_begin * 64 + tid - 192));
   __syncthreads();
 
   // A tile is copied global -> LDS without passing through registers, four 1 KB copies per wavefront: two of K, two of V^T.
@@ -1003,10 +1009,14 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
       // one barrier per tile: tile kt is in LDS, and every wavefront is done with tile kt - 1, whose half takes tile kt + 1
       __syncthreads();
       const bool more = kt + 1 < kt_end;
-      uint32_t side = 0;  // wavefront 0: the next tile's 64 window entries, wavefront 1: its timestamps
+      // The next tile's 64 window entries, which every wavefront puts into one of the four copies, and its timestamps, which
+      // the wavefronts bring in turn: no SIMD has more of this to do than another.
+      float next_pos = 0.0f;
+      uint32_t next_time = 0;
+      const bool times = wave == (t & 3);
       if (more) {
-        if (wave == 0) side = __float_as_uint(pos_at(64 * t + 191 + lane));
-        if (wave == 1) side = tile_time(j0 + 64 + lane);
+        next_pos = pos_at(64 * t + 191 + lane);
+        if (times) next_time = time_low(j0 + 64 + lane);
         fetch(kt + 1, buf ^ 1);
       }
       const uint8_t* ks = &sm.kv[buf][0][0];
@@ -1136,8 +1146,8 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
       }
       if (more) {
         fetched(kt + 1, buf ^ 1);
-        if (wave == 0) pos_put(64 * t + 191 + lane, __uint_as_float(side));
-        if (wave == 1) sm.tk[buf ^ 1][lane] = side;
+        pos_put_copy(wave, 64 * t + 191 + lane, next_pos);
+        if (times) sm.tk[buf ^ 1][lane] = relative_time(j0 + 64 + lane, next_time);
       }
     }
   };
@@ -1162,10 +1172,10 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
   }
   // oacc[db][e]: d_h element 32*db + 8*(e/4) + 4*g + e%4 of the lane's query; undo the log2 e scaling, apply 1/n
   const float sc = hd.inv_n * kLn2;
-  if (item.slot != kDirect) {
-    // part of a split query tile: fp32 partial [slot][head][query][d_h], summed by attention_reduce
+  if (wk.slot != kDirect) {
+    // a piece of a query tile: fp32 partial [slot][query][d_h], summed by attention_reduce
     if (!q_ok) return;
-    float* prow = partials + ((static_cast<uint64_t>(item.slot) * hd.H + h) * kAttnQ + ql) * 64;
+    float* prow = partials + (static_cast<uint64_t>(wk.slot) * kAttnQ + ql) * 64;
 #pragma unroll
     for (int db = 0; db < 2; ++db)
 #pragma unroll
@@ -1191,25 +1201,25 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
   }
 }
 
-// Sum the fp32 partials of a split query tile in chunk order and write the bf16 output.
-__global__ __launch_bounds__(256) void attention_reduce(HstuDims hd, const ReqDev* __restrict__ reqs,
+// Sum the fp32 partials of a query tile that was cut, in the order of their slots, and write the output.
+__global__ __launch_bounds__(256) void attention_reduce(HstuDims hd, const AttnItem* __restrict__ items,
                                                         const AttnGroup* __restrict__ groups,
                                                         const float* __restrict__ partials, uint16_t* __restrict__ o,
                                                         uint32_t o_half) {
-  // blockIdx.x = (group, head); blockIdx.y = which 16 of the tile's query rows: a thread owns one 16-byte piece of
-  // one row, so that the chunks' loads of a whole tile are in flight at once
-  const AttnGroup gr = groups[blockIdx.x / hd.H];
-  const uint32_t h = blockIdx.x % hd.H;
-  const ReqDev rq = reqs[gr.req];
+  // blockIdx.x = query tile and head; blockIdx.y = which 16 of the tile's query rows: a thread owns one 16-byte piece of
+  // one row, so that the pieces' loads of a whole tile are in flight at once
+  const AttnGroup gr = groups[blockIdx.x];
+  const AttnItem it = items[gr.item_head >> 4];
+  const uint32_t h = gr.item_head & 15;
   const uint32_t idx = blockIdx.y * 256 + threadIdx.x;
   const uint32_t row = idx >> 4, c4 = idx & 15;
-  const uint32_t qi = gr.qt * kAttnQ + row;
-  if (row >= kAttnQ || qi >= rq.new_len) return;
-  const float* src = partials + ((static_cast<uint64_t>(gr.slot0) * hd.H + h) * kAttnQ + row) * 64 + 4 * c4;
-  const uint64_t step = static_cast<uint64_t>(hd.H) * kAttnQ * 64;  // from one chunk's partial to the next
+  const uint32_t qi = it.qt * kAttnQ + row;
+  if (row >= kAttnQ || qi >= it.new_len) return;
+  const float* src = partials + (static_cast<uint64_t>(gr.slot0) * kAttnQ + row) * 64 + 4 * c4;
+  constexpr uint64_t step = kAttnQ * 64;  // from one piece's partial to the next
   float4 acc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
   uint32_t k = 0;
-  for (; k + 4 <= gr.chunks; k += 4) {  // four loads in flight; the sum keeps the chunk order
+  for (; k + 4 <= gr.pieces; k += 4) {  // four loads in flight; the sum keeps their order
     const float4 v0 = *reinterpret_cast<const float4*>(src + (k + 0) * step);
     const float4 v1 = *reinterpret_cast<const float4*>(src + (k + 1) * step);
     const float4 v2 = *reinterpret_cast<const float4*>(src + (k + 2) * step);
@@ -1219,7 +1229,7 @@ __global__ __launch_bounds__(256) void attention_reduce(HstuDims hd, const ReqDe
     acc.x += v2.x; acc.y += v2.y; acc.z += v2.z; acc.w += v2.w;
     acc.x += v3.x; acc.y += v3.y; acc.z += v3.z; acc.w += v3.w;
   }
-  for (; k < gr.chunks; ++k) {
+  for (; k < gr.pieces; ++k) {
     const float4 v = *reinterpret_cast<const float4*>(src + k * step);
     acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
   }
@@ -1231,7 +1241,7 @@ __global__ __launch_bounds__(256) void attention_reduce(HstuDims hd, const ReqDe
     w.x = pack_bf16x2(acc.x, acc.y);
     w.y = pack_bf16x2(acc.z, acc.w);
   }
-  *reinterpret_cast<uint2*>(o + static_cast<uint64_t>(rq.x_off + qi) * hd.d + h * 64 + 4 * c4) = w;
+  *reinterpret_cast<uint2*>(o + static_cast<uint64_t>(it.x_off + qi) * hd.d + h * 64 + 4 * c4) = w;
 }
 
 // Are a request's timestamps non-decreasing?  Block (c, r) looks at tokens 2048 c + 1 .. 2048 (c + 1) of request r
@@ -1461,17 +1471,17 @@ hipError_t launch_attention(const HstuDims& hd, uint32_t layer, const void* q, c
   if (sl.N == 0) return hipSuccess;
   const long long* t = reinterpret_cast<const long long*>(ts);
   if (o_half)
-    hipLaunchKernelGGL(attention_bf16_mfma<true>, dim3(sl.n_work), dim3(256), 0, stream, hd, layer, static_cast<const uint16_t*>(q), pos,
-                       time, kv, sl.ts_marks, sl.epoch, sl.items, sl.work, sl.partials, page_tables, t, static_cast<uint16_t*>(o));
+    hipLaunchKernelGGL(attention_bf16_mfma<true>, dim3(sl.n_blocks), dim3(256), 0, stream, hd, layer, static_cast<const uint16_t*>(q), pos,
+                       time, kv, sl.ts_marks, sl.epoch, sl.items, sl.work, sl.dies, sl.partials, page_tables, t, static_cast<uint16_t*>(o));
   else
-    hipLaunchKernelGGL(attention_bf16_mfma<false>, dim3(sl.n_work), dim3(256), 0, stream, hd, layer, static_cast<const uint16_t*>(q), pos,
-                       time, kv, sl.ts_marks, sl.epoch, sl.items, sl.work, sl.partials, page_tables, t, static_cast<uint16_t*>(o));
+    hipLaunchKernelGGL(attention_bf16_mfma<false>, dim3(sl.n_blocks), dim3(256), 0, stream, hd, layer, static_cast<const uint16_t*>(q), pos,
+                       time, kv, sl.ts_marks, sl.epoch, sl.items, sl.work, sl.dies, sl.partials, page_tables, t, static_cast<uint16_t*>(o));
   return hipGetLastError();
 }
 
 hipError_t launch_attention_reduce(const HstuDims& hd, const StepLists& sl, void* o, bool o_half, hipStream_t stream) {
   if (sl.n_groups == 0) return hipSuccess;
-  hipLaunchKernelGGL(attention_reduce, dim3(sl.n_groups * hd.H, (kAttnQ * 16 + 255) / 256), dim3(256), 0, stream, hd, sl.reqs, sl.groups, sl.partials, static_cast<uint16_t*>(o), o_half ? 1u : 0u);
+  hipLaunchKernelGGL(attention_reduce, dim3(sl.n_groups, (kAttnQ * 16 + 255) / 256), dim3(256), 0, stream, hd, sl.items, sl.groups, sl.partials, static_cast<uint16_t*>(o), o_half ? 1u : 0u);
   return hipGetLastError();
 }
 

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <cstdint>
 
+#include "attn_schedule.h"
+
 namespace racer {
 
 // Device counters (unsigned long long each)
@@ -109,11 +111,6 @@ struct HstuDims {
   uint32_t pt_shift;  // log2(pt) when pt is a power of two, else 32
 };
 
-struct ReqDev {  // device copy of one request
-  uint32_t prefix_len, new_len;
-  uint32_t page_table_off, ts_off, x_off;
-};
-
 struct KvView {
   uint8_t* base;
   uint64_t page_size;
@@ -121,52 +118,40 @@ struct KvView {
   unsigned long long* counters;
 };
 
-constexpr uint32_t kAttnMaxItemPages = 640;  // page-table entries one attention item may span
-
-// One attention work item: 128 queries of one request against the key tiles [kt_begin, kt_end)
-// (64 keys each).  A query tile whose key range was cut into several items accumulates
-// through fp32 partial slots (slot .. slot + chunks - 1) that a reduction pass adds up in
-// order; an item that covers its whole key range writes the output directly (slot = kDirect).
-struct AttnItem {
-  uint32_t prefix_len, new_len, page_table_off, ts_off, x_off;  // of the request
-  uint32_t req, qt, kt_begin, kt_end, slot;
+// What a workgroup of the fp32 attention does: 16 queries of one request
+constexpr uint32_t kF32Queries = 16;
+struct F32Tile {
+  uint32_t req, q0;
 };
-struct AttnGroup {
-  uint32_t req, qt, slot0, chunks;
-};
-constexpr uint32_t kDirect = 0xFFFFFFFFu;
-
-// What one attention workgroup does: an item for one head.  Workgroup ids go round-robin over
-// the chip's kXcds dies, each with an L2 of its own, so entry i of the work list runs on die
-// i % kXcds: the host lays the list out so that the items of all query tiles that read the
-// same keys of the same head sit on one die, next to each other, and share those keys through
-// its L2 instead of each fetching them from memory.  Entries with item = kNoWork pad the list.
-struct AttnWork {
-  uint32_t item, head;
-};
-constexpr uint32_t kF32Queries = 16;  // queries per block of the fp32 attention
-constexpr uint32_t kXcds = 8;
-constexpr uint32_t kNoWork = 0xFFFFFFFFu;
 
 // Up to 128 consecutive new-token rows of one request (projection GEMM tile)
 struct RowTile {
   uint32_t row0, rows, req, pad;
 };
 
-// Work lists built on the host for one step (fp32 models: only reqs, and work with (request, first query of a 16-query tile))
+// Where each die's attention work lies in the work list: block i does entry begin[i % kXcds] + i / kXcds
+struct AttnDies {
+  uint32_t begin[kXcds + 1];
+};
+
+// Work lists built on the host for one step
 struct StepLists {
-  const ReqDev* reqs;        // [B]
-  const uint32_t* ts_marks;  // [B] = epoch where the request's timestamps decrease somewhere
+  const ReqDev* reqs;          // [B]
+  const uint32_t* ts_marks;    // [B] = epoch where the request's timestamps decrease somewhere
   uint32_t epoch;
-  const AttnItem* items;     // grouped by (request, key chunk)
-  const AttnWork* work;      // [n_work] workgroup -> (item, head), die-interleaved
-  uint32_t n_work;
-  const AttnGroup* groups;   // query tiles that were split
-  const RowTile* row_tiles;  // projection tiles, none crosses a request
-  uint32_t n_row_tiles;
-  const uint32_t* group_req; // request of rows 0, 32, .. and, behind the last of these, of the last row
-  float* partials;           // [slot][head][128][64]
+  // bf16 models (attn_schedule.h)
+  const AttnItem* items;
+  const AttnWork* work;
+  AttnDies dies;
+  uint32_t n_blocks;
+  const AttnGroup* groups;
   uint32_t n_groups;
+  float* partials;             // [slot][128][64]
+  const RowTile* row_tiles;    // projection tiles, none crosses a request
+  uint32_t n_row_tiles;
+  const uint32_t* group_req;   // request of rows 0, 32, .. and, behind the last of these, of the last row
+  const F32Tile* f32_tiles;    // fp32 models
+  uint32_t n_f32_tiles;
   uint32_t B, N;
 };
 
@@ -208,7 +193,7 @@ hipError_t launch_layer_back_fused(const HstuDims& hd, const void* o, const void
 hipError_t launch_attention(const HstuDims& hd, uint32_t layer, const void* q, const float* pos,
                             const float* time, const KvView& kv, const StepLists& sl,
                             const int32_t* page_tables, const int64_t* ts, void* o, bool o_half, hipStream_t stream);
-// adds up the fp32 partials of split attention items (no-op when nothing was split)
+// adds up the fp32 partials of query tiles cut into pieces (no-op when none was)
 hipError_t launch_attention_reduce(const HstuDims& hd, const StepLists& sl, void* o, bool o_half, hipStream_t stream);
 // bf16 models: pos and time must be the tables multiplied by log2(e) (launch_scale_bias), and
 // q must already be multiplied by log2(e) (launch_gemm_front stores it that way)

@@ -169,19 +169,10 @@ int32_t scratch_address(uint8_t** out) {
 
 // Host-side arrays of prepare_step, kept from call to call for their memory.
 struct StepScratch {
-  struct QTile { uint32_t req, qt, n_kt, n_ch, slot0; };
-  struct Unit { uint32_t item0, n_items; uint64_t weight; };
-  std::vector<QTile> qtiles;
-  std::vector<Unit> units;
-  std::vector<uint32_t> order;
-  std::vector<racer::AttnItem> items;
-  std::vector<racer::AttnGroup> groups;
+  racer::AttnSchedule attn;
+  std::vector<racer::ReqDev> reqs;
   std::vector<racer::RowTile> row_tiles;
-  std::vector<racer::AttnWork> die_list[racer::kXcds];
-  void clear() {
-    qtiles.clear(); units.clear(); items.clear(); groups.clear(); row_tiles.clear();
-    for (auto& l : die_list) l.clear();
-  }
+  std::vector<racer::F32Tile> f32_tiles;
 };
 
 struct racer_pool {
@@ -756,30 +747,14 @@ namespace {
 
 // Upper bounds of a step's list bytes and partial-output bytes for up to B requests, N new tokens and sequences of up
 // to max_seq tokens (pool_reserve sizes the work spaces with them; prepare_step's own sizes never exceed them).
-// Q query tiles (128 new tokens of one request), V visits of 64-key tiles; a query tile is cut into at most
-// n_kt / chunk + 1 items, and the chunk is at least V * H / kAttnItemsWanted tiles unless the item's page-table slice
-// caps it, and at least kAttnMinChunk.
-// One item per resident block of the chip (256 CUs x 4): with twice as many, the partial sums of a 131k-token step and
-// their reduction cost 8 us a layer and saved nothing; with one, 32 x 512 queries behind 16 384 keys are not cut at all.
-constexpr uint64_t kAttnItemsWanted = 1024;
-// Small steps: a block needs about 5 us before its first tile and 1.3 us per tile, so two tiles an item, spread over
-// idle CUs, beat eight in one block (one request of 64 new tokens 18 -> 11 us, 13 ragged prefills 35 -> 14 us).
-constexpr uint32_t kAttnMinChunk = 2;
-uint32_t attn_chunk_cap(uint32_t page_tokens) {  // an item's slice of the page table (a chunk and a quarter at most) must fit the kernel's LDS copy
-  return std::max<uint32_t>(1, static_cast<uint32_t>((static_cast<uint64_t>(racer::kAttnMaxItemPages) - 2) * page_tokens / 64 * 4 / 5));
-}
 struct StepBounds { uint64_t list_bytes, partial_bytes; };
 StepBounds step_bounds(uint64_t B, uint64_t N, uint64_t max_seq, uint32_t H, uint32_t page_tokens) {
-  const uint64_t Q = N / 128 + B;
-  const uint64_t V = Q * (max_seq / 64 + 1);
-  const uint64_t by_chunk = std::min<uint64_t>(kAttnItemsWanted / H + 1, V / kAttnMinChunk + 1);
-  const uint64_t items = Q + std::max<uint64_t>(by_chunk, V / attn_chunk_cap(page_tokens) + 1);
+  const racer::AttnBounds a = racer::attn_bounds(B, N, max_seq, H, page_tokens);
   StepBounds b;
-  b.list_bytes = sizeof(racer::ReqDev) * (B + 1) + 4 * (N / 32 + B + 2) + sizeof(racer::AttnWork) * (N / racer::kF32Queries + B) + sizeof(racer::AttnItem) * items +
-                 (sizeof(racer::AttnGroup) + sizeof(racer::RowTile)) * (Q + 1) +
-                 sizeof(racer::AttnWork) * racer::kXcds * items * H + 7 * 256;
-  b.partial_bytes = items * H * 128 * 64 * sizeof(float);
-  b.partial_bytes += b.partial_bytes / 4;
+  b.list_bytes = sizeof(racer::ReqDev) * (B + 1) + 4 * (N / 32 + B + 2) + sizeof(racer::F32Tile) * (N / racer::kF32Queries + B) +
+                 sizeof(racer::AttnItem) * a.items + (sizeof(racer::AttnWork) + sizeof(racer::AttnGroup)) * a.work +
+                 sizeof(racer::RowTile) * (a.items + 1) + 8 * 256;
+  b.partial_bytes = a.work * 128 * 64 * sizeof(float);
   return b;
 }
 
@@ -826,84 +801,19 @@ int32_t prepare_step(racer_pool* p, racer_hstu* m, const racer_hstu_req* reqs, u
   sl.N = static_cast<uint32_t>(N);
   if (N == 0) return RACER_OK;
 
-  // Attention work items.  The score matrix of a request is a staircase: late query tiles see
-  // many more key tiles than early ones, and one long request would otherwise set the
-  // kernel's duration.  Key ranges are therefore cut at multiples of `chunk` tiles (sized so
-  // that about one item per resident block slot exists; a remainder of up to a quarter of a chunk
-  // joins the chunk before it, so with chunks of two or three tiles every remainder is an item of its
-  // own), which also makes the items of different query tiles with the same chunk index read
-  // exactly the same keys.
   StepScratch& w = p->step;
-  w.clear();
-  const uint32_t q_block = fp32 ? racer::kF32Queries : 128;
-  uint64_t visits = 0;
-  if (!fp32)
-    for (uint32_t r = 0; r < B; ++r) {
-      const uint32_t T = reqs[r].new_len;
-      for (uint32_t qt = 0; qt * q_block < T; ++qt) {
-        const uint64_t last = static_cast<uint64_t>(reqs[r].prefix_len) + std::min<uint64_t>(qt * q_block + q_block - 1, T - 1);
-        w.qtiles.push_back({r, qt, static_cast<uint32_t>(last / 64 + 1), 0, 0});
-        visits += last / 64 + 1;
-      }
-    }
-  else
+  w.row_tiles.clear();
+  w.f32_tiles.clear();
+  w.reqs.resize(B);
+  for (uint32_t r = 0; r < B; ++r)
+    w.reqs[r] = racer::ReqDev{reqs[r].prefix_len, reqs[r].new_len, static_cast<uint32_t>(reqs[r].page_table_off),
+                              static_cast<uint32_t>(reqs[r].ts_off), static_cast<uint32_t>(reqs[r].x_off)};
+  w.attn.build(w.reqs.data(), fp32 ? 0 : B, c.H, c.page_tokens);
+  if (fp32)
     for (uint32_t r = 0; r < B; ++r)
-      for (uint32_t q0 = 0; q0 < reqs[r].new_len; q0 += q_block) w.die_list[0].push_back({r, q0});
-  uint32_t chunk = static_cast<uint32_t>(std::max<uint64_t>(kAttnMinChunk, (visits * c.H + kAttnItemsWanted - 1) / kAttnItemsWanted));
-  chunk = std::min(chunk, attn_chunk_cap(c.page_tokens));
-  uint32_t n_slots = 0;
-  for (StepScratch::QTile& t : w.qtiles) {
-    t.n_ch = t.n_kt / chunk;
-    if (t.n_ch == 0 || t.n_kt % chunk > chunk / 4) ++t.n_ch;
-    if (t.n_ch > 1) {
-      t.slot0 = n_slots;
-      w.groups.push_back({t.req, t.qt, n_slots, t.n_ch});
-      n_slots += t.n_ch;
-    }
-  }
-  // units: the items of one request with the same chunk index, for one head
-  for (size_t q0 = 0; q0 < w.qtiles.size();) {
-    size_t q1 = q0;
-    uint32_t max_ch = 0;
-    while (q1 < w.qtiles.size() && w.qtiles[q1].req == w.qtiles[q0].req) max_ch = std::max(max_ch, w.qtiles[q1++].n_ch);
-    const racer_hstu_req& rq = reqs[w.qtiles[q0].req];
-    for (uint32_t k = 0; k < max_ch; ++k) {
-      StepScratch::Unit u{static_cast<uint32_t>(w.items.size()), 0, 0};
-      for (size_t q = q0; q < q1; ++q) {
-        const StepScratch::QTile& t = w.qtiles[q];
-        if (k >= t.n_ch) continue;
-        const uint32_t b = k * chunk, e = k + 1 == t.n_ch ? t.n_kt : b + chunk;
-        w.items.push_back({rq.prefix_len, rq.new_len, static_cast<uint32_t>(rq.page_table_off), static_cast<uint32_t>(rq.ts_off),
-                           static_cast<uint32_t>(rq.x_off), t.req, t.qt, b, e, t.n_ch > 1 ? t.slot0 + k : racer::kDirect});
-        u.weight += e - b;
-      }
-      u.n_items = static_cast<uint32_t>(w.items.size()) - u.item0;
-      w.units.push_back(u);
-    }
-    q0 = q1;
-  }
-  // heaviest unit first onto the least loaded die; a die's list keeps that order, so its last
-  // workgroups are the short ones
-  w.order.resize(w.units.size());
-  for (uint32_t i = 0; i < w.order.size(); ++i) w.order[i] = i;
-  std::sort(w.order.begin(), w.order.end(), [&](uint32_t a, uint32_t b) {
-    return w.units[a].weight != w.units[b].weight ? w.units[a].weight > w.units[b].weight : a < b;
-  });
-  const uint32_t n_dies = fp32 ? 1 : racer::kXcds;
-  uint64_t die_load[racer::kXcds] = {};
-  size_t die_len = w.die_list[0].size();
-  for (uint32_t ui : w.order)
-    for (uint32_t h = 0; h < c.H; ++h) {
-      uint32_t best = 0;
-      for (uint32_t x = 1; x < racer::kXcds; ++x)
-        if (die_load[x] < die_load[best]) best = x;
-      die_load[best] += w.units[ui].weight;
-      for (uint32_t i = 0; i < w.units[ui].n_items; ++i) w.die_list[best].push_back({w.units[ui].item0 + i, h});
-      die_len = std::max(die_len, w.die_list[best].size());
-    }
-  const size_t n_work = die_len * n_dies;
-  const uint64_t partial_bytes = static_cast<uint64_t>(n_slots) * c.H * q_block * 64 * sizeof(float);
-  int32_t rc = ensure_partials(p, partial_bytes + partial_bytes / 4, stream);
+      for (uint32_t q0 = 0; q0 < reqs[r].new_len; q0 += racer::kF32Queries) w.f32_tiles.push_back({r, q0});
+  const uint64_t partial_bytes = static_cast<uint64_t>(w.attn.n_slots) * 128 * 64 * sizeof(float);
+  int32_t rc = ensure_partials(p, partial_bytes, stream);
   if (rc) return rc;
   if (!fp32 && !ctx->fused)
     for (uint32_t r = 0; r < B; ++r)
@@ -919,11 +829,12 @@ int32_t prepare_step(racer_pool* p, racer_hstu* m, const racer_hstu_req* reqs, u
     return at;
   };
   const uint64_t off_reqs = place(sizeof(racer::ReqDev) * B);
-  const uint64_t off_items = place(sizeof(racer::AttnItem) * w.items.size());
-  const uint64_t off_groups = place(sizeof(racer::AttnGroup) * w.groups.size());
+  const uint64_t off_items = place(sizeof(racer::AttnItem) * w.attn.items.size());
+  const uint64_t off_work = place(sizeof(racer::AttnWork) * w.attn.work.size());
+  const uint64_t off_groups = place(sizeof(racer::AttnGroup) * w.attn.groups.size());
   const uint64_t off_row_tiles = place(sizeof(racer::RowTile) * w.row_tiles.size());
   const uint64_t off_group_req = place(sizeof(uint32_t) * n_groups32);  // request of every 32nd row, and of the last one
-  const uint64_t off_work = place(sizeof(racer::AttnWork) * n_work);
+  const uint64_t off_f32_tiles = place(sizeof(racer::F32Tile) * w.f32_tiles.size());
   if ((rc = ensure_lists(p, total, total * 2)) || (rc = ensure_ts_marks(p, B, stream))) return rc;
   p->step_epoch += 1;
   // Small lists travel as an argument of the kernel that begins the step, larger ones it reads from pinned staging.
@@ -932,16 +843,15 @@ int32_t prepare_step(racer_pool* p, racer_hstu* m, const racer_hstu_req* reqs, u
   uint8_t* hbuf = arg.bytes;
   int which = 0;
   if (!by_argument && (rc = p->hstage.acquire(total, &hbuf, &which))) return rc;
-  racer::ReqDev* hr = reinterpret_cast<racer::ReqDev*>(hbuf + off_reqs);
-  for (uint32_t r = 0; r < B; ++r)
-    hr[r] = racer::ReqDev{reqs[r].prefix_len, reqs[r].new_len, static_cast<uint32_t>(reqs[r].page_table_off),
-                          static_cast<uint32_t>(reqs[r].ts_off), static_cast<uint32_t>(reqs[r].x_off)};
-  auto put = [&](uint64_t at, const void* src, uint64_t bytes) {
-    if (bytes) std::memcpy(hbuf + at, src, bytes);
+  auto put = [&](uint64_t at, const auto& v) {
+    if (!v.empty()) std::memcpy(hbuf + at, v.data(), v.size() * sizeof(v[0]));
   };
-  put(off_items, w.items.data(), sizeof(racer::AttnItem) * w.items.size());
-  put(off_groups, w.groups.data(), sizeof(racer::AttnGroup) * w.groups.size());
-  put(off_row_tiles, w.row_tiles.data(), sizeof(racer::RowTile) * w.row_tiles.size());
+  put(off_reqs, w.reqs);
+  put(off_items, w.attn.items);
+  put(off_work, w.attn.work);
+  put(off_groups, w.attn.groups);
+  put(off_row_tiles, w.row_tiles);
+  put(off_f32_tiles, w.f32_tiles);
   if (ctx->fused) {
     uint32_t* gr = reinterpret_cast<uint32_t*>(hbuf + off_group_req);
     uint64_t next = 0;
@@ -953,23 +863,22 @@ int32_t prepare_step(racer_pool* p, racer_hstu* m, const racer_hstu_req* reqs, u
     }
     *gr = last;
   }
-  racer::AttnWork* hw = reinterpret_cast<racer::AttnWork*>(hbuf + off_work);
-  for (uint32_t x = 0; x < n_dies; ++x)
-    for (size_t i = 0; i < die_len; ++i)
-      hw[i * n_dies + x] = i < w.die_list[x].size() ? w.die_list[x][i] : racer::AttnWork{racer::kNoWork, 0};
 
   sl.reqs = reinterpret_cast<const racer::ReqDev*>(p->hl_dev + off_reqs);
   sl.ts_marks = p->ts_marks;
   sl.epoch = p->step_epoch;
   sl.items = reinterpret_cast<const racer::AttnItem*>(p->hl_dev + off_items);
-  sl.groups = reinterpret_cast<const racer::AttnGroup*>(p->hl_dev + off_groups);
-  sl.partials = reinterpret_cast<float*>(p->hp_dev);
   sl.work = reinterpret_cast<const racer::AttnWork*>(p->hl_dev + off_work);
-  sl.n_work = static_cast<uint32_t>(n_work);
-  sl.n_groups = static_cast<uint32_t>(w.groups.size());
+  std::copy(std::begin(w.attn.begin), std::end(w.attn.begin), sl.dies.begin);
+  sl.n_blocks = w.attn.blocks;
+  sl.groups = reinterpret_cast<const racer::AttnGroup*>(p->hl_dev + off_groups);
+  sl.n_groups = static_cast<uint32_t>(w.attn.groups.size());
+  sl.partials = reinterpret_cast<float*>(p->hp_dev);
   sl.row_tiles = reinterpret_cast<const racer::RowTile*>(p->hl_dev + off_row_tiles);
   sl.n_row_tiles = static_cast<uint32_t>(w.row_tiles.size());
   sl.group_req = reinterpret_cast<const uint32_t*>(p->hl_dev + off_group_req);
+  sl.f32_tiles = reinterpret_cast<const racer::F32Tile*>(p->hl_dev + off_f32_tiles);
+  sl.n_f32_tiles = static_cast<uint32_t>(w.f32_tiles.size());
   // the lists to the device, and which requests' timestamps never decrease (the attention kernels' 32-bit time paths rely on it)
   HIP_TRY(racer::launch_begin_step(sl, longest, ts, p->d_counters, by_argument ? &arg : nullptr, hbuf, p->hl_dev, total, stream));
   if (!by_argument && (rc = p->hstage.mark(which, stream))) return rc;
@@ -996,6 +905,8 @@ int32_t pool_reserve(racer_pool_t* p, const racer_hstu_t* m, const racer_reserve
     const StepBounds b = step_bounds(r->max_requests, r->max_new_tokens, r->max_seq_tokens, c.H, c.page_tokens);
     if ((rc = ensure_lists(p, b.list_bytes, b.list_bytes)) || (rc = ensure_ts_marks(p, r->max_requests, stream))) return rc;
     if ((rc = p->hstage.reserve(b.list_bytes))) return rc;
+    if (c.elem == RACER_ELEM_BF16)
+      p->step.attn.reserve(racer::attn_bounds(r->max_requests, r->max_new_tokens, r->max_seq_tokens, c.H, c.page_tokens), c.H);
     if (c.elem == RACER_ELEM_BF16 && (rc = ensure_partials(p, b.partial_bytes, stream))) return rc;
     if ((rc = ensure_hstu_ws(p, (r->max_new_tokens * c.d * esize + 255) & ~255ull, stream))) return rc;
   }

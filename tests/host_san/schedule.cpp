@@ -1,0 +1,102 @@
+// The attention schedule (csrc/attn_schedule.h, host code) over random and edge steps, built with sanitizers by
+// tests/test_attn_schedule.py: every key tile of every query tile and head is covered once, by pieces whose pages fit a
+// workgroup's table; partial outputs have slots of their own in the order of the keys; the stated bounds hold; and the
+// pieces of a step that is cut are no larger than a place's share.
+#include <cmath>
+#include <cstdio>
+#include <cstdlib>
+#include <random>
+
+#include "../../paper_2605_04450_amd/csrc/attn_schedule.h"
+
+#define CHECK(cond)                                                                 \
+  do {                                                                              \
+    if (!(cond)) {                                                                  \
+      std::fprintf(stderr, "schedule.cpp:%d: check failed: %s\n", __LINE__, #cond); \
+      std::exit(1);                                                                 \
+    }                                                                               \
+  } while (0)
+
+using namespace racer;
+
+static void check(const std::vector<ReqDev>& reqs, uint32_t H, uint32_t pt, AttnSchedule& s) {
+  uint64_t N = 0, longest = 1;
+  for (const ReqDev& r : reqs) {
+    N += r.new_len;
+    longest = std::max<uint64_t>(longest, r.prefix_len + r.new_len);
+  }
+  s.build(reqs.data(), static_cast<uint32_t>(reqs.size()), H, pt);
+  const AttnBounds b = attn_bounds(reqs.size(), N, longest, H, pt);
+  CHECK(s.items.size() <= b.items && s.work.size() <= b.work && s.n_slots <= b.work && s.groups.size() <= b.work);
+  // the lists of the dies, and a workgroup for every entry
+  CHECK(s.begin[0] == 0 && s.begin[kXcds] == s.work.size());
+  for (uint32_t x = 0; x < kXcds; ++x) CHECK(s.begin[x] <= s.begin[x + 1] && (s.begin[x + 1] - s.begin[x]) * kXcds <= s.blocks);
+  std::vector<std::vector<AttnWork>> of(s.items.size() * H);
+  for (const AttnWork& w : s.work) {
+    CHECK((w.item_head >> 4) < s.items.size() && (w.item_head & 15) < H);
+    CHECK(w.kt_begin < w.kt_end && (w.kt_end - 1) * 64ull / pt - w.kt_begin * 64ull / pt < kAttnMaxItemPages);
+    CHECK((w.kt_end * 64ull - 1) / pt - w.kt_begin * 64ull / pt < kAttnMaxItemPages);
+    of[(w.item_head >> 4) * H + (w.item_head & 15)].push_back(w);
+  }
+  std::vector<AttnGroup> group(of.size(), AttnGroup{0, 0, 0});
+  uint64_t slots = 0;
+  for (const AttnGroup& g : s.groups) {
+    CHECK(g.pieces >= 2 && g.slot0 == slots);
+    slots += g.pieces;
+    group[(g.item_head >> 4) * H + (g.item_head & 15)] = g;
+  }
+  CHECK(slots == s.n_slots);
+  size_t item = 0;
+  for (uint32_t r = 0; r < reqs.size(); ++r)
+    for (uint32_t q0 = 0; q0 < reqs[r].new_len; q0 += 128, ++item) {
+      const AttnItem& t = s.items[item];
+      CHECK(t.req == r && t.qt == q0 / 128 && t.prefix_len == reqs[r].prefix_len && t.new_len == reqs[r].new_len && t.x_off == reqs[r].x_off);
+      const uint32_t last = t.prefix_len + std::min(q0 + 127, t.new_len - 1);
+      for (uint32_t h = 0; h < H; ++h) {
+        auto& p = of[item * H + h];
+        const AttnGroup& g = group[item * H + h];
+        std::sort(p.begin(), p.end(), [](const AttnWork& a, const AttnWork& c) { return a.kt_begin < c.kt_begin; });
+        CHECK(p.size() == (g.pieces ? g.pieces : 1));
+        uint32_t at = 0;
+        for (size_t k = 0; k < p.size(); ++k) {
+          CHECK(p[k].kt_begin == at && p[k].slot == (g.pieces ? g.slot0 + k : kDirect));
+          at = p[k].kt_end;
+        }
+        CHECK(at == last / 64 + 1);
+      }
+    }
+  CHECK(item == s.items.size());
+}
+
+static std::vector<ReqDev> requests(const std::vector<std::pair<uint32_t, uint32_t>>& lens) {
+  std::vector<ReqDev> r;
+  uint32_t x = 0;
+  for (const auto& l : lens) {
+    r.push_back({l.first, l.second, 0, 0, x});
+    x += l.second;
+  }
+  return r;
+}
+
+int main() {
+  AttnSchedule s;  // one object over all steps, as in a pool
+  for (uint32_t H : {1u, 4u, 16u})
+    for (uint32_t pt : {8u, 24u, 64u, 800u}) {
+      check(requests({{0, 1}}), H, pt, s);
+      check(requests({{0, 0}, {5, 0}, {63, 1}, {64, 128}, {0, 129}}), H, pt, s);
+      check(requests({{2973, 64}}), H, pt, s);
+      check(requests({{1u << 20, 3}, {0, 5000}}), H, pt, s);
+      check(requests(std::vector<std::pair<uint32_t, uint32_t>>(700, {0, 1})), H, pt, s);
+      check(requests(std::vector<std::pair<uint32_t, uint32_t>>(32, {16384, 512})), H, pt, s);
+    }
+  std::mt19937 g(1);
+  auto log_size = [&](double e) { return static_cast<uint32_t>(std::exp((g() % 10000) / 10000.0 * e)); };
+  const uint32_t pts[] = {8, 16, 24, 40, 64, 256, 800};
+  for (int it = 0; it < 1500; ++it) {
+    std::vector<std::pair<uint32_t, uint32_t>> l(1 + g() % (it % 50 == 0 ? 300 : 12));
+    for (auto& p : l) p = {g() % 4 ? log_size(10.0) - 1 : 0, g() % 8 ? log_size(8.0) : g() % 2};
+    check(requests(l), 1 + g() % 16, pts[g() % 7], s);
+  }
+  std::puts("attention schedule: ok");
+  return 0;
+}

@@ -31,7 +31,7 @@ constexpr uint32_t kAttnItemCost = 2;  // what an item costs besides its key til
 // Small steps: a workgroup needs about 3 us before its first tile and 1.1 us per tile, so two tiles an item, spread over
 // idle CUs, beat eight in one (one request of 64 new tokens 18 -> 11 us, 13 ragged prefills 35 -> 14 us).
 constexpr uint32_t kAttnMinTiles = 2;
-constexpr uint32_t kAttnMaxItemPages = 640;  // page-table entries one item may span
+constexpr uint32_t kAttnMaxItemPages = 608;  // page-table entries one item may span
 
 struct ReqDev {  // device copy of one request
   uint32_t prefix_len, new_len;

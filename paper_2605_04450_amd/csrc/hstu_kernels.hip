@@ -499,7 +499,7 @@ __global__ __launch_bounds__(64 * WPB, KD <= 256 ? 4 : 2) void layer_half_fused(
   // ---- activation rows: issue the loads ---------------------------------------------------------
   // One load instruction covers 128 bytes of eight rows.  A piece (64 columns of the 32 rows) is dealt out to the
   // operand layout (lane = token, 8 of every 16 elements) through 4 KB of wave-private LDS; chunk c of row r sits at
-  // c ^ (r mod 8).  Rows past the end read the first row; their results are never stored.
+  // c ^ (r / 2 mod 8), where no two lanes served together meet in a bank.  Rows past the end read the first row; their results are never stored.
   const uint32_t st_r = lane >> 3, st_c = lane & 7;
   auto issue_piece = [&](const uint16_t* src, int p, u32x4 (&v)[4]) {
 #pragma unroll
@@ -513,10 +513,10 @@ __global__ __launch_bounds__(64 * WPB, KD <= 256 ? 4 : 2) void layer_half_fused(
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const uint32_t r = 8 * i + st_r;
-      *reinterpret_cast<u32x4*>(stage + r * 128 + 16 * (st_c ^ (r & 7))) = v[i];
+      *reinterpret_cast<u32x4*>(stage + r * 128 + 16 * (st_c ^ (r >> 1 & 7))) = v[i];
     }
 #pragma unroll
-    for (int s2 = 0; s2 < 4; ++s2) dst[at + s2] = *reinterpret_cast<const u32x4*>(stage + li * 128 + 16 * ((2 * s2 + g) ^ (li & 7)));
+    for (int s2 = 0; s2 < 4; ++s2) dst[at + s2] = *reinterpret_cast<const u32x4*>(stage + li * 128 + 16 * ((2 * s2 + g) ^ (li >> 1 & 7)));
   };
   u32x4 xr[kSt];  // this lane's half of its token's row: raw, then normalised (and gated) half precision
   {
@@ -767,15 +767,17 @@ constexpr float kLn2 = 0.6931471805599453f;
 constexpr uint32_t kAttnQ = 128;     // queries per block
 constexpr uint32_t kPosRing = 256;   // a tile needs 191 distances, the next one 64 new ones
 constexpr uint32_t kPosMirror = 24;  // the first entries once more behind the end: a lane reads up to 24 from its first
+constexpr uint32_t kPosCopy = 304;   // (the two, and what spreads the copies over the banks)
 
 struct AttnShared {
-  // two staged key tiles: K [key][d_h] and V^T [d_h][key], 64 rows of 128 bytes each; chunk c (16 bytes) of row r sits
-  // at c ^ (r mod 8), which spreads the operand reads of eight neighbouring lanes over all banks
+  // Two staged key tiles: K [key][d_h] and V^T [d_h][key], 64 rows of 128 bytes each.  A 16-byte read is served for sixteen
+  // lanes at a time, {0-3, 12-15, 20-27} and {4-11, 16-19, 28-31} of either half wavefront, over 64 banks: chunk c (16
+  // bytes) of row r sits at c ^ (r / 2 mod 8), where the operand reads of such lanes (a row each) meet in no bank.
   uint8_t kv[2][2][8192];
-  // copy s holds entry x of the positional window at (x - s) mod kPosRing, so that any 8 consecutive entries can be
-  // read as aligned 16-byte words of one of the copies; a copy is 96 bytes (mod 128) long, which spreads the
-  // reads of eight neighbouring lanes (two per copy) over all banks
-  float pos[4][kPosRing + kPosMirror];
+  // Copy s holds entry x of the positional window at (x - s) mod kPosRing, so that any 8 consecutive entries can be
+  // read as aligned 16-byte words of one of the copies.  The copies lie 192 bytes (mod 256) apart: no bank is met twice
+  // here either.
+  float pos[4][kPosCopy];
   uint32_t tk[2][64];  // key timestamps of the staged tiles relative to the request's first one
   float time[64];
   float rtime[32];     // rtime[c] = time bias of a gap with c leading zero bits (32-bit gaps, n_time <= 32)
@@ -812,9 +814,9 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
                                                               const uint32_t* __restrict__ ts_marks, uint32_t epoch,
                                                               const AttnItem* __restrict__ items,
                                                               const AttnWork* __restrict__ work,
+                                                              AttnDies dies,
                                                               float* __restrict__ partials,
                                                               const int32_t* __restrict__ page_tables,
-                                                              AttnDies dies,
                                                               const long long* __restrict__ ts,
                                                               uint16_t* __restrict__ o) {
   __shared__ __attribute__((aligned(16))) AttnShared sm;
@@ -919,10 +921,10 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
   __syncthreads();
 
   // A tile is copied global -> LDS without passing through registers, four 1 KB copies per wavefront: two of K, two of V^T.
-  // A lane's 16 bytes of copy i: LDS row 16 * wave + 8 * i + r with r = lane / 8, chunk position lane % 8.  LDS row R of K
-  // holds key R with bits 2 and 3 swapped: the 8 keys a lane holds after the first product are then consecutive, and the
-  // matching V^T operand is one 16-byte read.
-  const uint32_t r8 = lane >> 3, part = (lane & 7) ^ r8;
+  // A lane's 16 bytes of copy i: LDS row 16 * wave + 8 * i + r with r = lane / 8, chunk position lane % 8, chunk part ^ 4 i.
+  // LDS row R of K holds key R with bits 2 and 3 swapped: the 8 keys a lane holds after the first product are then
+  // consecutive, and the matching V^T operand is one 16-byte read.
+  const uint32_t r8 = lane >> 3, part = (lane & 7) ^ (r8 >> 1);
   const uint32_t krow = 16 * wave + (r8 & 3) + 8 * (r8 >> 2);  // + 4 i
   const uint32_t vrow = 16 * wave + r8;                        // + 8 i
   const uint32_t kconst = krow * 128 + part * 16, vconst = (vrow * hd.pt + part * 8) * 2;
@@ -939,9 +941,9 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
         const uint8_t* kbase = in_scalar(pb + koff + static_cast<uint64_t>(tb) * 128);
         const uint8_t* vbase = in_scalar(pb + voff + static_cast<uint64_t>(tb) * 2);
         copy_to_lds<1>(lds, kbase, kconst);
-        copy_to_lds<1>(lds + 1024, kbase + 512, kconst);
+        copy_to_lds<1>(lds + 1024, kbase + 512, kconst ^ 64);
         copy_to_lds<1>(lds + 8192, vbase, vconst);
-        copy_to_lds<1>(lds + 8192 + 1024, vbase + 16 * hd.pt, vconst);
+        copy_to_lds<1>(lds + 8192 + 1024, vbase + 16 * hd.pt, vconst ^ 64);
         return;
       }
     }
@@ -962,13 +964,13 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
     for (uint32_t i = 0; i < 2; ++i) {
       uint32_t ip = 0;
       const uint8_t* kb = block_of(j0 + krow + 4 * i, koff, &ip);
-      const uint8_t* src = kb ? kb + (ip * 128 + part * 16) : zero;
+      const uint8_t* src = kb ? kb + (ip * 128 + (part ^ 4 * i) * 16) : zero;
       copy_to_lds_from(lds + i * 1024, src);
     }
-    uint32_t ip = 0;  // V^T: 8 consecutive keys inside one page (page_tokens % 8 == 0)
-    const uint8_t* vb = block_of(j0 + part * 8, voff, &ip);
 #pragma unroll
-    for (uint32_t i = 0; i < 2; ++i) {
+    for (uint32_t i = 0; i < 2; ++i) {  // V^T: 8 consecutive keys inside one page (page_tokens % 8 == 0)
+      uint32_t ip = 0;
+      const uint8_t* vb = block_of(j0 + (part ^ 4 * i) * 8, voff, &ip);
       const uint8_t* src = vb ? vb + ((vrow + 8 * i) * hd.pt + ip) * 2 : zero;
       copy_to_lds_from(lds + 8192 + i * 1024, src);
     }
@@ -979,14 +981,15 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
     wait_vm<0>();
     const uint32_t j0 = kt * 64;
     if (j0 + 64 <= S || (S & 7) == 0) return;
-    if (j0 + part * 8 < S && j0 + part * 8 + 8 > S) {
 #pragma unroll
-      for (uint32_t i = 0; i < 2; ++i) {
+    for (uint32_t i = 0; i < 2; ++i) {
+      const uint32_t j = j0 + (part ^ 4 * i) * 8;
+      if (j < S && j + 8 > S) {
         u32x4* c = reinterpret_cast<u32x4*>(&sm.kv[buf][1][wave * 2048 + i * 1024 + lane * 16]);
         u32x4 v = *c;
 #pragma unroll
         for (uint32_t e = 0; e < 8; ++e)
-          if (j0 + part * 8 + e >= S) v[e >> 1] &= (e & 1) ? 0x0000FFFFu : 0xFFFF0000u;
+          if (j + e >= S) v[e >> 1] &= (e & 1) ? 0x0000FFFFu : 0xFFFF0000u;
         *c = v;
       }
     }
@@ -995,7 +998,7 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
   // operand reads: row li (+ 32) of a tile, chunk 2 * st + g
   uint32_t chunk_off[4];
 #pragma unroll
-  for (uint32_t st = 0; st < 4; ++st) chunk_off[st] = li * 128 + 16 * ((2 * st + g) ^ (li & 7));
+  for (uint32_t st = 0; st < 4; ++st) chunk_off[st] = li * 128 + 16 * ((2 * st + g) ^ (li >> 1 & 7));
   const uint32_t pos_c0 = 8 * g + 127 - ql;  // the lane's first window entry of the item's first half tile
   const float* pos_copy = sm.pos[pos_c0 & 3];
 
@@ -1008,6 +1011,15 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
       const uint32_t j0 = kt * 64, t = kt - kt_begin, buf = t & 1;
       // one barrier per tile: tile kt is in LDS, and every wavefront is done with tile kt - 1, whose half takes tile kt + 1
       __syncthreads();
+      // The four blocks of a CU take turns at going first, one tile each: left to itself a SIMD serves its older wavefronts
+      // first, and of blocks that start together with equal work the last ends half as much later again as the first, with
+      // nothing beside it to cover its latencies (32 x 512 queries behind 16 384 keys, d = 512: 0.88 ms, now 0.83).
+      switch (t & 3) {
+        case 0: __builtin_amdgcn_s_setprio(3); break;
+        case 1: __builtin_amdgcn_s_setprio(2); break;
+        case 2: __builtin_amdgcn_s_setprio(1); break;
+        default: __builtin_amdgcn_s_setprio(0);
+      }
       const bool more = kt + 1 < kt_end;
       // The next tile's 64 window entries, which every wavefront puts into one of the four copies, and its timestamps, which
       // the wavefronts bring in turn: no SIMD has more of this to do than another.

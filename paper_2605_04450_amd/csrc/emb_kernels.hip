@@ -11,6 +11,8 @@
 // Because a set's victim candidates are fixed once the probe has stamped the hits, the
 // k-th unique miss of a set (by first occurrence) simply takes the k-th candidate, so
 // the insertion order needs no serial loop: each unique miss computes its own rank.
+#include <algorithm>
+
 #include "kernels.h"
 
 namespace racer {
@@ -285,18 +287,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_sgpr(80))) void emb_
   int my_way = -1;
   if (i0 < n) {
     const uint32_t l32 = lane & 31, half = lane >> 5;
-#pragma unroll 4
-    for (uint32_t it = 0; it < 32; ++it) {
-      const uint32_t a = 2 * it + half;
-      const uint32_t id_a = __shfl(id32, a, kWave);
-      const uint32_t set_a = __shfl(set, a, kWave);
-      const uint32_t nw_a = __shfl(nw, a, kWave);
-      bool match = false;
-      if (l32 < nw_a) match = v.tags[static_cast<uint64_t>(set_a) * v.w_max + l32] == id_a;
-      const unsigned long long m = __ballot(match);
-      const uint32_t lo = static_cast<uint32_t>(m), hi = static_cast<uint32_t>(m >> 32);
-      if (lane == 2 * it) my_way = lo ? __ffs(lo) - 1 : -1;
-      if (lane == 2 * it + 1) my_way = hi ? __ffs(hi) - 1 : -1;
+    for (uint32_t it0 = 0; 2 * it0 < lb; it0 += 4) {
+#pragma unroll
+      for (uint32_t k = 0; k < 4; ++k) {
+        const uint32_t it = it0 + k, a = 2 * it + half;
+        const uint32_t id_a = __shfl(id32, a, kWave);
+        const uint32_t set_a = __shfl(set, a, kWave);
+        const uint32_t nw_a = __shfl(nw, a, kWave);
+        bool match = false;
+        if (l32 < nw_a) match = v.tags[static_cast<uint64_t>(set_a) * v.w_max + l32] == id_a;
+        const unsigned long long m = __ballot(match);
+        const uint32_t lo = static_cast<uint32_t>(m), hi = static_cast<uint32_t>(m >> 32);
+        if (lane == 2 * it) my_way = lo ? __ffs(lo) - 1 : -1;
+        if (lane == 2 * it + 1) my_way = hi ? __ffs(hi) - 1 : -1;
+      }
     }
   }
   const bool hit = valid && my_way >= 0;
@@ -393,11 +397,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_sgpr(80))) void emb_
 // row with 16-byte lanes, so a wavefront keeps eight independent lookups in flight per
 // instruction and nothing is serialised over the lookups of a batch.
 // ---------------------------------------------------------------------------------------
-constexpr uint32_t kW32Rounds = 2;  // lookups per group of eight lanes (more leaves too few blocks for a Mid-sized batch)
-template <int PASSES>  // row_bytes / 128
+template <int PASSES, uint32_t ROUNDS>  // row_bytes / 128; lookups per group of eight lanes
 __global__ __launch_bounds__(256) void emb_probe_gather_w32(EmbView v, MissWs ws, IdSrc ids, uint32_t n, uint8_t* __restrict__ out,
                                                             uint8_t* __restrict__ hit_flags, uint32_t batch) {
-  constexpr uint32_t kRounds = kW32Rounds;
+  constexpr uint32_t kRounds = ROUNDS;
   constexpr uint32_t kPerBlock = 32 * kRounds;  // lookups per block: 4 waves x 8 groups x rounds
   __shared__ uint2 s_miss[kPerBlock];
   __shared__ uint4 s_win[kPerBlock];
@@ -495,21 +498,21 @@ __global__ __launch_bounds__(256) void emb_probe_gather_w32(EmbView v, MissWs ws
 // row): a wavefront's eight lookups are 8 / bag whole bags.  The rows of the hits pass
 // through a wave-private LDS tile, from which every lane sums its 4-byte word of an output
 // row over the bag's members in order, in fp32, and rounds once (the definition of the pooled
-// row).  A bag with a missing member is left to the miss path, as in the generic kernel.
+// row).  A bag with a missing member is left to the miss path, as in the generic kernel.  Rows of more than 512
+// bytes are summed 512 bytes at a time, so that their tile leaves room for eight wavefronts per SIMD (1024-byte rows, 262 144
+// lookups by eights: 50 us, 63 with the whole rows in LDS, 65 in the generic kernel; 16 384 by fours 11 and 47).
 // ---------------------------------------------------------------------------------------
-// (The second launch bound keeps the registers where they allow 6, 5, 4, 4 wavefronts per SIMD: at 98 instead of 96 a
-// pooled gather of 2.1M 256-byte rows took 220 us instead of 198.)
-template <int PASSES>  // row_bytes / 128
-__global__ __launch_bounds__(256, PASSES == 1 ? 6 : PASSES == 2 ? 5 : 4) void emb_probe_gather_w32_bag(EmbView v, MissWs ws, IdSrc ids, uint32_t n, uint32_t bag, uint8_t* __restrict__ out,
-                                                                uint8_t* __restrict__ hit_flags, uint32_t batch) {
-  constexpr uint32_t kRounds = 4;
+template <int PASSES, uint32_t ROUNDS>  // row_bytes / 128; lookups per group of eight lanes
+__device__ __forceinline__ void probe_gather_w32_bag(const EmbView& v, const MissWs& ws, const IdSrc& ids, uint32_t n, uint32_t bag,
+                                                     uint8_t* __restrict__ out, uint8_t* __restrict__ hit_flags, uint32_t batch) {
+  constexpr uint32_t kRounds = ROUNDS;
   constexpr uint32_t kPerBlock = 32 * kRounds;  // lookups per block: 4 waves x 8 groups x rounds
-  constexpr uint32_t kRowWords = PASSES * 32;   // 4-byte words per row
+  constexpr int kPart = PASSES < 4 ? PASSES : 4;  // 128-byte pieces of the rows summed at a time: 4 KB of LDS per wavefront
   __shared__ uint2 s_miss[kPerBlock];
   __shared__ uint4 s_win[kPerBlock];
   __shared__ uint32_t s_n[3];  // misses, claimed ids, waiting output rows
   __shared__ uint32_t s_cnt[3];
-  __shared__ __attribute__((aligned(16))) uint32_t s_rows[4][8][kRowWords];
+  __shared__ __attribute__((aligned(16))) uint32_t s_rows[4][8][kPart * 32];
   const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, grp = lane >> 3, j = lane & 7;
   if (tid < 3) s_n[tid] = s_cnt[tid] = 0;
   __syncthreads();
@@ -588,8 +591,6 @@ __global__ __launch_bounds__(256, PASSES == 1 ? 6 : PASSES == 2 ? 5 : 4) void em
       if (hit[r]) v.stamps[set[r]] = batch;
       if (hit_flags && active[r]) hit_flags[i] = hit[r] ? 1 : 0;
     }
-#pragma unroll
-    for (int c = 0; c < PASSES; ++c) *reinterpret_cast<uint4*>(&s_rows[wave][grp][4 * (j + 8 * c)]) = row[r][c];
     // a bag with a missing member waits for the miss path, which needs every member's location
     const unsigned long long miss_m = __ballot(miss[r]);  // eight equal bits per group
     const uint32_t bag_first = (grp / bag) * bag;
@@ -601,30 +602,36 @@ __global__ __launch_bounds__(256, PASSES == 1 ? 6 : PASSES == 2 ? 5 : 4) void em
       if (deferred && grp == bag_first)
         ws.def_list[blockIdx.x * ws.seg + atomicAdd(&s_n[2], 1u)] = static_cast<uint32_t>(i / bag);
     }
-    // ordered sums: word w of the wavefront's output rows
-    const uint32_t out_words = kRowWords * (8 / bag);
-    for (uint32_t w = lane; w < out_words; w += 64) {
-      const uint32_t orow = w / kRowWords, word = w % kRowWords, first = orow * bag;
-      if (i0[r] + first >= n || ((miss_m >> (8 * first)) & bag_mask) != 0) continue;
-      uint32_t res;
-      if (bf16) {
-        float a0 = 0.0f, a1 = 0.0f;
-        for (uint32_t f = 0; f < bag; ++f) {
-          const uint32_t x = s_rows[wave][first + f][word];
-          const float v0 = bf16_to_f32(x & 0xFFFFu), v1 = bf16_to_f32(x >> 16);
-          a0 = f == 0 ? v0 : a0 + v0;
-          a1 = f == 0 ? v1 : a1 + v1;
+    // ordered sums: word w of this part of the wavefront's output rows
+#pragma unroll
+    for (int c0 = 0; c0 < PASSES; c0 += kPart) {
+      constexpr uint32_t kWords = kPart * 32;
+      const uint32_t words = c0 + kPart <= PASSES ? kWords : (PASSES - c0) * 32;
+#pragma unroll
+      for (int c = c0; c < c0 + kPart && c < PASSES; ++c) *reinterpret_cast<uint4*>(&s_rows[wave][grp][4 * (j + 8 * (c - c0))]) = row[r][c];
+      for (uint32_t w = lane; w < kWords * (8 / bag); w += 64) {
+        const uint32_t orow = w / kWords, word = w % kWords, first = orow * bag;
+        if (word >= words || i0[r] + first >= n || ((miss_m >> (8 * first)) & bag_mask) != 0) continue;
+        uint32_t res;
+        if (bf16) {
+          float a0 = 0.0f, a1 = 0.0f;
+          for (uint32_t f = 0; f < bag; ++f) {
+            const uint32_t x = s_rows[wave][first + f][word];
+            const float v0 = bf16_to_f32(x & 0xFFFFu), v1 = bf16_to_f32(x >> 16);
+            a0 = f == 0 ? v0 : a0 + v0;
+            a1 = f == 0 ? v1 : a1 + v1;
+          }
+          res = f32_to_bf16(a0) | (f32_to_bf16(a1) << 16);
+        } else {
+          float a0 = 0.0f;
+          for (uint32_t f = 0; f < bag; ++f) {
+            const float v0 = __uint_as_float(s_rows[wave][first + f][word]);
+            a0 = f == 0 ? v0 : a0 + v0;
+          }
+          res = __float_as_uint(a0);
         }
-        res = f32_to_bf16(a0) | (f32_to_bf16(a1) << 16);
-      } else {
-        float a0 = 0.0f;
-        for (uint32_t f = 0; f < bag; ++f) {
-          const float v0 = __uint_as_float(s_rows[wave][first + f][word]);
-          a0 = f == 0 ? v0 : a0 + v0;
-        }
-        res = __float_as_uint(a0);
+        reinterpret_cast<uint32_t*>(out + ((i0[r] + first) / bag) * v.row_bytes)[32 * c0 + word] = res;
       }
-      reinterpret_cast<uint32_t*>(out + ((i0[r] + first) / bag) * v.row_bytes)[word] = res;
     }
   }
   if (j == 0) {
@@ -640,6 +647,20 @@ __global__ __launch_bounds__(256, PASSES == 1 ? 6 : PASSES == 2 ? 5 : 4) void em
     if (s_cnt[2]) atomicAdd(&v.counters[ctr_index(kCtrInvalid)], static_cast<unsigned long long>(s_cnt[2]));
   }
   miss_tail<true, false>(v, ws, batch, s_miss, s_n[0], s_win, &s_n[1], out);
+}
+
+// One round: 43 to 52 registers, so that eight wavefronts fit a SIMD if the scalar ones let them (see the generic kernel).
+template <int PASSES>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_num_sgpr(80))) void emb_probe_gather_w32_bag1(
+    EmbView v, MissWs ws, IdSrc ids, uint32_t n, uint32_t bag, uint8_t* __restrict__ out, uint8_t* __restrict__ hit_flags, uint32_t batch) {
+  probe_gather_w32_bag<PASSES, 1>(v, ws, ids, n, bag, out, hit_flags, batch);
+}
+// Four rounds, for many lookups of narrow rows.  (The second launch bound keeps the registers where they allow 6 and 5
+// wavefronts per SIMD: at 98 instead of 96 a pooled gather of 2.1M 256-byte rows took 220 us instead of 198.)
+template <int PASSES>
+__global__ __launch_bounds__(256, PASSES == 1 ? 6 : 5) void emb_probe_gather_w32_bag4(
+    EmbView v, MissWs ws, IdSrc ids, uint32_t n, uint32_t bag, uint8_t* __restrict__ out, uint8_t* __restrict__ hit_flags, uint32_t batch) {
+  probe_gather_w32_bag<PASSES, 4>(v, ws, ids, n, bag, out, hit_flags, batch);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -915,24 +936,27 @@ __device__ __forceinline__ void gather_waiting(const EmbView& v, const MissWs& w
   }
 }
 
-// SETS: settle_sets, 16 units per stretch; else settle_quarter, four.
+// Units per stretch: of kFew ids (settle_sets), or of kQuarter.
+__host__ __device__ __forceinline__ uint32_t set_parts(const MissWs& ws) { return ws.seg >= 64 ? 16 : ws.seg / kFew; }
+__host__ __device__ __forceinline__ uint32_t quarter_parts(const MissWs& ws) { return ws.seg >= 64 ? 4 : ws.seg / kQuarter; }
 template <bool REFILL, bool SETS>
 __device__ __forceinline__ void settle_units(const EmbView& v, const MissWs& ws, uint32_t bag, uint8_t* __restrict__ out,
                                              uint32_t n_seg, uint32_t batch) {
-  constexpr uint32_t kParts = SETS ? 16 : 4, kTake = SETS ? kFew : kQuarter;
+  constexpr uint32_t kTake = SETS ? kFew : kQuarter;
+  const uint32_t parts = SETS ? set_parts(ws) : quarter_parts(ws);
   __shared__ uint32_t s_cnt[4];
   if (threadIdx.x < 4) s_cnt[threadIdx.x] = 0;
   __syncthreads();
   const uint32_t wave = (blockIdx.x * 256 + threadIdx.x) >> 6, n_waves = (gridDim.x * 256) >> 6;
   SettleCounts cnt{0, 0, 0, 0};
-  for (uint32_t unit = wave; unit < kParts * n_seg; unit += n_waves) {
-    const uint32_t seg = unit / kParts, part = unit % kParts, both = ws.seg_cnt[seg];
+  for (uint32_t unit = wave; unit < parts * n_seg; unit += n_waves) {
+    const uint32_t seg = unit / parts, part = unit % parts, both = ws.seg_cnt[seg];
     const uint32_t n_win = both & 0xFFFFu, n_def = both >> 16;
-    for (uint32_t w0 = kTake * part; w0 < n_win; w0 += kParts * kTake) {
+    for (uint32_t w0 = kTake * part; w0 < n_win; w0 += parts * kTake) {
       if constexpr (SETS) settle_sets(v, ws, batch, seg, w0, n_win, &cnt);
       else settle_quarter<REFILL>(v, ws, batch, seg, w0, n_win, &cnt);
     }
-    if (!REFILL) gather_waiting(v, ws, bag, out, seg, part, kParts, n_def);
+    if (!REFILL) gather_waiting(v, ws, bag, out, seg, part, parts, n_def);
   }
   if ((threadIdx.x & 31) == 0) {
     if (cnt.unique) atomicAdd(&s_cnt[0], cnt.unique);
@@ -953,10 +977,11 @@ __device__ __forceinline__ void settle_units(const EmbView& v, const MissWs& ws,
 
 __device__ __forceinline__ void apply_units(const EmbView& v, const MissWs& ws, uint32_t n_seg, uint32_t batch) {
   const uint32_t wave = (blockIdx.x * 256 + threadIdx.x) >> 6, n_waves = (gridDim.x * 256) >> 6, lane = threadIdx.x & 63;
-  for (uint32_t unit = wave; unit < 4 * n_seg; unit += n_waves) {
-    const uint32_t seg = unit >> 2, part = unit & 3, n_win = ws.seg_cnt[seg] & 0xFFFFu;
+  const uint32_t parts = quarter_parts(ws);
+  for (uint32_t unit = wave; unit < parts * n_seg; unit += n_waves) {
+    const uint32_t seg = unit / parts, part = unit % parts, n_win = ws.seg_cnt[seg] & 0xFFFFu;
     if (lane >= kQuarter) continue;
-    for (uint32_t k = kQuarter * part + lane; k < n_win; k += 4 * kQuarter) {
+    for (uint32_t k = kQuarter * part + lane; k < n_win; k += parts * kQuarter) {
       const uint32_t u = seg * ws.seg + k;
       const int32_t way = ws.u_way[u];
       if (way < 0) continue;
@@ -989,12 +1014,12 @@ __global__ __launch_bounds__(256, 8) void miss_settle_sets(EmbView v, MissWs ws,
 // 100 000 slots for 1M rows, whole lookup call: 1000 lookups 27 us, 32 768 149 us (with a settle kernel that waits for all of
 // its blocks before it writes tags: 32 and 198, and it hangs where the blocks do not all fit the chip at once); 65 536
 // lookups 266 us against 264 in two kernels, 262 144 902 against 857: then a set has 15 and more new ids, and one half
-// wavefront walks its chain and moves its rows while others idle.
-constexpr uint32_t kFewStretches = 512;
-// Grids of the separate kernels: two rounds of resident blocks for a lookup (whose batch may well have no miss), more
-// for a refill, whose ids are mostly misses or come late in the list (the colder ones): with 1024 blocks the host
+// wavefront walks its chain and moves its rows while others idle.  (Shorter stretches: up to as many lookups.)
+constexpr uint32_t kFewStretches = 512, kFewLookups = 32768;
+// Grids of the separate kernels: as many blocks as are resident for a lookup, whose batch may well have no miss (83k new ids
+// 70 us, twice as many blocks 72, half as many 110; no miss 7.9, 8.2 and 7.9), more for a refill, whose ids are mostly misses or come late in the list (the colder ones): with 1024 blocks the host
 // link idled for the first 0.4 ms of a 4M-id call.
-constexpr uint32_t kSettleGrid = 4096;
+constexpr uint32_t kSettleGrid = 2048;
 constexpr uint32_t kRefillGrid = 8192;
 
 // ---------------------------------------------------------------------------------------
@@ -1209,33 +1234,50 @@ hipError_t launch_fill_u32(uint32_t* p, uint64_t n, uint32_t value, hipStream_t 
   return hipGetLastError();
 }
 
+// How many lookups a wavefront takes.  With few in all, latency counts, and one round (eight lookups) leaves the most
+// wavefronts: 1000 lookups of 512-byte rows 5.0 us instead of 5.9 with two rounds, 16 384 7.4 and 8.0, 32 768 11.5 and 10.4;
+// pooled by eight, one round instead of four, 256-byte rows: 4096 lookups 6.0 and 10.5 us, 32 768 8.4 and 11.7, 65 536 13.8
+// and 13.5, 2.1M 204 and 177; rows of 384 bytes and more gain at every size (512 bytes: 524 288 lookups 66 and 75 us).
+constexpr uint32_t kFewLookups1 = 16384, kFewPooled = 32768;
+// The generic kernel: as many wavefronts as the chip holds before one takes more than eight lookups, at most 32 for short
+// bags.  512-byte rows by threes, 4096 lookups 24 -> 8.5 us, 65 536 37 -> 18.5, 524 288 101 -> 81; by sixteens, 4096 lookups
+// 19.7 -> 10.7, 524 288 57 (78 with 33 lookups a wavefront: half of the lanes copy nothing in the last pass).
+constexpr uint32_t kGenericWaves = 8192;
+
 hipError_t launch_emb_probe(const EmbView& v, MissWs& ws, const IdSrc& ids, uint32_t n, uint32_t bag, uint8_t* out,
                             uint8_t* hit_flags, uint32_t batch, hipStream_t stream) {
   if (n == 0) return hipSuccess;
   const dim3 block(256);
-  if (bag == 1 && v.w_max == 32 && v.row_bytes % 128 == 0 && v.row_bytes <= 1024) {
-    ws.seg = 32 * kW32Rounds;
-    const dim3 grid((n + ws.seg - 1) / ws.seg);
-    switch (v.row_bytes / 128) {
+  const uint32_t passes = v.row_bytes / 128;
+  const bool fast = v.w_max == 32 && v.row_bytes % 128 == 0 && passes <= 8;
+  auto run = [&](auto kernel, auto... more) {
+    hipLaunchKernelGGL(kernel, dim3((n + ws.seg - 1) / ws.seg), block, 0, stream, v, ws, ids, n, more..., out, hit_flags, batch);
+  };
+  if (bag == 1 && fast) {
+    const bool few = n <= kFewLookups1;
+    ws.seg = few ? 32 : 64;
+    switch (passes) {
 #define RACER_W32_CASE(P) \
-  case P: hipLaunchKernelGGL(emb_probe_gather_w32<P>, grid, block, 0, stream, v, ws, ids, n, out, hit_flags, batch); break;
+  case P: few ? run(emb_probe_gather_w32<P, 1>) : run(emb_probe_gather_w32<P, 2>); break;
       RACER_W32_CASE(1) RACER_W32_CASE(2) RACER_W32_CASE(3) RACER_W32_CASE(4)
       RACER_W32_CASE(5) RACER_W32_CASE(6) RACER_W32_CASE(7) RACER_W32_CASE(8)
 #undef RACER_W32_CASE
     }
-  } else if ((bag == 2 || bag == 4 || bag == 8) && v.w_max == 32 && v.row_bytes % 128 == 0 && v.row_bytes <= 512) {
-    ws.seg = 128;
-    const dim3 grid((n + ws.seg - 1) / ws.seg);
-    switch (v.row_bytes / 128) {
-#define RACER_W32_BAG_CASE(P) \
-  case P: hipLaunchKernelGGL(emb_probe_gather_w32_bag<P>, grid, block, 0, stream, v, ws, ids, n, bag, out, hit_flags, batch); break;
-      RACER_W32_BAG_CASE(1) RACER_W32_BAG_CASE(2) RACER_W32_BAG_CASE(3) RACER_W32_BAG_CASE(4)
+  } else if ((bag == 2 || bag == 4 || bag == 8) && fast) {
+    const bool few = passes > 2 || n <= kFewPooled;
+    ws.seg = few ? 32 : 128;
+    switch (passes) {
+#define RACER_W32_BAG_CASE(P, R) \
+  case P: few ? run(emb_probe_gather_w32_bag1<P>, bag) : run(emb_probe_gather_w32_bag##R<P>, bag); break;
+      RACER_W32_BAG_CASE(1, 4) RACER_W32_BAG_CASE(2, 4) RACER_W32_BAG_CASE(3, 1) RACER_W32_BAG_CASE(4, 1)
+      RACER_W32_BAG_CASE(5, 1) RACER_W32_BAG_CASE(6, 1) RACER_W32_BAG_CASE(7, 1) RACER_W32_BAG_CASE(8, 1)
 #undef RACER_W32_BAG_CASE
     }
   } else {
-    const uint32_t lb = (64 / bag) * bag;
+    const uint32_t most = bag <= 8 ? 32 : 64, each = std::max(kMinStretch / 4, std::min(most, n / kGenericWaves + 1));
+    const uint32_t lb = std::min((each + bag - 1) / bag, 64 / bag) * bag;
     ws.seg = 4 * lb;
-    hipLaunchKernelGGL(emb_probe_gather, dim3((n + ws.seg - 1) / ws.seg), block, 0, stream, v, ws, ids, n, bag, lb, out, hit_flags, batch);
+    run(emb_probe_gather, bag, lb);
   }
   return hipGetLastError();
 }
@@ -1245,8 +1287,8 @@ hipError_t launch_emb_miss_path(const EmbView& v, const MissWs& ws, uint32_t n, 
   if (n == 0) return hipSuccess;
   const dim3 block(256);
   const uint32_t n_seg = (n + ws.seg - 1) / ws.seg;
-  if (n_seg <= kFewStretches) {
-    hipLaunchKernelGGL(miss_settle_sets, dim3(4 * n_seg), block, 0, stream, v, ws, bag, out, n_seg, batch);  // a unit per wavefront
+  if (n_seg <= kFewStretches || n <= kFewLookups) {
+    hipLaunchKernelGGL(miss_settle_sets, dim3((set_parts(ws) * n_seg + 3) / 4), block, 0, stream, v, ws, bag, out, n_seg, batch);  // a unit per wavefront
   } else {
     const dim3 grid(n_seg < kSettleGrid ? n_seg : kSettleGrid);  // four units (quarters of a stretch) per block and pass
     hipLaunchKernelGGL(miss_settle<false>, grid, block, 0, stream, v, ws, bag, out, n_seg, batch);

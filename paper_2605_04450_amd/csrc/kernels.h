@@ -68,6 +68,7 @@ struct HashEnt {
 // Scratch of the miss path.  A probe block lists what it finds in its own stretch of the lists: block b owns
 // [b * seg, (b + 1) * seg) of the per-lookup arrays.  Tables are keyed by the batch number, so nothing is cleared
 // between calls on one pool.
+constexpr uint32_t kMinStretch = 32;  // lookups per probe block at the least
 struct MissWs {
   uint32_t seg;             // lookups per probe block (set by the probe's launch)
   uint32_t* any;            // = batch when some block of the batch had a miss

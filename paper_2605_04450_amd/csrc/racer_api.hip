@@ -137,8 +137,8 @@ constexpr uint64_t align256(uint64_t x) { return (x + 255) & ~255ull; }
 // one fill clears them
 constexpr uint64_t kOffHents = 256;
 constexpr uint64_t kClearBytes = sizeof(racer::HashEnt) + sizeof(unsigned long long);  // per table slot
-constexpr uint64_t kOffSegCnt = kOffHents + align256(kClearBytes * kNoallocHash);   // u32 [lookups / 64 + 2]
-constexpr uint64_t kOffDefList = kOffSegCnt + align256(4 * (kNoallocMaxLookups / 64 + 2));  // u32 [lookups]
+constexpr uint64_t kOffSegCnt = kOffHents + align256(kClearBytes * kNoallocHash);   // u32 [lookups / kMinStretch + 2]
+constexpr uint64_t kOffDefList = kOffSegCnt + align256(4 * (kNoallocMaxLookups / racer::kMinStretch + 2));  // u32 [lookups]
 constexpr uint64_t kOffLoc = kOffDefList + align256(4 * kNoallocMaxLookups);        // i64 [lookups]
 constexpr uint64_t kOffHslot = kOffLoc + align256(8 * kNoallocMaxLookups);          // u32 [hash]
 constexpr uint64_t kOffRec = kOffHslot + align256(4 * kNoallocHash);                // uint4 [lookups]
@@ -298,7 +298,7 @@ int32_t ensure_miss_ws(racer_pool* p, uint64_t n, hipStream_t stream) {
   racer::MissWs& w = p->ws;
   int32_t rc;
   if ((rc = dev_alloc(&w.any, 64, true, stream))) return rc;
-  if ((rc = dev_alloc(&w.seg_cnt, cap / 64 + 2, false, stream))) return rc;
+  if ((rc = dev_alloc(&w.seg_cnt, cap / racer::kMinStretch + 2, false, stream))) return rc;
   if ((rc = dev_alloc(&w.def_list, cap, false, stream))) return rc;
   if ((rc = dev_alloc(&w.loc, cap, false, stream))) return rc;
   if ((rc = dev_alloc(&w.hents, hsize, true, stream))) return rc;

@@ -1,0 +1,31 @@
+"""GPU parity of lookups where a probe kernel's split changes: around the numbers of lookups from which a wavefront takes more
+of them, rows of up to 1024 bytes pooled in parts of 512, bags that do not divide a wavefront; a cold and a warm batch and one
+that is mostly resident each, with evictions between them and ids outside the table."""
+import numpy as np
+import pytest
+
+from paper_2605_04450_amd import synth
+from tests.test_gpu_emb import make_pair, run_batches
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("row_bytes,bag,n", [
+    (128, 1, 16384), (256, 1, 16385), (512, 1, 33), (2048, 1, 257),
+    (128, 2, 32768), (256, 8, 32776), (256, 4, 40),           # one round, four rounds, a remainder
+    (384, 2, 1002), (512, 8, 33000),
+    (640, 4, 1000), (768, 8, 264), (896, 2, 34), (1024, 8, 4104), (1024, 4, 36),
+    (64, 1, 8200), (512, 3, 24600), (512, 16, 160), (1024, 5, 655), (32, 64, 8256),  # the kernel for any row width and bag
+])
+@pytest.mark.parametrize("bf16", [True, False])
+def test_lookups_at_the_edges_of_the_splits(row_bytes, bag, n, bf16):
+    rng = np.random.default_rng(row_bytes + bag)
+    rows, d = 20000, row_bytes // (2 if bf16 else 4)
+    table = synth.make_table(rng, rows, d, bf16=bf16)
+    pool, orc = make_pair(1280, 8 * row_bytes, d, bf16, 16, 32, table, 0.5)  # 5120 slots
+    batches = [synth.zipf_ids(rng, rows, 0.9, n), synth.zipf_ids(rng, rows, 0.9, n), synth.zipf_ids(rng, rows, 1.4, n)]
+    for ids in batches:
+        ids[rng.integers(n)] = rows
+        ids[rng.integers(n)] = -1
+    run_batches(pool, orc, table, batches, bag=bag, tag="split edge")
+    pool.close()

@@ -724,6 +724,235 @@ __global__ __launch_bounds__(64 * WPB, KD <= 256 ? 4 : 2) void layer_half_fused(
 }
 
 // ---------------------------------------------------------------------------------------
+// Small steps, whose kernels are chains of a few dependent round trips: the back half of a layer and the front half of the
+// next one in one kernel (both work on rows alone), or either of them alone at the ends of a step.
+// A block takes 32 rows and a slice of the front half's columns.  It computes the whole back half of its rows (each
+// slice again: a few hundred MFMA cycles) and keeps the layer's output, as bf16 like the matrix it also stores, in LDS.
+// The four wavefronts normalise eight rows each, lanes along the rows, and leave the operand in LDS; in the products they
+// have output columns of their own, so that weight fragments go from memory straight into registers, a tile ahead, and
+// nothing is staged.  What bounds it: about six dependent steps (rows, LayerNorm, product, LayerNorm, product, stores).
+// Steps of four layers with the halves in kernels of their own and joined: 64 rows of d = 256 88 -> 65 us, 8192 rows
+// 154 -> 135; 2470 rows of d = 128 97 -> 84; 1024 rows of d = 64 63 -> 51, of d = 512 148 -> 120.
+// ---------------------------------------------------------------------------------------
+struct JoinArgs {
+  HstuDims hd;
+  uint32_t layer;          // of the front half
+  uint32_t n_rows, groups, front_tiles;  // row groups of 32; column tiles of the front half per wavefront
+  // back half
+  const uint16_t* o;
+  const uint16_t* gate;
+  const float* ln2_g;
+  const float* ln2_b;
+  const uint16_t* w2f;
+  const float* b2;
+  uint16_t* y;
+  // front half
+  const float* ln1_g;
+  const float* ln1_b;
+  const uint16_t* w1f;
+  const float* b1;
+  uint16_t* u;
+  uint16_t* q;
+  KvView kv;
+  const ReqDev* reqs;
+  const uint32_t* group_req;
+  const int32_t* page_tables;
+  const uint16_t* x;       // the back half's residual, or (alone) what the front half takes
+};
+
+template <int KD, bool BACK, bool FRONT>
+__global__ __launch_bounds__(256, KD <= 256 ? 2 : 1) void layer_join(JoinArgs a) {
+  constexpr int kSt = KD / 16;       // MFMA steps over the contraction
+  constexpr int kOwn = KD / 64;      // 16-byte pieces of a row per lane, eight lanes along a row
+  constexpr uint32_t kRowBytes = KD * 2;
+  __shared__ __attribute__((aligned(16))) uint8_t operand[32 * kRowBytes];
+  __shared__ __attribute__((aligned(16))) uint8_t rows[BACK ? 32 * kRowBytes : 16];
+  __shared__ __attribute__((aligned(16))) uint8_t otile[FRONT ? 4 * 2048 : 16];
+  const uint32_t tid = threadIdx.x, lane = tid & 63, g = lane >> 5, li = lane & 31;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t slice = blockIdx.x / a.groups, group = blockIdx.x - slice * a.groups, r0 = group * 32;
+  const HstuDims& hd = a.hd;
+  // piece c of row r sits at c ^ swizzle: the operand reads (a row per lane) of lanes that are served together meet in no bank
+  auto at = [](uint32_t r, uint32_t c) { return r * kRowBytes + 16 * (c ^ (KD >= 128 ? r & 15 : r >> 1 & 7)); };
+  const uint32_t own_r = 8 * wave + (lane >> 3), own_c = lane & 7;  // this lane's pieces: own_c + 8 k of row own_r
+  const bool own_ok = r0 + own_r < a.n_rows;
+  const uint64_t own_off = static_cast<uint64_t>(own_ok ? r0 + own_r : 0) * KD + 8 * own_c;
+  auto load_own = [&](const uint16_t* m, u32x4 (&v)[kOwn]) {
+#pragma unroll
+    for (int k = 0; k < kOwn; ++k) v[k] = *reinterpret_cast<const u32x4*>(m + own_off + 64 * k);
+  };
+  // weight fragments of a column tile
+  u32x4 w[kSt];
+  auto load_w = [&](const uint16_t* wf, uint32_t cb, int st) {
+    return *reinterpret_cast<const u32x4*>(reinterpret_cast<const uint8_t*>(wf) + static_cast<uint64_t>(cb) * (kSt * 1024) + st * 1024 + lane * 16);
+  };
+  const uint32_t front0 = FRONT ? (slice * 4 + wave) * a.front_tiles : 0;  // this wavefront's first column tile of the front half
+  const bool has_back = BACK && wave < KD / 32;
+  if (BACK && has_back) unrolled<kSt>([&](auto st) { w[st] = load_w(a.w2f, wave, st); });
+  if (FRONT && !BACK) unrolled<kSt>([&](auto st) { w[st] = load_w(a.w1f, front0, st); });
+  u32x4 v[kOwn];
+  load_own(BACK ? a.o : a.x, v);
+  u32x4 gt[BACK ? kOwn : 1];
+  if constexpr (BACK) load_own(a.gate, gt);
+
+  // ---- FRONT: where this lane's token goes (dependent loads, on their way during the back half) --------------------
+  const bool row_ok = r0 + li < a.n_rows;
+  const uint8_t* page_ptr = nullptr;
+  uint32_t tok = 0;
+  if (FRONT && row_ok) {
+    const uint32_t row = r0 + li;
+    const ReqDev rq = a.reqs[request_of(a.reqs, row, a.group_req[group], a.group_req[group + 1])];
+    uint32_t pi;
+    split_token(hd, rq.prefix_len + (row - rq.x_off), &pi, &tok);
+    const int32_t page = a.page_tables[rq.page_table_off + pi];
+    if (page < 0 || static_cast<uint32_t>(page) >= a.kv.n_pages) {
+      if (slice == 0 && wave == 0 && g == 0) atomicAdd(&a.kv.counters[ctr_index(kCtrBadPages)], 1ull);
+    } else {
+      page_ptr = a.kv.base + static_cast<uint64_t>(page) * a.kv.page_size;
+    }
+  }
+
+  // LayerNorm of row own_r (two passes in fp32, over the eight lanes that share it), times the gate, into the operand
+  auto normalise = [&](auto first, const float* ln_g, const float* ln_b) {
+    constexpr bool kFirst = decltype(first)::value;  // of the front half: bf16 rows, no gate
+    float s = 0.0f;
+    unrolled<kOwn>([&](auto k) {
+      float x[8];
+      unpack_in<kFirst>(v[k], x);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) s += x[e];
+    });
+    const float mean = group_sum<8>(s) / KD;
+    float qq = 0.0f;
+    unrolled<kOwn>([&](auto k) {
+      float x[8];
+      unpack_in<kFirst>(v[k], x);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) qq += (x[e] - mean) * (x[e] - mean);
+    });
+    const float rstd = 1.0f / sqrtf(group_sum<8>(qq) / KD + hd.eps);
+    unrolled<kOwn>([&](auto k) {
+      float x[8], gg[8], bb[8];
+      unpack_in<kFirst>(v[k], x);
+      load8(ln_g + 8 * own_c + 64 * k, gg);
+      load8(ln_b + 8 * own_c + 64 * k, bb);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] = (x[e] - mean) * rstd * gg[e] + bb[e];
+      if constexpr (!kFirst) {
+        float uv[8];
+        unpack8h(gt[k], uv);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] *= uv[e];
+      }
+      *reinterpret_cast<u32x4*>(operand + at(own_r, own_c + 8 * k)) =
+          u32x4{pack2_f16(x[0], x[1]), pack2_f16(x[2], x[3]), pack2_f16(x[4], x[5]), pack2_f16(x[6], x[7])};
+    });
+  };
+  u32x4 xr[kSt];  // the token-side operand: lane (g, li) holds elements 16 st + 8 g .. + 8 of row li
+  auto read_operand = [&]() {
+    unrolled<kSt>([&](auto st) { xr[st] = *reinterpret_cast<const u32x4*>(operand + at(li, 2 * st + g)); });
+  };
+  // acc[e]: column 32 cb + 8 (e / 4) + 4 g + e % 4 of this lane's token, on top of the bias; the registers of the weights
+  // take the next tile's as they become free
+  auto product = [&](const float* bias, uint32_t cb, const uint16_t* next_w, uint32_t next_cb) {
+    f32x16 acc;
+#pragma unroll
+    for (int r4 = 0; r4 < 4; ++r4) {
+      const float4 b = *reinterpret_cast<const float4*>(bias + cb * 32 + 8 * r4 + 4 * g);
+      acc[4 * r4] = b.x; acc[4 * r4 + 1] = b.y; acc[4 * r4 + 2] = b.z; acc[4 * r4 + 3] = b.w;
+    }
+    unrolled<kSt>([&](auto st) {
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, w[st]), __builtin_bit_cast(f16x8, xr[st]), acc, 0, 0, 0);
+      if (next_w) w[st] = load_w(next_w, next_cb, st);
+    });
+    return acc;
+  };
+
+  if constexpr (BACK) {
+    normalise(std::false_type{}, a.ln2_g, a.ln2_b);
+    __syncthreads();
+    read_operand();
+    const uint64_t res_off = static_cast<uint64_t>(row_ok ? r0 + li : 0) * KD + 4 * g;
+    for (uint32_t cb = wave; cb < KD / 32; cb += 4) {
+      u32x2 res[4];  // the residual of this lane's token, four runs of four columns
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4) res[r4] = *reinterpret_cast<const u32x2*>(a.x + res_off + 32 * cb + 8 * r4);
+      const bool last = cb + 4 >= KD / 32;
+      const f32x16 acc = product(a.b2, cb, last ? (FRONT ? a.w1f : nullptr) : a.w2f, last ? front0 : cb + 4);
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4) {
+        float y[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t x = res[r4][e >> 1];
+          y[e] = __uint_as_float(e & 1 ? x & 0xFFFF0000u : x << 16) + acc[4 * r4 + e];
+        }
+        *reinterpret_cast<u32x2*>(rows + at(li, 4 * cb + r4) + 8 * g) = u32x2{pack2_bf16(y[0], y[1]), pack2_bf16(y[2], y[3])};
+      }
+    }
+    if (FRONT && !has_back) unrolled<kSt>([&](auto st) { w[st] = load_w(a.w1f, front0, st); });
+    __syncthreads();
+    unrolled<kOwn>([&](auto k) { v[k] = *reinterpret_cast<const u32x4*>(rows + at(own_r, own_c + 8 * k)); });
+    if (slice == 0 && own_ok) unrolled<kOwn>([&](auto k) { *reinterpret_cast<u32x4*>(a.y + own_off + 64 * k) = v[k]; });
+  }
+  if constexpr (FRONT) {
+    normalise(std::true_type{}, a.ln1_g, a.ln1_b);
+    __syncthreads();
+    read_operand();
+    // stores as in the large kernel: row-major outputs turned into 16-byte pieces in wave-private LDS, V^T by lanes
+    const uint32_t st_row = lane >> 2, st_col = lane & 3;
+    const bool st_ok[2] = {r0 + st_row < a.n_rows, r0 + st_row + 16 < a.n_rows};
+    const uint64_t st_off = static_cast<uint64_t>(r0 + st_row) * KD + 8 * st_col;
+    uint8_t* kdst[2] = {nullptr, nullptr};
+#pragma unroll
+    for (int h2 = 0; h2 < 2; ++h2) {
+      const uint64_t own = reinterpret_cast<uint64_t>(page_ptr);
+      const uint32_t rl = st_row + 16 * h2;
+      const uint32_t lo = __shfl(static_cast<uint32_t>(own), rl, 64), hi = __shfl(static_cast<uint32_t>(own >> 32), rl, 64);
+      const uint32_t tk = __shfl(tok, rl, 64);
+      const uint64_t pp = (static_cast<uint64_t>(hi) << 32) | lo;
+      if (pp) kdst[h2] = reinterpret_cast<uint8_t*>(pp) + tk * 128 + 16 * st_col;
+    }
+    uint8_t* ot = &otile[0] + wave * 2048;
+    for (uint32_t t = 0; t < a.front_tiles; ++t) {
+      const uint32_t cb = front0 + t, n0 = cb * 32;
+      const bool more = t + 1 < a.front_tiles;
+      const f32x16 acc = product(a.b1, cb, more ? a.w1f : nullptr, cb + 1);
+      const uint32_t which = n0 / KD, c0 = n0 % KD;  // 0: U, 1: V, 2: Q, 3: K
+      float z[16];
+#pragma unroll
+      for (int e = 0; e < 16; ++e) z[e] = acc[e] * __builtin_amdgcn_rcpf(1.0f + __expf(-acc[e]));
+      if (which == 1) {
+        if (page_ptr) {
+          const uint32_t head = c0 / 64, cc = c0 % 64 + 4 * g;
+          uint16_t* dst = reinterpret_cast<uint16_t*>(const_cast<uint8_t*>(page_ptr) + kv_block_offset(hd, a.layer, 1, head, 2)) + tok;
+#pragma unroll
+          for (int e = 0; e < 16; ++e)
+            dst[static_cast<uint64_t>(cc + 8 * (e / 4) + e % 4) * hd.pt] = static_cast<uint16_t>(pack2_bf16(z[e], 0.0f));
+        }
+        continue;
+      }
+      const float sc = which == 2 ? 1.4426950408889634f : 1.0f;
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4)
+        *reinterpret_cast<u32x2*>(ot + li * 64 + 16 * (r4 ^ ((li >> 2) & 3)) + 8 * g) =
+            which == 0 ? u32x2{pack2_f16(z[4 * r4], z[4 * r4 + 1]), pack2_f16(z[4 * r4 + 2], z[4 * r4 + 3])}
+                       : u32x2{pack2_bf16(z[4 * r4] * sc, z[4 * r4 + 1] * sc), pack2_bf16(z[4 * r4 + 2] * sc, z[4 * r4 + 3] * sc)};
+#pragma unroll
+      for (int h2 = 0; h2 < 2; ++h2) {
+        const u32x4 o16 = *reinterpret_cast<const u32x4*>(ot + (st_row + 16 * h2) * 64 + 16 * (st_col ^ ((st_row >> 2) & 3)));
+        if (which == 3) {
+          if (kdst[h2]) *reinterpret_cast<u32x4*>(kdst[h2] + kv_block_offset(hd, a.layer, 0, c0 / 64, 2) + (c0 % 64) * 2) = o16;
+        } else if (st_ok[h2]) {
+          *reinterpret_cast<u32x4*>((which == 0 ? a.u : a.q) + st_off + 16 * KD * h2 + c0) = o16;
+        }
+      }
+      __builtin_amdgcn_wave_barrier();  // the tile is read before the next one is written
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------------------
 // bf16 paged attention on MFMA, d_h = 64.  A block of four wavefronts owns 128 consecutive
 // queries of one request and one head (32 per wavefront) and walks
 // a range of key tiles (64 keys), K [key][d_h] and V^T [d_h][key] of the tile in
@@ -1457,6 +1686,68 @@ hipError_t launch_layer_back_fused(const HstuDims& hd, const void* o, const void
   a.resid = static_cast<const uint16_t*>(x);
   a.y = static_cast<uint16_t*>(y);
   return launch_layer_half<false>(a, hd.d / 32, stream);
+}
+
+// Up to how many rows a step's layer halves are joined: a block of 32 rows reads all of W2 and its part of W1, one of
+// layer_half_fused does so for 128, and from some number of rounds of blocks on that weighs more than the launches.  Steps of
+// four layers, joined and not: d = 64, 65 536 rows 150 and 165 us, 131 072 rows 255 and 252; d = 128, 65 536 rows 264 and 278;
+// d = 256, 24 576 rows 265 and 275, 32 768 rows 329 and 323; d = 512, 8192 rows 260 and 276, 12 288 rows 461 and 431.
+bool layers_joined(const HstuDims& hd, uint32_t N) {
+  return layer_halves_fused(hd) && N <= (hd.d <= 128 ? 65536u : hd.d == 256 ? 24576u : 8192u);
+}
+
+template <bool BACK, bool FRONT>
+static void run_join(const JoinArgs& a, uint32_t blocks, hipStream_t stream) {
+  switch (a.hd.d) {
+    case 64: hipLaunchKernelGGL((layer_join<64, BACK, FRONT>), dim3(blocks), dim3(256), 0, stream, a); break;
+    case 128: hipLaunchKernelGGL((layer_join<128, BACK, FRONT>), dim3(blocks), dim3(256), 0, stream, a); break;
+    case 256: hipLaunchKernelGGL((layer_join<256, BACK, FRONT>), dim3(blocks), dim3(256), 0, stream, a); break;
+    case 512: hipLaunchKernelGGL((layer_join<512, BACK, FRONT>), dim3(blocks), dim3(256), 0, stream, a); break;
+  }
+}
+
+hipError_t launch_layer_join(const HstuDims& hd, const LayerBack* back, const LayerFront* front, const void* x, const KvView& kv,
+                             const StepLists& sl, const int32_t* page_tables, hipStream_t stream) {
+  if (sl.N == 0) return hipSuccess;
+  if (!layer_halves_fused(hd) || (!back && !front)) return hipErrorInvalidValue;
+  JoinArgs a{};
+  a.hd = hd;
+  a.n_rows = sl.N;
+  a.groups = (sl.N + 31) / 32;
+  a.x = static_cast<const uint16_t*>(x);
+  if (back) {
+    a.o = static_cast<const uint16_t*>(back->o);
+    a.gate = static_cast<const uint16_t*>(back->u);
+    a.ln2_g = back->ln_g;
+    a.ln2_b = back->ln_b;
+    a.w2f = static_cast<const uint16_t*>(back->w2f);
+    a.b2 = back->b2;
+    a.y = static_cast<uint16_t*>(back->y);
+  }
+  uint32_t slices = 1;
+  if (front) {
+    a.layer = front->layer;
+    a.ln1_g = front->ln_g;
+    a.ln1_b = front->ln_b;
+    a.w1f = static_cast<const uint16_t*>(front->w1f);
+    a.b1 = front->b1;
+    a.u = static_cast<uint16_t*>(front->u);
+    a.q = static_cast<uint16_t*>(front->q);
+    a.kv = kv;
+    a.reqs = sl.reqs;
+    a.group_req = sl.group_req;
+    a.page_tables = page_tables;
+    // Slices of the front half's columns, down to one tile per wavefront, while there are CUs without a block.  (2048 rows of
+    // d = 256: 84 us with 256 blocks, 94 with 128, 91 with 1024.)
+    const uint32_t most = hd.d / 32;  // of four wavefronts with one tile each
+    while (slices < most && a.groups * slices < 256) slices *= 2;
+    a.front_tiles = most / slices;
+  }
+  const uint32_t blocks = a.groups * slices;
+  if (back && front) run_join<true, true>(a, blocks, stream);
+  else if (back) run_join<true, false>(a, blocks, stream);
+  else run_join<false, true>(a, blocks, stream);
+  return hipGetLastError();
 }
 
 hipError_t launch_gemm_front(const HstuDims& hd, uint32_t layer, const void* xn, const void* w1, const float* b1,

@@ -189,6 +189,13 @@ hipError_t launch_layer_front_fused(const HstuDims& hd, uint32_t layer, const vo
 hipError_t launch_layer_back_fused(const HstuDims& hd, const void* o, const void* u, const float* ln_g,
                                    const float* ln_b, const void* w2f, const float* b2, const void* x, void* y,
                                    const StepLists& sl, hipStream_t stream);
+// Small steps of such models: a back half and the next layer's front half in one kernel, or one of them alone (the other
+// null).  x: the back half's residual, or what a front half alone takes.  The front's u must not be the back's.
+struct LayerBack { const void *o, *u; const float *ln_g, *ln_b; const void* w2f; const float* b2; void* y; };
+struct LayerFront { uint32_t layer; const float *ln_g, *ln_b; const void* w1f; const float* b1; void *u, *q; };
+bool layers_joined(const HstuDims& hd, uint32_t N);
+hipError_t launch_layer_join(const HstuDims& hd, const LayerBack* back, const LayerFront* front, const void* x, const KvView& kv,
+                             const StepLists& sl, const int32_t* page_tables, hipStream_t stream);
 // o_half (bf16 models): the output is written in half precision (the step's own matrix between the attention and the
 // second LayerNorm) instead of bf16 (what a caller of the attention alone gets)
 hipError_t launch_attention(const HstuDims& hd, uint32_t layer, const void* q, const float* pos,

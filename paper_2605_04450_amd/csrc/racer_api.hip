@@ -763,7 +763,8 @@ struct StepCtx {
   racer::KvView kv;
   racer::StepLists sl;
   uint64_t esize;
-  bool fused;  // layer halves in one kernel each
+  bool fused;   // layer halves in one kernel each
+  bool joined;  // a back half and the next front half in one kernel
 };
 
 // Validate the requests, build the attention work lists and the row -> request maps, ship them to the device on
@@ -799,6 +800,7 @@ int32_t prepare_step(racer_pool* p, racer_hstu* m, const racer_hstu_req* reqs, u
   sl = racer::StepLists{};
   sl.B = B;
   sl.N = static_cast<uint32_t>(N);
+  ctx->joined = racer::layers_joined(ctx->hd, sl.N);
   if (N == 0) return RACER_OK;
 
   StepScratch& w = p->step;
@@ -937,6 +939,38 @@ int32_t hstu_step(racer_pool_t* p, racer_hstu_t* m, const racer_hstu_req* reqs, 
   const bool bf16 = c.elem == RACER_ELEM_BF16;
   const uint64_t w1_layer = d * 4 * d * ctx.esize, w2_layer = d * d * ctx.esize;
   const void* x_cur = x_in;
+  if (ctx.joined) {
+    auto f = [](const void* v, uint64_t at) { return static_cast<const float*>(v) + at; };
+    auto b8 = [](const void* v) { return static_cast<const uint8_t*>(v); };
+    uint8_t* us[2] = {u, xn};  // a layer's back half reads its U while the next one's is written
+    auto front = [&](uint32_t l) {
+      return racer::LayerFront{l, f(m->w.ln1_g, l * d), f(m->w.ln1_b, l * d), b8(m->w1t) + l * w1_layer, f(m->w.b1, l * 4 * d), us[l & 1], q};
+    };
+    {
+      const racer::LayerFront fr = front(0);
+      ProfScope t(p, RACER_PROF_GEMM_FRONT, stream);
+      HIP_TRY(racer::launch_layer_join(ctx.hd, nullptr, &fr, x_in, ctx.kv, sl, page_tables, stream));
+    }
+    for (uint32_t l = 0; l < c.L; ++l) {
+      {
+        ProfScope t(p, RACER_PROF_ATTENTION, stream);
+        HIP_TRY(racer::launch_attention(ctx.hd, l, q, m->pos_s, m->time_s, ctx.kv, sl, page_tables, ts, o, /*o_half=*/true, stream));
+      }
+      if (sl.n_groups) {
+        ProfScope t(p, RACER_PROF_ATTN_REDUCE, stream);
+        HIP_TRY(racer::launch_attention_reduce(ctx.hd, sl, o, /*o_half=*/true, stream));
+      }
+      const bool last = l + 1 == c.L;
+      void* x_next = last ? out : static_cast<void*>(xb[l & 1]);
+      const racer::LayerBack bk{o, us[l & 1], f(m->w.ln2_g, l * d), f(m->w.ln2_b, l * d), b8(m->w2t) + l * w2_layer, f(m->w.b2, l * d), x_next};
+      racer::LayerFront fr{};
+      if (!last) fr = front(l + 1);
+      ProfScope t(p, RACER_PROF_GEMM_BACK, stream);
+      HIP_TRY(racer::launch_layer_join(ctx.hd, &bk, last ? nullptr : &fr, x_cur, ctx.kv, sl, page_tables, stream));
+      x_cur = x_next;
+    }
+    return RACER_OK;
+  }
   for (uint32_t l = 0; l < c.L; ++l) {
     void* x_next = (l + 1 == c.L) ? out : static_cast<void*>(xb[l & 1]);
     const float* ln1_g = static_cast<const float*>(m->w.ln1_g) + l * d;

@@ -1,0 +1,33 @@
+"""GPU parity of steps whose layer halves are joined in one kernel, where its split changes: the number of column slices, the
+last group of 32 rows, and the number of rows from which the halves are kernels of their own.  Every request is a copy of the
+first one, which the oracle computes, and gets the same rows; two layers, so that a back half feeds a front half."""
+import numpy as np
+import pytest
+
+from tests.test_gpu_hstu import Case, assert_close
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d,rows", [
+    (64, 1), (64, 31), (64, 4096), (64, 4097), (64, 65536), (64, 65537),
+    (128, 33), (128, 2048), (128, 2081), (128, 8192), (128, 65536), (128, 65537),
+    (256, 32), (256, 1024), (256, 1025), (256, 4097), (256, 8191), (256, 24576), (256, 24577),
+    (512, 65), (512, 512), (512, 513), (512, 2049), (512, 8192), (512, 8193),
+])
+def test_copies_of_one_request_get_the_same_rows(d, rows):
+    T = min(rows, 37)
+    n = (rows + T - 1) // T
+    new = [T] * n
+    new[-1] = rows - T * (n - 1)
+    c = Case(24, 2, d, d // 64, 24, True, 100, 16, 64.0, (n * 4 + 31) // 32 * 32 + 32)
+    reqs, pts, ts, x = c.inputs([0] * n, new)
+    for r in reqs:
+        ts[r[3]:r[3] + r[1]] = ts[:r[1]]
+        x[r[4]:r[4] + r[1]] = x[:r[1]]
+    got = c.run_gpu(reqs, pts, ts, x)
+    assert_close(got[:T], c.run_oracle(reqs[:1], pts, ts, x[:T]), True, "first copy")
+    for r in reqs[1:]:
+        assert np.array_equal(got[r[4]:r[4] + r[1]], got[:r[1]]), r
+    assert c.pool.stats()["bad_pages"] == 0
+    c.close()

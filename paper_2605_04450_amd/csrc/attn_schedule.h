@@ -111,14 +111,21 @@ class AttnSchedule {
       }
     const uint32_t page_cap = attn_page_cap(page_tokens);
     uint64_t share = std::max<uint64_t>(kAttnMinTiles + kAttnItemCost, (total * H + kAttnBlocks - 1) / kAttnBlocks);
-    // Cut at all?  Then into the smallest pieces that all places together can take, what the pieces cost included.
+    // Cut at all?  Then into the smallest pieces of which all places together can take one each, or, if the query tiles alone
+    // fill them, into pieces of a place's share with what the pieces cost included.
     const bool cut = largest + kAttnItemCost > share + share / 4 || largest > page_cap;
-    if (cut)
-      for (;; share += 1 + share / 32) {
-        uint64_t all = 0;
-        for (const AttnItem& t : items) all += tiles_of(t) + kAttnItemCost * ((tiles_of(t) + share - kAttnItemCost - 1) / (share - kAttnItemCost));
-        if (all * H <= share * kAttnBlocks) break;
+    if (cut) {
+      const bool one_each = 2 * static_cast<uint64_t>(items.size()) * H <= kAttnBlocks;
+      for (;; share += one_each ? 1 : 1 + share / 32) {
+        uint64_t count = 0, all = 0;
+        for (const AttnItem& t : items) {
+          const uint64_t n = (tiles_of(t) + share - kAttnItemCost - 1) / (share - kAttnItemCost);
+          count += n;
+          all += tiles_of(t) + kAttnItemCost * n;
+        }
+        if (one_each ? count * H <= kAttnBlocks : all * H <= share * kAttnBlocks) break;
       }
+    }
     const uint32_t piece = static_cast<uint32_t>(std::min<uint64_t>(share - kAttnItemCost, page_cap));
     const uint32_t whole = cut ? piece : 0xFFFFFFFFu;  // up to this size nothing is cut
     // units: query tiles of one request (cut ones: their pieces with the same keys), and, of one that is a large part of

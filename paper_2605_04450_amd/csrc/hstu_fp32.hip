@@ -16,8 +16,8 @@ __device__ __forceinline__ float wave_sum(float v) {
 // ---------------------------------------------------------------------------------------
 // Layer halves.  FRONT: [U|V|Q|K] = SiLU(LN1(X) W1 + b1), K and V into the pages;  BACK: Y = X + (LN2(O) * U) W2 + b2.
 // A block computes 64 output columns of 8 rows: a wavefront normalises its two rows into LDS (which no other wavefront
-// reads: no barrier) and then owns the 64 columns of them, one per lane; the first 16 rows of W are already on their way
-// during the LayerNorm.  8 rows a block give 512 blocks for 1024 tokens of a d = 64 model.
+// reads: no barrier) and then owns the 64 columns of them, one per lane; the first 16 rows of W, and
+// what the stores need, are already on their way during the LayerNorm.  8 rows a block give 512 blocks for 1024 tokens of a d = 64 model.
 // 1024 tokens, d = 64: front 9 us (LayerNorm and product as two kernels, one thread per output: 4 + 13), back 5 us (4 + 9).
 // ---------------------------------------------------------------------------------------
 constexpr uint32_t kRowsPerWave = 2, kRowsPerBlock = 4 * kRowsPerWave, kMaxWidth = 1024, kAhead = 16;
@@ -55,6 +55,27 @@ __global__ __launch_bounds__(256) void layer_half_f32(HalfArgsF32 a) {
   uint32_t row[kRowsPerWave];
 #pragma unroll
   for (uint32_t r = 0; r < kRowsPerWave; ++r) row[r] = row0 + r < a.N ? row0 + r : row0;
+  // what the end needs, on its way during the LayerNorm and the product: bias, residual, where K and V of the rows go
+  const float bias = a.bias[col_ok ? col : 0];
+  const uint32_t which = col / d, c_out = col % d;  // FRONT: 0: U, 1: V, 2: Q, 3: K
+  float resid[kRowsPerWave];
+  const uint8_t* page_ptr[kRowsPerWave];  // of a row's page (nullptr: a bad page id)
+  uint32_t tok[kRowsPerWave];
+#pragma unroll
+  for (uint32_t r = 0; r < kRowsPerWave; ++r) {
+    resid[r] = 0.0f;
+    page_ptr[r] = nullptr;
+    tok[r] = 0;
+    if (!FRONT) {
+      if (col_ok) resid[r] = a.resid[static_cast<uint64_t>(row[r]) * d + col];
+    } else if (col_ok && (which & 1)) {
+      const ReqDev rq = a.reqs[request_of(a.reqs, row[r], 0, a.B - 1)];
+      uint32_t pi;
+      split_token(a.hd, rq.prefix_len + (row[r] - rq.x_off), &pi, &tok[r]);
+      const int32_t page = a.page_tables[rq.page_table_off + pi];
+      if (page >= 0 && static_cast<uint32_t>(page) < a.kv.n_pages) page_ptr[r] = a.kv.base + static_cast<uint64_t>(page) * a.kv.page_size;
+    }
+  }
   float s[kRowsPerWave], qq[kRowsPerWave];
 #pragma unroll
   for (uint32_t r = 0; r < kRowsPerWave; ++r) s[r] = qq[r] = 0.0f;
@@ -111,40 +132,32 @@ __global__ __launch_bounds__(256) void layer_half_f32(HalfArgsF32 a) {
     for (uint32_t k = 0; k < kAhead; ++k) wr[k] = wn[k];
   }
   if (!col_ok) return;
-  const float bias = a.bias[col];
 #pragma unroll
   for (uint32_t r = 0; r < kRowsPerWave; ++r) {
     if (row0 + r >= a.N) continue;
     const float sum = (acc[r][0] + acc[r][1]) + (acc[r][2] + acc[r][3]);
     if (!FRONT) {
-      const uint64_t i = static_cast<uint64_t>(row[r]) * d + col;
-      a.y[i] = a.resid[i] + sum + bias;
+      a.y[static_cast<uint64_t>(row[r]) * d + col] = resid[r] + sum + bias;
       continue;
     }
     const float z = silu(sum + bias);
-    const uint32_t which = col / d, c = col % d;  // 0: U, 1: V, 2: Q, 3: K
-    if (which == 0 || which == 2) {
-      (which == 0 ? a.u : a.q)[static_cast<uint64_t>(row[r]) * d + c] = z;
+    if ((which & 1) == 0) {
+      (which == 0 ? a.u : a.q)[static_cast<uint64_t>(row[r]) * d + c_out] = z;
       continue;
     }
-    const ReqDev rq = a.reqs[request_of(a.reqs, row[r], 0, a.B - 1)];
-    uint32_t pi, tok;
-    split_token(a.hd, rq.prefix_len + (row[r] - rq.x_off), &pi, &tok);
-    const int32_t page = a.page_tables[rq.page_table_off + pi];
-    if (page < 0 || static_cast<uint32_t>(page) >= a.kv.n_pages) {
-      if (c == 0) atomicAdd(&a.kv.counters[ctr_index(kCtrBadPages)], 1ull);
+    if (!page_ptr[r]) {
+      if (c_out == 0) atomicAdd(&a.kv.counters[ctr_index(kCtrBadPages)], 1ull);
       continue;
     }
-    const uint32_t head = c / a.hd.dh, cc = c % a.hd.dh;
-    float* blk = reinterpret_cast<float*>(a.kv.base + static_cast<uint64_t>(page) * a.kv.page_size +
-                                          kv_block_offset(a.hd, a.layer, which == 1 ? 1 : 0, head, 4));
-    if (which == 3) blk[static_cast<uint64_t>(tok) * a.hd.dh + cc] = z;  // K: [token][d_h]
-    else blk[static_cast<uint64_t>(cc) * a.hd.pt + tok] = z;             // V: [d_h][token]
+    const uint32_t head = c_out / a.hd.dh, cc = c_out % a.hd.dh;
+    float* blk = reinterpret_cast<float*>(const_cast<uint8_t*>(page_ptr[r]) + kv_block_offset(a.hd, a.layer, which == 1 ? 1 : 0, head, 4));
+    if (which == 3) blk[static_cast<uint64_t>(tok[r]) * a.hd.dh + cc] = z;  // K: [token][d_h]
+    else blk[static_cast<uint64_t>(cc) * a.hd.pt + tok[r]] = z;             // V: [d_h][token]
   }
 }
 
 // ---------------------------------------------------------------------------------------
-// Paged attention: one block per (16 queries of one request, head), d_h <= 16 * NS.  The four wavefronts take groups of 16
+// Paged attention: one block per (16 queries of one request, head), d_h <= 16 * NS.  The wavefronts take groups of 16
 // keys in turn and add their sums at the end; nothing is shared before that, so there is no barrier in the loop and a
 // wavefront's loads for the next group fly during the current one.  Both products run on v_mfma_f32_16x16x4_f32 (full
 // fp32 multiply-adds): S^T = K Q^T leaves a lane with one query (lane % 16) and the four keys 4 * (lane / 16) + r; these
@@ -157,13 +170,13 @@ __global__ __launch_bounds__(256) void layer_half_f32(HalfArgsF32 a) {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 static_assert(kF32Queries == 16, "one MFMA tile of queries");
 
-template <int NS>
-__global__ __launch_bounds__(256) void attention_f32(HstuDims hd, uint32_t layer, const float* __restrict__ q,
+template <int NS, uint32_t WAVES>
+__global__ __launch_bounds__(64 * WAVES) void attention_f32(HstuDims hd, uint32_t layer, const float* __restrict__ q,
                                                      const float* __restrict__ pos, const float* __restrict__ time,
                                                      KvView kv, const ReqDev* __restrict__ reqs,
                                                      const F32Tile* __restrict__ tiles, const int32_t* __restrict__ page_tables,
                                                      const long long* __restrict__ ts, float* __restrict__ o) {
-  __shared__ __attribute__((aligned(16))) f32x4 sums[3][NS][64];
+  __shared__ __attribute__((aligned(16))) f32x4 sums[WAVES - 1][NS][64];
   __shared__ float times[64];
   const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, li = lane & 15, h = blockIdx.y;
   const F32Tile tile = tiles[blockIdx.x];
@@ -271,8 +284,8 @@ __global__ __launch_bounds__(256) void attention_f32(HstuDims hd, uint32_t layer
   Group cur, next;
   if (wave < n_groups) fetch(16 * wave, cur);
   __syncthreads();  // times is there
-  for (uint32_t k = wave; k < n_groups; k += 4) {
-    if (k + 4 < n_groups) fetch(16 * (k + 4), next);
+  for (uint32_t k = wave; k < n_groups; k += WAVES) {
+    if (k + WAVES < n_groups) fetch(16 * (k + WAVES), next);
     f32x4 s4 = {cur.bias[0], cur.bias[1], cur.bias[2], cur.bias[3]};
 #pragma unroll
     for (uint32_t e = 0; e < 4; ++e) s4[e] += times[time_bucket(ts_p - cur.t[e], hd.n_time)];
@@ -307,7 +320,7 @@ __global__ __launch_bounds__(256) void attention_f32(HstuDims hd, uint32_t layer
 #pragma unroll
   for (uint32_t s = 0; s < NS; ++s) {
 #pragma unroll
-    for (uint32_t w = 0; w < 3; ++w) acc[s] += sums[w][s][lane];
+    for (uint32_t w = 0; w < WAVES - 1; ++w) acc[s] += sums[w][s][lane];
     float* dst = o + static_cast<uint64_t>(rq.x_off + q0 + li) * hd.d + h * dh;
 #pragma unroll
     for (uint32_t e = 0; e < 4; ++e)
@@ -329,17 +342,29 @@ hipError_t launch_layer_half_f32(const HstuDims& hd, uint32_t layer, bool front,
   return hipGetLastError();
 }
 
+// Steps of few query tiles take about a wavefront per group of 16 keys, up to 16 a block (eight where the heads are wider
+// than 32: 16 would spill): 4 requests x 256 tokens, 2 heads, 13.3 us with four, 11.1 with eight, 10.4 with 16.
+constexpr uint64_t kF32FewBlocks = 512;
 hipError_t launch_attention_f32(const HstuDims& hd, uint32_t layer, const float* q, const float* pos, const float* time, const KvView& kv,
                                 const StepLists& sl, const int32_t* page_tables, const int64_t* ts, float* o, hipStream_t stream) {
   if (sl.n_f32_tiles == 0) return hipSuccess;
   if (hd.dh > 64) return hipErrorInvalidValue;
-  const dim3 grid(sl.n_f32_tiles, hd.H), block(256);
+  const dim3 grid(sl.n_f32_tiles, hd.H);
   const long long* t = reinterpret_cast<const long long*>(ts);
+  const bool few = static_cast<uint64_t>(sl.n_f32_tiles) * hd.H <= kF32FewBlocks;
+  const uint32_t waves = !few || sl.longest <= 64 ? 4 : sl.longest <= 192 ? 8 : 16;
+  auto run = [&](auto kernel, uint32_t w) {
+    hipLaunchKernelGGL(kernel, grid, dim3(64 * w), 0, stream, hd, layer, q, pos, time, kv, sl.reqs, sl.f32_tiles, page_tables, t, o);
+  };
   switch ((hd.dh + 15) / 16) {
-    case 1: hipLaunchKernelGGL(attention_f32<1>, grid, block, 0, stream, hd, layer, q, pos, time, kv, sl.reqs, sl.f32_tiles, page_tables, t, o); break;
-    case 2: hipLaunchKernelGGL(attention_f32<2>, grid, block, 0, stream, hd, layer, q, pos, time, kv, sl.reqs, sl.f32_tiles, page_tables, t, o); break;
-    case 3: hipLaunchKernelGGL(attention_f32<3>, grid, block, 0, stream, hd, layer, q, pos, time, kv, sl.reqs, sl.f32_tiles, page_tables, t, o); break;
-    default: hipLaunchKernelGGL(attention_f32<4>, grid, block, 0, stream, hd, layer, q, pos, time, kv, sl.reqs, sl.f32_tiles, page_tables, t, o); break;
+#define RACER_F32_CASE(S, MOST)                                    \
+  case S:                                                          \
+    if (waves == 4) run(attention_f32<S, 4>, 4);                   \
+    else if (waves == 8 || MOST == 8) run(attention_f32<S, 8>, 8); \
+    else run(attention_f32<S, MOST>, MOST);                        \
+    break;
+    RACER_F32_CASE(1, 16) RACER_F32_CASE(2, 16) RACER_F32_CASE(3, 8) RACER_F32_CASE(4, 8)
+#undef RACER_F32_CASE
   }
   return hipGetLastError();
 }

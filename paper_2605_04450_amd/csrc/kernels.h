@@ -153,6 +153,7 @@ struct StepLists {
   const uint32_t* group_req;   // request of rows 0, 32, .. and, behind the last of these, of the last row
   const F32Tile* f32_tiles;    // fp32 models
   uint32_t n_f32_tiles;
+  uint32_t longest;            // tokens of the longest request, cached ones included
   uint32_t B, N;
 };
 

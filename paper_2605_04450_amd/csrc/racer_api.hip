@@ -881,6 +881,7 @@ int32_t prepare_step(racer_pool* p, racer_hstu* m, const racer_hstu_req* reqs, u
   sl.group_req = reinterpret_cast<const uint32_t*>(p->hl_dev + off_group_req);
   sl.f32_tiles = reinterpret_cast<const racer::F32Tile*>(p->hl_dev + off_f32_tiles);
   sl.n_f32_tiles = static_cast<uint32_t>(w.f32_tiles.size());
+  sl.longest = longest;
   // the lists to the device, and which requests' timestamps never decrease (the attention kernels' 32-bit time paths rely on it)
   HIP_TRY(racer::launch_begin_step(sl, longest, ts, p->d_counters, by_argument ? &arg : nullptr, hbuf, p->hl_dev, total, stream));
   if (!by_argument && (rc = p->hstage.mark(which, stream))) return rc;

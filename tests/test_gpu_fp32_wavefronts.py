@@ -1,0 +1,37 @@
+"""GPU parity of the fp32 attention where the number of wavefronts per block changes (longest request of 64 and 192 tokens, 512
+blocks) and around it, for all widths of a head, with keys that do not fill the last wavefront's group."""
+import numpy as np
+import pytest
+
+from tests.test_gpu_hstu import Case, assert_close
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d,H", [(16, 1), (64, 2), (48, 1), (128, 2)])
+@pytest.mark.parametrize("prefix,new", [
+    ([0, 0], [64, 3]), ([0, 0], [65, 17]), ([0, 0, 0], [192, 1, 33]), ([0, 0], [193, 16]),
+    ([300, 0, 17], [40, 260, 1]), ([1021], [1]),
+])
+def test_sequences_around_the_borders(d, H, prefix, new):
+    c = Case(41, 1, d, H, 8, False, 300, 16, 300.0, 512)
+    total = [p + n for p, n in zip(prefix, new)]
+    reqs, pts, ts, x = c.inputs([0] * len(new), total)
+    if any(prefix):
+        offs = np.concatenate([[0], np.cumsum(prefix)])
+        first = [(0, p, r[2], r[3], int(o)) for p, r, o in zip(prefix, reqs, offs)]
+        xa = np.concatenate([x[r[4]: r[4] + p] for p, r in zip(prefix, reqs)])
+        assert_close(c.run_gpu(first, pts, ts, xa), c.run_oracle(first, pts, ts, xa), False, "cached part")
+    offs = np.concatenate([[0], np.cumsum(new)])
+    second = [(p, n, r[2], r[3], int(o)) for p, n, r, o in zip(prefix, new, reqs, offs)]
+    xb = np.concatenate([x[r[4] + p: r[4] + p + n] for p, n, r in zip(prefix, new, reqs)])
+    assert_close(c.run_gpu(second, pts, ts, xb), c.run_oracle(second, pts, ts, xb), False, "new part")
+    c.close()
+
+
+@pytest.mark.parametrize("requests", [64, 65])
+def test_around_512_blocks(requests):
+    c = Case(42, 1, 32, 2, 8, False, 100, 16, 100.0, 1280)
+    reqs, pts, ts, x = c.inputs([0] * requests, [64] * (requests - 1) + [70])
+    assert_close(c.run_gpu(reqs, pts, ts, x), c.run_oracle(reqs, pts, ts, x), False, "%d requests" % requests)
+    c.close()

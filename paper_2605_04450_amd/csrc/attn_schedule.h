@@ -42,19 +42,22 @@ struct ReqDev {  // device copy of one request
 struct AttnItem {
   uint32_t prefix_len, new_len, page_table_off, ts_off, x_off;  // of the request
   uint32_t req, qt;
+  uint32_t slot0, pieces;  // cut into more than one: piece k of head h leaves its partial output in slot slot0 + h * pieces + k
 };
 
-// What one workgroup does: key tiles [kt_begin, kt_end) of a query tile for one head.  slot: where its fp32 partial output goes,
-// kDirect: it covers all keys and writes the output itself.
+// What one workgroup does: piece k of a query tile (key tiles k * piece up to the next piece, the last one up to the last
+// tile) for one head.  A list entry is as short as it can be: steps whose lists fit a kernel argument are the ones that
+// need no staging, and that a graph can capture.
 struct AttnWork {
-  uint32_t item_head, kt_begin, kt_end, slot;  // item << 4 | head
+  uint32_t item_head, k;  // item << 4 | head
 };
-constexpr uint32_t kDirect = 0xFFFFFFFFu;
 constexpr uint32_t kMaxHeads = 16;
 
-struct AttnGroup {  // a query tile and head whose partial outputs are slots slot0 .. slot0 + pieces - 1
-  uint32_t item_head, slot0, pieces;
-};
+// key tiles that a query tile sees
+constexpr uint32_t attn_tiles(const AttnItem& t) {
+  const uint32_t last = t.qt * 128 + 127 < t.new_len ? t.qt * 128 + 127 : t.new_len - 1;
+  return (t.prefix_len + last) / 64 + 1;
+}
 
 // key tiles whose pages an item's slice of the page table can name
 inline uint32_t attn_page_cap(uint32_t page_tokens) {
@@ -76,7 +79,8 @@ class AttnSchedule {
   std::vector<AttnWork> work;      // die x's list: entries [begin[x], begin[x + 1])
   uint32_t begin[kXcds + 1] = {};
   uint32_t blocks = 0;             // workgroups to launch
-  std::vector<AttnGroup> groups;
+  std::vector<uint32_t> groups;    // the query tiles whose partial outputs are to be added up
+  uint32_t piece = 0;              // key tiles of a piece
   uint32_t n_slots = 0;
 
   // Memory for steps within these bounds (touched, so that the first of them pays for none of it).
@@ -89,11 +93,10 @@ class AttnSchedule {
     have(items, b.items);
     have(work, b.work);
     have(sorted_, b.work);
-    have(groups, b.items * H);
+    have(groups, b.items);
     have(atoms_, b.work / H + b.items);
     have(units_, b.work / H + b.items);
     have(die_, b.work + b.items * H);
-    have(slot0_, b.items * H);
   }
 
   void build(const ReqDev* reqs, uint32_t B, uint32_t H, uint32_t page_tokens) {
@@ -104,8 +107,8 @@ class AttnSchedule {
     for (uint32_t r = 0; r < B; ++r)
       for (uint32_t q0 = 0; q0 < reqs[r].new_len; q0 += 128) {
         const ReqDev& q = reqs[r];
-        items.push_back({q.prefix_len, q.new_len, q.page_table_off, q.ts_off, q.x_off, r, q0 / 128});
-        const uint32_t n = tiles_of(items.back());
+        items.push_back({q.prefix_len, q.new_len, q.page_table_off, q.ts_off, q.x_off, r, q0 / 128, 0, 1});
+        const uint32_t n = attn_tiles(items.back());
         total += n + kAttnItemCost;
         largest = std::max(largest, n);
       }
@@ -119,29 +122,36 @@ class AttnSchedule {
       for (;; share += one_each ? 1 : 1 + share / 32) {
         uint64_t count = 0, all = 0;
         for (const AttnItem& t : items) {
-          const uint64_t n = (tiles_of(t) + share - kAttnItemCost - 1) / (share - kAttnItemCost);
+          const uint64_t n = (attn_tiles(t) + share - kAttnItemCost - 1) / (share - kAttnItemCost);
           count += n;
-          all += tiles_of(t) + kAttnItemCost * n;
+          all += attn_tiles(t) + kAttnItemCost * n;
         }
         if (one_each ? count * H <= kAttnBlocks : all * H <= share * kAttnBlocks) break;
       }
     }
-    const uint32_t piece = static_cast<uint32_t>(std::min<uint64_t>(share - kAttnItemCost, page_cap));
-    const uint32_t whole = cut ? piece : 0xFFFFFFFFu;  // up to this size nothing is cut
+    piece = static_cast<uint32_t>(std::min<uint64_t>(share - kAttnItemCost, page_cap));
+    if (cut)
+      for (uint32_t i = 0; i < items.size(); ++i) {
+        AttnItem& t = items[i];
+        t.pieces = pieces_of(attn_tiles(t), piece, page_cap);
+        if (t.pieces < 2) continue;
+        t.slot0 = n_slots;
+        n_slots += t.pieces * H;
+        groups.push_back(i);
+      }
     // units: query tiles of one request (cut ones: their pieces with the same keys), and, of one that is a large part of
     // the whole step, runs of them
     for (uint32_t i0 = 0; i0 < items.size();) {
       uint32_t i1 = i0, most = 0;
-      while (i1 < items.size() && items[i1].req == items[i0].req) most = std::max(most, pieces_of(tiles_of(items[i1++]), whole, piece, page_cap));
+      while (i1 < items.size() && items[i1].req == items[i0].req) most = std::max(most, items[i1++].pieces);
       for (uint32_t k = 0; k < most; ++k) {
         Unit u{0, 0, static_cast<uint32_t>(atoms_.size()), 0};
         for (uint32_t i = i1; i-- > i0;) {  // the largest first
-          const uint32_t n = tiles_of(items[i]), pieces = pieces_of(n, whole, piece, page_cap);
-          if (k >= pieces) continue;
-          const uint32_t b = pieces > 1 ? k * piece : 0, e = k + 1 == pieces ? n : b + piece;
-          atoms_.push_back({i, b, e, pieces > 1});
-          u.weight += e - b + kAttnItemCost;
-          u.largest = std::max(u.largest, e - b);
+          if (k >= items[i].pieces) continue;
+          atoms_.push_back({i, k});
+          const uint32_t size = size_of(items[i], k);
+          u.weight += size + kAttnItemCost;
+          u.largest = std::max(u.largest, size);
           ++u.n;
           if (u.weight > total / (4 * kXcds)) {
             units_.push_back(u);
@@ -178,14 +188,14 @@ class AttnSchedule {
         uint32_t& to = at[die_[u * H + h]];
         for (uint32_t a = 0; a < units_[u].n; ++a) {
           const Atom& t = atoms_[units_[u].atom0 + a];
-          work[to++] = {t.item << 4 | h, t.kt_begin, t.kt_end, t.part ? 0 : kDirect};
+          work[to++] = {t.item << 4 | h, t.k};
         }
       }
     if (!cut) return;
     sorted_.resize(work.size());
     for (uint32_t x = 0; x < kXcds; ++x) {  // by size, else in the order they have
-      count_.assign(whole + kAttnMinTiles + 1, 0);
-      auto place = [&](const AttnWork& w) -> uint32_t& { return count_[whole + kAttnMinTiles - (w.kt_end - w.kt_begin)]; };
+      count_.assign(piece + kAttnMinTiles + 1, 0);
+      auto place = [&](const AttnWork& w) -> uint32_t& { return count_[piece + kAttnMinTiles - size_of(items[w.item_head >> 4], w.k)]; };
       for (uint32_t i = begin[x]; i < begin[x + 1]; ++i) ++place(work[i]);
       uint32_t to = begin[x];
       for (uint32_t& c : count_) {
@@ -196,38 +206,21 @@ class AttnSchedule {
       for (uint32_t i = begin[x]; i < begin[x + 1]; ++i) sorted_[place(work[i])++] = work[i];
     }
     work.swap(sorted_);
-    // slots of the partial outputs, those of a query tile and head in the order of the keys
-    slot0_.assign(items.size() * static_cast<uint64_t>(H), 0);
-    for (uint32_t i = 0; i < items.size(); ++i) {
-      const uint32_t n = pieces_of(tiles_of(items[i]), whole, piece, page_cap);
-      if (n < 2) continue;
-      for (uint32_t h = 0; h < H; ++h) {
-        groups.push_back({i << 4 | h, n_slots, n});
-        slot0_[static_cast<uint64_t>(i) * H + h] = n_slots;
-        n_slots += n;
-      }
-    }
-    for (AttnWork& w : work)
-      if (w.slot != kDirect) w.slot = slot0_[static_cast<uint64_t>(w.item_head >> 4) * H + (w.item_head & 15)] + w.kt_begin / piece;
   }
 
  private:
-  struct Atom { uint32_t item, kt_begin, kt_end; bool part; };
+  struct Atom { uint32_t item, k; };
   struct Unit { uint64_t weight; uint32_t largest, atom0, n; };
   std::vector<Atom> atoms_;
   std::vector<Unit> units_;
   std::vector<uint8_t> die_;  // [unit][head]
-  std::vector<uint32_t> slot0_, count_;
+  std::vector<uint32_t> count_;
   std::vector<AttnWork> sorted_;
 
-  static uint32_t tiles_of(const AttnItem& t) {
-    const uint32_t last = t.prefix_len + std::min(t.qt * 128 + 127, t.new_len - 1);
-    return last / 64 + 1;
-  }
+  uint32_t size_of(const AttnItem& t, uint32_t k) const { return k + 1 == t.pieces ? attn_tiles(t) - k * piece : piece; }
   // How many pieces a query tile of n key tiles is cut into, at multiples of `piece`; a last piece of less than
   // kAttnMinTiles joins the one before it.
-  static uint32_t pieces_of(uint32_t n, uint32_t whole, uint32_t piece, uint32_t page_cap) {
-    if (n <= whole) return 1;
+  static uint32_t pieces_of(uint32_t n, uint32_t piece, uint32_t page_cap) {
     uint32_t k = (n + piece - 1) / piece;
     if (k > 1 && n - (k - 1) * piece < kAttnMinTiles && n - (k - 2) * piece <= page_cap) --k;
     return k;

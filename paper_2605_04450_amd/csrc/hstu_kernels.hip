@@ -1106,7 +1106,8 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
     for (int e = 0; e < 16; ++e) oacc[b2][e] = 0.0f;
 
   const uint64_t koff = kv_block_offset(hd, layer, 0, h, 2), voff = kv_block_offset(hd, layer, 1, h, 2);
-  const uint32_t kt_begin = scalar(wk.kt_begin), kt_end = scalar(wk.kt_end);
+  const uint32_t kt_begin = scalar(wk.k) * dies.piece;
+  const uint32_t kt_end = scalar(wk.k + 1 == item.pieces ? attn_tiles(item) : kt_begin + dies.piece);
   // the item's slice of the page table goes to LDS once, so that a tile fetch is a single
   // global round trip instead of two dependent ones
   uint32_t page0, unused_ip;
@@ -1413,10 +1414,10 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
   }
   // oacc[db][e]: d_h element 32*db + 8*(e/4) + 4*g + e%4 of the lane's query; undo the log2 e scaling, apply 1/n
   const float sc = hd.inv_n * kLn2;
-  if (wk.slot != kDirect) {
+  if (item.pieces > 1) {
     // a piece of a query tile: fp32 partial [slot][query][d_h], summed by attention_reduce
     if (!q_ok) return;
-    float* prow = partials + (static_cast<uint64_t>(wk.slot) * kAttnQ + ql) * 64;
+    float* prow = partials + (static_cast<uint64_t>(item.slot0 + h * item.pieces + wk.k) * kAttnQ + ql) * 64;
 #pragma unroll
     for (int db = 0; db < 2; ++db)
 #pragma unroll
@@ -1444,23 +1445,22 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
 
 // Sum the fp32 partials of a query tile that was cut, in the order of their slots, and write the output.
 __global__ __launch_bounds__(256) void attention_reduce(HstuDims hd, const AttnItem* __restrict__ items,
-                                                        const AttnGroup* __restrict__ groups,
+                                                        const uint32_t* __restrict__ groups,
                                                         const float* __restrict__ partials, uint16_t* __restrict__ o,
                                                         uint32_t o_half) {
-  // blockIdx.x = query tile and head; blockIdx.y = which 16 of the tile's query rows: a thread owns one 16-byte piece of
+  // blockIdx.x = cut query tile and head; blockIdx.y = which 16 of the tile's query rows: a thread owns one 16-byte piece of
   // one row, so that the pieces' loads of a whole tile are in flight at once
-  const AttnGroup gr = groups[blockIdx.x];
-  const AttnItem it = items[gr.item_head >> 4];
-  const uint32_t h = gr.item_head & 15;
+  const AttnItem it = items[groups[blockIdx.x / hd.H]];
+  const uint32_t h = blockIdx.x % hd.H;
   const uint32_t idx = blockIdx.y * 256 + threadIdx.x;
   const uint32_t row = idx >> 4, c4 = idx & 15;
   const uint32_t qi = it.qt * kAttnQ + row;
   if (row >= kAttnQ || qi >= it.new_len) return;
-  const float* src = partials + (static_cast<uint64_t>(gr.slot0) * kAttnQ + row) * 64 + 4 * c4;
+  const float* src = partials + (static_cast<uint64_t>(it.slot0 + h * it.pieces) * kAttnQ + row) * 64 + 4 * c4;
   constexpr uint64_t step = kAttnQ * 64;  // from one piece's partial to the next
   float4 acc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
   uint32_t k = 0;
-  for (; k + 4 <= gr.pieces; k += 4) {  // four loads in flight; the sum keeps their order
+  for (; k + 4 <= it.pieces; k += 4) {  // four loads in flight; the sum keeps their order
     const float4 v0 = *reinterpret_cast<const float4*>(src + (k + 0) * step);
     const float4 v1 = *reinterpret_cast<const float4*>(src + (k + 1) * step);
     const float4 v2 = *reinterpret_cast<const float4*>(src + (k + 2) * step);
@@ -1470,7 +1470,7 @@ __global__ __launch_bounds__(256) void attention_reduce(HstuDims hd, const AttnI
     acc.x += v2.x; acc.y += v2.y; acc.z += v2.z; acc.w += v2.w;
     acc.x += v3.x; acc.y += v3.y; acc.z += v3.z; acc.w += v3.w;
   }
-  for (; k < gr.pieces; ++k) {
+  for (; k < it.pieces; ++k) {
     const float4 v = *reinterpret_cast<const float4*>(src + k * step);
     acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
   }
@@ -1784,7 +1784,7 @@ hipError_t launch_attention(const HstuDims& hd, uint32_t layer, const void* q, c
 
 hipError_t launch_attention_reduce(const HstuDims& hd, const StepLists& sl, void* o, bool o_half, hipStream_t stream) {
   if (sl.n_groups == 0) return hipSuccess;
-  hipLaunchKernelGGL(attention_reduce, dim3(sl.n_groups, (kAttnQ * 16 + 255) / 256), dim3(256), 0, stream, hd, sl.items, sl.groups, sl.partials, static_cast<uint16_t*>(o), o_half ? 1u : 0u);
+  hipLaunchKernelGGL(attention_reduce, dim3(sl.n_groups * hd.H, (kAttnQ * 16 + 255) / 256), dim3(256), 0, stream, hd, sl.items, sl.groups, sl.partials, static_cast<uint16_t*>(o), o_half ? 1u : 0u);
   return hipGetLastError();
 }
 

@@ -133,6 +133,7 @@ struct RowTile {
 // Where each die's attention work lies in the work list: block i does entry begin[i % kXcds] + i / kXcds
 struct AttnDies {
   uint32_t begin[kXcds + 1];
+  uint32_t piece;  // key tiles of a piece (of query tiles that are cut)
 };
 
 // Work lists built on the host for one step
@@ -145,7 +146,7 @@ struct StepLists {
   const AttnWork* work;
   AttnDies dies;
   uint32_t n_blocks;
-  const AttnGroup* groups;
+  const uint32_t* groups;      // query tiles whose partial outputs are to be added up
   uint32_t n_groups;
   float* partials;             // [slot][128][64]
   const RowTile* row_tiles;    // projection tiles, none crosses a request

@@ -752,7 +752,7 @@ StepBounds step_bounds(uint64_t B, uint64_t N, uint64_t max_seq, uint32_t H, uin
   const racer::AttnBounds a = racer::attn_bounds(B, N, max_seq, H, page_tokens);
   StepBounds b;
   b.list_bytes = sizeof(racer::ReqDev) * (B + 1) + 4 * (N / 32 + B + 2) + sizeof(racer::F32Tile) * (N / racer::kF32Queries + B) +
-                 sizeof(racer::AttnItem) * a.items + (sizeof(racer::AttnWork) + sizeof(racer::AttnGroup)) * a.work +
+                 (sizeof(racer::AttnItem) + sizeof(uint32_t)) * a.items + sizeof(racer::AttnWork) * a.work +
                  sizeof(racer::RowTile) * (a.items + 1) + 8 * 256;
   b.partial_bytes = a.work * 128 * 64 * sizeof(float);
   return b;
@@ -833,7 +833,7 @@ int32_t prepare_step(racer_pool* p, racer_hstu* m, const racer_hstu_req* reqs, u
   const uint64_t off_reqs = place(sizeof(racer::ReqDev) * B);
   const uint64_t off_items = place(sizeof(racer::AttnItem) * w.attn.items.size());
   const uint64_t off_work = place(sizeof(racer::AttnWork) * w.attn.work.size());
-  const uint64_t off_groups = place(sizeof(racer::AttnGroup) * w.attn.groups.size());
+  const uint64_t off_groups = place(sizeof(uint32_t) * w.attn.groups.size());
   const uint64_t off_row_tiles = place(sizeof(racer::RowTile) * w.row_tiles.size());
   const uint64_t off_group_req = place(sizeof(uint32_t) * n_groups32);  // request of every 32nd row, and of the last one
   const uint64_t off_f32_tiles = place(sizeof(racer::F32Tile) * w.f32_tiles.size());
@@ -872,8 +872,9 @@ int32_t prepare_step(racer_pool* p, racer_hstu* m, const racer_hstu_req* reqs, u
   sl.items = reinterpret_cast<const racer::AttnItem*>(p->hl_dev + off_items);
   sl.work = reinterpret_cast<const racer::AttnWork*>(p->hl_dev + off_work);
   std::copy(std::begin(w.attn.begin), std::end(w.attn.begin), sl.dies.begin);
+  sl.dies.piece = w.attn.piece;
   sl.n_blocks = w.attn.blocks;
-  sl.groups = reinterpret_cast<const racer::AttnGroup*>(p->hl_dev + off_groups);
+  sl.groups = reinterpret_cast<const uint32_t*>(p->hl_dev + off_groups);
   sl.n_groups = static_cast<uint32_t>(w.attn.groups.size());
   sl.partials = reinterpret_cast<float*>(p->hp_dev);
   sl.row_tiles = reinterpret_cast<const racer::RowTile*>(p->hl_dev + off_row_tiles);

@@ -27,25 +27,27 @@ static void check(const std::vector<ReqDev>& reqs, uint32_t H, uint32_t pt, Attn
   }
   s.build(reqs.data(), static_cast<uint32_t>(reqs.size()), H, pt);
   const AttnBounds b = attn_bounds(reqs.size(), N, longest, H, pt);
-  CHECK(s.items.size() <= b.items && s.work.size() <= b.work && s.n_slots <= b.work && s.groups.size() <= b.work);
+  CHECK(s.items.size() <= b.items && s.work.size() <= b.work && s.n_slots <= b.work && s.groups.size() <= b.items);
   // the lists of the dies, and a workgroup for every entry
   CHECK(s.begin[0] == 0 && s.begin[kXcds] == s.work.size());
   for (uint32_t x = 0; x < kXcds; ++x) CHECK(s.begin[x] <= s.begin[x + 1] && (s.begin[x + 1] - s.begin[x]) * kXcds <= s.blocks);
-  std::vector<std::vector<AttnWork>> of(s.items.size() * H);
+  struct Piece { uint32_t k, kt_begin, kt_end; };
+  std::vector<std::vector<Piece>> of(s.items.size() * H);
   for (const AttnWork& w : s.work) {
     CHECK((w.item_head >> 4) < s.items.size() && (w.item_head & 15) < H);
-    CHECK(w.kt_begin < w.kt_end && (w.kt_end - 1) * 64ull / pt - w.kt_begin * 64ull / pt < kAttnMaxItemPages);
-    CHECK((w.kt_end * 64ull - 1) / pt - w.kt_begin * 64ull / pt < kAttnMaxItemPages);
-    of[(w.item_head >> 4) * H + (w.item_head & 15)].push_back(w);
+    const AttnItem& t = s.items[w.item_head >> 4];
+    const uint32_t kt_begin = w.k * s.piece, kt_end = w.k + 1 == t.pieces ? attn_tiles(t) : kt_begin + s.piece;
+    CHECK(w.k < t.pieces && kt_begin < kt_end && (kt_end * 64ull - 1) / pt - kt_begin * 64ull / pt < kAttnMaxItemPages);
+    of[(w.item_head >> 4) * H + (w.item_head & 15)].push_back({w.k, kt_begin, kt_end});
   }
-  std::vector<AttnGroup> group(of.size(), AttnGroup{0, 0, 0});
   uint64_t slots = 0;
-  for (const AttnGroup& g : s.groups) {
-    CHECK(g.pieces >= 2 && g.slot0 == slots);
-    slots += g.pieces;
-    group[(g.item_head >> 4) * H + (g.item_head & 15)] = g;
+  size_t n_cut = 0;
+  for (uint32_t i : s.groups) {
+    CHECK(i < s.items.size() && s.items[i].pieces >= 2 && s.items[i].slot0 == slots);
+    slots += s.items[i].pieces * H;
   }
-  CHECK(slots == s.n_slots);
+  for (const AttnItem& t : s.items) n_cut += t.pieces > 1;
+  CHECK(slots == s.n_slots && n_cut == s.groups.size());
   size_t item = 0;
   for (uint32_t r = 0; r < reqs.size(); ++r)
     for (uint32_t q0 = 0; q0 < reqs[r].new_len; q0 += 128, ++item) {
@@ -54,12 +56,11 @@ static void check(const std::vector<ReqDev>& reqs, uint32_t H, uint32_t pt, Attn
       const uint32_t last = t.prefix_len + std::min(q0 + 127, t.new_len - 1);
       for (uint32_t h = 0; h < H; ++h) {
         auto& p = of[item * H + h];
-        const AttnGroup& g = group[item * H + h];
-        std::sort(p.begin(), p.end(), [](const AttnWork& a, const AttnWork& c) { return a.kt_begin < c.kt_begin; });
-        CHECK(p.size() == (g.pieces ? g.pieces : 1));
+        std::sort(p.begin(), p.end(), [](const Piece& a, const Piece& c) { return a.k < c.k; });
+        CHECK(p.size() == t.pieces);
         uint32_t at = 0;
         for (size_t k = 0; k < p.size(); ++k) {
-          CHECK(p[k].kt_begin == at && p[k].slot == (g.pieces ? g.slot0 + k : kDirect));
+          CHECK(p[k].k == k && p[k].kt_begin == at);
           at = p[k].kt_end;
         }
         CHECK(at == last / 64 + 1);

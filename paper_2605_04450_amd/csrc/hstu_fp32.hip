@@ -164,7 +164,7 @@ __global__ __launch_bounds__(256) void layer_half_f32(HalfArgsF32 a) {
 // are, step r for register r, the second operand of O^T += V^T P^T, whose first operand is then four consecutive keys of
 // one row of V^T: one 16-byte load straight from the page, as K's are (which elements of d_h a step contracts over does not
 // matter as long as K and Q agree: lane group g takes 16 s + 4 g .. + 4).
-// 4 requests x 256 tokens, 2 heads: 11 us (one wavefront per query and head, whose lanes fetched whole rows of K and V on
+// 4 requests x 256 tokens, 2 heads: 10.4 us (one wavefront per query and head, whose lanes fetched whole rows of K and V on
 // their own, 71 us; 16-query blocks on tiles staged in LDS, 22 us).
 // ---------------------------------------------------------------------------------------
 typedef float f32x4 __attribute__((ext_vector_type(4)));

@@ -347,7 +347,7 @@ __global__ __launch_bounds__(256) void gemm_front_bf16(HstuDims hd, uint32_t lay
 // A tile's weights are fetched while the tile before it is multiplied, and waited for just before that tile's results
 // are stored: the wait (which counts loads and stores in issue order) then never covers stores just issued.
 // A block sweeps all column tiles when there are rows enough to fill the chip, else the columns are cut too, down to one
-// tile a block (the launcher's rule).
+// tile a block (the launcher's rule).  Steps with fewer rows take layer_join instead (layers_joined says which).
 // What bounds it, d = 256, 131 440 rows: the front half moves 0.40 GB (0.34 of them its rows), and vector (51% of its
 // cycles), matrix (30%) and LDS (36%) work lie only partly on top of one another (28% of the time neither of the first two
 // runs); the back half moves 0.31 GB at 4.9 TB/s.  Three blocks per CU and the rows in uneven rounds 126 and 68 us, four,
@@ -985,11 +985,15 @@ __global__ __launch_bounds__(256, KD <= 256 ? 2 : 1) void layer_join(JoinArgs a)
 // What the vector unit has to do is fixed by that (671 of its cycles per 32x32 block, 256 of the matrix unit), so
 // the rest is to keep it fed: the copies to LDS pass through no registers, which leaves the 128 that four wavefronts
 // per SIMD allow, and the block needs 40 KB of LDS, so that four are resident per CU.  With tiles staged through registers
-// (168 of them, 48 KB, three per SIMD) a launch over 195M (query, key) pairs, d = 256, took 0.382 ms, now 0.335 to 0.365
-// depending on the card (550 to 596 TFLOP/s); over 32 x 512 queries behind 16 384 keys, d = 512, 0.971 ms, now 0.85 to 0.88
-// (635 to 657 TFLOP/s).  By the counters the vector unit is busy 74% of the time (55% before), one of the two units 88% (68%).
-// The 128 registers are 14 too few: 36 bytes of scratch a lane, stored once in front of the loop (39 MB of writes in the
-// first of these launches) and reloaded only in the path of tiles that lie in several pages or end a sequence.
+// (168 of them, 48 KB, three per SIMD) a launch over 195M (query, key) pairs, d = 256, took 0.382 ms, so 0.335; over 32 x 512
+// queries behind 16 384 keys, d = 512, 0.971 ms, so 0.88.  By the counters the vector unit is busy 74% of the time (55% before),
+// one of the two units 88% (68%).
+// Behind that came what a launch loses at its end and to LDS banks: the order of the work lists with wavefronts that take
+// turns at going first (64 users back with 64 tokens behind 2048 and 64 new histories 0.424 -> 0.355 ms, the d = 512 launch
+// 0.881 -> 0.833), and rows laid out for how 16-byte reads are served (0.332 -> 0.324, 0.827 -> 0.817).  On one card the
+// first of these launches now runs at 617 TFLOP/s, the second at 683 (cards differ by up to 6%).
+// The 128 registers are too few by seven: 28 bytes of scratch a lane, stored once in front of the loop and reloaded only
+// in the path of tiles that lie in several pages or end a sequence.
 // ---------------------------------------------------------------------------------------
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;

@@ -206,7 +206,7 @@ hipError_t launch_attention(const HstuDims& hd, uint32_t layer, const void* q, c
 // adds up the fp32 partials of query tiles cut into pieces (no-op when none was)
 hipError_t launch_attention_reduce(const HstuDims& hd, const StepLists& sl, void* o, bool o_half, hipStream_t stream);
 // bf16 models: pos and time must be the tables multiplied by log2(e) (launch_scale_bias), and
-// q must already be multiplied by log2(e) (launch_gemm_front stores it that way)
+// q must already be multiplied by log2(e) (the front halves store it that way)
 hipError_t launch_scale_bias(const float* in, float* out, uint64_t n, hipStream_t stream);
 hipError_t launch_scale_q(const void* in, void* out, uint64_t n, hipStream_t stream);
 // the library's half-precision copy of a bf16 weight matrix: transposed, or (fragments) in the operand order of the fused

@@ -761,7 +761,7 @@ struct JoinArgs {
 };
 
 template <int KD, bool BACK, bool FRONT>
-__global__ __launch_bounds__(256, KD <= 256 ? 2 : 1) void layer_join(JoinArgs a) {
+__device__ __forceinline__ void layer_join_block(JoinArgs a, const ReqDev* reqs, const uint32_t* group_req) {
   constexpr int kSt = KD / 16;       // MFMA steps over the contraction
   constexpr int kOwn = KD / 64;      // 16-byte pieces of a row per lane, eight lanes along a row
   constexpr uint32_t kRowBytes = KD * 2;
@@ -801,7 +801,7 @@ __global__ __launch_bounds__(256, KD <= 256 ? 2 : 1) void layer_join(JoinArgs a)
   uint32_t tok = 0;
   if (FRONT && row_ok) {
     const uint32_t row = r0 + li;
-    const ReqDev rq = a.reqs[request_of(a.reqs, row, a.group_req[group], a.group_req[group + 1])];
+    const ReqDev rq = reqs[request_of(reqs, row, group_req[group], group_req[group + 1])];
     uint32_t pi;
     split_token(hd, rq.prefix_len + (row - rq.x_off), &pi, &tok);
     const int32_t page = a.page_tables[rq.page_table_off + pi];
@@ -950,6 +950,11 @@ __global__ __launch_bounds__(256, KD <= 256 ? 2 : 1) void layer_join(JoinArgs a)
       __builtin_amdgcn_wave_barrier();  // the tile is read before the next one is written
     }
   }
+}
+
+template <int KD, bool BACK, bool FRONT>
+__global__ __launch_bounds__(256, KD <= 256 ? 2 : 1) void layer_join(JoinArgs a) {
+  layer_join_block<KD, BACK, FRONT>(a, a.reqs, a.group_req);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1489,16 +1494,17 @@ __global__ __launch_bounds__(256) void attention_reduce(HstuDims hd, const AttnI
   *reinterpret_cast<uint2*>(o + static_cast<uint64_t>(it.x_off + qi) * hd.d + h * 64 + 4 * c4) = w;
 }
 
-// Are a request's timestamps non-decreasing?  Block (c, r) looks at tokens 2048 c + 1 .. 2048 (c + 1) of request r
+// Are a request's timestamps non-decreasing?  A block looks at tokens 2048 c + 1 .. 2048 (c + 1) of requests r0, r0 + stride, ..
 // (eight per thread, all loads independent).  The first block that finds a decrease marks and counts the request.
 constexpr uint32_t kTsChunk = 2048;
 template <typename GetReq>
-__device__ __forceinline__ void check_timestamps(const GetReq& req, uint32_t B, uint32_t* __restrict__ marks, uint32_t epoch,
-                                                 const long long* __restrict__ ts, unsigned long long* __restrict__ counters) {
-  for (uint32_t r = blockIdx.y; r < B; r += gridDim.y) {  // (the grid's second dimension stops at 65 535)
+__device__ __forceinline__ void check_timestamps(const GetReq& req, uint32_t B, uint32_t c, uint32_t r0, uint32_t stride,
+                                                 uint32_t* __restrict__ marks, uint32_t epoch, const long long* __restrict__ ts,
+                                                 unsigned long long* __restrict__ counters) {
+  for (uint32_t r = r0; r < B; r += stride) {  // (the grid's second dimension stops at 65 535)
     const ReqDev rq = req(r);
     const uint32_t S = rq.prefix_len + rq.new_len;
-    const uint32_t j0 = blockIdx.x * kTsChunk + 1;
+    const uint32_t j0 = c * kTsChunk + 1;
     if (j0 >= S) continue;  // uniform over the block
     const long long* t = ts + rq.ts_off;
     bool bad = false;
@@ -1536,7 +1542,7 @@ __global__ __launch_bounds__(256) void begin_step(const uint4* __restrict__ src,
       if (i < n16) dst[i] = v[k];
     }
   }
-  if (ts) check_timestamps([&](uint32_t r) { return reinterpret_cast<const ReqDev*>(src)[r]; }, B, marks, epoch, ts, counters);
+  if (ts) check_timestamps([&](uint32_t r) { return reinterpret_cast<const ReqDev*>(src)[r]; }, B, blockIdx.x, blockIdx.y, gridDim.y, marks, epoch, ts, counters);
 }
 // The same for a small step, whose lists (the requests first) come as an argument: no copy engine, no staging buffer to
 // wait for (10 us of host time and 5 us of the stream's a step).
@@ -1544,7 +1550,29 @@ __global__ __launch_bounds__(256) void begin_step_with_lists(ListArg arg, uint4*
                                                              uint32_t* __restrict__ marks, uint32_t epoch,
                                                              const long long* __restrict__ ts, unsigned long long* __restrict__ counters) {
   if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < n16) dst[threadIdx.x] = reinterpret_cast<const uint4*>(arg.bytes)[threadIdx.x];
-  if (ts) check_timestamps([&](uint32_t r) { return reinterpret_cast<const ReqDev*>(arg.bytes)[r]; }, B, marks, epoch, ts, counters);
+  if (ts) check_timestamps([&](uint32_t r) { return reinterpret_cast<const ReqDev*>(arg.bytes)[r]; }, B, blockIdx.x, blockIdx.y, gridDim.y, marks, epoch, ts, counters);
+}
+// The same again beside the first layer's front half, for joined halves: blocks from first_block on begin the step, the others,
+// which read the requests out of the argument, are layer_join's.  One kernel less in the chain of a small step: one request of
+// 64 behind 2973, pass 101 -> 98 us, 13 ragged prefills 108 -> 105.5.
+struct BeginArgs {
+  uint32_t first_block, chunks, B, n16, group_req_at;
+  uint32_t epoch;
+  uint32_t* marks;
+  uint4* dst;
+  const long long* ts;
+  unsigned long long* counters;
+};
+template <int KD>
+__global__ __launch_bounds__(256, KD <= 256 ? 2 : 1) void layer_first(JoinArgs a, BeginArgs b, ListArg arg) {
+  const ReqDev* reqs = reinterpret_cast<const ReqDev*>(arg.bytes);
+  if (blockIdx.x >= b.first_block) {
+    const uint32_t i = blockIdx.x - b.first_block;
+    if (i == 0 && threadIdx.x < b.n16) b.dst[threadIdx.x] = reinterpret_cast<const uint4*>(arg.bytes)[threadIdx.x];
+    check_timestamps([&](uint32_t r) { return reqs[r]; }, b.B, i % b.chunks, i / b.chunks, b.B, b.marks, b.epoch, b.ts, b.counters);
+    return;
+  }
+  layer_join_block<KD, false, true>(a, reqs, reinterpret_cast<const uint32_t*>(arg.bytes + b.group_req_at));
 }
 static_assert(kListArgBytes / 16 <= 256, "one 16-byte word of the lists per thread");
 
@@ -1710,8 +1738,12 @@ static void run_join(const JoinArgs& a, uint32_t blocks, hipStream_t stream) {
   }
 }
 
+static uint32_t ts_chunks(uint32_t max_seq) { return max_seq < 2 ? 1 : (max_seq - 1 + kTsChunk - 1) / kTsChunk; }
+
+bool begin_joins(const StepLists& sl, uint32_t max_seq) { return static_cast<uint64_t>(ts_chunks(max_seq)) * sl.B <= 512; }
+
 hipError_t launch_layer_join(const HstuDims& hd, const LayerBack* back, const LayerFront* front, const void* x, const KvView& kv,
-                             const StepLists& sl, const int32_t* page_tables, hipStream_t stream) {
+                             const StepLists& sl, const int32_t* page_tables, hipStream_t stream, const BeginStep* begin) {
   if (sl.N == 0) return hipSuccess;
   if (!layer_halves_fused(hd) || (!back && !front)) return hipErrorInvalidValue;
   JoinArgs a{};
@@ -1748,6 +1780,21 @@ hipError_t launch_layer_join(const HstuDims& hd, const LayerBack* back, const La
     a.front_tiles = most / slices;
   }
   const uint32_t blocks = a.groups * slices;
+  if (begin) {
+    if (back || !front) return hipErrorInvalidValue;
+    BeginArgs b{blocks, ts_chunks(begin->max_seq), sl.B, static_cast<uint32_t>((begin->list_bytes + 15) / 16),
+                static_cast<uint32_t>(reinterpret_cast<const uint8_t*>(sl.group_req) - begin->list_dst), sl.epoch,
+                const_cast<uint32_t*>(sl.ts_marks), reinterpret_cast<uint4*>(begin->list_dst),
+                reinterpret_cast<const long long*>(begin->ts), begin->counters};
+    const dim3 grid(blocks + b.chunks * sl.B);
+    switch (hd.d) {
+      case 64: hipLaunchKernelGGL(layer_first<64>, grid, dim3(256), 0, stream, a, b, *begin->arg); break;
+      case 128: hipLaunchKernelGGL(layer_first<128>, grid, dim3(256), 0, stream, a, b, *begin->arg); break;
+      case 256: hipLaunchKernelGGL(layer_first<256>, grid, dim3(256), 0, stream, a, b, *begin->arg); break;
+      case 512: hipLaunchKernelGGL(layer_first<512>, grid, dim3(256), 0, stream, a, b, *begin->arg); break;
+    }
+    return hipGetLastError();
+  }
   if (back && front) run_join<true, true>(a, blocks, stream);
   else if (back) run_join<true, false>(a, blocks, stream);
   else run_join<false, true>(a, blocks, stream);
@@ -1794,7 +1841,7 @@ hipError_t launch_attention_reduce(const HstuDims& hd, const StepLists& sl, void
 
 hipError_t launch_begin_step(const StepLists& sl, uint32_t max_seq, const int64_t* ts, unsigned long long* counters, const ListArg* arg,
                              const uint8_t* pinned, uint8_t* list_dst, uint64_t list_bytes, hipStream_t stream) {
-  const uint32_t chunks = max_seq < 2 ? 1 : (max_seq - 1 + kTsChunk - 1) / kTsChunk;
+  const uint32_t chunks = ts_chunks(max_seq);
   // blocks for the copy too, where the requests do not ask for as many
   const uint64_t copy_rows = arg ? 0 : std::min<uint64_t>(1024, (list_bytes / (256 * 16 * kCopyAhead) + chunks - 1) / chunks);
   const dim3 grid(chunks, static_cast<uint32_t>(std::max<uint64_t>(copy_rows, std::min<uint32_t>(sl.B, 65535)))), block(256);

@@ -196,8 +196,19 @@ hipError_t launch_layer_back_fused(const HstuDims& hd, const void* o, const void
 struct LayerBack { const void *o, *u; const float *ln_g, *ln_b; const void* w2f; const float* b2; void* y; };
 struct LayerFront { uint32_t layer; const float *ln_g, *ln_b; const void* w1f; const float* b1; void *u, *q; };
 bool layers_joined(const HstuDims& hd, uint32_t N);
+// begin: the first front half's kernel also begins the step (as launch_begin_step with an argument), which it does where
+// begin_joins says so: with up to 512 blocks' worth of timestamps, which find room beside the rows'.
+struct BeginStep {
+  const ListArg* arg;
+  uint32_t max_seq;
+  const int64_t* ts;
+  unsigned long long* counters;
+  uint8_t* list_dst;
+  uint64_t list_bytes;
+};
+bool begin_joins(const StepLists& sl, uint32_t max_seq);
 hipError_t launch_layer_join(const HstuDims& hd, const LayerBack* back, const LayerFront* front, const void* x, const KvView& kv,
-                             const StepLists& sl, const int32_t* page_tables, hipStream_t stream);
+                             const StepLists& sl, const int32_t* page_tables, hipStream_t stream, const BeginStep* begin = nullptr);
 // o_half (bf16 models): the output is written in half precision (the step's own matrix between the attention and the
 // second LayerNorm) instead of bf16 (what a caller of the attention alone gets)
 hipError_t launch_attention(const HstuDims& hd, uint32_t layer, const void* q, const float* pos,

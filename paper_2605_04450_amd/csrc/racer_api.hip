@@ -765,12 +765,15 @@ struct StepCtx {
   uint64_t esize;
   bool fused;   // layer halves in one kernel each
   bool joined;  // a back half and the next front half in one kernel
+  bool begins;  // the first front half's kernel begins the step, with:
+  racer::ListArg arg;
+  uint64_t list_bytes;
 };
 
 // Validate the requests, build the attention work lists and the row -> request maps, ship them to the device on
-// `stream`, and have the timestamps looked at.
+// `stream`, and have the timestamps looked at (or, if the caller says that it can, leave these two to the first layer's kernel).
 int32_t prepare_step(racer_pool* p, racer_hstu* m, const racer_hstu_req* reqs, uint32_t B, uint64_t n_page_entries,
-                     const int64_t* ts, hipStream_t stream, StepCtx* ctx) {
+                     const int64_t* ts, hipStream_t stream, bool can_begin, StepCtx* ctx) {
   const racer_hstu_cfg& c = m->cfg;
   if (!p->device || c.page_tokens != p->cfg.page_tokens || c.elem != p->cfg.elem) return RACER_EINVAL;
   const uint64_t esize = c.elem == RACER_ELEM_BF16 ? 2 : 4;
@@ -841,8 +844,7 @@ int32_t prepare_step(racer_pool* p, racer_hstu* m, const racer_hstu_req* reqs, u
   p->step_epoch += 1;
   // Small lists travel as an argument of the kernel that begins the step, larger ones it reads from pinned staging.
   const bool by_argument = total <= racer::kListArgBytes;
-  racer::ListArg arg;
-  uint8_t* hbuf = arg.bytes;
+  uint8_t* hbuf = ctx->arg.bytes;
   int which = 0;
   if (!by_argument && (rc = p->hstage.acquire(total, &hbuf, &which))) return rc;
   auto put = [&](uint64_t at, const auto& v) {
@@ -884,7 +886,10 @@ int32_t prepare_step(racer_pool* p, racer_hstu* m, const racer_hstu_req* reqs, u
   sl.n_f32_tiles = static_cast<uint32_t>(w.f32_tiles.size());
   sl.longest = longest;
   // the lists to the device, and which requests' timestamps never decrease (the attention kernels' 32-bit time paths rely on it)
-  HIP_TRY(racer::launch_begin_step(sl, longest, ts, p->d_counters, by_argument ? &arg : nullptr, hbuf, p->hl_dev, total, stream));
+  ctx->begins = can_begin && by_argument && ctx->joined && racer::begin_joins(sl, longest);
+  ctx->list_bytes = total;
+  if (ctx->begins) return RACER_OK;
+  HIP_TRY(racer::launch_begin_step(sl, longest, ts, p->d_counters, by_argument ? &ctx->arg : nullptr, hbuf, p->hl_dev, total, stream));
   if (!by_argument && (rc = p->hstage.mark(which, stream))) return rc;
   return RACER_OK;
 }
@@ -923,7 +928,7 @@ int32_t hstu_step(racer_pool_t* p, racer_hstu_t* m, const racer_hstu_req* reqs, 
   hipStream_t stream = static_cast<hipStream_t>(stream_v);
   const racer_hstu_cfg& c = m->cfg;
   StepCtx ctx;
-  int32_t rc = prepare_step(p, m, reqs, B, n_page_entries, ts, stream, &ctx);
+  int32_t rc = prepare_step(p, m, reqs, B, n_page_entries, ts, stream, /*can_begin=*/true, &ctx);
   if (rc) return rc;
   p->last_stream = stream;
   const racer::StepLists& sl = ctx.sl;
@@ -950,8 +955,9 @@ int32_t hstu_step(racer_pool_t* p, racer_hstu_t* m, const racer_hstu_req* reqs, 
     };
     {
       const racer::LayerFront fr = front(0);
+      const racer::BeginStep begin{&ctx.arg, sl.longest, ts, p->d_counters, p->hl_dev, ctx.list_bytes};
       ProfScope t(p, RACER_PROF_GEMM_FRONT, stream);
-      HIP_TRY(racer::launch_layer_join(ctx.hd, nullptr, &fr, x_in, ctx.kv, sl, page_tables, stream));
+      HIP_TRY(racer::launch_layer_join(ctx.hd, nullptr, &fr, x_in, ctx.kv, sl, page_tables, stream, ctx.begins ? &begin : nullptr));
     }
     for (uint32_t l = 0; l < c.L; ++l) {
       {
@@ -1042,7 +1048,7 @@ int32_t hstu_attn_paged(racer_pool_t* p, racer_hstu_t* m, uint32_t layer, const 
   if (!p || !m || (B && !reqs) || layer >= m->cfg.L) return RACER_EINVAL;
   hipStream_t stream = static_cast<hipStream_t>(stream_v);
   StepCtx ctx;
-  int32_t rc = prepare_step(p, m, reqs, B, n_page_entries, ts, stream, &ctx);
+  int32_t rc = prepare_step(p, m, reqs, B, n_page_entries, ts, stream, /*can_begin=*/false, &ctx);
   if (rc) return rc;
   p->last_stream = stream;
   if (ctx.sl.N == 0) return RACER_OK;

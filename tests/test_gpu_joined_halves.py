@@ -31,3 +31,21 @@ def test_copies_of_one_request_get_the_same_rows(d, rows):
         assert np.array_equal(got[r[4]:r[4] + r[1]], got[:r[1]]), r
     assert c.pool.stats()["bad_pages"] == 0
     c.close()
+
+
+@pytest.mark.parametrize("d,new", [(64, 2067), (128, 300), (256, 33), (512, 64)])
+def test_the_first_layers_kernel_looks_at_every_timestamp(d, new):
+    """Its blocks take 2048 tokens of a request each: a decrease at either end of these is counted and computed as such."""
+    c = Case(25, 1, d, d // 64, 24, True, 100, 16, 64.0, 160)
+    reqs, pts, ts, x = c.inputs([0, 0], [new, 5])
+    assert_close(c.run_gpu(reqs, pts, ts, x), c.run_oracle(reqs, pts, ts, x), True, "ordered")
+    assert c.pool.stats()["unordered_ts"] == 0
+    at = [j for j in (1, 2047, 2048, 2049) if j < new - 1] + [new - 1]
+    for n, j in enumerate(at):
+        t = ts.copy()
+        t[j] = t[j - 1] - 1
+        got = c.run_gpu(reqs, pts, t, x)
+        assert c.pool.stats()["unordered_ts"] == n + 1, j
+        if n == 0 or j == at[-1]:
+            assert_close(got, c.run_oracle(reqs, pts, t, x), True, "decrease at %d" % j)
+    c.close()

@@ -917,7 +917,7 @@ __device__ __forceinline__ void layer_join_block(JoinArgs a, const ReqDev* reqs,
     for (uint32_t t = 0; t < a.front_tiles; ++t) {
       const uint32_t cb = front0 + t, n0 = cb * 32;
       const bool more = t + 1 < a.front_tiles;
-      const f32x16 acc = product(a.b1, cb, more ? a.w1f : nullptr, cb + 1);
+      const f32x16 acc = product(par + kBackPar + 2 * KD + n0 - b1_0, more ? a.w1f : nullptr, cb + 1);
       const uint32_t which = n0 / KD, c0 = n0 % KD;  // 0: U, 1: V, 2: Q, 3: K
       float z[16];
 #pragma unroll
@@ -996,10 +996,17 @@ __global__ __launch_bounds__(256, KD <= 256 ? 2 : 1) void layer_join(JoinArgs a)
 // Behind that came what a launch loses at its end and to LDS banks: the order of the work lists with wavefronts that take
 // turns at going first (64 users back with 64 tokens behind 2048 and 64 new histories 0.424 -> 0.355 ms, the d = 512 launch
 // 0.881 -> 0.833), and rows laid out for how 16-byte reads are served (0.332 -> 0.324, 0.827 -> 0.817).  On one card the
-// first of these launches now runs at 617 TFLOP/s, the second at 683 (cards differ by up to 6%).  By the counters no LDS read
-// meets another in a bank; the vector unit is busy 78% of the time, one of the two units 92%.
-// The 128 registers are too few by seven: 28 bytes of scratch a lane, stored once in front of the loop and reloaded only
-// in the path of tiles that lie in several pages or end a sequence.
+// first of these launches then ran at 617 TFLOP/s, the second at 683 (cards differ by up to 6%).  By the counters no LDS read
+// meets another in a bank.
+// A third of the vector instructions beside the epilogue were addresses: of the page (now in scalar registers, its number read a
+// tile ahead), of the staged operands (now constants of two copies of the loop's body), of the next window entries; and
+// conditions that were kept in vector registers.  Without them, with the next tile's copies between the two halves instead of in
+// front of them (their requests meet fewer operand reads; 128 users back with 64 tokens behind 3072 530 -> 521 us a step) and with
+// the first two tiles on their way together, steps take 3 to 5% less: 64 histories of 2048 2044 -> 1975 us, 32 x 512 behind
+// 16 384 7.40 -> 7.12 ms, the 128 users 545 -> 520, one of them 102.2 -> 99.3, 13 ragged prefills 103.1 -> 99.
+// Measured on it, timing only: without the reciprocal 8% of the d = 512 step, without SiLU and bias 28%, one-bucket bias
+// everywhere 1 to 4%.  Kept out, each slower: four copies of the body (by 1%), the last block's bucket remembered (by 2%).
+// The 128 registers are too few by five: 20 bytes of scratch a lane, stored once in front of the loop and reloaded behind it.
 // ---------------------------------------------------------------------------------------
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
@@ -1020,7 +1027,7 @@ struct AttnShared {
   uint32_t tk[2][64];  // key timestamps of the staged tiles relative to the request's first one
   float time[64];
   float rtime[32];     // rtime[c] = time bias of a gap with c leading zero bits (32-bit gaps, n_time <= 32)
-  int32_t pages[kAttnMaxItemPages];  // page ids of the item's key range (-1: outside the pool)
+  int32_t pages[kAttnMaxItemPages];  // page ids of the item's key range (-1: outside the pool); the last entry is never one: -1
 };
 static_assert(sizeof(AttnShared) <= 40960, "four blocks per CU");
 
@@ -1079,20 +1086,23 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
     const uint32_t bkt = 95 - tid;  // floor(log2(gap)) of a gap with tid - 64 leading zeros
     sm.rtime[tid - 64] = time[(static_cast<uint64_t>(layer) * hd.H + h) * hd.n_time + (bkt < hd.n_time - 1 ? bkt : hd.n_time - 1)];
   }
-  const float* pos_h = pos + (static_cast<uint64_t>(layer) * hd.H + h) * hd.n_pos;
+  // (a pointer made of integers: that it is global memory has to be said)
+  typedef __attribute__((address_space(1))) const uint8_t* GlobalBytes;
+  typedef __attribute__((address_space(1))) const float* GlobalFloats;
+  const GlobalBytes pos_h = (GlobalBytes)in_scalar(reinterpret_cast<const uint8_t*>(pos + (static_cast<uint64_t>(layer) * hd.H + h) * hd.n_pos));
 
   // A wavefront takes 32 queries and all keys of a tile.  With at most 64 queries in the block, the wavefronts are
   // paired instead: each pair takes 32 queries, one of it the first and the other the second half of every tile, and their
   // sums are added at the end, so that no SIMD idles (128 requests of 64 queries: 122 -> 108 us).
   const bool paired = T - q0 <= 64;
   const uint32_t grp = paired ? wave & 1 : wave;
-  const uint32_t sb_first = paired ? wave >> 1 : 0, sb_last = paired ? wave >> 1 : 1;
   const uint32_t ql = 32 * grp + li;  // query index inside the block
   const uint32_t qi = q0 + ql;
   const bool q_ok = qi < T;
   const uint32_t p = P + qi;
   const uint32_t first = q0 + 32 * grp;
   const bool grp_active = first < T;
+  const uint32_t halves = scalar(!grp_active ? 0 : paired ? 1 << (wave >> 1) : 3);  // the half tiles that are the wavefront's, a bit each
   const uint32_t grp_first = P + first, grp_last = P + (first + 31 < T - 1 ? first + 31 : T - 1);
   const uint32_t tq = static_cast<uint32_t>((q_ok ? tsr[p] : ts_base) - ts_base);
   uint32_t tq_first = 0, tq_last = 0;
@@ -1116,6 +1126,8 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
     for (int e = 0; e < 16; ++e) oacc[b2][e] = 0.0f;
 
   const uint64_t koff = kv_block_offset(hd, layer, 0, h, 2), voff = kv_block_offset(hd, layer, 1, h, 2);
+  const uint8_t* const k_head = in_scalar(kv.base + koff);  // the head's keys and values in page 0
+  const uint8_t* const v_head = in_scalar(kv.base + voff);
   const uint32_t kt_begin = scalar(wk.k) * dies.piece;
   const uint32_t kt_end = scalar(wk.k + 1 == item.pieces ? attn_tiles(item) : kt_begin + dies.piece);
   // the item's slice of the page table goes to LDS once, so that a tile fetch is a single
@@ -1134,30 +1146,32 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
       }
       sm.pages[i] = pg;
     }
+    if (tid == 0) sm.pages[kAttnMaxItemPages - 1] = -1;
   }
   // Positional window: entry x = (key - first key of the item) + (127 - query in the block) holds the (reversed, scaled)
   // bias of distance pos_top - x.  Negative distances belong to keys after the query, which the causal select removes.
   const int32_t pos_top = static_cast<int32_t>(P + q0 + kAttnQ - 1 - kt_begin * 64);
-  auto pos_at = [&](uint32_t x) {
-    int32_t i = pos_top - static_cast<int32_t>(x);
-    i = i < 0 ? 0 : (i > static_cast<int32_t>(hd.n_pos) - 1 ? static_cast<int32_t>(hd.n_pos) - 1 : i);
-    return pos_h[i];
+  auto pos_at = [&](uint32_t x0, uint32_t x) {  // entry x0 + x
+    const int32_t i = min(max(pos_top - static_cast<int32_t>(x0) - static_cast<int32_t>(x), 0), static_cast<int32_t>(hd.n_pos) - 1);
+    // (32 bits of byte offset: distances of 2^30 would take 275 GB of keys and values)
+    return *(GlobalFloats)(pos_h + static_cast<uint32_t>(i) * 4u);
   };
-  auto pos_put_copy = [&](uint32_t s, uint32_t x, float v) {
+  auto pos_put_copy = [&](uint32_t s, uint32_t x, float v, bool mirror) {
     const uint32_t at = (x - s) & (kPosRing - 1);
     sm.pos[s][at] = v;
-    if (at < kPosMirror) sm.pos[s][kPosRing + at] = v;
+    if (mirror && at < kPosMirror) sm.pos[s][kPosRing + at] = v;
   };
   // Key times: the low half as loaded, and what the tile keeps of it.  (Apart, so that nothing waits for the load where it
-  // is issued: there the wait held up the wavefront's copies of the tile by a round trip to memory.)
-  auto time_low = [&](uint32_t j) { return reinterpret_cast<const uint32_t*>(tsr)[2 * static_cast<uint64_t>(j < S ? j : S - 1)]; };
-  auto relative_time = [&](uint32_t j, uint32_t low) { return j < S ? low - static_cast<uint32_t>(ts_base) : 0u; };
-  if (tid < 191) {
-    const float v = pos_at(tid);
+  // is issued: there the wait held up the wavefront's copies of the tile by a round trip to memory.)  Keys past the end of the
+  // sequence come after every query: the causal select removes them, whatever their time.
+  auto time_low = [&](uint32_t j) { return reinterpret_cast<const uint32_t*>(tsr)[2 * static_cast<uint64_t>(min(j, S - 1))]; };
+  auto relative_time = [&](uint32_t low) { return low - static_cast<uint32_t>(ts_base); };
+  if (tid < 255) {  // of the first two tiles
+    const float v = pos_at(0, tid);
 #pragma unroll
-    for (uint32_t s = 0; s < 4; ++s) pos_put_copy(s, tid, v);
+    for (uint32_t s = 0; s < 4; ++s) pos_put_copy(s, tid, v, true);
   }
-  if (tid >= 192) sm.tk[0][tid - 192] = relative_time(kt_begin * 64 + tid - 192, time_low(kt_begin * 64 + tid - 192));
+  if (tid >= 128) (&sm.tk[0][0])[tid - 128] = relative_time(time_low(kt_begin * 64 + tid - 128));
   __syncthreads();
 
   // A tile is copied global -> LDS without passing through registers, four 1 KB copies per wavefront: two of K, two of V^T.
@@ -1170,22 +1184,23 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
   const uint32_t kconst = krow * 128 + part * 16, vconst = (vrow * hd.pt + part * 8) * 2;
   const bool one_page_tiles = hd.pt_shift < 32 && hd.pt >= 64;
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(&sm.kv[0][0][0])) + wave * 2048;
-  auto fetch = [&](uint32_t kt, uint32_t buf) {
+  // The page of a tile, or -1 if it may sit in several.  It is read a tile ahead, beside other LDS reads that are waited for
+  // there, so that the copies of a tile start right behind the barrier.  (Asked for tiles up to one past the item's.)
+  const uint32_t whole_tiles = one_page_tiles ? S / 64 : 0;  // tiles before this one sit in one page each, inside the sequence
+  auto page_of = [&](uint32_t kt) -> int32_t { return sm.pages[kt < whole_tiles ? ((kt * 64) >> hd.pt_shift) - page0 : kAttnMaxItemPages - 1]; };
+  auto fetch = [&](uint32_t kt, uint32_t buf, int32_t page) {
     const uint32_t j0 = kt * 64;
     const uint32_t lds = lds0 + buf * 16384;
-    if (one_page_tiles && j0 + 64 <= S) {
-      const int32_t page = __builtin_amdgcn_readfirstlane(sm.pages[(j0 >> hd.pt_shift) - page0]);
-      if (page >= 0) {  // the whole tile sits in one page and inside the sequence: scalar bases, no per-lane arithmetic
-        const uint32_t tb = j0 & (hd.pt - 1);
-        const uint8_t* pb = kv.base + static_cast<uint64_t>(page) * kv.page_size;
-        const uint8_t* kbase = in_scalar(pb + koff + static_cast<uint64_t>(tb) * 128);
-        const uint8_t* vbase = in_scalar(pb + voff + static_cast<uint64_t>(tb) * 2);
-        copy_to_lds<1>(lds, kbase, kconst);
-        copy_to_lds<1>(lds + 1024, kbase + 512, kconst ^ 64);
-        copy_to_lds<1>(lds + 8192, vbase, vconst);
-        copy_to_lds<1>(lds + 8192 + 1024, vbase + 16 * hd.pt, vconst ^ 64);
-        return;
-      }
+    if (page >= 0) {  // the whole tile sits in one page and inside the sequence: scalar bases, no per-lane arithmetic
+      const uint32_t tb = j0 & (hd.pt - 1);
+      const uint64_t pb = static_cast<uint64_t>(page) * kv.page_size;
+      const uint8_t* kbase = k_head + pb + static_cast<uint64_t>(tb) * 128;
+      const uint8_t* vbase = v_head + pb + static_cast<uint64_t>(tb) * 2;
+      copy_to_lds<1>(lds, kbase, kconst);
+      copy_to_lds<1>(lds + 1024, kbase + 512, kconst ^ 64);
+      copy_to_lds<1>(lds + 8192, vbase, vconst);
+      copy_to_lds<1>(lds + 8192 + 1024, vbase + 16 * hd.pt, vconst ^ 64);
+      return;
     }
     // (The block's base passes through an empty asm, so that its sum with a lane's place in the block, the same for every
     // tile, is not kept in registers over the whole loop.)
@@ -1218,7 +1233,6 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
   // Behind the copies: keys past the end of the sequence that share a chunk of V^T with the last ones hold whatever the
   // page held before, and are cleared by the lane that copied them.
   auto fetched = [&](uint32_t kt, uint32_t buf) {
-    wait_vm<0>();
     const uint32_t j0 = kt * 64;
     if (j0 + 64 <= S || (S & 7) == 0) return;
 #pragma unroll
@@ -1240,15 +1254,30 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
 #pragma unroll
   for (uint32_t st = 0; st < 4; ++st) chunk_off[st] = li * 128 + 16 * ((2 * st + g) ^ (li >> 1 & 7));
   const uint32_t pos_c0 = 8 * g + 127 - ql;  // the lane's first window entry of the item's first half tile
-  const float* pos_copy = sm.pos[pos_c0 & 3];
+  const uint8_t* pos_copy = reinterpret_cast<const uint8_t*>(sm.pos[pos_c0 & 3]);
+  const uint32_t pos_c = (pos_c0 & ~3u) * 4;
 
-  fetch(kt_begin, 0);
+  // both buffers are free at first: two tiles are on their way at once (items of small steps have two)
+  int32_t next_page = __builtin_amdgcn_readfirstlane(page_of(kt_begin + 1));
+  fetch(kt_begin, 0, __builtin_amdgcn_readfirstlane(page_of(kt_begin)));
+  if (kt_begin + 1 < kt_end) {
+    fetch(kt_begin + 1, 1, next_page);
+    wait_vm<4>();  // the first tile's: whatever the path, the second one's are four copies behind them
+  } else {
+    wait_vm<0>();
+  }
   fetched(kt_begin, 0);
   // (the general requests have a loop of their own, so that what it needs does not weigh on the other's registers)
   auto sweep = [&](auto fast_tag) {
     constexpr bool FAST = decltype(fast_tag)::value;
-    for (uint32_t kt = kt_begin; kt < kt_end; ++kt) {
-      const uint32_t j0 = kt * 64, t = kt - kt_begin, buf = t & 1;
+    // Two tiles per turn of the loop: the buffer is a constant of the code, and addresses in LDS are the same for every tile.
+    // (2: any tile, for the general requests.)
+    auto tile = [&](uint32_t kt, auto half_tag) {
+      constexpr uint32_t HALF = decltype(half_tag)::value;
+      uint32_t t = kt - kt_begin;
+      asm volatile("" : "+s"(t));  // (opaque: what follows from it is scalar, or one vector instruction, instead of a register that steps along)
+      const uint32_t j0 = (kt_begin + t) * 64;
+      const uint32_t buf = HALF < 2 ? HALF : t & 1;
       // one barrier per tile: tile kt is in LDS, and every wavefront is done with tile kt - 1, whose half takes tile kt + 1
       __syncthreads();
       // The four blocks of a CU take turns at going first, one tile each: left to itself a SIMD serves its older wavefronts
@@ -1256,11 +1285,12 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
       // nothing beside it to cover its latencies (32 x 512 queries behind 16 384 keys, d = 512: 0.88 ms, now 0.83).  Not where
       // the launch's last round is mostly empty (AttnSchedule::ends_evenly).
       if constexpr (TURNS) {
-        switch (t & 3) {
-          case 0: __builtin_amdgcn_s_setprio(3); break;
-          case 1: __builtin_amdgcn_s_setprio(2); break;
-          case 2: __builtin_amdgcn_s_setprio(1); break;
-          default: __builtin_amdgcn_s_setprio(0);
+        if (t & 2) {
+          if (buf) __builtin_amdgcn_s_setprio(0);
+          else __builtin_amdgcn_s_setprio(1);
+        } else {
+          if (buf) __builtin_amdgcn_s_setprio(2);
+          else __builtin_amdgcn_s_setprio(3);
         }
       }
       const bool more = kt + 1 < kt_end;
@@ -1268,30 +1298,23 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
       // the wavefronts bring in turn: no SIMD has more of this to do than another.
       float next_pos = 0.0f;
       uint32_t next_time = 0;
-      const bool times = wave == (t & 3);
-      if (more) {
-        next_pos = pos_at(64 * t + 191 + lane);
-        if (times) next_time = time_low(j0 + 64 + lane);
-        fetch(kt + 1, buf ^ 1);
-      }
+      auto bring = [&]() {
+        if (!more || t == 0) return;
+        next_pos = pos_at(64 * t, 191 + lane);
+        if (wave == (t & 3)) next_time = time_low(j0 + 64 + lane);
+        fetch(kt + 1, buf ^ 1, next_page);
+      };
       const uint8_t* ks = &sm.kv[buf][0][0];
       const uint8_t* vs = &sm.kv[buf][1][0];
-      // first and last key time of the two halves
-      uint32_t tkb[4] = {0, 0, 0, 0};
-      if (FAST) {
-        const uint32_t mine = sm.tk[buf][lane];
-        tkb[0] = __builtin_amdgcn_readlane(mine, 0);
-        tkb[1] = __builtin_amdgcn_readlane(mine, 31);
-        tkb[2] = __builtin_amdgcn_readlane(mine, 32);
-        tkb[3] = __builtin_amdgcn_readlane(mine, 63);
-      }
+      const int32_t page_after = page_of(kt_begin + t + 2);
+      const uint32_t key_time = FAST ? sm.tk[buf][lane] : 0;
       auto k_frag = [&](int sb, int st) { return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(ks + sb * 4096 + chunk_off[st])); };
       auto v_frag = [&](int sb, int s2, int db) {
         return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(vs + db * 4096 + chunk_off[2 * sb + s2]));
       };
       // S^T = K Q^T on top of the positional bias: lane's window entries x0 .. x0+7 and x0+16 .. x0+23
       auto scores_begin = [&](int sb) {
-        const float* pw = pos_copy + (((pos_c0 & ~3u) + 64 * t + 32 * sb) & (kPosRing - 1));
+        const float* pw = reinterpret_cast<const float*>(pos_copy + ((pos_c + 256 * t + 128 * sb) & (4 * kPosRing - 1)));
         const f32x4 w0 = *reinterpret_cast<const f32x4*>(pw), w1 = *reinterpret_cast<const f32x4*>(pw + 4);
         const f32x4 w2 = *reinterpret_cast<const f32x4*>(pw + 16), w3 = *reinterpret_cast<const f32x4*>(pw + 20);
         f32x16 sacc;
@@ -1313,8 +1336,10 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
         float c_lo = 0.0f, c_hi = 0.0f;
         uint32_t thr = 0;
         if (FAST && !diag) {
-          const uint32_t bmin = bucket_u32(tq_first - tkb[2 * sb + 1], hd.n_time);
-          const uint32_t bmax = bucket_u32(tq_last - tkb[2 * sb], hd.n_time);
+          const uint32_t tk_first = __builtin_amdgcn_readlane(key_time, 32 * sb), tk_last = __builtin_amdgcn_readlane(key_time, 32 * sb + 31);
+          const uint32_t gap_min = tq_first - tk_last, gap_max = tq_last - tk_first;
+          const uint32_t bmin = bucket_u32(gap_min, hd.n_time);
+          const uint32_t bmax = bucket_u32(gap_max, hd.n_time);
           c_lo = sm.time[bmin];
           if (bmin == bmax) {
             mode = 0;
@@ -1391,7 +1416,8 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
       };
   #pragma unroll
       for (uint32_t sb = 0; sb < 2; ++sb) {
-        if (sb < sb_first || sb > sb_last || !grp_active || j0 + 32 * sb > grp_last) continue;  // the wavefront's, and some pair visible
+        if (sb == 1) bring();
+        if (!(halves >> sb & 1) || j0 + 32 * sb > grp_last) continue;  // the wavefront's, and some pair visible
         f32x16 s = scores_begin(sb);
   #pragma unroll
         for (int st = 0; st < 4; ++st) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_frag(sb, st), qf[st], s, 0, 0, 0);
@@ -1399,11 +1425,26 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
         epilogue(sb, s, pk);
         accumulate(sb, pk);
       }
-      if (more) {
+      next_page = __builtin_amdgcn_readfirstlane(page_after);
+      uint32_t at = t;  // (the conditions are computed again: carried through the tile they take vector registers)
+      asm volatile("" : "+s"(at));
+      if (at + 1 < kt_end - kt_begin) {
+        wait_vm<0>();
         fetched(kt + 1, buf ^ 1);
-        pos_put_copy(wave, 64 * t + 191 + lane, next_pos);
-        if (times) sm.tk[buf ^ 1][lane] = relative_time(j0 + 64 + lane, next_time);
+        if (at == 0) return;  // (the second tile's window and times came with the first's)
+        pos_put_copy(wave, 64 * at + 191 + lane, next_pos, buf == 1 && (at & 2) == 0);  // (only such tiles bring the ring's first entries)
+        if (wave == (at & 3)) sm.tk[buf ^ 1][lane] = relative_time(next_time);
       }
+    };
+    if constexpr (FAST) {
+      for (uint32_t kt = kt_begin;;) {
+        tile(kt, std::integral_constant<uint32_t, 0>{});
+        if (++kt == kt_end) break;
+        tile(kt, std::integral_constant<uint32_t, 1>{});
+        if (++kt == kt_end) break;
+      }
+    } else {
+      for (uint32_t kt = kt_begin; kt < kt_end; ++kt) tile(kt, std::integral_constant<uint32_t, 2>{});
     }
   };
   if (fast) sweep(std::true_type{});

@@ -42,3 +42,22 @@ def test_values_behind_the_end_of_a_sequence_do_not_matter(pt):
     c.pool.mem.view(torch.int16).fill_(0x7FC0)  # NaN everywhere
     assert_close(c.run_gpu(reqs, pts, ts, x), c.run_oracle(reqs, pts, ts, x), True, "NaN behind the end")
     c.close()
+
+
+@pytest.mark.parametrize("pt", [16, 64, 128])
+@pytest.mark.parametrize("ordered", [True, False])
+def test_items_of_one_to_ten_key_tiles(pt, ordered):
+    # so many query tiles that none is cut: their items have 2, 4, 6, 8 and 9 or 10 key tiles, an odd or even last one, one
+    # that ends at its 64th key or before; the window's ring of 256 distances wraps twice
+    lens = [64 * 10, 64 * 10 - 1, 64 * 9, 64 * 9 - 5, 64 * 8 + 1, 64 * 10 - 32, 64, 65, 129] + [640] * 55
+    c = Case(13, 1, 512, 8, pt, True, 300, 24, 640.0, (60000 // pt // 32 + 2) * 32)
+    reqs, pts, ts, x = c.inputs([0] * len(lens), lens)
+    if not ordered:
+        for r in reqs[:9:2]:  # these requests take the general path
+            ts[r[3] + r[1] // 2] -= 100_000
+    got = c.run_gpu(reqs, pts, ts, x)
+    some = reqs[:9]
+    n = some[-1][4] + some[-1][1]
+    assert_close(got[:n], c.run_oracle(some, pts, ts, x[:n]), True, "items of many key tiles")
+    assert c.pool.stats()["bad_pages"] == 0
+    c.close()

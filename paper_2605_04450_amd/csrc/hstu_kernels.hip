@@ -917,7 +917,7 @@ __device__ __forceinline__ void layer_join_block(JoinArgs a, const ReqDev* reqs,
     for (uint32_t t = 0; t < a.front_tiles; ++t) {
       const uint32_t cb = front0 + t, n0 = cb * 32;
       const bool more = t + 1 < a.front_tiles;
-      const f32x16 acc = product(par + kBackPar + 2 * KD + n0 - b1_0, more ? a.w1f : nullptr, cb + 1);
+      const f32x16 acc = product(a.b1, cb, more ? a.w1f : nullptr, cb + 1);
       const uint32_t which = n0 / KD, c0 = n0 % KD;  // 0: U, 1: V, 2: Q, 3: K
       float z[16];
 #pragma unroll

@@ -730,7 +730,9 @@ __global__ __launch_bounds__(64 * WPB, KD <= 256 ? 4 : 2) void layer_half_fused(
 // slice again: a few hundred MFMA cycles) and keeps the layer's output, as bf16 like the matrix it also stores, in LDS.
 // The four wavefronts normalise eight rows each, lanes along the rows, and leave the operand in LDS; in the products they
 // have output columns of their own, so that weight fragments go from memory straight into registers, a tile ahead, and
-// nothing is staged.  What bounds it: about six dependent steps (rows, LayerNorm, product, LayerNorm, product, stores).
+// nothing is staged.  What bounds it: about six dependent steps (rows, LayerNorm, product, LayerNorm, product, stores), so
+// nothing that a step needs is asked for only there: parameters, biases and the residual come with the rows, a row's page is on
+// its way during the back half (64 rows of d = 256 9.2 -> 8.2 us a kernel, 8192 rows 27.9 -> 25.6, 2470 of d = 128 9.9 -> 8.7).
 // Steps of four layers with the halves in kernels of their own and joined: 64 rows of d = 256 88 -> 65 us, 8192 rows
 // 154 -> 135; 2470 rows of d = 128 97 -> 84; 1024 rows of d = 64 63 -> 51, of d = 512 148 -> 120.
 // ---------------------------------------------------------------------------------------
@@ -768,6 +770,9 @@ __device__ __forceinline__ void layer_join_block(JoinArgs a, const ReqDev* reqs,
   __shared__ __attribute__((aligned(16))) uint8_t operand[32 * kRowBytes];
   __shared__ __attribute__((aligned(16))) uint8_t rows[BACK ? 32 * kRowBytes : 16];
   __shared__ __attribute__((aligned(16))) uint8_t otile[FRONT ? 4 * 2048 : 16];
+  // LayerNorm scales and shifts and biases: [ln2_g | ln2_b | b2] and [ln1_g | ln1_b | b1, the slice's columns]
+  constexpr int kBackPar = BACK ? 3 * KD : 0;
+  __shared__ __attribute__((aligned(16))) float par[kBackPar + (FRONT ? 6 * KD : 0)];
   const uint32_t tid = threadIdx.x, lane = tid & 63, g = lane >> 5, li = lane & 31;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint32_t slice = blockIdx.x / a.groups, group = blockIdx.x - slice * a.groups, r0 = group * 32;
@@ -788,32 +793,72 @@ __device__ __forceinline__ void layer_join_block(JoinArgs a, const ReqDev* reqs,
   };
   const uint32_t front0 = FRONT ? (slice * 4 + wave) * a.front_tiles : 0;  // this wavefront's first column tile of the front half
   const bool has_back = BACK && wave < KD / 32;
-  if (BACK && has_back) unrolled<kSt>([&](auto st) { w[st] = load_w(a.w2f, wave, st); });
-  if (FRONT && !BACK) unrolled<kSt>([&](auto st) { w[st] = load_w(a.w1f, front0, st); });
+  // Everything whose address is known goes out at once: what the first LayerNorm needs, the parameters of all that follows, the
+  // residual, the first weights.  The parameters go to LDS, a word or a few per thread, and the residual into the tile of output
+  // rows, where each lane finds its part and puts the result in its place.
   u32x4 v[kOwn];
   load_own(BACK ? a.o : a.x, v);
-  u32x4 gt[BACK ? kOwn : 1];
+  u32x4 gt[BACK ? kOwn : 1], res[BACK ? kOwn : 1];
   if constexpr (BACK) load_own(a.gate, gt);
-
-  // ---- FRONT: where this lane's token goes (dependent loads, on their way during the back half) --------------------
-  const bool row_ok = r0 + li < a.n_rows;
-  const uint8_t* page_ptr = nullptr;
-  uint32_t tok = 0;
-  if (FRONT && row_ok) {
-    const uint32_t row = r0 + li;
-    const ReqDev rq = reqs[request_of(reqs, row, group_req[group], group_req[group + 1])];
-    uint32_t pi;
-    split_token(hd, rq.prefix_len + (row - rq.x_off), &pi, &tok);
-    const int32_t page = a.page_tables[rq.page_table_off + pi];
-    if (page < 0 || static_cast<uint32_t>(page) >= a.kv.n_pages) {
-      if (slice == 0 && wave == 0 && g == 0) atomicAdd(&a.kv.counters[ctr_index(kCtrBadPages)], 1ull);
-    } else {
-      page_ptr = a.kv.base + static_cast<uint64_t>(page) * a.kv.page_size;
+  constexpr int kPar = (KD + 255) / 256, kB1 = FRONT ? (4 * KD + 255) / 256 : 1;  // words per thread: of an array of KD, of b1
+  const uint32_t b1_n = FRONT ? a.front_tiles * 128 : 0, b1_0 = slice * b1_n;
+  float pb[BACK ? 3 * kPar : 1], pf[FRONT ? 2 * kPar : 1], p1[kB1];
+  auto par_words = [&](auto f) {  // f(word of the thread, where it lies in an array of KD)
+#pragma unroll
+    for (int j = 0; j < kPar; ++j)
+      if (KD % 256 == 0 || tid < KD) f(j, tid + 256 * j);
+  };
+  auto b1_words = [&](auto f) {
+#pragma unroll
+    for (int j = 0; j < kB1; ++j)
+      if (tid + 256 * j < b1_n) f(j, tid + 256 * j);
+  };
+  par_words([&](int j, uint32_t i) {
+    if constexpr (BACK) {
+      pb[3 * j] = a.ln2_g[i];
+      pb[3 * j + 1] = a.ln2_b[i];
+      pb[3 * j + 2] = a.b2[i];
     }
+    if constexpr (FRONT) {
+      pf[2 * j] = a.ln1_g[i];
+      pf[2 * j + 1] = a.ln1_b[i];
+    }
+  });
+  if constexpr (FRONT) b1_words([&](int j, uint32_t i) { p1[j] = a.b1[b1_0 + i]; });
+  if constexpr (BACK) load_own(a.x, res);
+  if (BACK && has_back) unrolled<kSt>([&](auto st) { w[st] = load_w(a.w2f, wave, st); });
+  if (FRONT && !BACK) unrolled<kSt>([&](auto st) { w[st] = load_w(a.w1f, front0, st); });
+
+  // ---- FRONT: where this lane's token goes -------------------------------------------------------------------------
+  // (The request through scalar loads where the group's rows are of two requests at most, so that it is not waited for behind the
+  // loads above; the page's number is looked at when the front half begins.)
+  const bool row_ok = r0 + li < a.n_rows;
+  int32_t page = -1;
+  uint32_t tok = 0;
+  if constexpr (FRONT) {
+    const uint32_t row = row_ok ? r0 + li : a.n_rows - 1;
+    const uint32_t lo = group_req[group], hi = group_req[group + 1];
+    uint32_t first, table;  // of the row's request: the token that its row 0 would be, and its page table
+    if (hi - lo <= 1) {
+      auto word = [](uint32_t x) { return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(x)); };
+      const uint32_t first0 = word(reqs[lo].prefix_len - reqs[lo].x_off), table0 = word(reqs[lo].page_table_off);
+      const uint32_t first1 = word(reqs[hi].prefix_len - reqs[hi].x_off), table1 = word(reqs[hi].page_table_off);
+      const bool second = word(reqs[hi].x_off) <= row;
+      first = second ? first1 : first0;
+      table = second ? table1 : table0;
+    } else {
+      const ReqDev rq = reqs[request_of(reqs, row, lo, hi)];
+      first = rq.prefix_len - rq.x_off;
+      table = rq.page_table_off;
+      asm volatile("" : "+v"(first), "+v"(table));  // (waited for here and not where the two ways meet)
+    }
+    uint32_t pi;
+    split_token(hd, first + row, &pi, &tok);
+    page = a.page_tables[table + pi];
   }
 
   // LayerNorm of row own_r (two passes in fp32, over the eight lanes that share it), times the gate, into the operand
-  auto normalise = [&](auto first, const float* ln_g, const float* ln_b) {
+  auto normalise = [&](auto first, const float* ln_g, const float* ln_b, auto ready) {  // ready(): the parameters are in LDS
     constexpr bool kFirst = decltype(first)::value;  // of the front half: bf16 rows, no gate
     float s = 0.0f;
     unrolled<kOwn>([&](auto k) {
@@ -831,6 +876,7 @@ __device__ __forceinline__ void layer_join_block(JoinArgs a, const ReqDev* reqs,
       for (int e = 0; e < 8; ++e) qq += (x[e] - mean) * (x[e] - mean);
     });
     const float rstd = 1.0f / sqrtf(group_sum<8>(qq) / KD + hd.eps);
+    ready();
     unrolled<kOwn>([&](auto k) {
       float x[8], gg[8], bb[8];
       unpack_in<kFirst>(v[k], x);
@@ -852,42 +898,60 @@ __device__ __forceinline__ void layer_join_block(JoinArgs a, const ReqDev* reqs,
   auto read_operand = [&]() {
     unrolled<kSt>([&](auto st) { xr[st] = *reinterpret_cast<const u32x4*>(operand + at(li, 2 * st + g)); });
   };
-  // acc[e]: column 32 cb + 8 (e / 4) + 4 g + e % 4 of this lane's token, on top of the bias; the registers of the weights
-  // take the next tile's as they become free
-  auto product = [&](const float* bias, uint32_t cb, const uint16_t* next_w, uint32_t next_cb) {
+  // acc[e]: column 8 (e / 4) + 4 g + e % 4 of a tile of this lane's token, on top of the tile's bias; the registers of the
+  // weights take the next tile's as they become free
+  auto product = [&](const float* bias, auto next, const uint16_t* next_w, uint32_t next_cb) {
     f32x16 acc;
 #pragma unroll
     for (int r4 = 0; r4 < 4; ++r4) {
-      const float4 b = *reinterpret_cast<const float4*>(bias + cb * 32 + 8 * r4 + 4 * g);
+      const float4 b = *reinterpret_cast<const float4*>(bias + 8 * r4 + 4 * g);
       acc[4 * r4] = b.x; acc[4 * r4 + 1] = b.y; acc[4 * r4 + 2] = b.z; acc[4 * r4 + 3] = b.w;
     }
     unrolled<kSt>([&](auto st) {
       acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, w[st]), __builtin_bit_cast(f16x8, xr[st]), acc, 0, 0, 0);
-      if (next_w) w[st] = load_w(next_w, next_cb, st);
+      if constexpr (decltype(next)::value) w[st] = load_w(next_w, next_cb, st);
     });
     return acc;
   };
 
+  // the parameters and the residual go to LDS before the first LayerNorm's second part
+  auto put_par = [&]() {
+    par_words([&](int j, uint32_t i) {
+      if constexpr (BACK) {
+        par[i] = pb[3 * j];
+        par[KD + i] = pb[3 * j + 1];
+        par[2 * KD + i] = pb[3 * j + 2];
+      }
+      if constexpr (FRONT) {
+        par[kBackPar + i] = pf[2 * j];
+        par[kBackPar + KD + i] = pf[2 * j + 1];
+      }
+    });
+    if constexpr (FRONT) b1_words([&](int j, uint32_t i) { par[kBackPar + 2 * KD + i] = p1[j]; });
+    if constexpr (BACK) unrolled<kOwn>([&](auto k) { *reinterpret_cast<u32x4*>(rows + at(own_r, own_c + 8 * k)) = res[k]; });
+    __syncthreads();
+  };
   if constexpr (BACK) {
-    normalise(std::false_type{}, a.ln2_g, a.ln2_b);
+    normalise(std::false_type{}, par, par + KD, put_par);
     __syncthreads();
     read_operand();
-    const uint64_t res_off = static_cast<uint64_t>(row_ok ? r0 + li : 0) * KD + 4 * g;
     for (uint32_t cb = wave; cb < KD / 32; cb += 4) {
-      u32x2 res[4];  // the residual of this lane's token, four runs of four columns
-#pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) res[r4] = *reinterpret_cast<const u32x2*>(a.x + res_off + 32 * cb + 8 * r4);
       const bool last = cb + 4 >= KD / 32;
-      const f32x16 acc = product(a.b2, cb, last ? (FRONT ? a.w1f : nullptr) : a.w2f, last ? front0 : cb + 4);
+      f32x16 acc;
+      if (FRONT) acc = product(par + 2 * KD + 32 * cb, std::true_type{}, last ? a.w1f : a.w2f, last ? front0 : cb + 4);
+      else if (last) acc = product(par + 2 * KD + 32 * cb, std::false_type{}, nullptr, 0);
+      else acc = product(par + 2 * KD + 32 * cb, std::true_type{}, a.w2f, cb + 4);
 #pragma unroll
       for (int r4 = 0; r4 < 4; ++r4) {
+        u32x2* run = reinterpret_cast<u32x2*>(rows + at(li, 4 * cb + r4) + 8 * g);  // four columns of this lane's token
+        const u32x2 before = *run;
         float y[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const uint32_t x = res[r4][e >> 1];
+          const uint32_t x = before[e >> 1];
           y[e] = __uint_as_float(e & 1 ? x & 0xFFFF0000u : x << 16) + acc[4 * r4 + e];
         }
-        *reinterpret_cast<u32x2*>(rows + at(li, 4 * cb + r4) + 8 * g) = u32x2{pack2_bf16(y[0], y[1]), pack2_bf16(y[2], y[3])};
+        *run = u32x2{pack2_bf16(y[0], y[1]), pack2_bf16(y[2], y[3])};
       }
     }
     if (FRONT && !has_back) unrolled<kSt>([&](auto st) { w[st] = load_w(a.w1f, front0, st); });
@@ -896,9 +960,16 @@ __device__ __forceinline__ void layer_join_block(JoinArgs a, const ReqDev* reqs,
     if (slice == 0 && own_ok) unrolled<kOwn>([&](auto k) { *reinterpret_cast<u32x4*>(a.y + own_off + 64 * k) = v[k]; });
   }
   if constexpr (FRONT) {
-    normalise(std::true_type{}, a.ln1_g, a.ln1_b);
+    if constexpr (BACK) normalise(std::true_type{}, par + kBackPar, par + kBackPar + KD, []() {});
+    else normalise(std::true_type{}, par + kBackPar, par + kBackPar + KD, put_par);
     __syncthreads();
     read_operand();
+    const uint8_t* page_ptr = nullptr;
+    if (page < 0 || static_cast<uint32_t>(page) >= a.kv.n_pages) {
+      if (row_ok && slice == 0 && wave == 0 && g == 0) atomicAdd(&a.kv.counters[ctr_index(kCtrBadPages)], 1ull);
+    } else if (row_ok) {
+      page_ptr = a.kv.base + static_cast<uint64_t>(page) * a.kv.page_size;
+    }
     // stores as in the large kernel: row-major outputs turned into 16-byte pieces in wave-private LDS, V^T by lanes
     const uint32_t st_row = lane >> 2, st_col = lane & 3;
     const bool st_ok[2] = {r0 + st_row < a.n_rows, r0 + st_row + 16 < a.n_rows};
@@ -916,8 +987,9 @@ __device__ __forceinline__ void layer_join_block(JoinArgs a, const ReqDev* reqs,
     uint8_t* ot = &otile[0] + wave * 2048;
     for (uint32_t t = 0; t < a.front_tiles; ++t) {
       const uint32_t cb = front0 + t, n0 = cb * 32;
-      const bool more = t + 1 < a.front_tiles;
-      const f32x16 acc = product(a.b1, cb, more ? a.w1f : nullptr, cb + 1);
+      f32x16 acc;
+      if (t + 1 < a.front_tiles) acc = product(par + kBackPar + 2 * KD + n0 - b1_0, std::true_type{}, a.w1f, cb + 1);
+      else acc = product(par + kBackPar + 2 * KD + n0 - b1_0, std::false_type{}, nullptr, 0);
       const uint32_t which = n0 / KD, c0 = n0 % KD;  // 0: U, 1: V, 2: Q, 3: K
       float z[16];
 #pragma unroll

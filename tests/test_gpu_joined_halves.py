@@ -54,3 +54,23 @@ def test_the_first_layers_kernel_looks_at_every_timestamp(d, new):
         if n == 0 or j == at[-1]:
             assert_close(got, c.run_oracle(reqs, pts, t, x), True, "decrease at %d" % j)
     c.close()
+
+
+# (Not d = 64, one head: the attention of a request's first token is then SiLU(q.k) v / n of a single key, whose relative error has
+# no bound where q.k, a sum of terms rounded to eight bits, is near zero, and the second LayerNorm takes the scale away.  Of several
+# heads not all are near zero at once.)
+@pytest.mark.parametrize("d,T", [(128, 3), (256, 1), (256, 15), (256, 16), (512, 11)])
+def test_rows_of_many_requests_in_a_group(d, T):
+    # a group of 32 rows holds rows of one, two or more requests; each finds the pages of its own
+    n = 70
+    c = Case(26, 2, d, d // 64, 8, True, 100, 16, 64.0, 800)
+    reqs, pts, ts, x = c.inputs([0] * n, [T + (i % 3 == 0) for i in range(n)])
+    assert_close(c.run_gpu(reqs, pts, ts, x), c.run_oracle(reqs, pts, ts, x), True, "short requests")
+    bad = pts.copy()
+    bad[reqs[40][2]] = c.pool.n_pages + 3  # a page that is not there: counted, and nobody else's rows change
+    got, ref = c.run_gpu(reqs, bad, ts, x), c.run_oracle(reqs, pts, ts, x)
+    keep = np.ones(len(x), bool)
+    keep[reqs[40][4]: reqs[40][4] + reqs[40][1]] = False
+    assert_close(got[keep], ref[keep], True, "beside a bad page")
+    assert c.pool.stats()["bad_pages"] > 0
+    c.close()

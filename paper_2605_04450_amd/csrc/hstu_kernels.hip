@@ -1569,37 +1569,51 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
   }
 }
 
-// Sum the fp32 partials of a query tile that was cut, in the order of their slots, and write the output.
+// Sum the fp32 partials of a query tile that was cut, in the order of their slots, and write the output.  QUARTERS: a wavefront
+// sums a quarter of them.
+constexpr uint32_t reduce_rows(bool quarters) { return quarters ? 4 : 16; }
+template <bool QUARTERS>
 __global__ __launch_bounds__(256) void attention_reduce(HstuDims hd, const AttnItem* __restrict__ items,
                                                         const uint32_t* __restrict__ groups,
                                                         const float* __restrict__ partials, uint16_t* __restrict__ o,
                                                         uint32_t o_half) {
-  // blockIdx.x = cut query tile and head; blockIdx.y = which 16 of the tile's query rows: a thread owns one 16-byte piece of
-  // one row, so that the pieces' loads of a whole tile are in flight at once
+  // blockIdx.x = cut query tile and head; blockIdx.y = which four or 16 of the tile's query rows.  A lane owns one 16-byte piece of
+  // one row and asks for eight partials at a time: they come from other dies' launches, through memory, and what counts is how
+  // often that is waited for.  (A round asks for its last partial again where it has fewer than eight.)  Wider rounds lose: 24
+  // partials of 64 rows, four heads, in rounds of 16, 5.4 us, in rounds of four 4.4, in quarters 4.0.
+  constexpr uint32_t kRows = reduce_rows(QUARTERS);
+  __shared__ __attribute__((aligned(16))) float4 quarter[QUARTERS ? 3 : 1][64];
   const AttnItem it = items[groups[blockIdx.x / hd.H]];
-  const uint32_t h = blockIdx.x % hd.H;
-  const uint32_t idx = blockIdx.y * 256 + threadIdx.x;
-  const uint32_t row = idx >> 4, c4 = idx & 15;
+  const uint32_t h = blockIdx.x % hd.H, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t row = blockIdx.y * kRows + (QUARTERS ? lane : threadIdx.x) / 16, c4 = lane & 15;
   const uint32_t qi = it.qt * kAttnQ + row;
-  if (row >= kAttnQ || qi >= it.new_len) return;
-  const float* src = partials + (static_cast<uint64_t>(it.slot0 + h * it.pieces) * kAttnQ + row) * 64 + 4 * c4;
+  if (it.qt * kAttnQ + blockIdx.y * kRows >= it.new_len) return;  // the whole block
+  const bool ok = qi < it.new_len;
+  const float* src = partials + (static_cast<uint64_t>(it.slot0 + h * it.pieces) * kAttnQ + (ok ? row : 0)) * 64 + 4 * c4;
   constexpr uint64_t step = kAttnQ * 64;  // from one piece's partial to the next
+  const uint32_t per = (it.pieces + 3) / 4, k0 = QUARTERS ? wave * per : 0, k1 = QUARTERS ? min(k0 + per, it.pieces) : it.pieces;
   float4 acc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-  uint32_t k = 0;
-  for (; k + 4 <= it.pieces; k += 4) {  // four loads in flight; the sum keeps their order
-    const float4 v0 = *reinterpret_cast<const float4*>(src + (k + 0) * step);
-    const float4 v1 = *reinterpret_cast<const float4*>(src + (k + 1) * step);
-    const float4 v2 = *reinterpret_cast<const float4*>(src + (k + 2) * step);
-    const float4 v3 = *reinterpret_cast<const float4*>(src + (k + 3) * step);
-    acc.x += v0.x; acc.y += v0.y; acc.z += v0.z; acc.w += v0.w;
-    acc.x += v1.x; acc.y += v1.y; acc.z += v1.z; acc.w += v1.w;
-    acc.x += v2.x; acc.y += v2.y; acc.z += v2.z; acc.w += v2.w;
-    acc.x += v3.x; acc.y += v3.y; acc.z += v3.z; acc.w += v3.w;
+  for (uint32_t k = k0; k < k1; k += 8) {
+    float4 v[8];
+#pragma unroll
+    for (uint32_t e = 0; e < 8; ++e) v[e] = *reinterpret_cast<const float4*>(src + min(k + e, k1 - 1) * step);
+#pragma unroll
+    for (uint32_t e = 0; e < 8; ++e) {
+      if (k + e >= k1) break;
+      acc.x += v[e].x; acc.y += v[e].y; acc.z += v[e].z; acc.w += v[e].w;
+    }
   }
-  for (; k < it.pieces; ++k) {
-    const float4 v = *reinterpret_cast<const float4*>(src + k * step);
-    acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+  if (QUARTERS) {
+    if (wave) quarter[wave - 1][lane] = acc;
+    __syncthreads();
+    if (wave) return;
+#pragma unroll
+    for (uint32_t e = 0; e < 3; ++e) {
+      const float4 v = quarter[e][lane];
+      acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+    }
   }
+  if (!ok) return;
   uint2 w;
   if (o_half) {
     w.x = pack2_f16(acc.x, acc.y);
@@ -1943,7 +1957,14 @@ hipError_t launch_attention(const HstuDims& hd, uint32_t layer, const void* q, c
 
 hipError_t launch_attention_reduce(const HstuDims& hd, const StepLists& sl, void* o, bool o_half, hipStream_t stream) {
   if (sl.n_groups == 0) return hipSuccess;
-  hipLaunchKernelGGL(attention_reduce, dim3(sl.n_groups * hd.H, (kAttnQ * 16 + 255) / 256), dim3(256), 0, stream, hd, sl.items, sl.groups, sl.partials, static_cast<uint16_t*>(o), o_half ? 1u : 0u);
+  // quarters where blocks of 16 rows would leave CUs without one or two (80 tiles of four heads, two or three partials each: 5.2 us so,
+  // 6.4 in quarters)
+  const uint32_t tiles = sl.n_groups * hd.H;
+  auto run = [&](auto kernel, uint32_t rows) {
+    hipLaunchKernelGGL(kernel, dim3(tiles, kAttnQ / rows), dim3(256), 0, stream, hd, sl.items, sl.groups, sl.partials, static_cast<uint16_t*>(o), o_half ? 1u : 0u);
+  };
+  if (tiles <= 64) run(attention_reduce<true>, reduce_rows(true));
+  else run(attention_reduce<false>, reduce_rows(false));
   return hipGetLastError();
 }
 

@@ -61,3 +61,30 @@ def test_items_of_one_to_ten_key_tiles(pt, ordered):
     assert_close(got[:n], c.run_oracle(some, pts, ts, x[:n]), True, "items of many key tiles")
     assert c.pool.stats()["bad_pages"] == 0
     c.close()
+
+
+@pytest.mark.parametrize("d,n,prefix,new", [
+    (64, 64, 200, 64), (64, 65, 200, 64),    # the most cut tiles whose partials are summed in quarters, and one more
+    (128, 32, 130, 1), (128, 33, 130, 1),
+    (64, 1, 4500, 64), (64, 1, 1000, 128),   # more partials than a quarter asks for at once; quarters of eight
+    (256, 1, 300, 3), (256, 1, 200, 2),      # fewer partials than quarters
+])
+def test_sums_of_few_and_many_partials(d, n, prefix, new):
+    """Requests with the same rows and keys: the first one as the oracle computes it, the others like the first."""
+    S = prefix + new
+    c = Case(14, 1, d, d // 64, 64, True, 300, 16, 1024.0, (n * -(-S // 64) * 4 // 3 // 32 + 2) * 32)
+    reqs, pts, ts, x = c.inputs([0] * n, [S] * n)
+    for r in reqs:
+        ts[r[3]:r[3] + S] = ts[:S]
+        x[r[4]:r[4] + S] = x[:S]
+    first = [(0, prefix, r[2], r[3], i * prefix) for i, r in enumerate(reqs)]
+    xa = np.concatenate([x[:prefix]] * n)
+    c.run_gpu(first, pts, ts, xa)
+    c.run_oracle(first[:1], pts, ts, xa[:prefix])
+    second = [(prefix, new, r[2], r[3], i * new) for i, r in enumerate(reqs)]
+    xb = np.concatenate([x[prefix:S]] * n)
+    got = c.run_gpu(second, pts, ts, xb)
+    assert_close(got[:new], c.run_oracle(second[:1], pts, ts, xb[:new]), True, "first copy")
+    for i in range(1, n):
+        assert np.array_equal(got[i * new:(i + 1) * new], got[:new]), i
+    c.close()

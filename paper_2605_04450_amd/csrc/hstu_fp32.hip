@@ -18,7 +18,10 @@ __device__ __forceinline__ float wave_sum(float v) {
 // A block computes 64 output columns of 8 rows: a wavefront normalises its two rows into LDS (which no other wavefront
 // reads: no barrier) and then owns the 64 columns of them, one per lane; the first 16 rows of W, and
 // what the stores need, are already on their way during the LayerNorm.  8 rows a block give 512 blocks for 1024 tokens of a d = 64 model.
-// 1024 tokens, d = 64: front 9 us (LayerNorm and product as two kernels, one thread per output: 4 + 13), back 5 us (4 + 9).
+// What bounds it is a chain of memory round trips: all loads whose address is known go out first, and the requests are searched by
+// ballot (four dependent loads per row, behind one another and in front of the rows, before).
+// 1024 tokens, d = 64: front 7.6 us (8.2 with that search, 9 before; LayerNorm and product as two kernels, one thread per output: 4
+// + 13), back 4.4 us (4.9; 4 + 9).  W 32 or 64 rows ahead instead of 16: 1 and 3% slower steps.
 // ---------------------------------------------------------------------------------------
 constexpr uint32_t kRowsPerWave = 2, kRowsPerBlock = 4 * kRowsPerWave, kMaxWidth = 1024, kAhead = 16;
 
@@ -43,37 +46,54 @@ struct HalfArgsF32 {
 template <bool FRONT>
 __global__ __launch_bounds__(256) void layer_half_f32(HalfArgsF32 a) {
   __shared__ __attribute__((aligned(16))) float xs[kRowsPerBlock][kMaxWidth + 4];
-  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t row0 = blockIdx.x * kRowsPerBlock + wave * kRowsPerWave;
   if (row0 >= a.N) return;  // (no barrier below)
   const uint32_t d = a.hd.d, col = blockIdx.y * 64 + lane;
   const bool col_ok = col < a.n_out;
+  uint32_t row[kRowsPerWave];
+#pragma unroll
+  for (uint32_t r = 0; r < kRowsPerWave; ++r) row[r] = row0 + r < a.N ? row0 + r : row0;
+  // What the kernel needs goes out at once, in the order in which it is needed: the first 64 columns of the rows (all there
+  // are, or the first of several rounds), scale, shift and gate, W, bias and residual.
+  ReqDev mine{};
+  if (FRONT && a.B <= 64) mine = a.reqs[min(lane, a.B - 1)];
+  const uint32_t c0 = lane < d ? lane : 0;
+  float in0[kRowsPerWave], gate0[kRowsPerWave], resid[kRowsPerWave];
+#pragma unroll
+  for (uint32_t r = 0; r < kRowsPerWave; ++r) in0[r] = a.in[static_cast<uint64_t>(row[r]) * d + c0];
+  const float gg0 = a.ln_g[c0], bb0 = a.ln_b[c0];
+#pragma unroll
+  for (uint32_t r = 0; r < kRowsPerWave; ++r) gate0[r] = FRONT ? 0.0f : a.gate[static_cast<uint64_t>(row[r]) * d + c0];
   const float* wc = a.w + (col_ok ? col : 0);
   float wr[kAhead];  // d is a multiple of 16
 #pragma unroll
   for (uint32_t k = 0; k < kAhead; ++k) wr[k] = wc[static_cast<uint64_t>(k) * a.n_out];
-  uint32_t row[kRowsPerWave];
-#pragma unroll
-  for (uint32_t r = 0; r < kRowsPerWave; ++r) row[r] = row0 + r < a.N ? row0 + r : row0;
-  // what the end needs, on its way during the LayerNorm and the product: bias, residual, where K and V of the rows go
   const float bias = a.bias[col_ok ? col : 0];
-  const uint32_t which = col / d, c_out = col % d;  // FRONT: 0: U, 1: V, 2: Q, 3: K
-  float resid[kRowsPerWave];
-  const uint8_t* page_ptr[kRowsPerWave];  // of a row's page (nullptr: a bad page id)
-  uint32_t tok[kRowsPerWave];
 #pragma unroll
-  for (uint32_t r = 0; r < kRowsPerWave; ++r) {
-    resid[r] = 0.0f;
-    page_ptr[r] = nullptr;
-    tok[r] = 0;
-    if (!FRONT) {
-      if (col_ok) resid[r] = a.resid[static_cast<uint64_t>(row[r]) * d + col];
-    } else if (col_ok && (which & 1)) {
-      const ReqDev rq = a.reqs[request_of(a.reqs, row[r], 0, a.B - 1)];
-      uint32_t pi;
-      split_token(a.hd, rq.prefix_len + (row[r] - rq.x_off), &pi, &tok[r]);
-      const int32_t page = a.page_tables[rq.page_table_off + pi];
-      if (page >= 0 && static_cast<uint32_t>(page) < a.kv.n_pages) page_ptr[r] = a.kv.base + static_cast<uint64_t>(page) * a.kv.page_size;
+  for (uint32_t r = 0; r < kRowsPerWave; ++r) resid[r] = FRONT ? 0.0f : a.resid[static_cast<uint64_t>(row[r]) * d + (col_ok ? col : 0)];
+  // Where K and V of the rows go: up to 64 requests are a lane each, the row's request one ballot away; more are searched.  (The
+  // page's number comes as a vector load, which is waited for where it is used; a scalar one every LDS read would wait for.)
+  const uint32_t which = col / d, c_out = col % d;  // FRONT: 0: U, 1: V, 2: Q, 3: K
+  int32_t page[kRowsPerWave];
+  uint32_t tok[kRowsPerWave];
+  if (FRONT) {
+#pragma unroll
+    for (uint32_t r = 0; r < kRowsPerWave; ++r) {
+      uint32_t first, table;  // of the row's request: the token that its row 0 would be, and its page table
+      if (a.B <= 64) {
+        const uint32_t req = __popcll(__ballot(lane < a.B && mine.x_off <= row[r])) - 1;
+        first = __builtin_amdgcn_readlane(mine.prefix_len - mine.x_off, req);
+        table = __builtin_amdgcn_readlane(mine.page_table_off, req);
+      } else {
+        const ReqDev rq = a.reqs[request_of(a.reqs, row[r], 0, a.B - 1)];
+        first = rq.prefix_len - rq.x_off;
+        table = rq.page_table_off;
+      }
+      uint32_t pi, any = 0;
+      asm volatile("" : "+v"(any));
+      split_token(a.hd, first + row[r], &pi, &tok[r]);
+      page[r] = a.page_tables[table + pi + any];
     }
   }
   float s[kRowsPerWave], qq[kRowsPerWave];
@@ -82,7 +102,7 @@ __global__ __launch_bounds__(256) void layer_half_f32(HalfArgsF32 a) {
   for (uint32_t c = lane; c < d; c += 64) {
 #pragma unroll
     for (uint32_t r = 0; r < kRowsPerWave; ++r) {
-      const float v = a.in[static_cast<uint64_t>(row[r]) * d + c];
+      const float v = c == lane ? in0[r] : a.in[static_cast<uint64_t>(row[r]) * d + c];
       xs[wave * kRowsPerWave + r][c] = v;
       s[r] += v;
     }
@@ -99,11 +119,12 @@ __global__ __launch_bounds__(256) void layer_half_f32(HalfArgsF32 a) {
 #pragma unroll
   for (uint32_t r = 0; r < kRowsPerWave; ++r) qq[r] = 1.0f / sqrtf(wave_sum(qq[r]) / d + a.hd.eps);
   for (uint32_t c = lane; c < d; c += 64) {
-    const float gg = a.ln_g[c], bb = a.ln_b[c];
+    const bool first = c == lane;
+    const float gg = first ? gg0 : a.ln_g[c], bb = first ? bb0 : a.ln_b[c];
 #pragma unroll
     for (uint32_t r = 0; r < kRowsPerWave; ++r) {
       float v = (xs[wave * kRowsPerWave + r][c] - s[r]) * qq[r] * gg + bb;
-      if (!FRONT) v *= a.gate[static_cast<uint64_t>(row[r]) * d + c];
+      if (!FRONT) v *= first ? gate0[r] : a.gate[static_cast<uint64_t>(row[r]) * d + c];
       xs[wave * kRowsPerWave + r][c] = v;
     }
   }
@@ -145,12 +166,12 @@ __global__ __launch_bounds__(256) void layer_half_f32(HalfArgsF32 a) {
       (which == 0 ? a.u : a.q)[static_cast<uint64_t>(row[r]) * d + c_out] = z;
       continue;
     }
-    if (!page_ptr[r]) {
+    if (page[r] < 0 || static_cast<uint32_t>(page[r]) >= a.kv.n_pages) {
       if (c_out == 0) atomicAdd(&a.kv.counters[ctr_index(kCtrBadPages)], 1ull);
       continue;
     }
     const uint32_t head = c_out / a.hd.dh, cc = c_out % a.hd.dh;
-    float* blk = reinterpret_cast<float*>(const_cast<uint8_t*>(page_ptr[r]) + kv_block_offset(a.hd, a.layer, which == 1 ? 1 : 0, head, 4));
+    float* blk = reinterpret_cast<float*>(a.kv.base + static_cast<uint64_t>(page[r]) * a.kv.page_size + kv_block_offset(a.hd, a.layer, which == 1 ? 1 : 0, head, 4));
     if (which == 3) blk[static_cast<uint64_t>(tok[r]) * a.hd.dh + cc] = z;  // K: [token][d_h]
     else blk[static_cast<uint64_t>(cc) * a.hd.pt + tok[r]] = z;             // V: [d_h][token]
   }

@@ -352,7 +352,9 @@ __global__ __launch_bounds__(256) void gemm_front_bf16(HstuDims hd, uint32_t lay
 // cycles), matrix (30%) and LDS (36%) work lie only partly on top of one another (28% of the time neither of the first two
 // runs); the back half moves 0.31 GB at 4.9 TB/s.  Three blocks per CU and the rows in uneven rounds 126 and 68 us, four,
 // which 40 KB of LDS and 128 registers allow, 119 to 123 and 61 to 64; 145 000 rows, where the last round was nearly
-// empty: 140 -> 126 us and 70 -> 67.
+// empty: 140 -> 126 us and 70 -> 67.  Stores into pages that the compiler knows to be global (it had waited for all LDS reads
+// before each pair of products, because a flat store counts as one), packing without a branch per run and fragments read four
+// steps ahead: the front half 120 -> 110.5 us in turn, a step of 64 histories of 2048 1.3% less, of 32 x 512 at d = 512 1.7%.
 // ---------------------------------------------------------------------------------------
 struct LayerHalfArgs {
   HstuDims hd;
@@ -424,6 +426,10 @@ __device__ __forceinline__ const uint8_t* in_scalar(const uint8_t* p) {  // a po
   const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(a)), hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(a >> 32));
   return reinterpret_cast<const uint8_t*>((static_cast<uint64_t>(hi) << 32) | lo);
 }
+// An address in a page.  A pointer that was put together from integers has to be said to be global: stores the compiler takes
+// for ones that may go to LDS make it wait for all LDS reads at each use of one.
+template <typename T>
+__device__ __forceinline__ __attribute__((address_space(1))) T* in_global(uint8_t* p) { return (__attribute__((address_space(1))) T*)p; }
 // (The LDS address goes into m0, which the compiler may use for itself between any two statements: one statement writes it,
 // waits and copies.  The instruction needs one wait state behind a write of m0, and five behind a vector instruction,
 // v_readfirstlane for one, that has written its scalar base.  The compiler keeps that distance for its own instructions
@@ -666,6 +672,16 @@ __global__ __launch_bounds__(64 * WPB, KD <= 256 ? 4 : 2) void layer_half_fused(
       const f16x8 wf = __builtin_bit_cast(f16x8, *reinterpret_cast<const u32x4*>(wb + st * 1024));
       acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wf, __builtin_bit_cast(f16x8, xr[st]), acc, 0, 0, 0);
     }
+    // Fragments are read four steps ahead (the bias and four, then one per product, 0x100: LDS reads, 0x8: MFMA); left to itself the
+    // compiler reads two, uses both and reads the next two.
+    if constexpr (kSt > 4) {
+      __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
+      unrolled<kSt - 4>([&](auto) {
+        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      });
+      __builtin_amdgcn_sched_group_barrier(0x8, 4, 0);
+    }
     if (FRONT) {
       const uint32_t which = n0 / KD, c0 = n0 % KD;  // 0: U, 1: V, 2: Q, 3: K
       float z[16];
@@ -676,27 +692,35 @@ __global__ __launch_bounds__(64 * WPB, KD <= 256 ? 4 : 2) void layer_half_fused(
         // V block [64][page_tokens]: the 32 lanes of a half-wave write 32 consecutive tokens of one feature
         if (page_ptr) {
           const uint32_t head = c0 / 64, cc = c0 % 64 + 4 * g;
-          uint16_t* dst = reinterpret_cast<uint16_t*>(const_cast<uint8_t*>(page_ptr) + kv_block_offset(hd, a.layer, 1, head, 2)) + tok;
+          uint8_t* dst = const_cast<uint8_t*>(page_ptr) + kv_block_offset(hd, a.layer, 1, head, 2) + 2 * (static_cast<uint64_t>(cc) * hd.pt + tok);
 #pragma unroll
-          for (int e = 0; e < 16; ++e)
-            dst[static_cast<uint64_t>(cc + 8 * (e / 4) + e % 4) * hd.pt] = static_cast<uint16_t>(pack2_bf16(z[e], 0.0f));
+          for (int e = 0; e < 16; e += 2) {
+            const uint32_t two = pack2_bf16(z[e], z[e + 1]);
+            *in_global<uint16_t>(dst + 2 * static_cast<uint64_t>(8 * (e / 4) + e % 4) * hd.pt) = static_cast<uint16_t>(two);
+            *in_global<uint16_t>(dst + 2 * static_cast<uint64_t>(8 * (e / 4) + e % 4 + 1) * hd.pt) = static_cast<uint16_t>(two >> 16);
+          }
         }
         continue;
       }
-      const float sc = which == 2 ? 1.4426950408889634f : 1.0f;  // the attention kernel wants q * log2(e)
       u32x2 run[4];
+      if (which == 0) {  // U is the library's own (half precision); Q and K are bf16
 #pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4)
-        run[r4] = which == 0  // U is the library's own (half precision); Q and K are bf16
-                      ? u32x2{pack2_f16(z[4 * r4], z[4 * r4 + 1]), pack2_f16(z[4 * r4 + 2], z[4 * r4 + 3])}
-                      : u32x2{pack2_bf16(z[4 * r4] * sc, z[4 * r4 + 1] * sc), pack2_bf16(z[4 * r4 + 2] * sc, z[4 * r4 + 3] * sc)};
+        for (int r4 = 0; r4 < 4; ++r4) run[r4] = u32x2{pack2_f16(z[4 * r4], z[4 * r4 + 1]), pack2_f16(z[4 * r4 + 2], z[4 * r4 + 3])};
+      } else {
+        if (which == 2) {  // the attention kernel wants q * log2(e)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) z[e] *= 1.4426950408889634f;
+        }
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) run[r4] = u32x2{pack2_bf16(z[4 * r4], z[4 * r4 + 1]), pack2_bf16(z[4 * r4 + 2], z[4 * r4 + 3])};
+      }
       u32x4 v[2];
       transposed(run, v);
       wait_vm<0>();
 #pragma unroll
       for (int h2 = 0; h2 < 2; ++h2) {
         if (which == 3) {  // K block [token][64]
-          if (kdst[h2]) *reinterpret_cast<u32x4*>(kdst[h2] + kv_block_offset(hd, a.layer, 0, c0 / 64, 2) + (c0 % 64) * 2) = v[h2];
+          if (kdst[h2]) *in_global<u32x4>(kdst[h2] + kv_block_offset(hd, a.layer, 0, c0 / 64, 2) + (c0 % 64) * 2) = v[h2];
         } else if (st_ok[h2]) {
           *reinterpret_cast<u32x4*>((which == 0 ? a.u : a.q) + st_off + 16 * KD * h2 + c0) = v[h2];
         }
@@ -997,10 +1021,13 @@ __device__ __forceinline__ void layer_join_block(JoinArgs a, const ReqDev* reqs,
       if (which == 1) {
         if (page_ptr) {
           const uint32_t head = c0 / 64, cc = c0 % 64 + 4 * g;
-          uint16_t* dst = reinterpret_cast<uint16_t*>(const_cast<uint8_t*>(page_ptr) + kv_block_offset(hd, a.layer, 1, head, 2)) + tok;
+          uint8_t* dst = const_cast<uint8_t*>(page_ptr) + kv_block_offset(hd, a.layer, 1, head, 2) + 2 * (static_cast<uint64_t>(cc) * hd.pt + tok);
 #pragma unroll
-          for (int e = 0; e < 16; ++e)
-            dst[static_cast<uint64_t>(cc + 8 * (e / 4) + e % 4) * hd.pt] = static_cast<uint16_t>(pack2_bf16(z[e], 0.0f));
+          for (int e = 0; e < 16; e += 2) {
+            const uint32_t two = pack2_bf16(z[e], z[e + 1]);
+            *in_global<uint16_t>(dst + 2 * static_cast<uint64_t>(8 * (e / 4) + e % 4) * hd.pt) = static_cast<uint16_t>(two);
+            *in_global<uint16_t>(dst + 2 * static_cast<uint64_t>(8 * (e / 4) + e % 4 + 1) * hd.pt) = static_cast<uint16_t>(two >> 16);
+          }
         }
         continue;
       }
@@ -1014,7 +1041,7 @@ __device__ __forceinline__ void layer_join_block(JoinArgs a, const ReqDev* reqs,
       for (int h2 = 0; h2 < 2; ++h2) {
         const u32x4 o16 = *reinterpret_cast<const u32x4*>(ot + (st_row + 16 * h2) * 64 + 16 * (st_col ^ ((st_row >> 2) & 3)));
         if (which == 3) {
-          if (kdst[h2]) *reinterpret_cast<u32x4*>(kdst[h2] + kv_block_offset(hd, a.layer, 0, c0 / 64, 2) + (c0 % 64) * 2) = o16;
+          if (kdst[h2]) *in_global<u32x4>(kdst[h2] + kv_block_offset(hd, a.layer, 0, c0 / 64, 2) + (c0 % 64) * 2) = o16;
         } else if (st_ok[h2]) {
           *reinterpret_cast<u32x4*>((which == 0 ? a.u : a.q) + st_off + 16 * KD * h2 + c0) = o16;
         }

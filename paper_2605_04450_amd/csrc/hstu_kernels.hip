@@ -1605,9 +1605,10 @@ __global__ __launch_bounds__(256) void attention_reduce(HstuDims hd, const AttnI
                                                         const float* __restrict__ partials, uint16_t* __restrict__ o,
                                                         uint32_t o_half) {
   // blockIdx.x = cut query tile and head; blockIdx.y = which four or 16 of the tile's query rows.  A lane owns one 16-byte piece of
-  // one row and asks for eight partials at a time: they come from other dies' launches, through memory, and what counts is how
-  // often that is waited for.  (A round asks for its last partial again where it has fewer than eight.)  Wider rounds lose: 24
-  // partials of 64 rows, four heads, in rounds of 16, 5.4 us, in rounds of four 4.4, in quarters 4.0.
+  // one row.  In quarters it asks for eight partials at a time: they come from other dies' launches, through memory, and what counts
+  // is how often that is waited for.  (A round asks for its last partial again where it has fewer than eight.)  24 partials of 64
+  // rows, four heads, in rounds of 16, 5.4 us, in rounds of four 4.4, in quarters 4.0.  Where blocks are many the requests count: rounds
+  // of four and the rest one by one (126 tiles of a few partials 6.0 us, in rounds of eight 7.2).
   constexpr uint32_t kRows = reduce_rows(QUARTERS);
   __shared__ __attribute__((aligned(16))) float4 quarter[QUARTERS ? 3 : 1][64];
   const AttnItem it = items[groups[blockIdx.x / hd.H]];
@@ -1620,16 +1621,21 @@ __global__ __launch_bounds__(256) void attention_reduce(HstuDims hd, const AttnI
   constexpr uint64_t step = kAttnQ * 64;  // from one piece's partial to the next
   const uint32_t per = (it.pieces + 3) / 4, k0 = QUARTERS ? wave * per : 0, k1 = QUARTERS ? min(k0 + per, it.pieces) : it.pieces;
   float4 acc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-  for (uint32_t k = k0; k < k1; k += 8) {
-    float4 v[8];
+  constexpr uint32_t kRound = QUARTERS ? 8 : 4;
+  auto add = [&](const float4& v) { acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w; };
+  uint32_t k = k0;
+  for (; QUARTERS ? k < k1 : k + kRound <= k1; k += kRound) {
+    float4 v[kRound];
 #pragma unroll
-    for (uint32_t e = 0; e < 8; ++e) v[e] = *reinterpret_cast<const float4*>(src + min(k + e, k1 - 1) * step);
+    for (uint32_t e = 0; e < kRound; ++e) v[e] = *reinterpret_cast<const float4*>(src + (QUARTERS ? min(k + e, k1 - 1) : k + e) * step);
 #pragma unroll
-    for (uint32_t e = 0; e < 8; ++e) {
-      if (k + e >= k1) break;
-      acc.x += v[e].x; acc.y += v[e].y; acc.z += v[e].z; acc.w += v[e].w;
+    for (uint32_t e = 0; e < kRound; ++e) {
+      if (QUARTERS && k + e >= k1) break;
+      add(v[e]);
     }
   }
+  if (!QUARTERS)
+    for (; k < k1; ++k) add(*reinterpret_cast<const float4*>(src + k * step));
   if (QUARTERS) {
     if (wave) quarter[wave - 1][lane] = acc;
     __syncthreads();

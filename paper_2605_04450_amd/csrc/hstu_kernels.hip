@@ -1596,66 +1596,74 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
   }
 }
 
-// Sum the fp32 partials of a query tile that was cut, in the order of their slots, and write the output.  QUARTERS: a wavefront
-// sums a quarter of them.
-constexpr uint32_t reduce_rows(bool quarters) { return quarters ? 4 : 16; }
-template <bool QUARTERS>
+// Sum the fp32 partials of a query tile that was cut, in the order of their slots, and write the output.
 __global__ __launch_bounds__(256) void attention_reduce(HstuDims hd, const AttnItem* __restrict__ items,
                                                         const uint32_t* __restrict__ groups,
                                                         const float* __restrict__ partials, uint16_t* __restrict__ o,
                                                         uint32_t o_half) {
-  // blockIdx.x = cut query tile and head; blockIdx.y = which four or 16 of the tile's query rows.  A lane owns one 16-byte piece of
-  // one row.  In quarters it asks for eight partials at a time: they come from other dies' launches, through memory, and what counts
-  // is how often that is waited for.  (A round asks for its last partial again where it has fewer than eight.)  24 partials of 64
-  // rows, four heads, in rounds of 16, 5.4 us, in rounds of four 4.4, in quarters 4.0.  Where blocks are many the requests count: rounds
-  // of four and the rest one by one (126 tiles of a few partials 6.0 us, in rounds of eight 7.2).
-  constexpr uint32_t kRows = reduce_rows(QUARTERS);
-  __shared__ __attribute__((aligned(16))) float4 quarter[QUARTERS ? 3 : 1][64];
+  // blockIdx.x = cut query tile and head; blockIdx.y = which 16 of the tile's query rows: a thread owns one 16-byte piece of
+  // one row, so that the pieces' loads of a whole tile are in flight at once
   const AttnItem it = items[groups[blockIdx.x / hd.H]];
-  const uint32_t h = blockIdx.x % hd.H, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint32_t row = blockIdx.y * kRows + (QUARTERS ? lane : threadIdx.x) / 16, c4 = lane & 15;
+  const uint32_t h = blockIdx.x % hd.H;
+  const uint32_t row = blockIdx.y * 16 + threadIdx.x / 16, c4 = threadIdx.x & 15;
   const uint32_t qi = it.qt * kAttnQ + row;
-  if (it.qt * kAttnQ + blockIdx.y * kRows >= it.new_len) return;  // the whole block
-  const bool ok = qi < it.new_len;
-  const float* src = partials + (static_cast<uint64_t>(it.slot0 + h * it.pieces) * kAttnQ + (ok ? row : 0)) * 64 + 4 * c4;
+  if (qi >= it.new_len) return;
+  const float* src = partials + (static_cast<uint64_t>(it.slot0 + h * it.pieces) * kAttnQ + row) * 64 + 4 * c4;
   constexpr uint64_t step = kAttnQ * 64;  // from one piece's partial to the next
-  const uint32_t per = (it.pieces + 3) / 4, k0 = QUARTERS ? wave * per : 0, k1 = QUARTERS ? min(k0 + per, it.pieces) : it.pieces;
   float4 acc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-  constexpr uint32_t kRound = QUARTERS ? 8 : 4;
   auto add = [&](const float4& v) { acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w; };
-  uint32_t k = k0;
-  for (; QUARTERS ? k < k1 : k + kRound <= k1; k += kRound) {
-    float4 v[kRound];
+  uint32_t k = 0;
+  for (; k + 4 <= it.pieces; k += 4) {  // four loads in flight (eight: 126 tiles of a few partials 7.2 us, so 6.0)
+    float4 v[4];
 #pragma unroll
-    for (uint32_t e = 0; e < kRound; ++e) v[e] = *reinterpret_cast<const float4*>(src + (QUARTERS ? min(k + e, k1 - 1) : k + e) * step);
+    for (uint32_t e = 0; e < 4; ++e) v[e] = *reinterpret_cast<const float4*>(src + (k + e) * step);
 #pragma unroll
-    for (uint32_t e = 0; e < kRound; ++e) {
-      if (QUARTERS && k + e >= k1) break;
-      add(v[e]);
-    }
+    for (uint32_t e = 0; e < 4; ++e) add(v[e]);
   }
-  if (!QUARTERS)
-    for (; k < k1; ++k) add(*reinterpret_cast<const float4*>(src + k * step));
-  if (QUARTERS) {
-    if (wave) quarter[wave - 1][lane] = acc;
-    __syncthreads();
-    if (wave) return;
-#pragma unroll
-    for (uint32_t e = 0; e < 3; ++e) {
-      const float4 v = quarter[e][lane];
-      acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
-    }
-  }
-  if (!ok) return;
+  for (; k < it.pieces; ++k) add(*reinterpret_cast<const float4*>(src + k * step));
   uint2 w;
   if (o_half) {
     w.x = pack2_f16(acc.x, acc.y);
     w.y = pack2_f16(acc.z, acc.w);
   } else {
-    w.x = pack_bf16x2(acc.x, acc.y);
-    w.y = pack_bf16x2(acc.z, acc.w);
+    w.x = pack2_bf16(acc.x, acc.y);
+    w.y = pack2_bf16(acc.z, acc.w);
   }
   *reinterpret_cast<uint2*>(o + static_cast<uint64_t>(it.x_off + qi) * hd.d + h * 64 + 4 * c4) = w;
+}
+
+// The same sums, in the same order, for few tiles of many partials (sums_by_rows): a wavefront sums one row, a lane one float of
+// it, and asks for 32 partials at a time, 16 where no more are left (a round that has fewer asks for the last one again).  They
+// come from other dies' launches, through memory, and what counts there is how often that is waited for.
+__global__ __launch_bounds__(256) void attention_reduce_rows(HstuDims hd, const AttnItem* __restrict__ items,
+                                                             const uint32_t* __restrict__ groups,
+                                                             const float* __restrict__ partials, uint16_t* __restrict__ o,
+                                                             uint32_t o_half) {
+  const AttnItem it = items[groups[blockIdx.x / hd.H]];
+  const uint32_t h = blockIdx.x % hd.H, col = threadIdx.x & 63;
+  const uint32_t row = blockIdx.y * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t qi = it.qt * kAttnQ + row;
+  if (qi >= it.new_len) return;  // the whole wavefront
+  const float* src = partials + (static_cast<uint64_t>(it.slot0 + h * it.pieces) * kAttnQ + row) * 64 + col;
+  constexpr uint64_t step = kAttnQ * 64;
+  float acc = 0.0f;
+  uint32_t k = 0;
+  auto round = [&](auto n) {
+    constexpr uint32_t kN = decltype(n)::value;
+    float v[kN];
+#pragma unroll
+    for (uint32_t e = 0; e < kN; ++e) v[e] = src[min(k + e, it.pieces - 1) * step];
+#pragma unroll
+    for (uint32_t e = 0; e < kN; ++e) acc = k + e < it.pieces ? acc + v[e] : acc;
+    k += kN;
+  };
+  while (k < it.pieces) {
+    if (it.pieces - k > 16) round(std::integral_constant<uint32_t, 32>{});
+    else round(std::integral_constant<uint32_t, 16>{});
+  }
+  const float right = __shfl_xor(acc, 1);
+  if ((col & 1) == 0)
+    *reinterpret_cast<uint32_t*>(o + static_cast<uint64_t>(it.x_off + qi) * hd.d + h * 64 + col) = o_half ? pack2_f16(acc, right) : pack2_bf16(acc, right);
 }
 
 // Are a request's timestamps non-decreasing?  A block looks at tokens 2048 c + 1 .. 2048 (c + 1) of requests r0, r0 + stride, ..
@@ -1990,14 +1998,12 @@ hipError_t launch_attention(const HstuDims& hd, uint32_t layer, const void* q, c
 
 hipError_t launch_attention_reduce(const HstuDims& hd, const StepLists& sl, void* o, bool o_half, hipStream_t stream) {
   if (sl.n_groups == 0) return hipSuccess;
-  // quarters where blocks of 16 rows would leave CUs without one or two (80 tiles of four heads, two or three partials each: 5.2 us so,
-  // 6.4 in quarters)
   const uint32_t tiles = sl.n_groups * hd.H;
   auto run = [&](auto kernel, uint32_t rows) {
     hipLaunchKernelGGL(kernel, dim3(tiles, kAttnQ / rows), dim3(256), 0, stream, hd, sl.items, sl.groups, sl.partials, static_cast<uint16_t*>(o), o_half ? 1u : 0u);
   };
-  if (tiles <= 64) run(attention_reduce<true>, reduce_rows(true));
-  else run(attention_reduce<false>, reduce_rows(false));
+  if (sl.sum_rows) run(attention_reduce_rows, 4);
+  else run(attention_reduce, 16);
   return hipGetLastError();
 }
 

@@ -150,6 +150,7 @@ struct StepLists {
   bool turns;                  // the blocks of a CU take turns at going first
   const uint32_t* groups;      // query tiles whose partial outputs are to be added up
   uint32_t n_groups;
+  bool sum_rows;               // by attention_reduce_rows (step_rules.h)
   float* partials;             // [slot][128][64]
   const RowTile* row_tiles;    // projection tiles, none crosses a request
   uint32_t n_row_tiles;

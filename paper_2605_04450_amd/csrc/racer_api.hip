@@ -887,6 +887,9 @@ int32_t prepare_step(racer_pool* p, racer_hstu* m, const racer_hstu_req* reqs, u
   sl.turns = w.attn.turns;
   sl.groups = reinterpret_cast<const uint32_t*>(p->hl_dev + off_groups);
   sl.n_groups = static_cast<uint32_t>(w.attn.groups.size());
+  uint64_t row_blocks = 0;  // of four rows, of all cut query tiles
+  for (uint32_t i : w.attn.groups) row_blocks += (std::min<uint32_t>(128, w.attn.items[i].new_len - w.attn.items[i].qt * 128) + 3) / 4;
+  sl.sum_rows = racer::sums_by_rows(row_blocks * c.H, w.attn.n_slots, w.attn.groups.size() * c.H);
   sl.partials = reinterpret_cast<float*>(p->hp_dev);
   sl.row_tiles = reinterpret_cast<const racer::RowTile*>(p->hl_dev + off_row_tiles);
   sl.n_row_tiles = static_cast<uint32_t>(w.row_tiles.size());

@@ -36,6 +36,17 @@ constexpr uint32_t join_max_rows(uint32_t d, uint64_t rows, uint64_t requests, u
   return d <= 128 ? 65536 : 24576;
 }
 
+// ---- sums of the partial outputs of cut query tiles ---------------------------------------------------------------
+// Both kernels add in the order of the keys.  attention_reduce_rows waits for memory once where attention_reduce waits for each
+// four partials, but asks for four times as many pieces of memory: it is ahead where partials are many and its blocks (of four
+// rows of a tile and head) few.  Steps of eight layers, attention_reduce and attention_reduce_rows, us:
+//   partials (d = 64, a request of 64): 2 141 and 143, 8 139 and 139, 12 135 and 132, 40 153 and 136, 94 198 and 158
+//   blocks, 24 partials (d = 256, 64 new tokens each): 64 176 and 166, 256 204 and 194, 512 253 and 246, 640 273 and 268
+//   blocks, 16 partials: 640 228 and 226, 960 302 and 303;  12: 640 208 and 207;  8: 512 187 and 187, 1024 222 and 224
+constexpr bool sums_by_rows(uint64_t blocks, uint64_t partials, uint64_t tiles) {
+  return 2 * blocks <= 5 * kCus && partials > 8 * tiles;
+}
+
 // ---- fp32 attention: wavefronts per block, which take groups of 16 keys in turn -----------------------------------
 // blocks: query tiles times heads.  longest: tokens of the longest request.  mean_keys: keys that a query tile sees, on average.
 // Up to a block per CU, about a wavefront per group of the longest request, 16 at most (eight where heads are wider than 32: 16

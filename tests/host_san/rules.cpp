@@ -50,7 +50,14 @@ static void joined_limits() {
   CHECK(join_max_rows(256, 20000, 300, 1 << 20) == 24576 && join_max_rows(64, 1, 1, 0) == 65536 && join_max_rows(128, 1, 1, 0) == 65536);
 }
 
+// Sums by rows: more than eight partials a tile, and no more than two and a half blocks per CU.
+static void sums_limits() {
+  CHECK(sums_by_rows(640, 4 * 9, 4) && !sums_by_rows(641, 4 * 9, 4) && !sums_by_rows(640, 4 * 8, 4));
+  CHECK(sums_by_rows(1, 9, 1) && !sums_by_rows(1, 2, 1) && !sums_by_rows(0, 0, 0));
+}
+
 int main() {
+  sums_limits();
   join_slices_fit_one_round();
   joined_limits();
   f32_waves_fit();

@@ -12,6 +12,7 @@
 #include <random>
 
 #include "../../paper_2605_04450_amd/csrc/attn_schedule.h"
+#include "../../paper_2605_04450_amd/csrc/step_rules.h"
 
 #define CHECK(cond)                                                                 \
   do {                                                                              \
@@ -148,6 +149,16 @@ int main() {
     l[17].first = 16384;
     check(requests(l), 4, 64, s);
     CHECK(!s.groups.empty());
+  }
+  // steps of tests/test_gpu_attention_tiles.py, whose keys lie in pieces of two key tiles: pieces, heads, requests, new tokens,
+  // and whether attention_reduce_rows adds them up
+  struct Sums { uint32_t H, n, pieces, len; bool by_rows; };
+  for (const Sums& c : {Sums{1, 1, 5, 1, false}, {1, 1, 6, 64, false}, {2, 2, 7, 33, false}, {4, 1, 8, 64, false}, {4, 16, 12, 64, false},
+                        {1, 1, 9, 64, true}, {1, 2, 16, 3, true}, {4, 1, 17, 64, true}, {4, 1, 24, 64, true}, {8, 1, 32, 128, true},
+                        {1, 1, 33, 64, true}, {2, 1, 48, 2, true}, {1, 1, 49, 100, true}, {4, 1, 94, 1, true}}) {
+    check(requests(std::vector<std::pair<uint32_t, uint32_t>>(c.n, {128 * c.pieces - c.len, c.len})), c.H, 64, s);
+    CHECK(s.piece == 2 && s.groups.size() == c.n && s.n_slots == c.n * c.H * c.pieces);
+    CHECK(sums_by_rows((c.len + 3) / 4 * c.n * c.H, s.n_slots, c.n * c.H) == c.by_rows);
   }
   std::mt19937 g(1);
   auto log_size = [&](double e) { return static_cast<uint32_t>(std::exp((g() % 10000) / 10000.0 * e)); };

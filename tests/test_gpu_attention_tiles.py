@@ -5,6 +5,9 @@ import numpy as np
 import pytest
 import torch
 
+from paper_2605_04450_amd import binding as B
+from paper_2605_04450_amd import device as Hn
+from paper_2605_04450_amd import synth
 from tests.test_gpu_hstu import Case, assert_close
 
 pytestmark = pytest.mark.gpu
@@ -88,3 +91,43 @@ def test_sums_of_few_and_many_partials(d, n, prefix, new):
     for i in range(1, n):
         assert np.array_equal(got[i * new:(i + 1) * new], got[:new]), i
     c.close()
+
+
+@pytest.mark.parametrize("d,n,pieces,new", [
+    (64, 1, 5, 1), (64, 1, 6, 64), (128, 2, 7, 33), (256, 1, 8, 64), (256, 16, 12, 64),      # attention_reduce, rounds of four
+    (64, 1, 9, 64), (64, 2, 16, 3), (256, 1, 17, 64), (256, 1, 24, 64), (512, 1, 32, 128),   # attention_reduce_rows: one round
+    (64, 1, 33, 64), (128, 1, 48, 2), (64, 1, 49, 100), (256, 1, 94, 1),                     # and several
+])
+def test_partials_are_added_in_the_order_of_the_keys(d, n, pieces, new):
+    """Pieces of two key tiles, q.k = 1 for every pair and one value other than zero in each piece: M in the first, between a
+    quarter and half a unit in M's last place in those that follow, -M in the last.  Added in the order of the keys they leave
+    M as it is each time, and then exactly nothing; any two of the small ones added first leave more."""
+    S, H = 128 * pieces, d // 64
+    w = synth.make_weights(np.random.default_rng(1), 1, d, H, 16, 16, True)
+    w["pos"][:] = 0
+    w["time"][:] = 0
+    model = Hn.Model(1, d, H, B.ELEM_BF16, 64, 16, 16, 1.0, w)
+    n_pages = (S // 64 // 32 + 2) * 32
+    pool = Hn.Pool(n_pages, model.page_size(), d * 2, B.ELEM_BF16, 64, 32, None, 0.0, zero_fill=True)
+    k = torch.zeros((S, d), dtype=torch.bfloat16, device=Hn.DEV)
+    v = torch.zeros_like(k)
+    k[:, ::64] = 1.0
+    big = 1 + torch.arange(d, device=Hn.DEV) % 64 / 128
+    v[::128] = (big * 2.0 ** -25).bfloat16()
+    v[0], v[S - 128] = big, -big
+    pages = np.arange(n_pages - S // 64, n_pages, dtype=np.int32)
+    Hn.write_prefix_kv(pool.mem.view(torch.bfloat16), 1, d, H, 64, pages, k, v, 0)
+    q = torch.zeros((n * new, d), dtype=torch.bfloat16, device=Hn.DEV)
+    q[:, ::64] = 1.0
+    o = torch.empty_like(q)
+    reqs = [(S - new, new, 0, 0, i * new) for i in range(n)]  # of the same pages
+    ts = torch.arange(S, dtype=torch.int64, device=Hn.DEV)
+    assert B.hstu_attn_paged(pool.h, model.h, 0, reqs, torch.from_numpy(pages).to(Hn.DEV), q, ts, o) == B.OK
+    assert not o.any()
+    v[S - 128] = 0  # without the last one: M times SiLU(1), as bf16 has it
+    Hn.write_prefix_kv(pool.mem.view(torch.bfloat16), 1, d, H, 64, pages, k, v, 0)
+    assert B.hstu_attn_paged(pool.h, model.h, 0, reqs, torch.from_numpy(pages).to(Hn.DEV), q, ts, o) == B.OK
+    want = big.double() / (1 + np.exp(-1.0))
+    assert ((o.double() - want).abs() <= 2 ** -8 * want * 1.01).all()  # half a unit each: SiLU(1) and the output, in bf16
+    model.close()
+    pool.close()

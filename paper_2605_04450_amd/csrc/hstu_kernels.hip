@@ -1515,7 +1515,9 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
       };
   #pragma unroll
       for (uint32_t sb = 0; sb < 2; ++sb) {
-        if (sb == 1) bring();
+        // (General requests read times from memory for each score and wait for all that is on its way: the copies go out in front,
+        // where the two wavefronts of a pair wait for them side by side.  128 x 64 behind 3072: between the halves 935 us, so 811.)
+        if (sb == (FAST ? 1 : 0)) bring();
         if (!(halves >> sb & 1) || j0 + 32 * sb > grp_last) continue;  // the wavefront's, and some pair visible
         f32x16 s = scores_begin(sb);
   #pragma unroll

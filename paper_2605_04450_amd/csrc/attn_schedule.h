@@ -59,6 +59,21 @@ constexpr uint32_t attn_tiles(const AttnItem& t) {
   return (t.prefix_len + last) / 64 + 1;
 }
 
+// Where the positional biases of an item are.  Entry x of its window is the bias of distance top - x, held within the table's
+// n_pos entries (negative distances belong to keys after the query, which the causal select removes).  A wavefront looks at
+// entries x0 .. x0 + 254 at most, which sit at base + min(max(first - x, 256), last): a base that all lanes agree on, in 64 bits,
+// and a few hundred entries from it.  top is below 2^31 + 127, n_pos any number but 0.
+struct PosEntries {
+  int64_t base;
+  uint32_t first, last;
+};
+constexpr PosEntries pos_entries(uint32_t top, uint32_t x0, uint32_t n_pos) {
+  const uint32_t longest = (n_pos < 0x80000100u ? n_pos : 0x80000100u) + 255;  // 256 and up: so that nothing is negative
+  const uint32_t nearest = top + 2 - x0 > 256 ? top + 2 - x0 : 256;            // distance top - x0 - 254
+  const uint32_t from = nearest < longest ? nearest : longest;
+  return {static_cast<int64_t>(from) - 512, top + 512 - x0 - from, longest + 256 - from};
+}
+
 // key tiles whose pages an item's slice of the page table can name
 inline uint32_t attn_page_cap(uint32_t page_tokens) {
   return static_cast<uint32_t>(std::max<uint64_t>(1, std::min<uint64_t>(1u << 30, (kAttnMaxItemPages - 2) * static_cast<uint64_t>(page_tokens) / 64)));

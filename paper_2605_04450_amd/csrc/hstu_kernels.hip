@@ -1248,12 +1248,11 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
     if (tid == 0) sm.pages[kAttnMaxItemPages - 1] = -1;
   }
   // Positional window: entry x = (key - first key of the item) + (127 - query in the block) holds the (reversed, scaled)
-  // bias of distance pos_top - x.  Negative distances belong to keys after the query, which the causal select removes.
-  const int32_t pos_top = static_cast<int32_t>(P + q0 + kAttnQ - 1 - kt_begin * 64);
-  auto pos_at = [&](uint32_t x0, uint32_t x) {  // entry x0 + x
-    const int32_t i = min(max(pos_top - static_cast<int32_t>(x0) - static_cast<int32_t>(x), 0), static_cast<int32_t>(hd.n_pos) - 1);
-    // (32 bits of byte offset: distances of 2^30 would take 275 GB of keys and values)
-    return *(GlobalFloats)(pos_h + static_cast<uint32_t>(i) * 4u);
+  // bias of distance pos_top - x.
+  const uint32_t pos_top = P + q0 + kAttnQ - 1 - kt_begin * 64;
+  auto pos_at = [&](uint32_t x0, uint32_t x) {  // entry x0 + x, x at most 254
+    const PosEntries e = pos_entries(pos_top, x0, hd.n_pos);
+    return *(GlobalFloats)(pos_h + 4 * e.base + min(max(e.first - x, 256u), e.last) * 4u);
   };
   auto pos_put_copy = [&](uint32_t s, uint32_t x, float v, bool mirror) {
     const uint32_t at = (x - s) & (kPosRing - 1);

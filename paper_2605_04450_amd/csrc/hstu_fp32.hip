@@ -72,12 +72,13 @@ __global__ __launch_bounds__(256) void layer_half_f32(HalfArgsF32 a) {
   const float bias = a.bias[col_ok ? col : 0];
 #pragma unroll
   for (uint32_t r = 0; r < kRowsPerWave; ++r) resid[r] = FRONT ? 0.0f : a.resid[static_cast<uint64_t>(row[r]) * d + (col_ok ? col : 0)];
-  // Where K and V of the rows go: up to 64 requests are a lane each, the row's request one ballot away; more are searched.  (The
+  // Where K and V of the rows go: up to 64 requests are a lane each, the row's request one ballot away; more are searched, by
+  // wavefronts with columns of K or V (1000 requests of 16, d = 128: 227 us with a search in every wavefront, so 212).  (The
   // page's number comes as a vector load, which is waited for where it is used; a scalar one every LDS read would wait for.)
   const uint32_t which = col / d, c_out = col % d;  // FRONT: 0: U, 1: V, 2: Q, 3: K
   int32_t page[kRowsPerWave];
   uint32_t tok[kRowsPerWave];
-  if (FRONT) {
+  if (FRONT && (a.B <= 64 || __any(which & 1))) {
 #pragma unroll
     for (uint32_t r = 0; r < kRowsPerWave; ++r) {
       uint32_t first, table;  // of the row's request: the token that its row 0 would be, and its page table

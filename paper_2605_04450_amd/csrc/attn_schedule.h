@@ -31,7 +31,10 @@ constexpr uint32_t kAttnItemCost = 2;  // what an item costs besides its key til
 // Small steps: a workgroup needs about 3 us before its first tile and 1.1 us per tile, so two tiles an item, spread over
 // idle CUs, beat eight in one (one request of 64 new tokens 18 -> 11 us, 13 ragged prefills 35 -> 14 us).
 constexpr uint32_t kAttnMinTiles = 2;
-constexpr uint32_t kAttnMaxItemPages = 608;  // page-table entries one item may span
+constexpr uint32_t kAttnMaxItemPages = 608;  // words of a workgroup's page list
+// Words of it beyond the pages that an item's tiles would fill if they began with a page: the item may begin inside one, and the
+// loop asks for the page of the second tile behind the item's last one (a word that may hold anything, and is not used).
+constexpr uint32_t kAttnSparePages = 2;
 
 struct ReqDev {  // device copy of one request
   uint32_t prefix_len, new_len;
@@ -76,7 +79,7 @@ constexpr PosEntries pos_entries(uint32_t top, uint32_t x0, uint32_t n_pos) {
 
 // key tiles whose pages an item's slice of the page table can name
 inline uint32_t attn_page_cap(uint32_t page_tokens) {
-  return static_cast<uint32_t>(std::max<uint64_t>(1, std::min<uint64_t>(1u << 30, (kAttnMaxItemPages - 2) * static_cast<uint64_t>(page_tokens) / 64)));
+  return static_cast<uint32_t>(std::max<uint64_t>(1, std::min<uint64_t>(1u << 30, (kAttnMaxItemPages - kAttnSparePages) * static_cast<uint64_t>(page_tokens) / 64)));
 }
 
 // Upper bounds for up to B requests, N new tokens and sequences of up to max_seq tokens: query tiles, and entries of all lists

@@ -1283,7 +1283,8 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
   const bool one_page_tiles = hd.pt_shift < 32 && hd.pt >= 64;
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(&sm.kv[0][0][0])) + wave * 2048;
   // The page of a tile, or -1 if it may sit in several.  It is read a tile ahead, beside other LDS reads that are waited for
-  // there, so that the copies of a tile start right behind the barrier.  (Asked for tiles up to one past the item's.)
+  // there, so that the copies of a tile start right behind the barrier.  (Asked for tiles up to the second behind the item's last one,
+  // whose word exists but may hold anything: kAttnSparePages.)
   const uint32_t whole_tiles = one_page_tiles ? S / 64 : 0;  // tiles before this one sit in one page each, inside the sequence
   auto page_of = [&](uint32_t kt) -> int32_t { return sm.pages[kt < whole_tiles ? ((kt * 64) >> hd.pt_shift) - page0 : kAttnMaxItemPages - 1]; };
   auto fetch = [&](uint32_t kt, uint32_t buf, int32_t page) {

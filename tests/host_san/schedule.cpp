@@ -43,6 +43,9 @@ static void check(const std::vector<ReqDev>& reqs, uint32_t H, uint32_t pt, Attn
     const AttnItem& t = s.items[w.item_head >> 4];
     const uint32_t kt_begin = w.k * s.piece, kt_end = w.k + 1 == t.pieces ? attn_tiles(t) : kt_begin + s.piece;
     CHECK(w.k < t.pieces && kt_begin < kt_end && (kt_end * 64ull - 1) / pt - kt_begin * 64ull / pt < kAttnMaxItemPages);
+    // the loop asks for the page of tile kt_end + 1, and the last word of the list is not a page's
+    if (pt >= 64 && (pt & (pt - 1)) == 0) CHECK((kt_end + 1) * 64ull / pt - kt_begin * 64ull / pt < kAttnMaxItemPages);
+    CHECK((kt_end * 64ull - 1) / pt - kt_begin * 64ull / pt < kAttnMaxItemPages - 1);
     of[(w.item_head >> 4) * H + (w.item_head & 15)].push_back({w.k, kt_begin, kt_end});
   }
   // the loads of the dies: each unit went to the least loaded one, and is closed when it weighs more than a 32nd of a head's work
@@ -152,6 +155,11 @@ int main() {
       check(requests(std::vector<std::pair<uint32_t, uint32_t>>(700, {0, 1})), H, pt, s);
       check(requests(std::vector<std::pair<uint32_t, uint32_t>>(32, {16384, 512})), H, pt, s);
     }
+  // items as long as a page list allows: of 606 tiles of 64 tokens, or from inside a page on
+  for (uint32_t pt : {64u, 128u, 256u, 8u, 24u}) {
+    check(requests(std::vector<std::pair<uint32_t, uint32_t>>(40, {1u << 20, 500})), 8, pt, s);
+    CHECK(s.piece == attn_page_cap(pt) || pt > 64);
+  }
   // equal query tiles that fill more than half of the places: one each, not one of a share and a remainder
   for (uint32_t n : {130u, 144u, 160u, 192u})
     for (uint32_t prefix : {1024u, 3072u}) {

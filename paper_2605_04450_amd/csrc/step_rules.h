@@ -8,7 +8,8 @@ namespace racer {
 constexpr uint32_t kCus = 256;
 
 // ---- joined layer halves (layer_join): 32 rows a block ------------------------------------------------------------
-// Blocks of layer_join that a CU holds: by their registers (200 and 368 of 512 per SIMD and lane) two, or one at d = 512.
+// Blocks of layer_join that a CU holds: by their registers (of 512 per SIMD and lane: at d = 256 174 to 236, at 512 318 to 459,
+// the back half alone the most) two, or one at d = 512, where 53 to 92 KB of the 160 KB of LDS would allow one or two.
 constexpr uint32_t join_per_cu(uint32_t d) { return d <= 256 ? 2 : 1; }
 
 // Slices of the front half's columns, down to one tile per wavefront, while there are CUs without a block, but no more

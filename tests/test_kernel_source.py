@@ -65,3 +65,24 @@ def test_settling_whole_sets_keeps_its_registers(tmp_path):
         if "miss_settle_sets" in name:
             scratch[name] = re.search(r"\.private_segment_fixed_size:\s+(\d+)", entry).group(1)
     assert scratch and set(scratch.values()) == {"0"}, scratch
+
+
+def test_joined_halves_fit_the_blocks_per_cu_that_the_rule_counts(tmp_path):
+    # join_slices brings no more blocks than the chip holds at once: two per CU, one at d = 512, a wavefront per SIMD each, of 512
+    # registers per SIMD and lane and 160 KB of LDS per CU
+    asm = tmp_path / "kernels.s"
+    subprocess.run(["hipcc", "--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang",
+                    "-packed-fp32-ops", "-w", "--cuda-device-only", "-S", os.path.join(CSRC, "hstu_kernels.hip"), "-o", str(asm)], check=True)
+    found = 0
+    for entry in re.split(r"\n  - \.agpr_count:", asm.read_text())[1:]:
+        field = lambda key: re.search(r"\.%s:\s+(\S+)" % key, entry).group(1)
+        width = re.search(r"layer_(?:join|first)ILi(\d+)E", field("name"))
+        if not width:
+            continue
+        found += 1
+        per_cu = 2 if int(width.group(1)) <= 256 else 1
+        registers = -(-int(field("vgpr_count")) // 8) * 8  # accumulation registers are counted in
+        assert registers * per_cu <= 512, (field("name"), registers)
+        assert int(field("group_segment_fixed_size")) * per_cu <= 160 * 1024, field("name")
+        assert field("private_segment_fixed_size") == "0", field("name")
+    assert found == 16  # four widths: both halves, either alone, and the one that begins a step

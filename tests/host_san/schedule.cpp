@@ -173,14 +173,23 @@ int main() {
     check(requests(l), 4, 64, s);
     CHECK(!s.groups.empty());
   }
-  // steps of tests/test_gpu_attention_tiles.py, whose keys lie in pieces of two key tiles: pieces, heads, requests, new tokens,
-  // and whether attention_reduce_rows adds them up
+  // steps of tests/test_gpu_attention_tiles.py: they are cut into as many pieces as it says, and added up by attention_reduce_rows
+  // or not; first those whose keys lie in pieces of two key tiles
   struct Sums { uint32_t H, n, pieces, len; bool by_rows; };
   for (const Sums& c : {Sums{1, 1, 5, 1, false}, {1, 1, 6, 64, false}, {2, 2, 7, 33, false}, {4, 1, 8, 64, false}, {4, 16, 12, 64, false},
                         {1, 1, 9, 64, true}, {1, 2, 16, 3, true}, {4, 1, 17, 64, true}, {4, 1, 24, 64, true}, {8, 1, 32, 128, true},
                         {1, 1, 33, 64, true}, {2, 1, 48, 2, true}, {1, 1, 49, 100, true}, {4, 1, 94, 1, true}}) {
     check(requests(std::vector<std::pair<uint32_t, uint32_t>>(c.n, {128 * c.pieces - c.len, c.len})), c.H, 64, s);
     CHECK(s.piece == 2 && s.groups.size() == c.n && s.n_slots == c.n * c.H * c.pieces);
+    CHECK(sums_by_rows((c.len + 3) / 4 * c.n * c.H, s.n_slots, c.n * c.H) == c.by_rows);
+  }
+  struct Cut { uint32_t H, n, prefix, len, pieces; bool by_rows; };
+  for (const Cut& c : {Cut{1, 40, 1100, 64, 9, true}, {1, 41, 1100, 64, 9, false}, {2, 20, 1100, 61, 9, true}, {2, 21, 1100, 61, 9, false},
+                       {1, 41, 1000, 64, 8, false}, {1, 40, 1000, 64, 8, false}, {1, 64, 520, 64, 5, false}, {2, 33, 600, 1, 5, false},
+                       {1, 1, 4500, 64, 36, true}, {1, 1, 4000, 64, 32, true}, {1, 1, 1000, 128, 9, true}, {1, 64, 200, 64, 2, false},
+                       {4, 1, 300, 3, 2, false}, {4, 1, 200, 2, 2, false}}) {
+    check(requests(std::vector<std::pair<uint32_t, uint32_t>>(c.n, {c.prefix, c.len})), c.H, 64, s);
+    CHECK(s.groups.size() == c.n && s.n_slots == c.n * c.H * c.pieces);
     CHECK(sums_by_rows((c.len + 3) / 4 * c.n * c.H, s.n_slots, c.n * c.H) == c.by_rows);
   }
   std::mt19937 g(1);

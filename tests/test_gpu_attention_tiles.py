@@ -66,11 +66,14 @@ def test_items_of_one_to_ten_key_tiles(pt, ordered):
     c.close()
 
 
+# (tests/host_san/schedule.cpp holds the numbers of partials and the kernels to these)
 @pytest.mark.parametrize("d,n,prefix,new", [
-    (64, 64, 200, 64), (64, 65, 200, 64),    # the most cut tiles whose partials are summed in quarters, and one more
-    (128, 32, 130, 1), (128, 33, 130, 1),
-    (64, 1, 4500, 64), (64, 1, 1000, 128),   # more partials than a quarter asks for at once; quarters of eight
-    (256, 1, 300, 3), (256, 1, 200, 2),      # fewer partials than quarters
+    (64, 40, 1100, 64), (64, 41, 1100, 64),   # the most blocks of attention_reduce_rows, nine partials a tile, and one tile more
+    (128, 20, 1100, 61), (128, 21, 1100, 61),  # of two heads, the last block with one row
+    (64, 41, 1000, 64), (64, 40, 1000, 64),   # eight partials: attention_reduce
+    (64, 64, 520, 64), (128, 33, 600, 1),     # five: a round of four and one more
+    (64, 1, 4500, 64), (64, 1, 4000, 64), (64, 1, 1000, 128),  # 36, 32 and 9: two rounds, a full one, part of one
+    (64, 64, 200, 64), (256, 1, 300, 3), (256, 1, 200, 2),     # two
 ])
 def test_sums_of_few_and_many_partials(d, n, prefix, new):
     """Requests with the same rows and keys: the first one as the oracle computes it, the others like the first."""

@@ -3,7 +3,11 @@ last group of 32 rows, and the number of rows from which the halves are kernels 
 first one, which the oracle computes, and gets the same rows; two layers, so that a back half feeds a front half."""
 import numpy as np
 import pytest
+import torch
 
+import oracle
+from paper_2605_04450_amd import device as Hn
+from paper_2605_04450_amd import synth
 from tests.test_gpu_hstu import Case, assert_close
 
 pytestmark = pytest.mark.gpu
@@ -56,7 +60,7 @@ def test_the_first_layers_kernel_looks_at_every_timestamp(d, new):
     c.close()
 
 
-# (Not d = 64, one head: the attention of a request's first token is then SiLU(q.k) v / n of a single key, whose relative error has
+# (d = 64, one head, is below, behind cached keys: the attention of a request's first token is then SiLU(q.k) v / n of a single key, whose relative error has
 # no bound where q.k, a sum of terms rounded to eight bits, is near zero, and the second LayerNorm takes the scale away.  Of several
 # heads not all are near zero at once.)
 @pytest.mark.parametrize("d,T", [(128, 3), (256, 1), (256, 15), (256, 16), (512, 11)])
@@ -73,4 +77,26 @@ def test_rows_of_many_requests_in_a_group(d, T):
     keep[reqs[40][4]: reqs[40][4] + reqs[40][1]] = False
     assert_close(got[keep], ref[keep], True, "beside a bad page")
     assert c.pool.stats()["bad_pages"] > 0
+    c.close()
+
+
+@pytest.mark.parametrize("d,T", [(64, 1), (64, 3), (64, 11), (64, 16), (128, 3)])
+def test_rows_of_many_requests_in_a_group_behind_cached_keys(d, T):
+    n, P = 70, 21
+    c = Case(27, 2, d, d // 64, 8, True, 100, 16, 64.0, 608)
+    new = [T + (i % 3 == 0) for i in range(n)]
+    whole, pts, ts, _ = c.inputs([P] * n, new)
+    x = synth.as_bf16_values(c.rng.standard_normal((sum(new), d)).astype(np.float32))
+    for (_, _, pto, _, _) in whole:
+        pages = pts[pto:pto + -(-P // 8)]
+        for layer in range(2):
+            k, v = (synth.as_bf16_values(c.rng.standard_normal((P, d)).astype(np.float32)) for _ in range(2))
+            Hn.write_prefix_kv(c.mem, 2, d, c.H, 8, pages, torch.from_numpy(k).to(Hn.DEV).bfloat16(), torch.from_numpy(v).to(Hn.DEV).bfloat16(), layer)
+            for j in range(P):
+                for h in range(c.H):
+                    for which, rows in enumerate((k, v)):
+                        at = oracle.kv_offset(c.cfg, int(pages[j // 8]), layer, which, h, j % 8)
+                        c.kv[at:at + 64] = rows[j, 64 * h:64 * h + 64]
+    assert_close(c.run_gpu(whole, pts, ts, x), c.run_oracle(whole, pts, ts, x), True, "short appends")
+    assert c.pool.stats()["bad_pages"] == 0
     c.close()

@@ -63,23 +63,26 @@ constexpr uint32_t attn_tiles(const AttnItem& t) {
 }
 
 // Where the positional biases of an item are.  Entry x of its window is the bias of distance top - x, held within the table's
-// n_pos entries (negative distances belong to keys after the query, which the causal select removes).  A wavefront looks at
-// entries x0 .. x0 + 254 at most, which sit at base + min(max(first - x, 256), last): a base that all lanes agree on, in 64 bits,
-// and a few hundred entries from it.  top is below 2^31 + 127, n_pos any number but 0.
+// n_pos entries (negative distances belong to keys after the query, which the causal select removes).  It sits at
+// base + min(max(first - x, 256), last): a base in 64 bits and, since an item has no more than kAttnMaxItemTiles key tiles, an
+// offset of less than 2^30 entries, 2^32 bytes.  top is below 2^31 + 127, n_pos any number but 0, x at most 191 past the
+// item's last key.
+constexpr uint32_t kAttnMaxItemTiles = 1u << 23;
 struct PosEntries {
   int64_t base;
   uint32_t first, last;
 };
-constexpr PosEntries pos_entries(uint32_t top, uint32_t x0, uint32_t n_pos) {
-  const uint32_t longest = (n_pos < 0x80000100u ? n_pos : 0x80000100u) + 255;  // 256 and up: so that nothing is negative
-  const uint32_t nearest = top + 2 - x0 > 256 ? top + 2 - x0 : 256;            // distance top - x0 - 254
-  const uint32_t from = nearest < longest ? nearest : longest;
-  return {static_cast<int64_t>(from) - 512, top + 512 - x0 - from, longest + 256 - from};
+constexpr PosEntries pos_entries(uint32_t top, uint32_t n_pos) {
+  constexpr uint32_t span = kAttnMaxItemTiles * 64 + 256;
+  const uint32_t nearest = top > span ? top - span : 0;  // no entry of the item is of a shorter distance, or of more than 0
+  const uint32_t from = nearest < n_pos - 1 ? nearest : n_pos - 1;
+  const uint32_t entries = n_pos - 1 - from < span ? n_pos - 1 - from : span;
+  return {static_cast<int64_t>(from) - 256, top - from + 256, entries + 256};  // 256 and up: so that nothing is negative
 }
 
 // key tiles whose pages an item's slice of the page table can name
 inline uint32_t attn_page_cap(uint32_t page_tokens) {
-  return static_cast<uint32_t>(std::max<uint64_t>(1, std::min<uint64_t>(1u << 30, (kAttnMaxItemPages - kAttnSparePages) * static_cast<uint64_t>(page_tokens) / 64)));
+  return static_cast<uint32_t>(std::max<uint64_t>(1, std::min<uint64_t>(kAttnMaxItemTiles, (kAttnMaxItemPages - kAttnSparePages) * static_cast<uint64_t>(page_tokens) / 64)));
 }
 
 // Upper bounds for up to B requests, N new tokens and sequences of up to max_seq tokens: query tiles, and entries of all lists

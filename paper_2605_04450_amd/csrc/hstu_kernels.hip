@@ -1248,11 +1248,11 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_mfma(HstuDims hd, uint3
     if (tid == 0) sm.pages[kAttnMaxItemPages - 1] = -1;
   }
   // Positional window: entry x = (key - first key of the item) + (127 - query in the block) holds the (reversed, scaled)
-  // bias of distance pos_top - x.
-  const uint32_t pos_top = P + q0 + kAttnQ - 1 - kt_begin * 64;
-  auto pos_at = [&](uint32_t x0, uint32_t x) {  // entry x0 + x, x at most 254
-    const PosEntries e = pos_entries(pos_top, x0, hd.n_pos);
-    return *(GlobalFloats)(pos_h + 4 * e.base + min(max(e.first - x, 256u), e.last) * 4u);
+  // bias of the distance between that query and the item's first key, less x.
+  const PosEntries pe = pos_entries(P + q0 + kAttnQ - 1 - kt_begin * 64, hd.n_pos);
+  const GlobalBytes pos_0 = pos_h + 4 * pe.base;
+  auto pos_at = [&](uint32_t x0, uint32_t x) {  // entry x0 + x
+    return *(GlobalFloats)(pos_0 + min(max(pe.first - x0 - x, 256u), pe.last) * 4u);
   };
   auto pos_put_copy = [&](uint32_t s, uint32_t x, float v, bool mirror) {
     const uint32_t at = (x - s) & (kPosRing - 1);

@@ -129,18 +129,25 @@ static std::vector<ReqDev> requests(const std::vector<std::pair<uint32_t, uint32
   return r;
 }
 
-// Entries of the positional window against the distance in 64 bits, also where distance or table pass 2^30 and 2^31 entries.
+// Entries of the positional window against the distance in 64 bits, also where distance or table pass 2^30 and 2^31 entries: at
+// the item's first key, around its middle and at its last tile, for items of a few tiles and of the most there are.
 static void positions() {
-  for (uint64_t top : {127ull, 128ull, 190ull, 400ull, 5000ull, (1ull << 30) - 1, 1ull << 30, (1ull << 30) + 300, (1ull << 31) - 2, (1ull << 31) + 126})
-    for (uint64_t n_pos : {1ull, 2ull, 100ull, 256ull, 4999ull, (1ull << 30) - 1, 1ull << 30, (1ull << 30) + 1, 1ull << 31, (1ull << 31) + 127, (1ull << 32) - 1})
-      for (uint64_t x0 = 0; x0 + 64 <= top || x0 == 0; x0 = x0 < 1024 || x0 + 1024 > top ? x0 + 64 : top / 64 * 64 - 512) {
-        const PosEntries e = pos_entries(static_cast<uint32_t>(top), static_cast<uint32_t>(x0), static_cast<uint32_t>(n_pos));
-        for (uint32_t x = 0; x < 255; ++x) {
-          const int64_t want = std::min<int64_t>(std::max<int64_t>(static_cast<int64_t>(top) - static_cast<int64_t>(x0) - x, 0), static_cast<int64_t>(n_pos) - 1);
-          const uint32_t off = std::min(std::max(e.first - x, 256u), e.last);
-          CHECK(off <= 510 && e.base + off == want);
-        }
+  for (uint64_t top : {127ull, 128ull, 190ull, 400ull, 5000ull, (1ull << 29) + 255, (1ull << 29) + 256, (1ull << 29) + 257, (1ull << 30) - 1, 1ull << 30,
+                       (1ull << 30) + 300, (1ull << 31) - 2, (1ull << 31) + 126})
+    for (uint64_t n_pos : {1ull, 2ull, 100ull, 256ull, 4999ull, (1ull << 29) + 1, (1ull << 30) - 1, 1ull << 30, (1ull << 30) + 1, 1ull << 31,
+                           (1ull << 31) + 127, (1ull << 32) - 1}) {
+      const PosEntries e = pos_entries(static_cast<uint32_t>(top), static_cast<uint32_t>(n_pos));
+      CHECK((e.last + 1ull) * 4 <= 1ull << 32);
+      for (uint64_t tiles : {1ull, 2ull, 606ull, static_cast<unsigned long long>(kAttnMaxItemTiles)}) {
+        const uint64_t end = std::min(64 * tiles + 191, top + 255);
+        for (uint64_t from : {uint64_t(0), end / 2, end > 600 ? end - 600 : 0})
+          for (uint64_t x = from; x < std::min(from + 600, end); ++x) {
+            const int64_t want = std::min<int64_t>(std::max<int64_t>(static_cast<int64_t>(top) - static_cast<int64_t>(x), 0), static_cast<int64_t>(n_pos) - 1);
+            CHECK(e.base + std::min(std::max(e.first - static_cast<uint32_t>(x), 256u), e.last) == want);
+          }
       }
+    }
+  CHECK(attn_page_cap(0xFFFFFFF8u) == kAttnMaxItemTiles && attn_page_cap(64) == kAttnMaxItemPages - kAttnSparePages);
 }
 
 int main() {

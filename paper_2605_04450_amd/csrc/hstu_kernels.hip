@@ -348,13 +348,13 @@ __global__ __launch_bounds__(256) void gemm_front_bf16(HstuDims hd, uint32_t lay
 // are stored: the wait (which counts loads and stores in issue order) then never covers stores just issued.
 // A block sweeps all column tiles when there are rows enough to fill the chip, else the columns are cut too, down to one
 // tile a block (the launcher's rule).  Steps with fewer rows take layer_join instead (layers_joined says which).
-// What bounds it, d = 256, 131 440 rows: the front half moves 0.40 GB (0.34 of them its rows), and vector (51% of its
-// cycles), matrix (30%) and LDS (36%) work lie only partly on top of one another (28% of the time neither of the first two
+// What bounds it, d = 256, 131 440 rows: the front half moves 0.39 GB (0.34 of them its rows), and vector (49% of its
+// cycles), matrix (30%) and LDS (32%) work lie only partly on top of one another (25% of the time neither of the first two
 // runs); the back half moves 0.31 GB at 4.9 TB/s.  Three blocks per CU and the rows in uneven rounds 126 and 68 us, four,
 // which 40 KB of LDS and 128 registers allow, 119 to 123 and 61 to 64; 145 000 rows, where the last round was nearly
 // empty: 140 -> 126 us and 70 -> 67.  Stores into pages that the compiler knows to be global (it had waited for all LDS reads
 // before each pair of products, because a flat store counts as one), packing without a branch per run and fragments read four
-// steps ahead: the front half 120 -> 110.5 us in turn, a step of 64 histories of 2048 1.3% less, of 32 x 512 at d = 512 1.7%.
+// steps ahead: the front half 120 -> 110.5 us in turn (108 to 117 on other cards), a step of 64 histories of 2048 1.3% less, of 32 x 512 at d = 512 1.7%.
 // ---------------------------------------------------------------------------------------
 struct LayerHalfArgs {
   HstuDims hd;
@@ -1086,7 +1086,7 @@ __global__ __launch_bounds__(256, KD <= 256 ? 2 : 1) void layer_join(JoinArgs a)
 //     requests spanning >= 2^31 s (or models with more than 32 buckets) use 64-bit gaps;
 //   - the causal select is applied only in blocks that touch the diagonal.
 //
-// What the vector unit has to do is fixed by that (632 of its cycles per 32x32 block, 256 of the matrix unit), so
+// What the vector unit has to do is fixed by that (633 of its cycles per 32x32 block, 256 of the matrix unit), so
 // the rest is to keep it fed: the copies to LDS pass through no registers, which leaves the 128 that four wavefronts
 // per SIMD allow, and the block needs 40 KB of LDS, so that four are resident per CU.  With tiles staged through registers
 // (168 of them, 48 KB, three per SIMD) a launch over 195M (query, key) pairs, d = 256, took 0.382 ms, so 0.335; over 32 x 512
@@ -1100,8 +1100,8 @@ __global__ __launch_bounds__(256, KD <= 256 ? 2 : 1) void layer_join(JoinArgs a)
 // A third of the vector instructions beside the epilogue were addresses: of the page (now in scalar registers, its number read a
 // tile ahead), of the staged operands (now constants of two copies of the loop's body), of the next window entries; and
 // conditions that were kept in vector registers.  Without them, with the next tile's copies between the two halves instead of in
-// front of them ( 128 users back with 64 tokens behind 3072 530 -> 521 us a step) and with
-// the first two tiles on their way together, a block takes 821 SIMD cycles (886) and steps take 3 to 5% less: 64 histories of 2048 2044 -> 1975 us, 32 x 512 behind
+// front of them (128 users back with 64 tokens behind 3072 530 -> 521 us a step) and with
+// the first two tiles on their way together, a block takes 823 SIMD cycles (886) and steps take 3 to 5% less: 64 histories of 2048 2044 -> 1975 us, 32 x 512 behind
 // 16 384 7.40 -> 7.12 ms, the 128 users 545 -> 520, one of them 102.2 -> 99.3, 13 ragged prefills 103.1 -> 99.
 // Measured on it, timing only: without the reciprocal 8% of the d = 512 step, without SiLU and bias 28%, one-bucket bias
 // everywhere 1 to 4%.  Kept out, each slower: four copies of the body (by 1%), the last block's bucket remembered (by 2%).

@@ -199,6 +199,10 @@ int main() {
     CHECK(s.groups.size() == c.n && s.n_slots == c.n * c.H * c.pieces);
     CHECK(sums_by_rows((c.len + 3) / 4 * c.n * c.H, s.n_slots, c.n * c.H) == c.by_rows);
   }
+  {  // of tests/test_gpu_step_capture.py: a prefill of 2300 tokens, one head: 17 of its 18 query tiles are cut, into 2 to 18 pieces
+    check(requests({{0, 2300}}), 1, 64, s);
+    CHECK(s.groups.size() == 17 && s.n_slots == 170 && sums_by_rows(17 * 32 - 1, 170, 17));
+  }
   std::mt19937 g(1);
   auto log_size = [&](double e) { return static_cast<uint32_t>(std::exp((g() % 10000) / 10000.0 * e)); };
   const uint32_t pts[] = {8, 16, 24, 40, 64, 256, 800};

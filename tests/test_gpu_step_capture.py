@@ -1,5 +1,5 @@
 """Steps whose lists fit a kernel argument (3 KB) can be captured in a graph: at sizes just inside that, for query tiles that
-are cut (one long request) and for whole ones (many short requests, few and many heads), every replay gives the eager result."""
+are cut (one long request, with few and with many partials) and for whole ones (many short requests, few and many heads), every replay gives the eager result."""
 import numpy as np
 import pytest
 import torch
@@ -11,7 +11,7 @@ from tests.test_gpu_hstu import Case
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("d,new", [(256, [32] * 31), (128, [20] * 35), (512, [5] * 24), (256, [60, 1300])])
+@pytest.mark.parametrize("d,new", [(256, [32] * 31), (128, [20] * 35), (512, [5] * 24), (256, [60, 1300]), (64, [2300])])
 def test_replays_equal_the_eager_step(d, new):
     c = Case(43, 2, d, d // 64, 64, True, 300, 16, 300.0, 256)
     reqs, pts, ts, x = c.inputs([0] * len(new), new)
